@@ -8,16 +8,26 @@
 // the residual adds the token's own compressed embedding; alpha = SoftMax probability of the
 // expert within its layer's head; the k largest are kept, ties to the lower expert id.
 //
-// A lightweight network (a few MFLOP per token): plain fp32 kernels, one launch per stage (the
-// dense stages are fp32 contractions; the fp32 matrix-core rate of this chip equals its vector
-// rate, and bf16 inputs would move the predicted probabilities by more than the parity bound).  The
-// recurrent part keeps a gate row of W_hh in the registers of each of the 4C threads of a
-// sequence's workgroup and the state in LDS; SparseMax finds its threshold by bisection on
-// sum(max(s - tau, 0)) = 1 and then takes the closed form on the support that bisection found.
+// All arithmetic is fp32 (bf16 inputs would move the predicted probabilities by more than the parity
+// bound).  Five launches per call:
+//   hash_dense      c0 = x W_in^T + b, and again for layer 1's gate pre-activations
+//   hash_recurrence both LSTM layers at once, layer 2 a few steps behind layer 1
+//   hash_attention  scores, SparseMax, weighted sum and residual, for blocks of 16 queries
+//   hash_heads      logits, SoftMax and the k best, for blocks of tokens and a MoE layer each
+// The contractions run on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32, twice the rate of
+// scalar-per-lane fp32 multiply-adds); with the weights as the first operand a lane ends up with
+// four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
+// where 15 of the instruction's 16 columns would idle, and stays on the vector units.
+// It is what bounds a call: 0.6 us a time step at C = 128, of which 0.33 us is the issue of the
+// multiply-adds.  Measured against one launch per layer and stage on the vector units (d = 768, C = 128,
+// 6 x 128 experts): 1 sequence of 128 tokens 375 -> 119 us, 8 of 333 tokens (top-3) 1059 -> 268 us,
+// 64 of 128 tokens 609 -> 171 us.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 #include "kernels.h"
 
@@ -36,253 +46,767 @@ std::mutex g_scratch_mu;
 float *g_scratch_ptr[kMaxDevices] = {};
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
 
-__device__ __forceinline__ float sigmoidf_(float v) { return 1.f / (1.f + __expf(-v)); }
-
-__device__ __forceinline__ float wave_sum(float v)
+// ---- fp32 matrix products -----------------------------------------------------------------------
+// D[16 x 16] += A[16 x 4] B[4 x 16]: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16] and holds
+// D[4 * (l / 16) + i][l % 16].  The order of the K values is free, so four instructions take 16
+// consecutive K values with lane group g = l / 16 at 4g .. 4g+3: one 16-byte load per operand.
+__device__ __forceinline__ f32x4 mfma4(const f32x4 &a, const f32x4 &b, f32x4 d)
 {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int j = 0; j < 4; ++j) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], d, 0, 0, 0);
+    return d;
 }
-__device__ __forceinline__ float wave_max(float v)
+// The loads above stay above: a wavefront has them all in flight (the compiler would rather save registers).
+__device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
+__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+
+// ---- exchange between lanes ---------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float quad(float v)                 // value of another lane of the quad (or row, below)
+{
+    return __builtin_bit_cast(float, dpp<CTRL>(__builtin_bit_cast(int, v)));
+}
+// Reductions over the 16 lanes of a row: lane ^ 1, lane ^ 2, then mirrored halves (their quads agree) and
+// mirrored rows; f(v, value of the other lane).
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kHalfMirror = 0x141, kMirror = 0x140;
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += quad<kXor1>(v);
+    v += quad<kXor2>(v);
+    v += quad<kHalfMirror>(v);
+    return v + quad<kMirror>(v);
+}
+__device__ __forceinline__ float row_max(float v)
+{
+    v = fmaxf(v, quad<kXor1>(v));
+    v = fmaxf(v, quad<kXor2>(v));
+    v = fmaxf(v, quad<kHalfMirror>(v));
+    return fmaxf(v, quad<kMirror>(v));
 }
 
-// The three dense stages (compress, gate pre-activations, heads) take kTokenBlock tokens per
-// workgroup: a thread owns one output unit, reads its weight row once and applies it to every
-// token of the block (the tokens' inputs sit in LDS and are read as broadcasts), so a weight matrix
-// is fetched once per block instead of once per token.  Each (token, unit) sum runs in index order.
-constexpr int kTokenBlock = 8;
-
-// c0[n, j] = b_in[j] + sum_i x[n, i] * w_in[j, i].  One workgroup of C threads per block of TB tokens.
-template <int C, int TB>
-__global__ __launch_bounds__(C) void hash_compress(const __bf16 *__restrict__ x, const float *__restrict__ w_in,
-                                                   const float *__restrict__ b_in, int d, int n_tokens,
-                                                   float *__restrict__ c0)
+// ---- exchange between workgroups of one launch --------------------------------------------------
+// Values that another workgroup reads while both run are stored and loaded at agent scope (past the
+// L2, which is not coherent between XCDs), through buffer descriptors with the sc1 bit.
+constexpr int kAgent = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes)
 {
-    extern __shared__ __attribute__((aligned(16))) float xs[];                              // [TB][d] the tokens' embeddings, fp32
-    const int n0 = blockIdx.x * TB, j = threadIdx.x;
-    const int nb = min(TB, n_tokens - n0);
-    for (int i = j; i < TB * d; i += C) {
-        const int tb = i / d;
-        xs[i] = tb < nb ? (float)x[(size_t)n0 * d + i] : 0.f;
-    }
-    __syncthreads();
-    const float4 *w = reinterpret_cast<const float4 *>(w_in + (size_t)j * d);
-    float acc[TB];
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+template <int POLICY>
+__device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t r, int byte)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, byte, 0, POLICY));
+}
+template <int POLICY>
+__device__ __forceinline__ void store_f32(__amdgpu_buffer_rsrc_t r, int byte, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, byte, 0, POLICY);
+}
+__device__ __forceinline__ int peek(const int *flag)
+{
+    return __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish(int *flag, int v)
+{
+    __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <int N>
+__device__ __forceinline__ void wait_memory()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Workgroup barrier that orders LDS accesses only: global loads stay in flight across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Counters of one call, in the part of the workspace that the attention writes later: the ticket the
+// recurrence's workgroups draw their role from, then per sequence a 64-byte line for layer 1's and one
+// for layer 2's input progress (chunks times wavefronts, and chunks).  Cleared by the first launch.
+constexpr int kLine = 16;
+__host__ __device__ constexpr size_t counter_words(size_t n_seq) { return kLine * (1 + 2 * n_seq); }
+
+// ---- operand tiles in LDS -----------------------------------------------------------------------
+// Rows of 32 values, loaded straight into LDS with whole lines per request.  (Fetched as matrix operands,
+// 16 bytes of a different row in every lane, each lane is a cache access of its own: the dense stages
+// were bound by those, 64 per load, at 45 % of the matrix rate.)  Within a step of 32 values lane
+// group g multiplies values 8g .. 8g+7, its two 16-byte pieces of an fp32 row, or the one of a bf16 row.
+// A row's pieces are stored exclusive-or'ed with the row number, so that neither the lane-linear writes
+// nor the reads of one piece of 16 rows meet in a bank.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, int voffset, char *dst)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, voffset, 0, 0, 0);
+}
+template <typename T>
+struct TileRow {                                               // T = float
+    static constexpr int kBytes = 128, kRowsPerLoad = 8;
+    static __device__ __forceinline__ int row(int lane) { return lane >> 3; }
+    static __device__ __forceinline__ int piece(int lane, int row) { return (lane & 7) ^ (row & 7); }
+    static __device__ __forceinline__ void read(const char *tile, int row, int g, float (&v)[8])
+    {
+        const char *p = tile + row * kBytes;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) acc[tb] = b_in[j];
-    for (int i = 0; i < d / 4; ++i) {
-        const float4 wv = w[i];
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 q = *reinterpret_cast<const f32x4 *>(p + (((2 * g + h) ^ (row & 7)) * 16));
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-            const float4 xv = *reinterpret_cast<const float4 *>(xs + tb * d + 4 * i);
-            acc[tb] += xv.x * wv.x;
-            acc[tb] += xv.y * wv.y;
-            acc[tb] += xv.z * wv.z;
-            acc[tb] += xv.w * wv.w;
+            for (int e = 0; e < 4; ++e) v[4 * h + e] = q[e];
         }
     }
+};
+template <>
+struct TileRow<__bf16> {
+    static constexpr int kBytes = 64, kRowsPerLoad = 16;
+    static __device__ __forceinline__ int row(int lane) { return lane >> 2; }
+    static __device__ __forceinline__ int piece(int lane, int row) { return (lane & 3) ^ ((row >> 1) & 3); }
+    static __device__ __forceinline__ void read(const char *tile, int row, int g, float (&v)[8])
+    {
+        const bf16x8 q = *reinterpret_cast<const bf16x8 *>(tile + row * kBytes + ((g ^ ((row >> 1) & 3)) * 16));
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb)
-        if (tb < nb) c0[(size_t)(n0 + tb) * C + j] = acc[tb];
-}
-
-// pre[n, g] = b_ih[g] + b_hh[g] + sum_i in[n, i] * w_ih[g, i].  One workgroup of 4C threads per block of TB tokens.
-template <int C, int TB>
-__global__ __launch_bounds__(4 * C) void hash_gates_in(const float *__restrict__ in, const float *__restrict__ w_ih,
-                                                       const float *__restrict__ b_ih, const float *__restrict__ b_hh,
-                                                       int n_tokens, float *__restrict__ pre)
-{
-    __shared__ __attribute__((aligned(16))) float row[TB][C];
-    const int n0 = blockIdx.x * TB, g = threadIdx.x;
-    const int nb = min(TB, n_tokens - n0);
-    for (int i = g; i < TB * C; i += 4 * C) (&row[0][0])[i] = i / C < nb ? in[(size_t)n0 * C + i] : 0.f;
-    __syncthreads();
-    const float4 *w = reinterpret_cast<const float4 *>(w_ih + (size_t)g * C);
-    float acc[TB];
+        for (int e = 0; e < 8; ++e) v[e] = (float)q[e];
+    }
+};
+// The loads of one wavefront for tiles of ROWS rows of a [rows, k] matrix, shared by SHARE wavefronts.
+// Every wavefront issues kLoads per tile (a tile of fewer loads is loaded twice over, with the same
+// bytes); rows and columns past the end repeat the last ones.
+template <typename T, int ROWS, int SHARE>
+struct TileLoader {
+    static constexpr int kAll = ROWS / TileRow<T>::kRowsPerLoad, kLoads = (kAll + SHARE - 1) / SHARE;
+    static_assert(ROWS % TileRow<T>::kRowsPerLoad == 0 && (kAll % SHARE == 0 || kAll < SHARE), "whole loads");
+    __amdgpu_buffer_rsrc_t rsrc;
+    int row_at[kLoads], piece[kLoads], dst[kLoads], last;
+    __device__ __forceinline__ TileLoader(const T *first_row, int rows_left, int k, int lane, int share)
+    {
+        const int rows = min(rows_left, ROWS);
+        rsrc = make_rsrc(first_row, (uint32_t)rows * (uint32_t)k * (uint32_t)sizeof(T));
+        last = k * (int)sizeof(T) - 16;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) acc[tb] = b_ih[g] + b_hh[g];
-#pragma unroll 4
-    for (int i = 0; i < C / 4; ++i) {
-        const float4 wv = w[i];
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-            const float4 xv = *reinterpret_cast<const float4 *>(&row[tb][4 * i]);
-            acc[tb] += xv.x * wv.x;
-            acc[tb] += xv.y * wv.y;
-            acc[tb] += xv.z * wv.z;
-            acc[tb] += xv.w * wv.w;
+        for (int i = 0; i < kLoads; ++i) {
+            const int q = (share * kLoads + i) % kAll, row = q * TileRow<T>::kRowsPerLoad + TileRow<T>::row(lane);
+            row_at[i] = min(row, rows - 1) * k * (int)sizeof(T);
+            piece[i] = TileRow<T>::piece(lane, row) * 16;
+            dst[i] = __builtin_amdgcn_readfirstlane(q) * 1024;
         }
     }
+    __device__ __forceinline__ void issue(int step, char *tile) const
+    {
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb)
-        if (tb < nb) pre[(size_t)(n0 + tb) * 4 * C + g] = acc[tb];
+        for (int i = 0; i < kLoads; ++i)
+            load_to_lds(rsrc, row_at[i] + min(step * TileRow<T>::kBytes + piece[i], last), tile + dst[i]);
+    }
+};
+
+// ---- dense stages -------------------------------------------------------------------------------
+// out[n, u] = bias_a[u] + bias_b[u] + sum_i in[n, i] w[u, i] for n_tokens tokens and `units` units (w is
+// [units, k], k a multiple of 8; bias_b may be null): the compressed embedding and layer 1's gate
+// pre-activations.  A wavefront makes TU x TT tiles of 16 units x 16 tokens; a workgroup is 4 =
+// WU (units) x WT (tokens) x KS (parts of the sum) wavefronts.  Operands run NB - 1 stages of G * 32
+// values ahead in a ring of NB stages, shared by the workgroup's wavefronts or (KS > 1) each wavefront
+// its own.
+//  * Small batches are bound by the latency of their loads and by what one compute unit can fetch
+//    (128 tokens: 33 us when 8 workgroups of 16 tokens read all weights each): one tile per wavefront
+//    and the long sum over d_model in four parts, so that the operands of a wavefront are in flight at
+//    once and the weights are spread over 64 workgroups.
+//  * Large ones by the matrix units: 2 x 2 tiles per wavefront.
+// Also clears the counters of the recurrence behind it.
+template <int TU, int TT, int WU, int WT, int KS, int G, int NB, typename IN>
+__global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, const float *__restrict__ w,
+                                                  const float *__restrict__ bias_a, const float *__restrict__ bias_b, int k,
+                                                  int units, int n_tokens, float *__restrict__ out,
+                                                  int *__restrict__ counters, int n_counters)
+{
+    static_assert(WU * WT * KS == 4 && (KS == 1 || (KS == 4 && TU * TT == 1)), "wavefronts of a workgroup");
+    constexpr int kShare = KS == 1 ? 4 : 1;
+    constexpr int WR = WU * TU * 16, XR = WT * TT * 16;        // rows staged together
+    constexpr int kW = WR * TileRow<float>::kBytes, kStep = kW + XR * TileRow<IN>::kBytes, kStage = G * kStep;
+    typedef TileLoader<float, WR, kShare> LoadW;
+    typedef TileLoader<IN, XR, kShare> LoadX;
+    constexpr int kStageLoads = G * (LoadW::kLoads + LoadX::kLoads);
+    __shared__ __attribute__((aligned(1024))) char ring[(4 / kShare) * NB * kStage];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), col = lane & 15, g = lane >> 4;
+    if (blockIdx.y == 0)
+        for (int i = blockIdx.x * 256 + tid; i < n_counters; i += gridDim.x * 256) counters[i] = 0;
+    const int part = KS == 1 ? 0 : wv, wu = KS == 1 ? wv % WU : 0, wt = KS == 1 ? wv / WU : 0;
+    const int n0 = blockIdx.x * XR, u0 = blockIdx.y * WR;
+    const int steps = (k + 31) / 32, per = (steps + KS - 1) / KS, first = part * per, last = min(steps, first + per);
+    const LoadW load_w(w + (size_t)u0 * k, units - u0, k, lane, wv % kShare);
+    const LoadX load_x(in + (size_t)n0 * k, n_tokens - n0, k, lane, wv % kShare);
+    char *mine = ring + (KS == 1 ? 0 : wv * NB * kStage);
+    f32x4 acc[TU][TT] = {};
+    const int end = min(k, last * 32);                         // of this wavefront's part of the sum
+    auto issue = [&](int s, int slot) {                        // past the end: the last values again, unused
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+            load_w.issue(s + h, mine + slot * kStage + h * kStep);
+            load_x.issue(s + h, mine + slot * kStage + h * kStep + kW);
+        }
+    };
+    if (first < last) {
+#pragma unroll
+        for (int b = 0; b < NB - 1; ++b) issue(first + b * G, b);
+        int slot = 0;
+        for (int s = first; s < last; s += G) {
+            wait_memory<(NB - 2) * kStageLoads>();
+            if (KS == 1) __builtin_amdgcn_s_barrier();         // everyone's part of this stage is here, and the slot
+                                                               // filled next has been read by everyone
+            issue(s + (NB - 1) * G, slot == 0 ? NB - 1 : slot - 1);
+            const char *tile = mine + slot * kStage;
+            slot = slot + 1 == NB ? 0 : slot + 1;
+            float a[G][TU][8], b[G][TT][8];
+#pragma unroll
+            for (int h = 0; h < G; ++h) {
+#pragma unroll
+                for (int i = 0; i < TU; ++i) TileRow<float>::read(tile + h * kStep, (wu * TU + i) * 16 + col, g, a[h][i]);
+#pragma unroll
+                for (int m = 0; m < TT; ++m) TileRow<IN>::read(tile + h * kStep + kW, (wt * TT + m) * 16 + col, g, b[h][m]);
+            }
+            if ((s + G) * 32 > end)                            // past the end of the sum
+#pragma unroll
+                for (int h = 0; h < G; ++h)
+#pragma unroll
+                    for (int i = 0; i < TU; ++i)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) a[h][i][e] = (s + h) * 32 + 8 * g < end ? a[h][i][e] : 0.f;
+#pragma unroll
+            for (int h = 0; h < G; ++h)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int m = 0; m < TT; ++m)
+#pragma unroll
+                        for (int i = 0; i < TU; ++i)
+                            acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][i][e], b[h][m][e], acc[i][m], 0, 0, 0);
+        }
+        wait_memory<0>();                                      // the last loads still write LDS
+    }
+    if (KS > 1) {                                              // the parts of the sum meet in the first wavefront
+        __shared__ f32x4 parts[KS][64];
+        parts[part][lane] = acc[0][0];
+        __syncthreads();
+        if (part) return;
+#pragma unroll
+        for (int q = 1; q < KS; ++q) acc[0][0] += parts[q][lane];
+    }
+#pragma unroll
+    for (int i = 0; i < TU; ++i) {
+        const int u = u0 + (wu * TU + i) * 16 + 4 * g;
+        f32x4 bias = load4(bias_a + u);
+        if (bias_b) bias += load4(bias_b + u);
+#pragma unroll
+        for (int m = 0; m < TT; ++m) {
+            const int n = n0 + (wt * TT + m) * 16 + col;
+            if (n < n_tokens) *reinterpret_cast<f32x4 *>(out + (size_t)n * units + u) = acc[i][m] + bias;
+        }
+    }
 }
 
-// The recurrence of one LSTM layer.  One workgroup of 4C threads per sequence: thread g owns gate
-// row g of W_hh (in registers) and, for g < C, the cell state of unit g.
+// ---- the recurrence -----------------------------------------------------------------------------
+// Sigmoid and tanh to about 2 ulp of their range: exponential by v_exp_f32, reciprocal with one Newton
+// step, and a Taylor polynomial of tanh below 1/4, where 2 / (1 + e) - 1 cancels (its next term,
+// 1382/155925 x^11, is below 2^-26 of tanh there).  The step of the recurrence is bound by the
+// instructions it issues, hence one straight line for both functions, told apart by three constants per
+// lane:  sigmoid(v) = 1 / (1 + exp(-v)),  tanh(v) = 2 / (1 + exp(-2v)) - 1.
+struct GateKind {
+    float scale, gain, small;      // of the exponent (base 2), of the reciprocal, bound of the polynomial
+};
+__device__ __forceinline__ GateKind gate_kind(bool is_tanh)
+{
+    constexpr float kLog2e = 1.44269504f;
+    return is_tanh ? GateKind{-2.f * kLog2e, 2.f, 0.25f} : GateKind{-kLog2e, 1.f, 0.f};
+}
+__device__ __forceinline__ float gate_value(float v, const GateKind &k)
+{
+    // an exponent of at most 126 keeps the Newton step away from infinity; NaN goes through
+    const float e = 1.f + __builtin_amdgcn_exp2f(__builtin_elementwise_minimum(v * k.scale, 126.f));
+    const float r = __builtin_amdgcn_rcpf(e);
+    const float n = fmaf(fmaf(-e, r, 1.f), r, r);
+    const float q = v * v;
+    const float t = v * fmaf(q, fmaf(q, fmaf(q, fmaf(q, 62.f / 2835.f, -17.f / 315.f), 2.f / 15.f), -1.f / 3.f), 1.f);
+    return fabsf(v) < k.small ? t : fmaf(k.gain, n, 1.f - k.gain);
+}
+
+constexpr int kSteps = 8;                                      // time steps per chunk of the hand-over between the layers
+
+template <int C>
+struct RecurrenceLds {
+    static constexpr int kSeg = C / 8, kSegPitch = kSeg + 4;   // the eight segments start in different banks
+    static constexpr int kRow = 8 * kSegPitch;
+    float h[2 * kSteps][kRow];                                 // the state after each step of two chunks
+    float pre[kSteps][4 * C];                                  // gate pre-activations of a chunk; a thread reads what it wrote
+    static constexpr int kInPitch = C + 16;
+    float in[2][kSteps * kInPitch];                            // layer 2's inputs of a chunk
+    int ticket;
+};
+
+// One LSTM layer over one sequence of T steps, by a workgroup of 4C threads.  Eight threads share the
+// eight gate rows of two units: each holds an eighth of the columns of all eight in registers, so that a
+// step reads only an eighth of the state per thread from LDS (with a whole gate row per thread the
+// 8 x 32 broadcast reads of 16 bytes took longer than the multiply-adds: 1.05 us a step at C = 128; with
+// quarters 0.65 us).  Slot j of lane l of the eight is row j ^ l, so that seven adds of permuted lanes
+// leave row l's sum in lane l; thread 4u+s then has gate s of unit u, the four gates meet in quad permutes
+// too, and a step has one barrier and no global access: pre-activations come and states go a chunk of
+// steps at a time.  What is left of a step is the issue of 128 multiply-adds and about 50 other
+// instructions per wavefront, two wavefronts per SIMD, and the latency from barrier to barrier.
+//   WAIT   pre arrives in chunks from another workgroup (progress in *arrived)
+//   POST   out is handed on to another workgroup (progress in *done: wavefronts x chunks)
+template <int C, bool WAIT, bool POST>
+__device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const float *__restrict__ w_hh, int T,
+                                           float *__restrict__ out, const int *arrived, int *done, RecurrenceLds<C> &lds)
+{
+    constexpr int kSeg = RecurrenceLds<C>::kSeg, kSegPitch = RecurrenceLds<C>::kSegPitch, kRow = RecurrenceLds<C>::kRow;
+    const int tid = threadIdx.x, u = tid >> 2, s = tid & 3;
+    const int l8 = tid & 7;
+    float w[8][kSeg];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int id = j ^ l8;                                 // gate id & 3 of unit 2 * (tid / 8) + (id >> 2)
+        const float *row = w_hh + (size_t)((id & 3) * C + (tid >> 3) * 2 + (id >> 2)) * C + l8 * kSeg;
+#pragma unroll
+        for (int i = 0; i < kSeg; i += 4) {
+            const f32x4 v = load4(row + i);
+            w[j][i] = v[0];
+            w[j][i + 1] = v[1];
+            w[j][i + 2] = v[2];
+            w[j][i + 3] = v[3];
+        }
+    }
+    const __amdgpu_buffer_rsrc_t pre_rsrc = make_rsrc(pre, (uint32_t)T * 4 * C * 4);
+    const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out, (uint32_t)T * C * 4);
+    const int my_gate = (s * C + u) * 4;
+    // this unit's place in a row of the state; the quad's other lanes write to the row's unused places
+    const int h_out = s == 0 ? (u / kSeg) * kSegPitch + u % kSeg : (u % 8) * kSegPitch + kSeg + s;
+    const int chunks = (T + kSteps - 1) / kSteps;
+    if (tid < kRow) lds.h[2 * kSteps - 1][tid] = 0.f;          // "the step before the first"
+    int seen = 0;
+    float next[kSteps];
+    auto fetch = [&](int c) {                                  // past the end: zeros (the descriptor ends there)
+        if (WAIT)
+            while (__builtin_amdgcn_readfirstlane(seen) < c + 1) seen = peek(arrived);
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) next[i] = load_f32<WAIT ? kAgent : 0>(pre_rsrc, (c * kSteps + i) * 4 * C * 4 + my_gate);
+        if (WAIT) seen = peek(arrived);                        // looked at when the next chunk is due
+    };
+    // chunk c's states, two per thread, from LDS to global memory (past the end: dropped)
+    auto store_chunk = [&](int c) {
+        const int step = 2 * tid / C, unit = 2 * tid % C;
+        const f32x2 v = *reinterpret_cast<const f32x2 *>(&lds.h[(c & 1) * kSteps + step][(unit / kSeg) * kSegPitch + unit % kSeg]);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), out_rsrc, ((c * kSteps + step) * C + unit) * 4, 0,
+                                              POST ? kAgent : 0);
+    };
+    // a wavefront's part of one more chunk of states has left for good
+    auto post = [&]() {
+        wait_memory<0>();
+        if ((tid & 63) == 0) __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    fetch(0);
+    lds_barrier();
+    const GateKind mine = gate_kind(s == 2), of_cell = gate_kind(true);
+    float cell = 0.f;
+    const float *h_in = &lds.h[2 * kSteps - 1][l8 * kSegPitch];
+    float *row = nullptr;
+    const float *z_in = nullptr;
+    auto step = [&]() {
+        float acc[8] = {};
+        acc[0] = *z_in;
+#pragma unroll
+        for (int k = 0; k < kSeg; k += 4) {
+            const f32x4 hv = load4(h_in + k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j] = fmaf(w[j][k + e], hv[e], acc[j]);
+        }
+        // lane ^ 7 (mirrored halves) holds the row in the slot ^ 7; then the quad
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] += quad<kHalfMirror>(acc[j ^ 7]);
+        const float z = (acc[0] + quad<kXor1>(acc[1])) + (quad<kXor2>(acc[2]) + quad<kXor3>(acc[3]));
+        const float a = gate_value(z, mine);
+        cell = quad<0x55>(a) * cell + quad<0x00>(a) * quad<0xAA>(a);
+        row[h_out] = quad<0xFF>(a) * gate_value(cell, of_cell);
+        h_in = row + l8 * kSegPitch;
+        row += kRow;
+        z_in += 4 * C;
+        lds_barrier();
+    };
+    for (int c = 0; c < chunks; ++c) {
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) lds.pre[i][tid] = next[i];
+        if (c > 0) store_chunk(c - 1);
+        const int n = __builtin_amdgcn_readfirstlane(min(kSteps, T - c * kSteps));
+        row = lds.h[(c & 1) * kSteps];
+        z_in = &lds.pre[0][tid];
+        // The store of the previous chunk's states gets three steps to complete, the loads of the next
+        // chunk's pre-activations get the second half of this one.
+        int i = 0;
+#pragma clang loop unroll(disable)
+        for (; i < min(n, 3); ++i) step();
+        if (POST && c > 0) post();
+#pragma clang loop unroll(disable)
+        for (; i < min(n, kSteps / 2); ++i) step();
+        if (c + 1 < chunks) fetch(c + 1);
+#pragma clang loop unroll(disable)
+        for (; i < n; ++i) step();
+    }
+    store_chunk(chunks - 1);
+    if (POST) post();
+}
+
+// D[4 x 64] += A[4 x 16] B[16 x 64] as 16 instructions of 16 4x4 blocks: lane l gives A[l % 4][l / 4]
+// (every instruction broadcasts one column of it to all blocks) and B[0..15][l], and holds D[0..3][l].
+template <int... J>
+__device__ __forceinline__ void mfma_rows(float a, const float *b, f32x4 &even, f32x4 &odd, std::integer_sequence<int, J...>)
+{
+    ((((J & 1) ? odd : even) = __builtin_amdgcn_mfma_f32_4x4x1f32(a, b[J], (J & 1) ? odd : even, 4, J, 0)), ...);
+}
+
+// Layer 2's gate pre-activations for one sequence, a chunk of kSteps tokens at a time as layer 1
+// finishes them.  They replace layer 1's in `pre`: layer 1 has consumed a token's before it hands the
+// token on.  A thread keeps its gate row of W_ih in registers, the tokens are the rows of a matrix
+// product of few rows (blocks of 4: a 16-row product took 3.4 us a chunk and held layer 2 up, 5 us
+// between chunks), and the results leave in whole lines.
+template <int C>
+__device__ __forceinline__ void gates_between(const float *__restrict__ h1, const float *__restrict__ w_ih,
+                                              const float *__restrict__ b_ih, const float *__restrict__ b_hh, int T,
+                                              float *__restrict__ pre, const int *arrived, int *done, RecurrenceLds<C> &lds)
+{
+    constexpr int kPitch = RecurrenceLds<C>::kInPitch;
+    static_assert(kSteps == 8 && kSteps * C / 4 <= 4 * C, "two blocks of four tokens, one 16-byte load per thread and chunk");
+    const int tid = threadIdx.x, lane = tid & 63;
+    float w[C];                                                // row tid
+#pragma unroll
+    for (int k = 0; k < C; k += 4) {
+        const f32x4 v = load4(w_ih + (size_t)tid * C + k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[k + e] = v[e];
+    }
+    const float bias = b_ih[tid] + b_hh[tid];
+    const __amdgpu_buffer_rsrc_t h_rsrc = make_rsrc(h1, (uint32_t)T * C * 4);
+    const __amdgpu_buffer_rsrc_t pre_rsrc = make_rsrc(pre, (uint32_t)T * 4 * C * 4);
+    const int chunks = (T + kSteps - 1) / kSteps;
+    int seen = 0;
+    for (int c = 0; c < chunks; ++c) {
+        while (__builtin_amdgcn_readfirstlane(seen) < (c + 1) * (C / 16)) seen = peek(arrived);
+        float *in = lds.in[c & 1];
+        if (tid < kSteps * C / 4) {                            // past the end: zeros
+            const i32x4 v = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(h_rsrc, (c * kSteps * C + tid * 4) * 4, 0, kAgent));
+            *reinterpret_cast<i32x4 *>(in + (tid / (C / 4)) * kPitch + (tid % (C / 4)) * 4) = v;
+        }
+        lds_barrier();
+        f32x4 even[2], odd[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            even[q] = f32x4{bias, bias, bias, bias};
+            odd[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        const float *ip = in + (lane & 3) * kPitch + (lane >> 2);
+#pragma unroll
+        for (int k = 0; k < C / 16; ++k)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                mfma_rows(ip[q * 4 * kPitch + k * 16], w + k * 16, even[q], odd[q], std::make_integer_sequence<int, 16>());
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)                        // past the end: dropped
+                store_f32<kAgent>(pre_rsrc, ((c * kSteps + q * 4 + i) * 4 * C + tid) * 4, even[q][i] + odd[q][i]);
+        wait_memory<0>();
+        lds_barrier();
+        if (tid == 0) publish(done, c + 1);
+    }
+}
+
+// Both LSTM layers of every sequence in one launch of 3 workgroups per sequence: layer 1, the gate
+// pre-activations between the layers, layer 2; the latter two work behind layer 1, chunk by chunk,
+// so that a call takes T plus about 30 steps instead of 2T.  A workgroup takes its role by ticket:
+// first all of layer 1, then all in between, then all of layer 2.  Tickets are drawn by workgroups
+// that run, so whatever a workgroup waits for is done by a workgroup that already runs and waits, if
+// at all, for a lower ticket only; layer 1 waits for nobody.  Hence every wait ends, whatever the
+// order in which workgroups are started and whatever else runs on the GPU.
+template <int C>
+__global__ __launch_bounds__(4 * C) void hash_recurrence(float *pre, const float *__restrict__ w_hh1,
+                                                         const float *__restrict__ w_ih2, const float *__restrict__ w_hh2,
+                                                         const float *__restrict__ b_ih2, const float *__restrict__ b_hh2,
+                                                         int n_seq, int T, float *h1, float *h2, int *counters)
+{
+    __shared__ __attribute__((aligned(16))) RecurrenceLds<C> lds;
+    if (threadIdx.x == 0) lds.ticket = __hip_atomic_fetch_add(counters, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int ticket = __builtin_amdgcn_readfirstlane(lds.ticket);
+    const int role = ticket / n_seq, seq = ticket % n_seq;
+    float *p = pre + (size_t)seq * T * 4 * C, *a = h1 + (size_t)seq * T * C, *b = h2 + (size_t)seq * T * C;
+    int *layer1_done = counters + kLine * (1 + 2 * seq), *gates_done = layer1_done + kLine;
+    if (role == 0) lstm_layer<C, false, true>(p, w_hh1, T, a, nullptr, layer1_done, lds);
+    else if (role == 1) gates_between<C>(a, w_ih2, b_ih2, b_hh2, T, p, layer1_done, gates_done, lds);
+    else lstm_layer<C, true, false>(p, w_hh2, T, b, gates_done, nullptr, lds);
+}
+
+// One layer alone, a workgroup per sequence: for batches of so many sequences that three workgroups
+// for each would not all run at a time, where doing the layers one after the other loses nothing.
 template <int C>
 __global__ __launch_bounds__(4 * C) void hash_lstm(const float *__restrict__ pre, const float *__restrict__ w_hh, int T,
                                                    float *__restrict__ out)
 {
-    __shared__ float h[C];
-    __shared__ float gates[4 * C];
-    const int b = blockIdx.x, g = threadIdx.x;
-    float w[C];
-#pragma unroll
-    for (int i = 0; i < C; ++i) w[i] = w_hh[(size_t)g * C + i];
-    if (g < C) h[g] = 0.f;
-    float cell = 0.f;
-    __syncthreads();
-    for (int t = 0; t < T; ++t) {
-        const size_t n = (size_t)b * T + t;
-        float acc = pre[n * 4 * C + g];
-#pragma unroll
-        for (int i = 0; i < C; ++i) acc += w[i] * h[i];
-        gates[g] = (g >= 2 * C && g < 3 * C) ? tanhf(acc) : sigmoidf_(acc);
-        __syncthreads();
-        if (g < C) {
-            cell = gates[C + g] * cell + gates[g] * gates[2 * C + g];
-            const float hv = gates[3 * C + g] * tanhf(cell);
-            h[g] = hv;
-            out[n * C + g] = hv;
-        }
-        __syncthreads();
-    }
+    __shared__ __attribute__((aligned(16))) RecurrenceLds<C> lds;
+    lstm_layer<C, false, false>(pre + (size_t)blockIdx.x * T * 4 * C, w_hh, T, out + (size_t)blockIdx.x * T * C, nullptr,
+                                nullptr, lds);
 }
 
-// Sparse attention + residual for one query token: r[t] = c0[t] + sum_u sparsemax_u(h2[t] . h2[u]) h2[u].
-// One wavefront per token; scores of the sequence in LDS.
+// ---- attention ----------------------------------------------------------------------------------
+// Sum / maximum over the 32 lanes of a half wavefront.
+__device__ __forceinline__ float half_sum(float v)
+{
+    v = row_sum(v);
+    return v + __shfl_xor(v, 16, 64);
+}
+__device__ __forceinline__ float half_max(float v)
+{
+    v = row_max(v);
+    return fmaxf(v, __shfl_xor(v, 16, 64));
+}
+
+// Sparse attention + residual: r[t] = c0[t] + sum_u sparsemax_u(h2[t] . h2[u]) h2[u], for `queries` (at
+// most 16) consecutive tokens of one sequence per workgroup of 8 wavefronts.  Scores and weights sit in
+// LDS, [queries][pitch]; both products run on the matrix units with the queries as columns.
+// SparseMax: the threshold tau with sum_u max(s_u - tau, 0) = 1 is (sum of the support - 1) / size of the
+// support; starting from the support of max - 1, taking the closed form on the scores above it and
+// dropping what falls below it ends, after a few rounds, with the support that reproduces itself.
 template <int C>
-__global__ __launch_bounds__(64) void hash_attention(const float *__restrict__ h2, const float *__restrict__ c0, int T,
-                                                     float *__restrict__ r)
+__global__ __launch_bounds__(512) void hash_attention(const float *__restrict__ h2, const float *__restrict__ c0, int T,
+                                                      int queries, int blocks_per_seq, int pitch, float *__restrict__ r)
 {
-    extern __shared__ float s[];                               // [T] scores, then weights
-    __shared__ float q[C];
-    const int n = blockIdx.x, lane = threadIdx.x;
-    const int seq0 = (n / T) * T;                              // first token of this sequence
-    for (int i = lane; i < C; i += 64) q[i] = h2[(size_t)n * C + i];
-    __syncthreads();
-    float mx = -FLT_MAX;
-    for (int u = lane; u < T; u += 64) {
-        const float *k = h2 + (size_t)(seq0 + u) * C;
-        float acc = 0.f;
-#pragma unroll 8
-        for (int i = 0; i < C; ++i) acc += q[i] * k[i];
-        s[u] = acc;
-        mx = fmaxf(mx, acc);
-    }
-    mx = wave_max(mx);
-    __syncthreads();
-    // threshold: sum_u max(s_u - tau, 0) is 1 somewhere in [max - 1, max]
-    float lo = mx - 1.f, hi = mx;
-    for (int it = 0; it < 30; ++it) {
-        const float tau = 0.5f * (lo + hi);
-        float part = 0.f;
-        for (int u = lane; u < T; u += 64) part += fmaxf(s[u] - tau, 0.f);
-        if (wave_sum(part) >= 1.f) lo = tau;
-        else hi = tau;
-    }
-    // closed form on the support the bisection found
-    float sum_s = 0.f, cnt = 0.f;
-    for (int u = lane; u < T; u += 64)
-        if (s[u] > lo) {
-            sum_s += s[u];
-            cnt += 1.f;
+    extern __shared__ __attribute__((aligned(16))) float s[];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, col = lane & 15, g = lane >> 4;
+    const int seq = blockIdx.x / blocks_per_seq, t0 = (blockIdx.x % blocks_per_seq) * queries;
+    const int nq = min(queries, T - t0);
+    const float *hs = h2 + (size_t)seq * T * C;
+    const int T16 = (T + 15) & ~15;
+    f32x4 q[C / 16];
+#pragma unroll
+    for (int k = 0; k < C / 16; ++k) q[k] = load4(hs + (size_t)(t0 + min(col, nq - 1)) * C + k * 16 + 4 * g);
+    for (int u0 = wv * 16; u0 < T16; u0 += 8 * 16) {
+        const float *key = hs + (size_t)min(u0 + col, T - 1) * C + 4 * g;
+        f32x4 k4[C / 16];
+#pragma unroll
+        for (int k = 0; k < C / 16; ++k) k4[k] = load4(key + k * 16);
+        loads_issued();
+        f32x4 d0 = {}, d1 = {};
+#pragma unroll
+        for (int k = 0; k < C / 16; k += 2) {
+            d0 = mfma4(k4[k], q[k], d0);
+            d1 = mfma4(k4[k + 1], q[k + 1], d1);
         }
-    sum_s = wave_sum(sum_s);
-    cnt = wave_sum(cnt);
-    const float tau = cnt > 0.f ? (sum_s - 1.f) / cnt : lo;
-    for (int u = lane; u < T; u += 64) s[u] = fmaxf(s[u] - tau, 0.f);
+        d0 += d1;
+        if (col < queries) *reinterpret_cast<f32x4 *>(s + col * pitch + u0 + 4 * g) = d0;
+    }
     __syncthreads();
-    for (int i = lane; i < C; i += 64) {
-        float acc = c0[(size_t)n * C + i];
-        for (int u = 0; u < T; ++u) {
-            const float p = s[u];                              // same address for every lane: a broadcast
-            if (p > 0.f) acc += p * h2[(size_t)(seq0 + u) * C + i];
+    for (int row = wv * 2 + (lane >> 5); row < ((nq + 1) & ~1); row += 16) {   // both halves of a wavefront take part
+        float *z = s + min(row, nq - 1) * pitch;
+        const int l = lane & 31;
+        // the first kHeld * 32 scores of a row in registers, what is beyond stays in LDS
+        constexpr int kHeld = 12;
+        float held[kHeld];
+        float mx = -FLT_MAX;
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i) held[i] = i * 32 + l < T ? z[i * 32 + l] : -FLT_MAX;
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i) mx = fmaxf(mx, held[i]);
+        for (int u = kHeld * 32 + l; u < T; u += 32) mx = fmaxf(mx, z[u]);
+        mx = half_max(mx);
+        float tau = -1.f, size = 0.f;                          // relative to the largest score
+        for (;;) {
+            float sum = 0.f, cnt = 0.f;
+            auto take = [&](float score) {
+                const float v = score - mx;
+                sum += v > tau ? v : 0.f;
+                cnt += v > tau ? 1.f : 0.f;
+            };
+#pragma unroll
+            for (int i = 0; i < kHeld; i += 4)
+                if (i * 32 < T) {
+#pragma unroll
+                    for (int e = i; e < i + 4; ++e) take(held[e]);
+                }
+            for (int u = kHeld * 32 + l; u < T; u += 32) take(z[u]);
+            sum = half_sum(sum);
+            cnt = half_sum(cnt);
+            if (!(cnt > 0.f) || (size > 0.f && cnt >= size)) break;   // the support stands: it shrinks or the loop ends
+            tau = (sum - 1.f) / cnt;
+            size = cnt;
         }
-        r[(size_t)n * C + i] = acc;
+        if (row < nq) {
+#pragma unroll
+            for (int i = 0; i < kHeld; ++i)
+                if (i * 32 + l < T16) z[i * 32 + l] = i * 32 + l < T ? fmaxf(held[i] - mx - tau, 0.f) : 0.f;
+            for (int u = kHeld * 32 + l; u < T16; u += 32) z[u] = u < T ? fmaxf(z[u] - mx - tau, 0.f) : 0.f;
+        }
+    }
+    __syncthreads();
+    if (wv * 16 >= C) return;
+    // r^T[c, query] = sum_u h2[u, c] p[query, u]: 16 columns c per wavefront
+    const int c = wv * 16;
+    f32x4 acc = {};
+    const float *p = s + min(col, nq - 1) * pitch + 4 * g;
+    const float *hv = hs + c + col;
+    for (int u0 = 0; u0 < T16; u0 += 64) {                     // four blocks of 16 keys' loads in flight
+        f32x4 pv[4], v[4];
+        bool any = false;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            pv[b] = u0 + b * 16 < T16 ? load4(p + u0 + b * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+            any |= pv[b][0] > 0.f || pv[b][1] > 0.f || pv[b][2] > 0.f || pv[b][3] > 0.f;
+        }
+        if (!__any(any)) continue;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[b][j] = hv[(size_t)min(u0 + b * 16 + 4 * g + j, T - 1) * C];
+        loads_issued();
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc = mfma4(v[b], pv[b], acc);
+    }
+    if (col < nq) {
+        const size_t at = ((size_t)seq * T + t0 + col) * C + c + 4 * g;
+        *reinterpret_cast<f32x4 *>(r + at) = acc + load4(c0 + at);
     }
 }
 
-// Heads: per MoE layer l the E logits of a token, their SoftMax, and the k most probable experts.
-// One workgroup of 256 threads per block of TB tokens; wavefront w takes the (token, layer) pairs
-// w, w+4, ...
-template <int C, int TB>
+// ---- heads --------------------------------------------------------------------------------------
+// Per MoE layer the E logits of a token, their SoftMax, and the k most probable experts.  A workgroup
+// takes TT*16 tokens and one layer: all operands go to LDS at once, its four wavefronts make NT tiles of
+// 16 experts in turn (matrix product, experts as rows), hand the logits over in LDS, and then take a
+// token per 16 lanes with NT logits in each lane's registers.
+template <int C, int NT, int TT>
+constexpr int heads_lds_bytes() { return C / 32 * (NT + TT) * 16 * TileRow<float>::kBytes; }
+
+template <int C, int NT, int TT>
 __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, const float *__restrict__ w_out,
-                                                  const float *__restrict__ b_out, int L, int E, int top_k,
-                                                  int n_tokens, int32_t *__restrict__ ids, float *__restrict__ alpha)
+                                                  const float *__restrict__ b_out, int E, int top_k, int n_tokens,
+                                                  int32_t *__restrict__ ids, float *__restrict__ alpha)
 {
-    extern __shared__ __attribute__((aligned(16))) float logit[];                           // [TB][L*E]
-    __shared__ __attribute__((aligned(16))) float row[TB][C];
-    const int n0 = blockIdx.x * TB, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nb = min(TB, n_tokens - n0);
-    const int LE = L * E;
-    for (int i = tid; i < TB * C; i += 256) (&row[0][0])[i] = i / C < nb ? r[(size_t)n0 * C + i] : 0.f;
-    __syncthreads();
-    for (int o = tid; o < LE; o += 256) {
-        const float4 *w = reinterpret_cast<const float4 *>(w_out + (size_t)o * C);
-        float acc[TB];
+    constexpr int kPitch = NT * 16 + 16, kMine = (NT + 3) / 4, kSteps32 = C / 32;
+    constexpr int kW = NT * 16 * TileRow<float>::kBytes, kStage = kW + TT * 16 * TileRow<float>::kBytes;
+    typedef TileLoader<float, NT * 16, 4> LoadW;
+    typedef TileLoader<float, TT * 16, 4> LoadX;
+    constexpr int kStepLoads = LoadW::kLoads + LoadX::kLoads;
+    static_assert(TT * 16 * kPitch * 4 <= heads_lds_bytes<C, NT, TT>(), "the logits replace the operands");
+    static_assert((kSteps32 - 1) * kStepLoads <= 63, "vmcnt range");
+    extern __shared__ __attribute__((aligned(1024))) char tiles[];
+    float *logit = reinterpret_cast<float *>(tiles);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15, g = lane >> 4;
+    const int l = blockIdx.y, n0 = blockIdx.x * TT * 16;
+    {
+        const LoadW load_w(w_out + (size_t)l * E * C, E, C, lane, wv);
+        const LoadX load_x(r + (size_t)n0 * C, n_tokens - n0, C, lane, wv);
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) acc[tb] = b_out[o];
-#pragma unroll 4
-        for (int i = 0; i < C / 4; ++i) {
-            const float4 wv4 = w[i];
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) {
-                const float4 xv = *reinterpret_cast<const float4 *>(&row[tb][4 * i]);
-                acc[tb] += xv.x * wv4.x;
-                acc[tb] += xv.y * wv4.y;
-                acc[tb] += xv.z * wv4.z;
-                acc[tb] += xv.w * wv4.w;
-            }
+        for (int s = 0; s < kSteps32; ++s) {
+            load_w.issue(s, tiles + s * kStage);
+            load_x.issue(s, tiles + s * kStage + kW);
         }
+    }
+    f32x4 acc[kMine][TT] = {};
+    auto multiply = [&](int s) {
+        const char *tile = tiles + s * kStage;
+        float b[TT][8];
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) logit[tb * LE + o] = acc[tb];
+        for (int m = 0; m < TT; ++m) TileRow<float>::read(tile + kW, m * 16 + col, g, b[m]);
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            if (NT < 4 && i * 4 + wv >= NT) continue;
+            float a[8];
+            TileRow<float>::read(tile, (i * 4 + wv) * 16 + col, g, a);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int m = 0; m < TT; ++m)
+                    acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[m][e], acc[i][m], 0, 0, 0);
+        }
+    };
+    wait_memory<(kSteps32 - 1) * kStepLoads>();
+    __builtin_amdgcn_s_barrier();
+    multiply(0);
+    wait_memory<(kSteps32 - 2) * kStepLoads>();
+    __builtin_amdgcn_s_barrier();
+    multiply(1);
+    if (kSteps32 > 2) {
+        wait_memory<kStepLoads>();
+        __builtin_amdgcn_s_barrier();
+        multiply(2);
+        wait_memory<0>();
+        __builtin_amdgcn_s_barrier();
+        multiply(3);
+    }
+    lds_barrier();                                             // every operand has been read
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        const int tile = i * 4 + wv;
+        if (NT < 4 && tile >= NT) continue;
+        f32x4 bias;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias[e] = b_out[l * E + min(tile * 16 + 4 * g + e, E - 1)];
+#pragma unroll
+        for (int m = 0; m < TT; ++m)
+            *reinterpret_cast<f32x4 *>(&logit[(m * 16 + col) * kPitch + tile * 16 + 4 * g]) = acc[i][m] + bias;
     }
     __syncthreads();
-    for (int pair = wv; pair < nb * L; pair += 4) {
-        const int tb = pair / L, l = pair % L, n = n0 + tb;
-        float *z = logit + tb * LE + l * E;
-        float mx = -FLT_MAX;
-        for (int e = lane; e < E; e += 64) mx = fmaxf(mx, z[e]);
-        mx = wave_max(mx);
-        float sum = 0.f;
-        for (int e = lane; e < E; e += 64) sum += __expf(z[e] - mx);
-        sum = wave_sum(sum);
+#pragma unroll 1
+    for (int m = 0; m < TT; ++m) {
+        const int tok = m * 16 + wv * 4 + g, n = n0 + tok;
+        float z[NT];                                           // logits of experts col, col + 16, ...
+#pragma unroll
+        for (int i = 0; i < NT; ++i) z[i] = i * 16 + col < E ? logit[tok * kPitch + i * 16 + col] : -FLT_MAX;
+        float mx = -FLT_MAX, sum = 0.f;
         for (int j = 0; j < top_k; ++j) {
             // largest remaining logit, ties to the lower expert id
             float best = -FLT_MAX;
             int arg = E;
-            for (int e = lane; e < E; e += 64)
-                if (z[e] > best) {
-                    best = z[e];
-                    arg = e;
-                }
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const float ob = __shfl_xor(best, o, 64);
-                const int oa = __shfl_xor(arg, o, 64);
-                if (ob > best || (ob == best && oa < arg)) {
-                    best = ob;
-                    arg = oa;
+            for (int i = 0; i < NT; ++i)
+                if (z[i] > best) {
+                    best = z[i];
+                    arg = i * 16 + col;
                 }
+            auto meet = [&](float ob, int oa) {
+                const bool other = ob > best || (ob == best && oa < arg);
+                best = other ? ob : best;
+                arg = other ? oa : arg;
+            };
+            meet(quad<kXor1>(best), dpp<kXor1>(arg));
+            meet(quad<kXor2>(best), dpp<kXor2>(arg));
+            meet(quad<kHalfMirror>(best), dpp<kHalfMirror>(arg));
+            meet(quad<kMirror>(best), dpp<kMirror>(arg));
+            if (j == 0) {
+                mx = best;
+#pragma unroll
+                for (int i = 0; i < NT; ++i) sum += __expf(z[i] - mx);     // an expert that is not there adds nothing
+                sum = row_sum(sum);
             }
-            if (lane == 0) {
+            if (col == 0 && n < n_tokens) {
                 const size_t at = ((size_t)l * n_tokens + n) * top_k + j;
                 ids[at] = arg < E ? arg : 0;
                 alpha[at] = __expf(best - mx) / sum;
             }
-            if (arg < E && lane == (arg & 63)) z[arg] = -FLT_MAX;          // taken
-            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+                if (i * 16 + col == arg) z[i] = -FLT_MAX;                  // taken
         }
     }
 }
+
+// ---- one call -----------------------------------------------------------------------------------
+// Sequences whose layers run side by side: three workgroups each, one per compute unit (a workgroup of
+// the recurrence fills the registers of its compute unit).
+constexpr int kSideBySide = 256 / 3;
+constexpr int kMaxScoreBytes = 144 * 1024;                     // LDS for an attention block's scores
 
 template <int C>
 int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, int32_t *ids, float *alpha, float *ws,
@@ -297,41 +821,64 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
     // workspace
     float *c0 = ws, *pre = c0 + (size_t)N * C, *h1 = pre + (size_t)N * 4 * C, *h2 = h1 + (size_t)N * C,
           *r = h2 + (size_t)N * C;
-    // Tokens per workgroup of the dense stages: 8 when that still gives every compute unit several
-    // workgroups, fewer for short batches (one 128-token sequence: 1, as many workgroups as tokens),
-    // and never more than fit 48 KiB of LDS.
-    constexpr size_t kLdsCap = 48 * 1024;
-    const int want = N >= 4096 ? kTokenBlock : N >= 1024 ? 2 : 1;
-    auto block_for = [&](size_t bytes_per_token) {
-        int tb = want;
-        while (tb > 1 && tb * bytes_per_token > kLdsCap) tb = tb == kTokenBlock ? 2 : 1;
-        return tb;
-    };
-    auto blocks = [&](int tb) { return dim3((N + tb - 1) / tb); };
-    const size_t x_bytes = d * sizeof(float), le_bytes = (size_t)sh.L * sh.E * sizeof(float);
+    int *counters = reinterpret_cast<int *>(r);                // N*C words, of which a sequence needs 2*kLine: C >= 4*kLine
+    static_assert(C >= 4 * kLine, "counters fit");
     const __bf16 *xb = (const __bf16 *)x;
-    switch (block_for(x_bytes)) {
-        case kTokenBlock: hipLaunchKernelGGL((hash_compress<C, kTokenBlock>), blocks(kTokenBlock), dim3(C), kTokenBlock * x_bytes, st, xb, w_in, b_in, d, N, c0); break;
-        case 2: hipLaunchKernelGGL((hash_compress<C, 2>), blocks(2), dim3(C), 2 * x_bytes, st, xb, w_in, b_in, d, N, c0); break;
-        default: hipLaunchKernelGGL((hash_compress<C, 1>), blocks(1), dim3(C), x_bytes, st, xb, w_in, b_in, d, N, c0); break;
-    }
+    // Tiles: as large as leave every compute unit (nearly) one workgroup.
+    const int n_counters = n_seq <= kSideBySide ? (int)counter_words(n_seq) : 0;
+    auto dense = [&](auto kernel, int tokens, int rows, auto in, const float *w, const float *ba, const float *bb, int k,
+                     int units, float *out, int n_clear) {
+        hipLaunchKernelGGL(kernel, dim3((N + tokens - 1) / tokens, units / rows), dim3(256), 0, st, in, w, ba, bb, k, units, N, out,
+                           counters, n_clear);
+    };
+    if (N >= 6144) dense(hash_dense<2, 2, 2, 2, 1, 2, 4, __bf16>, 64, 64, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
+    else if (N >= 2048) dense(hash_dense<1, 2, 2, 2, 1, 2, 4, __bf16>, 64, 32, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
+    else dense(hash_dense<1, 1, 1, 1, 4, 2, 4, __bf16>, 16, 16, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
     auto gates = [&](const float *in, const float *w_ih, const float *b_ih, const float *b_hh) {
-        switch (want) {
-            case kTokenBlock: hipLaunchKernelGGL((hash_gates_in<C, kTokenBlock>), blocks(kTokenBlock), dim3(4 * C), 0, st, in, w_ih, b_ih, b_hh, N, pre); break;
-            case 2: hipLaunchKernelGGL((hash_gates_in<C, 2>), blocks(2), dim3(4 * C), 0, st, in, w_ih, b_ih, b_hh, N, pre); break;
-            default: hipLaunchKernelGGL((hash_gates_in<C, 1>), blocks(1), dim3(4 * C), 0, st, in, w_ih, b_ih, b_hh, N, pre); break;
-        }
+        if (N >= 2048) dense(hash_dense<2, 2, 2, 2, 1, 2, 2, float>, 64, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
+        else dense(hash_dense<1, 1, 4, 1, 1, 2, 3, float>, 16, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
     };
     gates(c0, w_ih1, b_ih1, b_hh1);
-    hipLaunchKernelGGL(hash_lstm<C>, dim3(n_seq), dim3(4 * C), 0, st, pre, w_hh1, T, h1);
-    gates(h1, w_ih2, b_ih2, b_hh2);
-    hipLaunchKernelGGL(hash_lstm<C>, dim3(n_seq), dim3(4 * C), 0, st, pre, w_hh2, T, h2);
-    hipLaunchKernelGGL(hash_attention<C>, dim3(N), dim3(64), T * sizeof(float), st, h2, c0, T, r);
-    switch (block_for(le_bytes)) {
-        case kTokenBlock: hipLaunchKernelGGL((hash_heads<C, kTokenBlock>), blocks(kTokenBlock), dim3(256), kTokenBlock * le_bytes, st, r, w_out, b_out, sh.L, sh.E, sh.top_k, N, ids, alpha); break;
-        case 2: hipLaunchKernelGGL((hash_heads<C, 2>), blocks(2), dim3(256), 2 * le_bytes, st, r, w_out, b_out, sh.L, sh.E, sh.top_k, N, ids, alpha); break;
-        default: hipLaunchKernelGGL((hash_heads<C, 1>), blocks(1), dim3(256), le_bytes, st, r, w_out, b_out, sh.L, sh.E, sh.top_k, N, ids, alpha); break;
+    if (n_seq <= kSideBySide) {
+        hipLaunchKernelGGL(hash_recurrence<C>, dim3(3 * n_seq), dim3(4 * C), 0, st, pre, w_hh1, w_ih2, w_hh2, b_ih2, b_hh2,
+                           n_seq, T, h1, h2, counters);
+    } else {
+        hipLaunchKernelGGL(hash_lstm<C>, dim3(n_seq), dim3(4 * C), 0, st, pre, w_hh1, T, h1);
+        gates(h1, w_ih2, b_ih2, b_hh2);
+        hipLaunchKernelGGL(hash_lstm<C>, dim3(n_seq), dim3(4 * C), 0, st, pre, w_hh2, T, h2);
     }
+    // 16 queries per attention block, or 8 where the scores of 16 would not fit the LDS
+    const int pitch = (T + 15) / 16 * 16 + 4;
+    const int queries = 16 * pitch * 4 <= kMaxScoreBytes ? 16 : 8;
+    const int score_bytes = queries * pitch * 4, blocks_per_seq = (T + queries - 1) / queries;
+    if (score_bytes > 64 * 1024) {
+        static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&hash_attention<C>),
+                                                              hipFuncAttributeMaxDynamicSharedMemorySize, kMaxScoreBytes);
+        if (allowed != hipSuccess) return (int)allowed;
+    }
+    hipLaunchKernelGGL(hash_attention<C>, dim3(n_seq * blocks_per_seq), dim3(512), score_bytes, st, h2, c0, T, queries,
+                       blocks_per_seq, pitch, r);
+    hipError_t err = hipSuccess;
+    auto heads = [&](auto nt, auto tt) {
+        constexpr int NT = decltype(nt)::value, TT = decltype(tt)::value, kBytes = heads_lds_bytes<C, NT, TT>();
+        if (kBytes > 64 * 1024) {
+            static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&hash_heads<C, NT, TT>),
+                                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+            err = allowed;
+            if (err != hipSuccess) return;
+        }
+        hipLaunchKernelGGL((hash_heads<C, NT, TT>), dim3((N + TT * 16 - 1) / (TT * 16), sh.L), dim3(256), kBytes, st, r, w_out,
+                           b_out, sh.E, sh.top_k, N, ids, alpha);
+    };
+    auto heads_of = [&](auto tt) {
+        if (sh.E <= 16) heads(std::integral_constant<int, 1>(), tt);
+        else if (sh.E <= 64) heads(std::integral_constant<int, 4>(), tt);
+        else if (sh.E <= 128) heads(std::integral_constant<int, 8>(), tt);
+        else heads(std::integral_constant<int, 16>(), tt);
+    };
+    if (N >= 2048) heads_of(std::integral_constant<int, 2>());
+    else heads_of(std::integral_constant<int, 1>());
+    if (err != hipSuccess) return (int)err;
     return (int)hipGetLastError();
 }
 

@@ -83,6 +83,38 @@ def test_hash_forward_against_oracle(d, C, L, E, k, n_seq, T):
     say(f"  max |alpha - oracle| {worst:.2e}")
 
 
+@pytest.mark.parametrize("d,C,L,E,k,n_seq,T", [
+    # around the 8 time steps that the two LSTM layers hand over at a time
+    (64, 128, 1, 4, 1, 2, 7),
+    (64, 64, 1, 4, 1, 1, 8),
+    (64, 128, 1, 4, 1, 1, 9),
+    (64, 128, 1, 4, 1, 1, 12),
+    # the most sequences whose layers run side by side, and one more
+    (64, 64, 1, 4, 1, 85, 11),
+    (64, 64, 1, 4, 1, 86, 11),
+    # d_model with a remainder of 8 / 24 / 40 over a stage of the dense stage's operands; less than one stage
+    (8, 64, 1, 4, 1, 1, 3),
+    (200, 128, 1, 4, 1, 1, 20),
+    (1048, 128, 1, 4, 1, 1, 20),
+    # dense tiles by batch size: below and from 2048 tokens, from 6144
+    (72, 128, 2, 20, 2, 23, 89),
+    (72, 128, 2, 20, 2, 32, 64),
+    (72, 64, 2, 20, 2, 64, 96),
+    # tiles of 16 experts: one, four, eight and sixteen, full and partly filled
+    (64, 64, 3, 16, 3, 1, 40),
+    (64, 128, 3, 17, 3, 1, 40),
+    (64, 64, 2, 65, 1, 1, 40),
+    (64, 128, 2, 129, 1, 1, 40),
+    (64, 128, 1, 256, 8, 1, 40),
+    # attention: more scores than a row's registers hold, 8 queries per workgroup, the longest sequence
+    (64, 64, 1, 4, 1, 1, 385),
+    (64, 64, 1, 4, 1, 1, 2301),
+    (64, 128, 1, 4, 1, 1, 4096),
+])
+def test_hash_forward_at_the_edges_of_tiles_and_chunks(d, C, L, E, k, n_seq, T):
+    test_hash_forward_against_oracle(d, C, L, E, k, n_seq, T)
+
+
 def test_predicted_table_drives_the_layer():
     """Hash-building side to inference side: the predicted ids / alpha of layer l (top-2) are planned
     and run through the MoE layer, and the result equals the oracle's layer on the same table."""
