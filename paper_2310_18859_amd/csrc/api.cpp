@@ -291,20 +291,40 @@ int prefetch_allowed(const sida_ctx *c, const sida_plan *p, int32_t w)
     return SIDA_OK;
 }
 
-// alpha != NULL: the fused path - the gate values are moved along with the sort and the gather
-// pass is left to GEMM 1.
-int launch_dispatch(sida_ctx *c, const void *x, const int32_t *ids, int32_t T, const Ws &ws, const LayerTable *tbl,
-                    hipStream_t st, const float *alpha = nullptr)
+// The sort of one layer into the regions of ws.  alpha != NULL: the fused path - the gate values are
+// moved along with the sort and the gather pass is left to GEMM 1.
+SortJob sort_job(const Ws &ws, const int32_t *ids, const float *alpha, const LayerTable *tbl)
 {
-    {
-        Timed tm(c, SIDA_K_SORT, st);
-        HIP_TRY(c, (hipError_t)launch_sort(ids, T, c->cfg.E, ws.counts, ws.offsets, ws.block_hist, ws.perm, ws.inv, tbl,
-                                           ws.tiles, ws.max_tiles, st, alpha, ws.gate_perm));
+    SortJob j;
+    j.ids = ids;
+    j.alpha = alpha;
+    j.counts = ws.counts;
+    j.offsets = ws.offsets;
+    j.block_hist = ws.block_hist;
+    j.perm = ws.perm;
+    j.inv = ws.inv;
+    j.gate_perm = ws.gate_perm;
+    j.tiles = ws.tiles;
+    if (tbl) {
+        j.tbl = *tbl;
+    } else {
+        j.tbl.n = 0;
+        j.tbl.tile_m = kGemmTileM;
     }
-    if (!alpha) {
-        TimedKernel tk(c, SIDA_K_GATHER);
-        HIP_TRY(c, (hipError_t)launch_gather(x, ws.perm, T, c->cfg.d_model, ws.x_perm, st, tk.get(), c->top_k));
-    }
+    return j;
+}
+
+int launch_sorts(sida_ctx *c, const SortJob *jobs, int32_t n, int32_t T, hipStream_t st)
+{
+    Timed tm(c, SIDA_K_SORT, st);
+    HIP_TRY(c, (hipError_t)launch_sort(jobs, n, T, c->cfg.E, (int32_t)max_tiles(c->cfg, T), st));
+    return SIDA_OK;
+}
+
+int launch_rows(sida_ctx *c, const void *x, int32_t T, const Ws &ws, hipStream_t st)
+{
+    TimedKernel tk(c, SIDA_K_GATHER);
+    HIP_TRY(c, (hipError_t)launch_gather(x, ws.perm, T, c->cfg.d_model, ws.x_perm, st, tk.get(), c->top_k));
     return SIDA_OK;
 }
 
@@ -341,6 +361,41 @@ struct LayerArgs {
     const int32_t *ids;
     const float *alpha;
     void *y;
+};
+
+// Where a layer of a group keeps its sort: the last one in the workspace's own regions, the others in the
+// x_perm region, which the fused path does not use (12 bytes per row and 16 per token tile, of 2*d_model
+// bytes per row).
+struct SortRegions {
+    size_t stride, fit;                // bytes per layer, layers that fit the x_perm region
+    size_t counts, offsets, perm, inv, gate_perm, tiles;
+    SortRegions(const sida_config &cfg, int32_t T)
+    {
+        size_t off = 0;
+        auto take = [&](size_t bytes) {
+            const size_t at = off;
+            off = align_up(off + bytes, 256);
+            return at;
+        };
+        counts = take(sizeof(int32_t) * (size_t)cfg.E);
+        offsets = take(sizeof(int32_t) * ((size_t)cfg.E + 1));
+        perm = take(sizeof(int32_t) * (size_t)T);
+        inv = take(sizeof(int32_t) * (size_t)T);
+        gate_perm = take(sizeof(float) * (size_t)T);
+        tiles = take(sizeof(TileDesc) * max_tiles(cfg, T));
+        stride = off;
+        fit = 2 * (size_t)T * (size_t)cfg.d_model / stride;
+    }
+    void move(Ws *ws, size_t i) const
+    {
+        char *b = static_cast<char *>(ws->x_perm) + i * stride;
+        ws->counts = (int32_t *)(b + counts);
+        ws->offsets = (int32_t *)(b + offsets);
+        ws->perm = (int32_t *)(b + perm);
+        ws->inv = (int32_t *)(b + inv);
+        ws->gate_perm = (float *)(b + gate_perm);
+        ws->tiles = (TileDesc *)(b + tiles);
+    }
 };
 
 int check_layer_args(const sida_ctx *c, const LayerArgs &a)
@@ -392,17 +447,41 @@ int forward_layers(sida_ctx *c, int32_t n, const LayerArgs *layers, void *ws_dev
         return enqueue_prefetch(c, p, w, copy);
     };
 
+    const bool fused = c->fused;
+    LayerSchedule scheds[kSortJobs];
+    Ws regions[kSortJobs];
+    int32_t group_end = 0, group_begin = 0;
     for (int32_t li = 0; li < n; ++li) {
         const LayerArgs &a = layers[li];
         const sida_plan *p = a.plan;
         if (p->n_waves == 0) continue;
-        const Ws ws = carve(c->cfg, p->T, ws_dev);
-        LayerSchedule sched;
-        build_schedule(p, choose_tile_m(p), &sched);
-        const bool fused = c->fused;
-        rc = launch_dispatch(c, a.x, a.ids, p->T, ws, &sched.tbl, compute,      // also expands sched.tbl into tiles
-                             fused ? a.alpha : nullptr);
-        if (rc) return rc;
+        // The expert ids of all layers are known: consecutive layers of equally many tokens are sorted by
+        // one launch in front of the first of them (as a launch per layer a sort is 5 to 17 us of a
+        // layer's time on a mostly idle GPU).
+        if (li >= group_end) {
+            const SortRegions at(c->cfg, p->T);
+            const int32_t most = fused && sort_in_one_launch(p->T) ? (int32_t)std::min<size_t>(kSortJobs, at.fit + 1) : 1;
+            group_begin = li;
+            for (group_end = li + 1; group_end < n && group_end - li < most; ++group_end)
+                if (layers[group_end].plan->T != p->T) break;
+            SortJob jobs[kSortJobs];
+            for (int32_t i = li; i < group_end; ++i) {
+                Ws &ws = regions[i - li];
+                ws = carve(c->cfg, p->T, ws_dev);
+                if (i + 1 < group_end) at.move(&ws, (size_t)(i - li));
+                const sida_plan *pi = layers[i].plan;
+                build_schedule(pi, choose_tile_m(pi), &scheds[i - li]);
+                jobs[i - li] = sort_job(ws, layers[i].ids, fused ? layers[i].alpha : nullptr, &scheds[i - li].tbl);
+            }
+            rc = launch_sorts(c, jobs, group_end - li, p->T, compute);
+            if (rc) return rc;
+        }
+        const Ws &ws = regions[li - group_begin];
+        const LayerSchedule &sched = scheds[li - group_begin];
+        if (!fused) {
+            rc = launch_rows(c, a.x, p->T, ws, compute);
+            if (rc) return rc;
+        }
         if (c->debug & SIDA_DEBUG_CHECK_IDS) {                 // the sort's counts against the plan's
             CountTable want;
             std::memcpy(want.n, p->counts, sizeof want.n);
@@ -424,8 +503,12 @@ int forward_layers(sida_ctx *c, int32_t n, const LayerArgs *layers, void *ws_dev
             rc = launch_wave_ffn(c, sched, w, ws, p->T, compute, fused ? a.x : nullptr,
                                  fused && c->top_k == 1 ? a.y : nullptr);
             if (rc) return rc;
-            if (g >= kEventRing) HIP_TRY(c, hipEventSynchronize(c->ev_done[ring]));
-            HIP_TRY(c, hipEventRecord(c->ev_done[ring], compute));
+            // A pool with a slot for every expert never overwrites one: no copy waits for this wave.  (An
+            // event between two kernels is a gap of 5 to 6 us on the stream.)
+            if (c->cfg.S < (int64_t)c->cfg.L * c->cfg.E) {
+                if (g >= kEventRing) HIP_TRY(c, hipEventSynchronize(c->ev_done[ring]));
+                HIP_TRY(c, hipEventRecord(c->ev_done[ring], compute));
+            }
             c->forwarded_upto = g + 1;
         }
         if (!fused || c->top_k > 1) {
@@ -871,7 +954,11 @@ int sida_dispatch(sida_ctx *c, const void *x_dev, const int32_t *ids_dev, int32_
     if (!x_dev || !ids_dev) return SIDA_EINVAL;
     int rc = check_ws(c, T, workspace_dev, workspace_bytes);
     if (rc) return rc;
-    return launch_dispatch(c, x_dev, ids_dev, T, carve(c->cfg, T, workspace_dev), nullptr, static_cast<hipStream_t>(stream));
+    const Ws ws = carve(c->cfg, T, workspace_dev);
+    const SortJob job = sort_job(ws, ids_dev, nullptr, nullptr);
+    rc = launch_sorts(c, &job, 1, T, static_cast<hipStream_t>(stream));
+    if (rc) return rc;
+    return launch_rows(c, x_dev, T, ws, static_cast<hipStream_t>(stream));
 }
 
 int sida_grouped_ffn(sida_ctx *c, const sida_plan *plan, int32_t wave, void *workspace_dev, size_t workspace_bytes,

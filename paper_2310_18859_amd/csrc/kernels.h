@@ -33,11 +33,21 @@ struct LaunchEvents {
 
 // K-a: stable counting sort of T tokens by expert id.
 //   ids int32[T] -> counts[E], offsets[E+1], perm[T], inv[T];  block_hist is scratch [n_chunks*E].
-// When tbl is given (may be NULL) it is also expanded into token tiles, see launch_build_tiles.
-// With alpha (may be NULL) the gate values are moved along: gate_perm[r] = alpha[perm[r]].
-int launch_sort(const int32_t *ids, int32_t T, int32_t E, int32_t *counts, int32_t *offsets,
-                int32_t *block_hist, int32_t *perm, int32_t *inv, const LayerTable *tbl, TileDesc *tiles,
-                int32_t max_tiles, hipStream_t st, const float *alpha = nullptr, float *gate_perm = nullptr);
+// A job is one layer's sort.  Its expert table (tbl.n = 0: none) is also expanded into token tiles, see
+// launch_build_tiles; with alpha (may be NULL) the gate values are moved along: gate_perm[r] =
+// alpha[perm[r]].
+struct SortJob {
+    const int32_t *ids;
+    const float *alpha;
+    int32_t *counts, *offsets, *block_hist, *perm, *inv;
+    float *gate_perm;
+    TileDesc *tiles;
+    LayerTable tbl;
+};
+// Sorts up to kSortJobs jobs of the same T and E; more than one only where sort_in_one_launch(T).
+constexpr int kSortJobs = 8;
+bool sort_in_one_launch(int32_t T);
+int launch_sort(const SortJob *jobs, int32_t n, int32_t T, int32_t E, int32_t max_tiles, hipStream_t st);
 // K-a: x_perm[r,:] = x[perm[r] / k,:], rows of d bf16 values; T = rows of x_perm (k per token).
 int launch_gather(const void *x, const int32_t *perm, int32_t T, int32_t d, void *x_perm, hipStream_t st,
                   const LaunchEvents *ev = nullptr, int32_t k = 1);

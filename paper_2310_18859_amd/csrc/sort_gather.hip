@@ -28,6 +28,21 @@ namespace {
 constexpr int kChunk = 256;      // tokens per wavefront (4 rounds of 64)
 constexpr int kMaxE = 256;
 
+// The jobs of a launch, by value; row y of the grid does job y.
+struct SortJobs {
+    SortJob job[kSortJobs];
+};
+#define SIDA_SORT_JOB(j)                                    \
+    const int32_t *__restrict__ ids = (j).ids;              \
+    const float *__restrict__ alpha = (j).alpha;            \
+    int32_t *__restrict__ counts = (j).counts;              \
+    int32_t *__restrict__ offsets = (j).offsets;            \
+    int32_t *__restrict__ perm = (j).perm;                  \
+    int32_t *__restrict__ inv = (j).inv;                    \
+    float *__restrict__ gate_perm = (j).gate_perm;          \
+    TileDesc *__restrict__ tiles = (j).tiles;               \
+    const LayerTable &tbl = (j).tbl
+
 __device__ __forceinline__ int clamp_id(int k, int E) { return k < 0 ? 0 : (k >= E ? E - 1 : k); }
 
 __global__ __launch_bounds__(64) void sort_hist(const int32_t *__restrict__ ids, int T, int E,
@@ -199,12 +214,9 @@ __global__ __launch_bounds__(64) void sort_rank(const int32_t *__restrict__ ids,
 constexpr int kOneT = 4096;      // most tokens the single-workgroup sort takes
 
 template <int NWV, int CPW>
-__global__ __launch_bounds__(NWV * 64) void sort_one(const int32_t *__restrict__ ids, int T, int E,
-                                                     int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
-                                                     int32_t *__restrict__ perm, int32_t *__restrict__ inv,
-                                                     const float *__restrict__ alpha, float *__restrict__ gate_perm,
-                                                     const LayerTable tbl, TileDesc *__restrict__ tiles, int max_tiles)
+__global__ __launch_bounds__(NWV * 64) void sort_one(const SortJobs jobs, int T, int E, int max_tiles)
 {
+    SIDA_SORT_JOB(jobs.job[blockIdx.y]);
     constexpr int NCH = NWV * CPW;
     __shared__ int hist[NCH][kMaxE];               // per-chunk histogram, then first output row of (chunk, expert)
     __shared__ int s_off[kMaxE + 1];
@@ -335,12 +347,9 @@ __global__ __launch_bounds__(NWV * 64) void sort_one(const int32_t *__restrict__
 constexpr int kChunksT = 65536;
 constexpr int kFineChunk = 128;                    // two ranking rounds per workgroup
 constexpr int kIdLoads = 8;                        // 16-byte id loads in flight per thread
-__global__ __launch_bounds__(256) void sort_chunks(const int32_t *__restrict__ ids, int T, int E,
-                                                   int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
-                                                   int32_t *__restrict__ perm, int32_t *__restrict__ inv,
-                                                   const float *__restrict__ alpha, float *__restrict__ gate_perm,
-                                                   const LayerTable tbl, TileDesc *__restrict__ tiles, int max_tiles)
+__global__ __launch_bounds__(256) void sort_chunks(const SortJobs jobs, int T, int E, int max_tiles)
 {
+    SIDA_SORT_JOB(jobs.job[blockIdx.y]);
     __shared__ int s_rest[kMaxE];                  // tokens per expert from this chunk on
     __shared__ int s_before[kMaxE];                // ... in earlier chunks, then the next output row
     __shared__ int s_off[kMaxE + 1];
@@ -497,35 +506,30 @@ __global__ __launch_bounds__(256) void gather_rows(const uint4 *__restrict__ x, 
 
 }  // namespace
 
-int launch_sort(const int32_t *ids, int32_t T, int32_t E, int32_t *counts, int32_t *offsets,
-                int32_t *block_hist, int32_t *perm, int32_t *inv, const LayerTable *tbl, TileDesc *tiles,
-                int32_t max_tiles, hipStream_t st, const float *alpha, float *gate_perm)
+bool sort_in_one_launch(int32_t T) { return T <= kChunksT; }
+
+int launch_sort(const SortJob *jobs, int32_t n, int32_t T, int32_t E, int32_t max_tiles, hipStream_t st)
 {
+    if (n < 1 || n > kSortJobs || (n > 1 && T > kChunksT)) return (int)hipErrorInvalidValue;
+    bool aligned = true;                                     // ids are read 16 bytes at a time
+    for (int32_t i = 0; i < n; ++i) aligned = aligned && (reinterpret_cast<uintptr_t>(jobs[i].ids) & 15u) == 0;
+    if (T <= kOneT || (T <= kChunksT && aligned)) {
+        SortJobs a;
+        for (int32_t i = 0; i < n; ++i) a.job[i] = jobs[i];
+        if (T <= 8 * kChunk) hipLaunchKernelGGL((sort_one<8, 1>), dim3(1, n), dim3(512), 0, st, a, T, E, max_tiles);
+        else if (T <= kOneT) hipLaunchKernelGGL((sort_one<16, 1>), dim3(1, n), dim3(1024), 0, st, a, T, E, max_tiles);
+        else hipLaunchKernelGGL(sort_chunks, dim3((T + kFineChunk - 1) / kFineChunk, n), dim3(256), 0, st, a, T, E, max_tiles);
+        return (int)hipGetLastError();
+    }
     const int n_chunks = (T + kChunk - 1) / kChunk;
-    LayerTable none;
-    none.n = 0;
-    none.tile_m = kGemmTileM;
-    if (T <= kOneT) {
-        const LayerTable &t = tbl ? *tbl : none;
-        float *gp = alpha ? gate_perm : nullptr;
-        if (T <= 8 * kChunk)
-            hipLaunchKernelGGL((sort_one<8, 1>), dim3(1), dim3(512), 0, st, ids, T, E, counts, offsets, perm, inv, alpha, gp, t,
-                               tiles, max_tiles);
-        else
-            hipLaunchKernelGGL((sort_one<16, 1>), dim3(1), dim3(1024), 0, st, ids, T, E, counts, offsets, perm, inv, alpha, gp,
-                               t, tiles, max_tiles);
-        return (int)hipGetLastError();
+    for (int32_t i = 0; i < n; ++i) {
+        const SortJob &j = jobs[i];
+        hipLaunchKernelGGL(sort_hist, dim3(n_chunks), dim3(64), 0, st, j.ids, T, E, j.block_hist);
+        hipLaunchKernelGGL(sort_scan, dim3(1), dim3(1024), 0, st, j.block_hist, n_chunks, E, T, j.counts, j.offsets, j.tbl,
+                           j.tiles, max_tiles);
+        hipLaunchKernelGGL(sort_rank, dim3(n_chunks), dim3(64), 0, st, j.ids, T, E, j.block_hist, j.perm, j.inv, j.alpha,
+                           j.gate_perm);
     }
-    if (T <= kChunksT && (reinterpret_cast<uintptr_t>(ids) & 15u) == 0) {   // ids are read 16 bytes at a time
-        hipLaunchKernelGGL(sort_chunks, dim3((T + kFineChunk - 1) / kFineChunk), dim3(256), 0, st, ids, T, E, counts, offsets, perm, inv, alpha,
-                           alpha ? gate_perm : nullptr, tbl ? *tbl : none, tiles, max_tiles);
-        return (int)hipGetLastError();
-    }
-    hipLaunchKernelGGL(sort_hist, dim3(n_chunks), dim3(64), 0, st, ids, T, E, block_hist);
-    hipLaunchKernelGGL(sort_scan, dim3(1), dim3(1024), 0, st, block_hist, n_chunks, E, T, counts, offsets,
-                       tbl ? *tbl : none, tiles, max_tiles);
-    hipLaunchKernelGGL(sort_rank, dim3(n_chunks), dim3(64), 0, st, ids, T, E, block_hist, perm, inv, alpha,
-                       alpha ? gate_perm : nullptr);
     return (int)hipGetLastError();
 }
 
