@@ -169,30 +169,59 @@ struct LayerSchedule {
     int32_t tile_begin[SIDA_MAX_E];
     int32_t m_tiles[SIDA_MAX_E];
     int32_t m_tall[SIDA_MAX_E];       // leading tiles of the wave that belong to experts with more than one tile
+    int32_t m_few[SIDA_MAX_E];        // last tiles of the wave, streamed (few_tokens below)
+    int32_t few_rows[SIDA_MAX_E];     // token rows of those
 };
 
-// Token rows per tile for a layer.  A grouped GEMM is bound by the rows its tiles pull through LDS:
+// How a layer's experts are cut into tiles, by its token counts alone (not by its waves: a wavefront sums
+// over K in another order where tiles are streamed, and a layer gives the same bits in one wave as in
+// many).
+struct TileRule {
+    int32_t tile_m;                   // token rows per tile, 64 or 128
+    int32_t few;                      // experts of at most this many tokens are streamed, in tiles of 64 rows
+};
+
+// Token rows per tile.  A grouped GEMM is bound by the rows its tiles pull through LDS:
 // a tile of tile_m token rows and 256 weight rows costs tile_m + 256 rows per K-step whether or not
 // all its token rows exist.  64-row tiles pay when most experts have at most 64 tokens, i.e. when
 // halving the tile height adds few tiles: tiles(64) * 320 <= tiles(128) * 384.  (Measured on the
 // Switch-base-128 shape: 64-row tiles are 8-10 % faster at 8-16 tokens per expert, even at 64, and
 // 6 % slower at 128 tokens per expert.)
-int32_t choose_tile_m(const sida_plan *p)
+// Streamed (see grouped_ffn.hip) are
+//  * all tiles of a layer of few tiles, where walking them leaves most compute units idle - up to 20
+//    (16 experts, 300 tokens, Zipf(1): 51 -> 41 us a layer; 8 experts, 400 tokens: 46 -> 35 us; 32 tiles of 64
+//    rows: 56 -> 67 us) -
+//  * and of a layer of at most 10 rows per tile with hardly an expert of more than one (128 experts, 128
+//    tokens: 92 -> 81 us; 64 experts, 300 tokens, Zipf(1.2): 88 -> 80 us);
+//  * of a layer of many experts (fewer do not fill the chip beside the tiles that are walked) the experts
+//    with at most 64 tokens, as long as these have no more than 32 on average (128 experts: 2000 tokens,
+//    Zipf(1), 225 -> 210 us; 5461 tokens 277 -> 254 us; 39 tokens each 244 -> 253 us) and the others do
+//    not outweigh them by far (16384 tokens: 319 -> 325 us).
+TileRule tile_rule(const sida_plan *p)
 {
-    // A layer that is cut into waves launches a few experts at a time: small launches, hidden
-    // behind the copies; 64-row tiles give them more (and deeper-fetching) tiles.
-    if (p->n_waves > 1) return kGemmTileSmall;
-    int64_t t64 = 0, t128 = 0;
+    int64_t t64 = 0, t128 = 0, n_few = 0, few_rows = 0, rows = 0;
     for (int32_t i = 0; i < p->n_active; ++i) {
         const int32_t n = p->counts[p->order[i]];
+        rows += n;
         t64 += (n + kGemmTileSmall - 1) / kGemmTileSmall;
         t128 += (n + kGemmTileM - 1) / kGemmTileM;
+        if (n <= kGemmTileSmall) {
+            ++n_few;
+            few_rows += n;
+        }
     }
-    return 5 * t64 <= 6 * t128 ? kGemmTileSmall : kGemmTileM;
+    if (t64 <= 20 || (rows <= 10 * t64 && 8 * t64 <= 9 * p->n_active)) return TileRule{kGemmTileSmall, INT32_MAX};
+    // A layer that is cut into waves launches a few experts at a time: small launches, hidden
+    // behind the copies; 64-row tiles give them more (and deeper-fetching) tiles.
+    const int32_t tile_m = p->n_waves > 1 || 5 * t64 <= 6 * t128 ? kGemmTileSmall : kGemmTileM;
+    const bool stream = p->n_active >= 48 && few_rows <= 32 * n_few && rows <= 64 * (int64_t)p->n_active;
+    return TileRule{tile_m, stream ? kGemmTileSmall : 0};
 }
 
-void build_schedule(const sida_plan *p, int32_t tile_m, LayerSchedule *s)
+void build_schedule(const sida_plan *p, LayerSchedule *s)
 {
+    const TileRule rule = tile_rule(p);
+    const int32_t tile_m = rule.tile_m;
     int32_t idx[SIDA_MAX_E];
     for (int32_t i = 0; i < p->n_active; ++i) idx[i] = p->order[i];     // already grouped by wave
     std::stable_sort(idx, idx + p->n_active, [&](int32_t a, int32_t b) {
@@ -201,7 +230,7 @@ void build_schedule(const sida_plan *p, int32_t tile_m, LayerSchedule *s)
     });
     s->tbl.n = p->n_active;
     s->tbl.tile_m = tile_m;
-    for (int32_t w = 0; w < p->n_waves; ++w) s->tile_begin[w] = s->m_tiles[w] = s->m_tall[w] = 0;
+    for (int32_t w = 0; w < p->n_waves; ++w) s->tile_begin[w] = s->m_tiles[w] = s->m_tall[w] = s->m_few[w] = s->few_rows[w] = 0;
     int32_t at = 0, cur = -1;
     for (int32_t i = 0; i < p->n_active; ++i) {
         const int32_t e = idx[i];
@@ -214,7 +243,12 @@ void build_schedule(const sida_plan *p, int32_t tile_m, LayerSchedule *s)
         }
         const int32_t n_t = (p->counts[e] + tile_m - 1) / tile_m;
         s->m_tiles[w] += n_t;
-        if (n_t > 1) s->m_tall[w] += n_t;                            // sorted by count: these come first
+        if (p->counts[e] <= rule.few) {                              // sorted by count: these come last
+            s->m_few[w] += n_t;
+            s->few_rows[w] += p->counts[e];
+        } else if (n_t > 1) {
+            s->m_tall[w] += n_t;                                     // ... and these first
+        }
         at += n_t;
     }
 }
@@ -342,14 +376,16 @@ int launch_wave_ffn(sida_ctx *c, const LayerSchedule &s, int32_t w, const Ws &ws
     const TileDesc *tiles = ws.tiles + s.tile_begin[w];
     {
         TimedKernel tk(c, SIDA_K_GEMM1);
-        HIP_TRY(c, (hipError_t)launch_ffn_gemm1(x ? x : ws.x_perm, ws.h, c->pool, c->expert_bytes, tiles, s.m_tiles[w],
-                                                s.m_tall[w], c->cfg.d_model, c->cfg.d_ff, ws.sink, st, tk.get(),
+        HIP_TRY(c, (hipError_t)launch_ffn_gemm1(x ? x : ws.x_perm, ws.h, c->pool, c->expert_bytes, tiles,
+                                                s.m_tiles[w] - s.m_few[w], s.m_tall[w], s.m_few[w], s.few_rows[w],
+                                                c->cfg.d_model, c->cfg.d_ff, ws.sink, st, tk.get(),
                                                 x ? T / c->top_k : T, x ? ws.perm : nullptr, T, c->top_k, s.tbl.tile_m));
     }
     {
         TimedKernel tk(c, SIDA_K_GEMM2);
-        HIP_TRY(c, (hipError_t)launch_ffn_gemm2(ws.h, y ? y : ws.y_perm, c->pool, c->expert_bytes, tiles, s.m_tiles[w],
-                                                s.m_tall[w], c->cfg.d_model, c->cfg.d_ff, ws.sink, st, tk.get(), T,
+        HIP_TRY(c, (hipError_t)launch_ffn_gemm2(ws.h, y ? y : ws.y_perm, c->pool, c->expert_bytes, tiles,
+                                                s.m_tiles[w] - s.m_few[w], s.m_tall[w], s.m_few[w], s.few_rows[w],
+                                                c->cfg.d_model, c->cfg.d_ff, ws.sink, st, tk.get(), T,
                                                 y ? ws.perm : nullptr, y ? ws.gate_perm : nullptr, s.tbl.tile_m));
     }
     return SIDA_OK;
@@ -470,7 +506,7 @@ int forward_layers(sida_ctx *c, int32_t n, const LayerArgs *layers, void *ws_dev
                 ws = carve(c->cfg, p->T, ws_dev);
                 if (i + 1 < group_end) at.move(&ws, (size_t)(i - li));
                 const sida_plan *pi = layers[i].plan;
-                build_schedule(pi, choose_tile_m(pi), &scheds[i - li]);
+                build_schedule(pi, &scheds[i - li]);
                 jobs[i - li] = sort_job(ws, layers[i].ids, fused ? layers[i].alpha : nullptr, &scheds[i - li].tbl);
             }
             rc = launch_sorts(c, jobs, group_end - li, p->T, compute);
@@ -971,7 +1007,7 @@ int sida_grouped_ffn(sida_ctx *c, const sida_plan *plan, int32_t wave, void *wor
     rc = check_ws(c, plan->T, workspace_dev, workspace_bytes);
     if (rc) return rc;
     LayerSchedule sched;
-    build_schedule(plan, choose_tile_m(plan), &sched);
+    build_schedule(plan, &sched);
     const Ws ws = carve(c->cfg, plan->T, workspace_dev);
     rc = launch_tiles(c, sched, ws, static_cast<hipStream_t>(stream));
     if (rc) return rc;

@@ -24,13 +24,14 @@
 // owns NS stripes of 32 weight rows and all BM token rows, i.e. NS x BM/32 accumulator blocks of
 // 32x32 (fp32).  Two workgroups share a compute unit (8 wavefronts, two per SIMD), so that one's
 // result stores and tile switch overlap the other's MFMAs.  One LDS fragment read feeds NS MFMAs.
-// Launches with few tiles use workgroups of NWV = 2 wavefronts, three per compute unit.
+// Experts with few tokens take another kernel, or another role beside it in the same launch (stream_tile).
 //
 // LDS token tile layout: row r of a stage is 128 bytes; its 16-byte piece c is stored at piece
-// position c ^ (r & 7).  A direct-to-LDS load writes lane i's 16 bytes at offset 16*i of the
-// instruction's 1 KiB window (8 rows), so lane i fetches global piece (i%8) ^ (i/8) of row i/8; the
-// fragment reads (32 rows, same logical piece) then touch 8 different positions per 8 rows and are
-// bank-conflict free without padding.
+// position c ^ (r/2 & 7).  A direct-to-LDS load writes lane i's 16 bytes at offset 16*i of the
+// instruction's 1 KiB window (8 rows), so lane i fetches the global piece that belongs at position i%8 of
+// its row; the fragment reads (32 rows, same logical piece) then touch all 16 places of 256 bytes per 16
+// rows, which LDS reads at a time, and are bank-conflict free without padding (with r & 7, rows 8 apart
+// met: half of the LDS cycles were conflicts).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -49,6 +50,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Waits until at most N of this wavefront's vector memory operations are outstanding (they
 // complete in issue order).  Operations the kernel issues beyond the ones a count is derived
@@ -95,6 +97,8 @@ __device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t r, int voffse
 enum { kPlain = 0, kGather = 1, kScatter = 2 };
 
 constexpr int kWaves = 4;        // wavefronts per workgroup
+constexpr int kFewStripes = 2;   // weight stripes per workgroup of a few-token tile beside larger ones
+constexpr int kStreamLdsBytes = 32 * 1024;   // LDS of a few-token tile: kWaves parts of 64 x 32 sums
 
 struct GemmArgs {
     const __bf16 *A;             // token rows [a_rows, K]
@@ -103,6 +107,8 @@ struct GemmArgs {
     size_t expert_bytes, w_off;  // W_in at offset 0 of a slot, W_out behind it
     const TileDesc *tiles;
     int m_tiles, m_tall, gm, nw, N, K;      // gm x nw: block of the tile order (tile_order.h)
+    int m_few, few_rows;         // few-token tiles behind the m_tiles others, and their rows
+    int big_wgs;                 // workgroups that walk the m_tiles tiles
     uint32_t a_bytes;            // bytes of A
     char *sink;
     const int32_t *perm;         // fused modes: row maps, `map_len` entries
@@ -110,6 +116,172 @@ struct GemmArgs {
     int map_len, top_k;
     bool stream_once;            // weights of experts with a single token tile take the streaming cache policy
 };
+
+// ---- experts with few tokens ----------------------------------------------------------------------
+// An expert with few tokens is a stream of weights: one pass over W for at most 64 rows.  What counts is
+// that every compute unit has enough of it in flight all the time and the same share of it.  One workgroup
+// takes a token tile of at most 64 rows and NS stripes of 32 weight rows, and its four wavefronts split the
+// sum over K, so that
+//  * a wavefront's weights are one linear run, loaded D steps of 32 K values ahead into registers, with no
+//    barrier before the end of the sum - where four partial sums meet in LDS - and
+//  * a launch is many short workgroups (an expert's second GEMM: d/32 of them), which the hardware deals out
+//    as others end: no workgroup's share of tiles is larger than another's.
+// Token rows are loaded whole 64-byte pieces at a time (16 rows per load) and turned around in LDS, within
+// the wavefront: loaded as matrix operands, 16 bytes of another row in every lane, each lane is a cache
+// access of its own, and from about 8 rows on those bound the launch (128 experts x 23 tokens: 147 us; 113
+// this way).  Rows past the tile's end are outside the buffer descriptor: no request.
+// Measured against the 64-row tiles of the kernel below: 52 experts x 2.5 tokens 46 / 44 -> 39 / 40 us per
+// GEMM (6.1 TB/s of weights), 128 x 12: 107 / 99 -> 95 / 97 us, 8 x 8: 11 / 14 -> 10 / 8 us.
+template <int NS, int MI, int D, bool RELU, int FUSE, bool ONCE>
+__device__ __forceinline__ void stream_tile(const GemmArgs &g, const i32x4 &td, int stripe, f32x4 *red)
+{
+    constexpr int W = kWaves;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = g.N, K = g.K, row0 = td.y, rows = td.z;
+    const int n = K / (32 * W), k0 = wv * n;                    // this wavefront's steps of 32 K values
+    const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(g.pool + (size_t)td.x * g.expert_bytes + g.w_off, (uint32_t)N * (uint32_t)K * 2u);
+    const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(g.A, g.a_bytes);
+    constexpr int kT = 2 * MI;
+    int src[kT], dst[MI];
+    float gate[MI];
+#pragma unroll
+    for (int j = 0; j < kT; ++j) {
+        src[j] = row0 + min(j * 16 + (lane >> 2), rows - 1);
+        if (FUSE == kGather) src[j] = g.perm[src[j]];
+    }
+#pragma unroll
+    for (int m = 0; m < MI; ++m) {
+        const int r = row0 + min(m * 32 + (lane & 31), rows - 1);
+        dst[m] = r;
+        if (FUSE == kScatter) {
+            dst[m] = g.perm[r];
+            gate[m] = g.gate_perm[r];
+        }
+    }
+    bf16x8 w[D][2][NS], t[D][kT];
+    auto load_w = [&](int i, int f) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                w[i][j][s] = load_frag<ONCE>(w_rsrc, lane * 16, (stripe * NS + s) * (32 * K * 2) + (k0 + f) * 2048 + j * 1024);
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_w(i, min(i, n - 1));
+    int tok_v[kT];
+#pragma unroll
+    for (int j = 0; j < kT; ++j) {
+        if (FUSE == kGather && g.top_k != 1) src[j] /= g.top_k;
+        // rows past the end are out of the descriptor's range: zeros, no request
+        tok_v[j] = j * 16 + (lane >> 2) < rows ? src[j] * K * 2 + (lane & 3) * 16 : INT32_MIN;
+    }
+    auto load_t = [&](int i, int f) {
+#pragma unroll
+        for (int j = 0; j < kT; ++j) t[i][j] = load_frag<false>(a_rsrc, tok_v[j], (k0 + f) * 64);
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_t(i, min(i, n - 1));
+    f32x16 acc[NS][MI];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int m = 0; m < MI; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[s][m][r] = 0.f;
+    // token rows of a step, turned around in LDS: row r is 64 bytes, piece p at position p ^ (r/4 & 3)
+    char *turn = reinterpret_cast<char *>(red) + wv * (MI * 4096);
+    const int put_at = (lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) * 16);
+    int get_at[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) get_at[j] = (lane & 31) * 64 + (((j * 2 + half) ^ ((lane >> 2) & 3)) * 16);
+    auto multiply = [&](int i) {
+        char *slot = turn + (i & 1) * (MI * 2048);
+#pragma unroll
+        for (int j = 0; j < kT; ++j) *reinterpret_cast<bf16x8 *>(slot + j * 1024 + put_at) = t[i][j];
+#pragma unroll
+        for (int m = 0; m < MI; ++m)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const bf16x8 x = *reinterpret_cast<const bf16x8 *>(slot + m * 2048 + get_at[j]);
+#pragma unroll
+                for (int s = 0; s < NS; ++s) acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[i][j][s], x, acc[s][m], 0, 0, 0);
+            }
+    };
+    int f = 0;
+#pragma clang loop unroll(disable)
+    for (; f + D < n; f += D) {
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            multiply(i);
+            const int at = min(f + D + i, n - 1);
+            load_w(i, at);
+            load_t(i, at);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+        if (i == 0 || f + i < n) multiply(i);
+    // The parts of the sum meet in LDS, stripe by stripe.  A lane holds 4 x 4 consecutive output columns
+    // 8q + 4*half .. of its token; wavefront q sums column group q.
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        if (s) __syncthreads();
+#pragma unroll
+        for (int m = 0; m < MI; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                red[((wv * MI + m) * 4 + q) * 64 + lane] = f32x4{acc[s][m][4 * q], acc[s][m][4 * q + 1], acc[s][m][4 * q + 2], acc[s][m][4 * q + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < MI; ++m) {
+            const int q = wv, token = m * 32 + (lane & 31);
+            f32x4 v = red[(m * 4 + q) * 64 + lane];
+#pragma unroll
+            for (int p = 1; p < W; ++p) v += red[((p * MI + m) * 4 + q) * 64 + lane];
+            bf16x4 o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float e = v[j];
+                if (RELU) e = e > 0.f ? e : 0.f;
+                o[j] = (__bf16)e;
+                if (FUSE == kScatter) o[j] = (__bf16)(gate[m] * (float)o[j]);
+            }
+            if (token < rows) *reinterpret_cast<bf16x4 *>(g.C + (size_t)dst[m] * N + (stripe * NS + s) * 32 + q * 8 + half * 4) = o;
+        }
+    }
+}
+
+// Workgroup `block` of the few-token tiles: which tile and stripe.  Workgroup b runs on XCD b % 8 (round-robin
+// dispatch); the stripes of a token tile stay on one XCD, so that its rows are fetched into one L2.  Tiles
+// are dealt to the XCDs in turn, back and forth (they come with the most tokens first), and the stripes of
+// the last, incomplete round to all XCDs.
+template <int NS, bool RELU, int FUSE, bool ONCE>
+__device__ __forceinline__ void stream_block(const GemmArgs &g, int block, f32x4 *red)
+{
+    const int stripes = g.N / (32 * NS), rounds = g.m_few >> 3;
+    const int xcd = block & 7, local = block >> 3;
+    int mt = local / stripes, stripe = local - mt * stripes;
+    if (mt < rounds) {
+        mt = mt * 8 + ((mt & 1) ? 7 - xcd : xcd);
+    } else {
+        const int j = (local - rounds * stripes) * 8 + xcd;
+        mt = rounds * 8 + j / stripes;
+        stripe = j % stripes;
+        if (mt >= g.m_few) return;
+    }
+    typedef const __attribute__((address_space(4))) i32x4 *ConstTiles;
+    const i32x4 td = ((ConstTiles)(uintptr_t)(g.tiles + g.m_tiles))[mt];   // slot, row0, rows, expert
+    if (td.z > 32) stream_tile<NS, 2, 3, RELU, FUSE, ONCE>(g, td, stripe, red);
+    else stream_tile<NS, 1, 6, RELU, FUSE, ONCE>(g, td, stripe, red);
+}
+
+template <int NS, bool RELU, int FUSE, bool ONCE>
+__global__ __launch_bounds__(kWaves * 64, NS == 1 ? 3 : 2) void stream_gemm_nt(const GemmArgs g)
+{
+    __shared__ f32x4 red[kStreamLdsBytes / sizeof(f32x4)];
+    stream_block<NS, RELU, FUSE, ONCE>(g, blockIdx.x, red);
+}
 
 // Persistent workgroups: two per compute unit, each walks its tiles t = b, b+G, ...
 //
@@ -119,10 +291,10 @@ struct GemmArgs {
 // fetches its own first steps once more, unused, so that the loop has no data-dependent branch).
 // Per step a wavefront executes: one s_waitcnt, one s_barrier, its share of the token loads, and
 // per 16 K values BM/32 LDS fragment reads, NS*BM/32 MFMAs and NS weight-fragment loads.
-template <int BM, int NS, int NB, bool RELU, int FUSE, int NWV>
-__global__ __launch_bounds__(NWV * 64, NWV == kWaves ? 2 : 3) void grouped_gemm_nt(const GemmArgs g)
+template <int BM, int NS, int NB, bool RELU, int FUSE>
+__global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs g)
 {
-    constexpr int BN = NWV * NS * 32;
+    constexpr int NWV = kWaves, BN = NWV * NS * 32;
     constexpr int TS = NB + 1;                                  // token ring stages
     constexpr int kStageBytes = BM * 128;
     constexpr int kRingBytes = TS * kStageBytes;
@@ -142,9 +314,16 @@ __global__ __launch_bounds__(NWV * 64, NWV == kWaves ? 2 : 3) void grouped_gemm_
     static_assert(QN % NWV == 0 && TL * 8 <= 64, "token loads per wavefront");
     static_assert(kBase + STORES + 4 <= 63, "vmcnt range");
     static_assert(NWV * 64 * 16 <= kGemmSinkBytes / 2, "sink size");
-    static_assert(kRingBytes + kStage + NWV * kSide <= (NWV == kWaves ? 80 : 53) * 1024, "two (three) workgroups per compute unit");
+    static_assert(kRingBytes + kStage + NWV * kSide <= 80 * 1024, "two workgroups per compute unit");
+    static_assert(kRingBytes + kStage >= kStreamLdsBytes, "the few-token tiles' LDS");
 
     extern __shared__ __attribute__((aligned(1024))) char lds[];
+    if ((int)blockIdx.x >= g.big_wgs) {
+        f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+        if (g.stream_once) stream_block<kFewStripes, RELU, FUSE, true>(g, (int)blockIdx.x - g.big_wgs, red);
+        else stream_block<kFewStripes, RELU, FUSE, false>(g, (int)blockIdx.x - g.big_wgs, red);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     char *stg = lds + kRingBytes + wv * (32 * kOutPitch);
@@ -152,7 +331,7 @@ __global__ __launch_bounds__(NWV * 64, NWV == kWaves ? 2 : 3) void grouped_gemm_
     const int N = g.N, K = g.K;
     const int n_tiles_n = N / BN;
     const int total = g.m_tiles * n_tiles_n;
-    const int G = gridDim.x, wg = blockIdx.x;
+    const int G = g.big_wgs, wg = blockIdx.x;
     if (wg >= total) return;
     const int n = (total - wg + G - 1) / G;                     // tiles of this workgroup
     const int nkk = K / (64 * NB);
@@ -182,10 +361,10 @@ __global__ __launch_bounds__(NWV * 64, NWV == kWaves ? 2 : 3) void grouped_gemm_
 
     // ---- load side.  Direct load q of a stage fills token rows 8q .. 8q+7 (1 KiB): lane l covers
     // row l/8 of that window and stores at piece position l%8, so it fetches logical piece
-    // (l%8) ^ (row & 7).  Wavefront w issues loads w*TL .. w*TL+TL-1 of every stage, i.e. token
+    // (l%8) ^ (row/2 & 7).  Wavefront w issues loads w*TL .. w*TL+TL-1 of every stage, i.e. token
     // rows 8*TL*w .. 8*TL*(w+1)-1, and the NS*4 fragments of its own weight stripes.
     const int sub_row = lane >> 3;
-    const int piece = (lane & 7) ^ sub_row;
+    const int piece_of = lane & 7;
     const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(g.A, g.a_bytes);
     const __amdgpu_buffer_rsrc_t map_rsrc = make_rsrc(g.perm, FUSE == kPlain ? 0u : (uint32_t)g.map_len * 4u);
     const __amdgpu_buffer_rsrc_t gate_rsrc = make_rsrc(g.gate_perm, FUSE == kScatter ? (uint32_t)g.map_len * 4u : 0u);
@@ -207,7 +386,7 @@ __global__ __launch_bounds__(NWV * 64, NWV == kWaves ? 2 : 3) void grouped_gemm_
                 src = reinterpret_cast<const int *>(side)[j * 8 + sub_row];
                 if (g.top_k != 1) src /= g.top_k;
             }
-            tok_v[j] = src * K * 2 + piece * 16;
+            tok_v[j] = src * K * 2 + (piece_of ^ ((r >> 1) & 7)) * 16;
         }
         w_rsrc = make_rsrc(g.pool + (size_t)slot * g.expert_bytes + g.w_off, (uint32_t)N * (uint32_t)K * 2u);
 #pragma unroll
@@ -246,7 +425,7 @@ __global__ __launch_bounds__(NWV * 64, NWV == kWaves ? 2 : 3) void grouped_gemm_
     const int frag_row = lane & 31, half = lane >> 5;
     int x_at[KS];                                               // fragment offsets inside a stage
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) x_at[ks] = frag_row * 128 + (((ks * 2 + half) ^ (frag_row & 7)) * 16);
+    for (int ks = 0; ks < KS; ++ks) x_at[ks] = frag_row * 128 + (((ks * 2 + half) ^ ((frag_row >> 1) & 7)) * 16);
     f32x16 acc[NS][MI];
     auto clear = [&]() {
 #pragma unroll
@@ -341,19 +520,24 @@ __global__ __launch_bounds__(NWV * 64, NWV == kWaves ? 2 : 3) void grouped_gemm_
                 __builtin_amdgcn_s_barrier();                   // everyone's token rows of this step are in LDS, and
                                                                 // everyone is done reading the stage refilled next
                 issue_tokens();
+                // A fragment of the next 32-row block is read as soon as its predecessor has been multiplied, so
+                // that LDS answers behind the products.  Blocks past the tile's end are not multiplied (the
+                // first of them is read, to no effect).
                 const char *st = lds + rd_off;
-                // 32-row blocks of tokens past the tile's end are neither read nor multiplied
+                bf16x8 xf[KS];
+                auto read = [&](int im, int ks) { xf[ks] = *reinterpret_cast<const bf16x8 *>(st + im * 4096 + x_at[ks]); };
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) read(0, ks);
 #pragma unroll
                 for (int im = 0; im < MI; ++im)
                     if (im == 0 || im < live) {
-                        bf16x8 xf[KS];
 #pragma unroll
-                        for (int ks = 0; ks < KS; ++ks) xf[ks] = *reinterpret_cast<const bf16x8 *>(st + im * 4096 + x_at[ks]);
-#pragma unroll
-                        for (int ks = 0; ks < KS; ++ks)
+                        for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
                             for (int s = 0; s < NS; ++s)
                                 acc[s][im] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[b][ks][s], xf[ks], acc[s][im], 0, 0, 0);
+                            if (im + 1 < MI) read(im + 1, ks);
+                        }
                     }
                 issue_weights(w[b]);
                 rd_off = rd_off + kStageBytes == kRingBytes ? 0 : rd_off + kStageBytes;
@@ -397,32 +581,34 @@ int persistent_grid(hipStream_t st)
     return cus;
 }
 
-// One GEMM of the pair as one launch: BM token rows per tile, 4*NS*32 weight rows, NB K-steps ahead.
-template <int BM, int NS, int NB, bool RELU, int FUSE, int NWV = kWaves>
+// Weights that only one token tile reads are streamed past L2's replacement - when there are more of them
+// than stay in the 256 MB Infinity Cache from one pass to the next anyway (measured: a 128-token batch
+// over 52 experts, second GEMM 47 -> 43.5 us; 8 experts that are read again and again, 12 -> 14 us).
+bool worth_streaming(const GemmArgs &a) { return (int64_t)(a.m_tiles - a.m_tall + a.m_few) * a.N * a.K * 2 > (int64_t)128 << 20; }
+
+// One GEMM of the pair as one launch: BM token rows per tile, 4*NS*32 weight rows, NB K-steps ahead.  With
+// few-token tiles in the launch half of the workgroup slots go to the persistent workgroups of the others
+// and the rest to the stream of few-token workgroups, which also fills the slots that come free: a compute
+// unit that multiplies and streams at a time.  (128 experts, 5461 tokens, Zipf(1): 132 / 141 us as one
+// kind of tile, 126 / 126 us; with three quarters or all slots 128 / 126 and 131 / 126 us.)
+template <int BM, int NS, int NB, bool RELU, int FUSE>
 int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
-    constexpr int kLdsBytes = (NB + 1) * BM * 128 + NWV * 32 * (NS * 64 + 16) +
-                              NWV * (FUSE == kPlain ? 0 : (FUSE == kGather ? 256 : 2 * BM * 4));
-    static bool attr_set = false;                            // per kernel instantiation
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&grouped_gemm_nt<BM, NS, NB, RELU, FUSE, NWV>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        if (e != hipSuccess) return (int)e;
-        attr_set = true;
-    }
+    constexpr int kLdsBytes = (NB + 1) * BM * 128 + kWaves * 32 * (NS * 64 + 16) +
+                              kWaves * (FUSE == kPlain ? 0 : (FUSE == kGather ? 256 : 2 * BM * 4));
+    static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&grouped_gemm_nt<BM, NS, NB, RELU, FUSE>),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (allowed != hipSuccess) return (int)allowed;
     GemmArgs g = a;
-    // Weights that only one token tile reads are streamed past L2's replacement - when there are
-    // more of them than stay in the 256 MB Infinity Cache from one pass to the next anyway
-    // (measured: a 128-token batch over 52 experts, second GEMM 47 -> 43.5 us; 8 experts that are
-    // read again and again, 12 -> 14 us).
-    g.stream_once = (int64_t)(a.m_tiles - a.m_tall) * a.N * a.K * 2 > (int64_t)128 << 20;
-    const int n_tiles_n = a.N / (NWV * NS * 32);
+    g.stream_once = worth_streaming(a);
+    const int n_tiles_n = a.N / (kWaves * NS * 32);
     g.gm = tile_group_height(a.m_tiles, a.m_tall, a.K > a.N);
     g.nw = tile_block_width(n_tiles_n, g.gm);
     const int total = a.m_tiles * n_tiles_n;
-    const int cap = (NWV == kWaves ? 2 : 3) * persistent_grid(st);   // workgroups per compute unit
-    const int grid = total < cap ? (total + 7) / 8 * 8 : cap;   // multiple of 8 XCDs
-    hipExtLaunchKernelGGL((grouped_gemm_nt<BM, NS, NB, RELU, FUSE, NWV>), dim3(grid), dim3(NWV * 64), kLdsBytes, st,
+    const int cap = (a.m_few ? 1 : 2) * persistent_grid(st);  // two workgroups per compute unit
+    g.big_wgs = total < cap ? (total + 7) / 8 * 8 : cap;     // multiple of 8 XCDs
+    const int few_wgs = (a.m_few * (a.N / (32 * kFewStripes)) + 7) / 8 * 8;
+    hipExtLaunchKernelGGL((grouped_gemm_nt<BM, NS, NB, RELU, FUSE>), dim3(g.big_wgs + few_wgs), dim3(kWaves * 64), kLdsBytes, st,
                           ev ? ev->start : nullptr, ev ? ev->stop : nullptr, 0, g);
     return (int)hipGetLastError();
 }
@@ -435,8 +621,8 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 // workgroup with the most tiles.  A launch that leaves
 // workgroup slots idle streams every tile's weights through few registers per compute unit, so
 // narrow 64-row tiles also fetch four K-steps ahead instead of two where the K loop allows it (with
-// 128-row tiles a five-stage token ring would not leave room for two workgroups per compute unit,
-// and the loads of a wavefront complete in order, so the ring has to be as deep as the weights).
+// 128-row tiles four steps ahead, one workgroup per compute unit, change nothing: 96 tiles of K = 3072
+// 34 us either way).
 template <int BM, bool RELU, int FUSE>
 int launch_width(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
@@ -445,36 +631,45 @@ int launch_width(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
     bool wide = a.N % 256 == 0 && (t_wide + slots - 1) / slots * 8 <= (2 * t_wide + slots - 1) / slots * 5;
     // Wide tiles for at most three quarters of the workgroup slots, over mostly single-tile experts:
     // the launch is a stream of weights, and twice as many narrower tiles keep more of it in flight
-    // (64 experts, 8192 tokens, second GEMM: 95 -> 87 us; 128 experts, 512 tokens: 92 -> 81 us; with
-    // wide tiles for 0.8 of the slots the narrow ones are 6 % slower, and many-token experts prefer
-    // the wide tile at any count).
+    // (64 experts, 8192 tokens, second GEMM: 95 -> 87 us; 32 experts x 62 tokens, first GEMM: 38 -> 34 us;
+    // many-token experts prefer the wide tile at any count).
     if (wide && 4 * t_wide <= 3 * slots && 2 * a.m_tall <= a.m_tiles) wide = false;
     if (wide) return launch_as<BM, 2, 2, RELU, FUSE>(a, st, ev);
-    if constexpr (BM == kGemmTileSmall) {
-        // 128-wide tiles for at most three quarters of the workgroup slots, and few tokens per tile:
-        // workgroups of two wavefronts (64 weight rows), three per compute unit, put twice as many
-        // weight streams in flight.  (A 128-token batch's second GEMM, 312 tiles: 53 -> 47 us.  With
-        // tiles for 0.8 of the slots and more, or with full token tiles, fetching the token rows twice
-        // as often costs more than the streams gain.)
-        const int64_t rows = a.a_bytes / (2 * (int64_t)a.K);
-        if (4 * (int64_t)a.m_tiles * (a.N / 128) <= 3 * slots && rows <= 32 * (int64_t)a.m_tiles) {
-            if (a.K % 256 == 0) return launch_as<BM, 1, 4, RELU, FUSE, 2>(a, st, ev);
-            return launch_as<BM, 1, 2, RELU, FUSE, 2>(a, st, ev);
-        }
+    if constexpr (BM == kGemmTileSmall)
         if (a.K % 256 == 0) return launch_as<BM, 1, 4, RELU, FUSE>(a, st, ev);
-    }
     return launch_as<BM, 1, 2, RELU, FUSE>(a, st, ev);
+}
+
+// A launch of few-token tiles only.  One stripe per workgroup keeps most workgroups going; two, which
+// fetch the token rows half as often, are faster from 16 rows per tile on if that leaves at least 160
+// workgroups (128 experts x 23 tokens: 113 / 113 -> 112 / 106 us; 8 x 32 tokens, second GEMM, 96
+// workgroups: 9.4 -> 11.6 us).
+template <int NS, bool RELU, int FUSE>
+int launch_stream_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
+{
+    const int grid = (a.m_few * (a.N / (32 * NS)) + 7) / 8 * 8;
+    if (worth_streaming(a))
+        hipExtLaunchKernelGGL((stream_gemm_nt<NS, RELU, FUSE, true>), dim3(grid), dim3(kWaves * 64), 0, st, ev ? ev->start : nullptr,
+                              ev ? ev->stop : nullptr, 0, a);
+    else
+        hipExtLaunchKernelGGL((stream_gemm_nt<NS, RELU, FUSE, false>), dim3(grid), dim3(kWaves * 64), 0, st, ev ? ev->start : nullptr,
+                              ev ? ev->stop : nullptr, 0, a);
+    return (int)hipGetLastError();
 }
 
 template <bool RELU, int FUSE>
 int launch_shape(const GemmArgs &a, int tile_m, hipStream_t st, const LaunchEvents *ev)
 {
-    if (a.m_tiles <= 0) {                                    // nothing to launch: keep the events usable
+    if (a.m_tiles + a.m_few <= 0) {                          // nothing to launch: keep the events usable
         if (ev) {
             (void)hipEventRecord(ev->start, st);
             (void)hipEventRecord(ev->stop, st);
         }
         return 0;
+    }
+    if (a.m_tiles == 0) {
+        if (a.few_rows > 16 * a.m_few && a.m_few * (a.N / 64) >= 160) return launch_stream_as<2, RELU, FUSE>(a, st, ev);
+        return launch_stream_as<1, RELU, FUSE>(a, st, ev);
     }
     if (tile_m == kGemmTileSmall) return launch_width<kGemmTileSmall, RELU, FUSE>(a, st, ev);
     return launch_width<kGemmTileM, RELU, FUSE>(a, st, ev);
@@ -489,7 +684,7 @@ void forget_stream(hipStream_t st)
 }
 
 int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t expert_bytes, const TileDesc *tiles,
-                     int32_t m_tiles, int32_t m_tall, int32_t d, int32_t F, void *sink, hipStream_t st,
+                     int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F, void *sink, hipStream_t st,
                      const LaunchEvents *ev, int32_t a_rows, const int32_t *perm, int32_t map_len, int32_t top_k,
                      int32_t tile_m)
 {
@@ -502,6 +697,8 @@ int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t exper
     a.tiles = tiles;
     a.m_tiles = m_tiles;
     a.m_tall = m_tall;
+    a.m_few = m_few;
+    a.few_rows = few_rows;
     a.N = F;
     a.K = d;
     a.a_bytes = (uint32_t)((size_t)a_rows * d * 2);
@@ -513,7 +710,7 @@ int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t exper
 }
 
 int launch_ffn_gemm2(const void *h, void *y_perm, const char *pool, size_t expert_bytes, const TileDesc *tiles,
-                     int32_t m_tiles, int32_t m_tall, int32_t d, int32_t F, void *sink, hipStream_t st,
+                     int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F, void *sink, hipStream_t st,
                      const LaunchEvents *ev, int32_t a_rows, const int32_t *perm, const float *gate_perm, int32_t tile_m)
 {
     GemmArgs a{};
@@ -525,6 +722,8 @@ int launch_ffn_gemm2(const void *h, void *y_perm, const char *pool, size_t exper
     a.tiles = tiles;
     a.m_tiles = m_tiles;
     a.m_tall = m_tall;
+    a.m_few = m_few;
+    a.few_rows = few_rows;
     a.N = d;
     a.K = F;
     a.a_bytes = (uint32_t)((size_t)a_rows * F * 2);

@@ -54,7 +54,8 @@ int launch_gather(const void *x, const int32_t *perm, int32_t T, int32_t d, void
 // K-b: h = relu(x_perm W_in^T) then y_perm = h W_out^T for the experts in tbl.
 // tiles[0 .. m_tiles) are the token tiles of the experts to compute (see launch_build_tiles); the
 // first m_tall of them belong to experts with more than one tile; tile_m = rows per tile (64 when
-// most experts of the layer have at most 64 tokens, 128 otherwise).
+// most experts of the layer have at most 64 tokens, 128 otherwise).  Behind them come m_few tiles of at
+// most 64 rows each, few_rows altogether, that are streamed rather than walked.
 // sink: kGemmSinkBytes of device scratch that absorbs the stores of rows past a tile's end.
 // With a row map (perm, and for GEMM 2 gate_perm) the gather / combine passes are folded in:
 // GEMM 1 then reads row r from x[perm[r] / k] (x_perm = x in token order, k rows per token), GEMM 2 writes
@@ -62,13 +63,13 @@ int launch_gather(const void *x, const int32_t *perm, int32_t T, int32_t d, void
 // a_rows: rows of the token operand (x_perm / h, or x when gathering), map_len: entries of perm.
 // The experts are read from their pool slots in the slot layout below.
 int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t expert_bytes,
-                     const TileDesc *tiles, int32_t m_tiles, int32_t m_tall, int32_t d, int32_t F, void *sink,
-                     hipStream_t st, const LaunchEvents *ev, int32_t a_rows, const int32_t *perm = nullptr,
-                     int32_t map_len = 0, int32_t k = 1, int32_t tile_m = 128);
+                     const TileDesc *tiles, int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F,
+                     void *sink, hipStream_t st, const LaunchEvents *ev, int32_t a_rows,
+                     const int32_t *perm = nullptr, int32_t map_len = 0, int32_t k = 1, int32_t tile_m = 128);
 int launch_ffn_gemm2(const void *h, void *y_perm, const char *pool, size_t expert_bytes,
-                     const TileDesc *tiles, int32_t m_tiles, int32_t m_tall, int32_t d, int32_t F, void *sink,
-                     hipStream_t st, const LaunchEvents *ev, int32_t a_rows, const int32_t *perm = nullptr,
-                     const float *gate_perm = nullptr, int32_t tile_m = 128);
+                     const TileDesc *tiles, int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F,
+                     void *sink, hipStream_t st, const LaunchEvents *ev, int32_t a_rows,
+                     const int32_t *perm = nullptr, const float *gate_perm = nullptr, int32_t tile_m = 128);
 
 // Slot layout.  The host block of an expert is W_in [F, d] then W_out [d, F], row-major (the ABI);
 // a pool slot holds the same two matrices, each in MFMA-fragment order: a matrix [R, K] is cut

@@ -1,0 +1,85 @@
+"""Experts with few tokens: the tiles that the grouped FFN streams (64 rows, 32 or 64 weight rows per
+workgroup, the sum over K split between wavefronts), at the edges of their row blocks, for the smallest
+and odd K ranges of a wavefront, alone in a launch and beside larger tiles; in one wave and in many."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import assert_close, bf16_tensor_to_f32, make_runner, oracle_layer, say
+from paper_2310_18859_amd.runner import MoERunner
+from workloads import Workload, gen_gate, gen_x
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64]
+SEVERAL = [65, 130, 1, 64, 129]                        # experts of several streamed tiles
+# 50 experts of 1..45 tokens beside six of 65..250, which are walked in larger tiles
+BESIDE = [1 + (7 * i) % 45 for i in range(50)] + [65, 96, 127, 128, 129, 250]
+
+
+def ids_with_counts(counts, seed):
+    ids = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    return np.random.default_rng(seed).permutation(ids).astype(np.int32)
+
+
+def forward(r, x_bits, ids, alpha):
+    plan = r.ctx.moe_plan(0, ids)
+    x, i, a, y = r.to_device(x_bits, ids, alpha)
+    y.fill_(7.0)                                        # every row must be overwritten
+    torch.cuda.synchronize()
+    r.ctx.moe_layer_forward(plan, x, i, a, y, r.workspace, r.compute, r.copy)
+    r.sync()
+    return plan, y
+
+
+@pytest.mark.parametrize("name,counts,d,F", [
+    ("edges", EDGES, 128, 128),                         # one step of 32 K values per wavefront
+    ("edges", EDGES, 384, 640),                         # 3 and 5 steps: less than are loaded ahead
+    ("edges", EDGES, 768, 3072),
+    ("several-tiles", SEVERAL, 256, 896),               # 7 steps
+    ("beside-larger", BESIDE, 256, 512),
+    ("beside-larger", BESIDE, 128, 896),
+])
+def test_few_token_experts(name, counts, d, F):
+    T, E = sum(counts), len(counts)
+    say(f"few-token experts: {name} E={E} T={T} d={d} F={F}")
+    wl = Workload(600 + len(counts), name, 1, E, d, F, T, None, E, E)
+    x_bits, ids, alpha = gen_x(wl, 0), ids_with_counts(counts, d + F), gen_gate(wl, 0)
+    r = make_runner(wl)
+    ref = oracle_layer(wl, r, 0, x_bits, ids, alpha)
+    out = {}
+    for fused in (False, True):
+        r.ctx.set_fusion(fused)
+        _, y = forward(r, x_bits, ids, alpha)
+        assert_close(bf16_tensor_to_f32(y), ref, f"{name} fused={fused}")
+        out[fused] = y.view(torch.uint16).cpu().numpy()
+    assert np.array_equal(out[False], out[True])
+    # cut into waves of at most five experts: the same sums in the same order
+    rw = MoERunner(1, E, d, F, 10 if E > 10 else E, 5, T)
+    rw.host_weights = r.host_weights
+    rw.ctx.bind_host_weights([r.host_weights.data_ptr() + e * rw.expert_bytes for e in range(E)], keep=r.host_weights)
+    plan, y = forward(rw, x_bits, ids, alpha)
+    assert plan.n_waves >= (E + 4) // 5
+    assert np.array_equal(y.view(torch.uint16).cpu().numpy(), out[True])
+    rw.close()
+    r.close()
+
+
+def test_few_token_experts_two_per_token():
+    E, d, F, k = 9, 256, 384, 2
+    tokens = 70
+    say(f"few-token experts: {k} per token, E={E}")
+    wl = Workload(640, "few-topk", 1, E, d, F, tokens * k, None, E, E)
+    rng = np.random.default_rng(3)
+    x_bits, alpha = gen_x(wl, 0, tokens), gen_gate(wl, 0, tokens * k)
+    ids = rng.integers(0, E, tokens * k).astype(np.int32)
+    r = make_runner(wl)
+    r.ctx.set_top_k(k)
+    hw = r.host_weights.numpy()
+    ref = oracle.moe_forward_topk(x_bits, ids.reshape(tokens, k), alpha.reshape(tokens, k), [hw[e] for e in range(E)], d, F)
+    for fused in (False, True):
+        r.ctx.set_fusion(fused)
+        _, y = forward(r, x_bits, ids, alpha)
+        assert_close(bf16_tensor_to_f32(y), ref, f"top-{k} fused={fused}")
+    r.close()
