@@ -557,7 +557,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
 std::mutex g_cu_mu;
 std::unordered_map<hipStream_t, int> g_cu_cache;
 
-int persistent_grid(hipStream_t st)
+}  // namespace
+
+int stream_compute_units(hipStream_t st)
 {
     std::lock_guard<std::mutex> lk(g_cu_mu);
     auto &cache = g_cu_cache;
@@ -580,6 +582,8 @@ int persistent_grid(hipStream_t st)
     cache[st] = cus;
     return cus;
 }
+
+namespace {
 
 // Weights that only one token tile reads are streamed past L2's replacement - when there are more of them
 // than stay in the 256 MB Infinity Cache from one pass to the next anyway (measured: a 128-token batch
@@ -605,7 +609,7 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
     g.gm = tile_group_height(a.m_tiles, a.m_tall, a.K > a.N);
     g.nw = tile_block_width(n_tiles_n, g.gm);
     const int total = a.m_tiles * n_tiles_n;
-    const int cap = (a.m_few ? 1 : 2) * persistent_grid(st);  // two workgroups per compute unit
+    const int cap = (a.m_few ? 1 : 2) * stream_compute_units(st);  // two workgroups per compute unit
     g.big_wgs = total < cap ? (total + 7) / 8 * 8 : cap;     // multiple of 8 XCDs
     const int few_wgs = (a.m_few * (a.N / (32 * kFewStripes)) + 7) / 8 * 8;
     hipExtLaunchKernelGGL((grouped_gemm_nt<BM, NS, NB, RELU, FUSE>), dim3(g.big_wgs + few_wgs), dim3(kWaves * 64), kLdsBytes, st,
@@ -626,7 +630,7 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 template <int BM, bool RELU, int FUSE>
 int launch_width(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
-    const int64_t slots = 2 * (int64_t)persistent_grid(st);
+    const int64_t slots = 2 * (int64_t)stream_compute_units(st);
     const int64_t t_wide = (int64_t)a.m_tiles * (a.N / 256);
     bool wide = a.N % 256 == 0 && (t_wide + slots - 1) / slots * 8 <= (2 * t_wide + slots - 1) / slots * 5;
     // Wide tiles for at most three quarters of the workgroup slots, over mostly single-tile experts:

@@ -84,6 +84,8 @@ inline size_t slot_piece_offset(size_t r, size_t p, size_t K) { return ((r / 32)
 // plain copy of the host block into the slot).  d, F <= kMaxRelayoutK (a stripe is held in the
 // registers of one workgroup).
 constexpr int kMaxRelayoutK = 4096;
+// Compute units a stream's kernels may run on, a multiple of 8.
+int stream_compute_units(hipStream_t st);
 // A stream is about to be destroyed: drop what is cached about it (its handle may be reused).
 void forget_stream(hipStream_t st);
 // Expands tbl into token tiles: entry i gets ceil(count_i / tbl.tile_m) consecutive descriptors,
