@@ -29,6 +29,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "handover.h"
 #include "kernels.h"
 
 namespace sida {
@@ -335,8 +336,6 @@ __device__ __forceinline__ float gate_value(float v, const GateKind &k)
     return fabsf(v) < k.small ? t : fmaf(k.gain, n, 1.f - k.gain);
 }
 
-constexpr int kSteps = 8;                                      // time steps per chunk of the hand-over between the layers
-
 template <int C>
 struct RecurrenceLds {
     static constexpr int kSeg = C / 8, kSegPitch = kSeg + 4;   // the eight segments start in different banks
@@ -385,7 +384,6 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
     const int my_gate = (s * C + u) * 4;
     // this unit's place in a row of the state; the quad's other lanes write to the row's unused places
     const int h_out = s == 0 ? (u / kSeg) * kSegPitch + u % kSeg : (u % 8) * kSegPitch + kSeg + s;
-    const int chunks = (T + kSteps - 1) / kSteps;
     if (tid < kRow) lds.h[2 * kSteps - 1][tid] = 0.f;          // "the step before the first"
     int seen = 0;
     float next[kSteps];
@@ -438,27 +436,13 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
         z_in += 4 * C;
         lds_barrier();
     };
-    for (int c = 0; c < chunks; ++c) {
+    auto take = [&](int c) {
 #pragma unroll
         for (int i = 0; i < kSteps; ++i) lds.pre[i][tid] = next[i];
-        if (c > 0) store_chunk(c - 1);
-        const int n = __builtin_amdgcn_readfirstlane(min(kSteps, T - c * kSteps));
         row = lds.h[(c & 1) * kSteps];
         z_in = &lds.pre[0][tid];
-        // The store of the previous chunk's states gets three steps to complete, the loads of the next
-        // chunk's pre-activations get the second half of this one.
-        int i = 0;
-#pragma clang loop unroll(disable)
-        for (; i < min(n, 3); ++i) step();
-        if (POST && c > 0) post();
-#pragma clang loop unroll(disable)
-        for (; i < min(n, kSteps / 2); ++i) step();
-        if (c + 1 < chunks) fetch(c + 1);
-#pragma clang loop unroll(disable)
-        for (; i < n; ++i) step();
-    }
-    store_chunk(chunks - 1);
-    if (POST) post();
+    };
+    walk_chunks<kSteps, POST>(T, take, store_chunk, step, fetch, post, lds_barrier);
 }
 
 // D[4 x 64] += A[4 x 16] B[16 x 64] as 16 instructions of 16 4x4 blocks: lane l gives A[l % 4][l / 4]
