@@ -655,6 +655,13 @@ __global__ __launch_bounds__(512) void hash_attention(const float *__restrict__ 
 #pragma unroll
             for (int j = 0; j < 4; ++j) v[b][j] = hv[(size_t)min(u0 + b * 16 + 4 * g + j, T - 1) * C];
         loads_issued();
+        // A key of weight 0 is multiplied too.  A state is NaN or within [-1, 1]; a key with a NaN has a NaN score
+        // and weight 0 for every query: any finite number in its place (the median with a NaN is the least of
+        // the others) leaves it out of the sums.
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[b][j] = __builtin_amdgcn_fmed3f(v[b][j], -2.f, 2.f);
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc = mfma4(v[b], pv[b], acc);
     }

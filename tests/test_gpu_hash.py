@@ -115,6 +115,37 @@ def test_hash_forward_at_the_edges_of_tiles_and_chunks(d, C, L, E, k, n_seq, T):
     test_hash_forward_against_oracle(d, C, L, E, k, n_seq, T)
 
 
+def assert_agrees(got_ids, got_alpha, probs, k):
+    """ids [L, t, k] and alpha [L, t, k] are a valid choice by the oracle's probabilities [L, t, E]."""
+    chosen = np.take_along_axis(probs, got_ids.astype(np.int64), axis=2)
+    np.testing.assert_allclose(got_alpha, chosen, atol=ALPHA_TOL)
+    assert (chosen.min(axis=2) >= np.sort(probs, axis=2)[:, :, -k] - ALPHA_TOL).all()
+
+
+@pytest.mark.parametrize("n_seq,T,bad", [(1, 40, 37), (2, 100, 99), (1, 100, 65), (1, 500, 470)])
+def test_a_token_that_is_not_a_number_leaves_earlier_tokens_as_they_are(n_seq, T, bad):
+    """A NaN embedding at token t makes the LSTM states from t on NaN; their scores are NaN, their attention weights
+    0: tokens before t are those of the sequence cut off at t; other sequences do not change at all."""
+    say(f"hash function: NaN at token {bad} of {n_seq} x {T}")
+    d, C, L, E, k = 64, 128, 2, 20, 2
+    rng = np.random.default_rng(T + bad)
+    cfg = sm.SidaHashConfig(d, C, L, E, k, T)
+    params = make_params(rng, d, C, L, E)
+    x_bits = f32_to_bf16_bits(rng.standard_normal((n_seq * T, d)).astype(np.float32))
+    clean_ids, clean_alpha = run_hash(cfg, params, x_bits, n_seq, T)
+    broken = x_bits.copy()
+    broken[bad, 3] = 0x7FC0
+    ids, alpha = run_hash(cfg, params, broken, n_seq, T)
+    _, _, probs = hash_fn.hash_forward(params, bf16_bits_to_f32(x_bits[:bad]), L, E, k)
+    assert_agrees(ids[:, :bad], alpha[:, :bad], probs, k)
+    assert np.isnan(alpha[:, bad]).all()
+    # behind it no score is left: the residual, the token's own compressed embedding, goes to the heads alone
+    c0 = bf16_bits_to_f32(x_bits[bad + 1:T]).astype(np.float64) @ params["w_in"].T + params["b_in"]
+    e = np.exp((c0 @ params["w_out"].T + params["b_out"]).reshape(-1, L, E).transpose(1, 0, 2))
+    assert_agrees(ids[:, bad + 1:T], alpha[:, bad + 1:T], e / e.sum(axis=2, keepdims=True), k)
+    assert np.array_equal(ids[:, T:], clean_ids[:, T:]) and np.array_equal(alpha[:, T:], clean_alpha[:, T:])
+
+
 def test_predicted_table_drives_the_layer():
     """Hash-building side to inference side: the predicted ids / alpha of layer l (top-2) are planned
     and run through the MoE layer, and the result equals the oracle's layer on the same table."""
