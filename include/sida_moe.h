@@ -348,7 +348,9 @@ int sida_combine(sida_ctx *ctx, const float *alpha_dev, int32_t T, void *y_dev,
  * LSTM never cross a sequence boundary).  Outputs, device: ids_dev int32 and alpha_dev fp32, both
  * [L, n_seq * seq_len, top_k] - layer l's slice is exactly the ids / alpha array that
  * sida_moe_plan (after a copy to the host) and sida_moe_layer_forward take (with sida_set_top_k).
- * workspace_dev: device, 256-byte aligned, >= sida_hash_workspace_bytes(n_seq * seq_len).
+ * workspace_dev: device, 256-byte aligned, >= sida_hash_workspace_bytes(n_seq * seq_len), of this call
+ * alone until it is done: calls that use one workspace at the same time race, and their ids (always
+ * within 0 .. E-1) and alpha are then undefined; they may also take about a second longer.
  * Limits: C is 64 or 128; d_model a multiple of 8, 8 .. 8192; E <= SIDA_MAX_E; L*E <= 8192;
  * top_k <= min(E, SIDA_MAX_TOP_K);
  * seq_len <= max_seq_len <= 4096.  Asynchronous on `stream`. */
@@ -374,7 +376,7 @@ int sida_hash_forward(const sida_hash_config *cfg, const float *params_dev, cons
  * fit (more than 4095 tokens at C = 128, 8191 at C = 64) -> SIDA_ENOSPC, nothing enqueued.
  * All calls on one GPU share that GPU's array (it keeps the last call's contents, and nothing in
  * it needs clearing): calls that overlap in time on one GPU - on different streams or from
- * different threads - race; order them on one stream or with events. */
+ * different threads - race as calls with one workspace do; order them on one stream or with events. */
 #define SIDA_HASH_STATIC_SCRATCH_BYTES (16u << 20)
 int sida_hash_forward_static(const sida_hash_config *cfg, const float *params_dev, const void *x_dev, int32_t n_seq,
                              int32_t seq_len, int32_t *ids_dev, float *alpha_dev, void *stream);

@@ -12,6 +12,37 @@ namespace sida {
 
 constexpr int kSteps = 8;        // time steps per chunk of the hand-over between the layers
 
+// What a workgroup does, by the ticket it drew: layer 1 of a sequence (0), the gate pre-activations between
+// the layers (1), layer 2 (2).  Any number is a valid ticket: the counters stand in the caller's workspace,
+// and another call that uses it meanwhile (not allowed, and wrong results for both) may write over them.
+struct Role {
+    int what, seq;
+};
+SIDA_HD Role role_of(int ticket, int n_seq)
+{
+    const unsigned t = (unsigned)ticket, what = t / (unsigned)n_seq;
+    return Role{what < 2u ? (int)what : 2, (int)(t % (unsigned)n_seq)};
+}
+
+// Waits until the counter that peek() reads has reached `want`; `seen` is the most that it has shown.  In a
+// call that has its workspace to itself the counter gets there within microseconds: what is waited for is the
+// next chunk of a workgroup that already runs.  Another call that clears or writes over the counter would be
+// waited for without end, so a wait gives up after kMostPeeks (about a second), and every later one with it.
+constexpr int kMostPeeks = 1 << 20, kGaveUp = 0x7fffffff;
+template <class Peek>
+SIDA_HD void wait_for(int want, int &seen, Peek &&peek)
+{
+#pragma clang loop unroll(disable)
+    for (int left = kMostPeeks; seen < want; --left) {
+        if (left == 0) {
+            seen = kGaveUp;
+            return;
+        }
+        const int now = peek();
+        seen = now > seen ? now : seen;
+    }
+}
+
 // The walk of one wavefront of an LSTM layer's workgroup over a sequence of T time steps:
 //   take(c)    chunk c's inputs go where the steps read them
 //   store(c)   its part of chunk c's states starts on its way to memory

@@ -385,14 +385,16 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
     // this unit's place in a row of the state; the quad's other lanes write to the row's unused places
     const int h_out = s == 0 ? (u / kSeg) * kSegPitch + u % kSeg : (u % 8) * kSegPitch + kSeg + s;
     if (tid < kRow) lds.h[2 * kSteps - 1][tid] = 0.f;          // "the step before the first"
-    int seen = 0;
+    int seen = 0, ahead = 0;
     float next[kSteps];
     auto fetch = [&](int c) {                                  // past the end: zeros (the descriptor ends there)
-        if (WAIT)
-            while (__builtin_amdgcn_readfirstlane(seen) < c + 1) seen = peek(arrived);
+        if (WAIT) {
+            seen = max(seen, __builtin_amdgcn_readfirstlane(ahead));
+            wait_for(c + 1, seen, [&] { return __builtin_amdgcn_readfirstlane(peek(arrived)); });
+        }
 #pragma unroll
         for (int i = 0; i < kSteps; ++i) next[i] = load_f32<WAIT ? kAgent : 0>(pre_rsrc, (c * kSteps + i) * 4 * C * 4 + my_gate);
-        if (WAIT) seen = peek(arrived);                        // looked at when the next chunk is due
+        if (WAIT) ahead = peek(arrived);                       // looked at when the next chunk is due
     };
     // chunk c's states, two per thread, from LDS to global memory (past the end: dropped)
     auto store_chunk = [&](int c) {
@@ -479,7 +481,7 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
     const int chunks = (T + kSteps - 1) / kSteps;
     int seen = 0;
     for (int c = 0; c < chunks; ++c) {
-        while (__builtin_amdgcn_readfirstlane(seen) < (c + 1) * (C / 16)) seen = peek(arrived);
+        wait_for((c + 1) * (C / 16), seen, [&] { return __builtin_amdgcn_readfirstlane(peek(arrived)); });
         float *in = lds.in[c & 1];
         if (tid < kSteps * C / 4) {                            // past the end: zeros
             const i32x4 v = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(h_rsrc, (c * kSteps * C + tid * 4) * 4, 0, kAgent));
@@ -515,7 +517,8 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
 // first all of layer 1, then all in between, then all of layer 2.  Tickets are drawn by workgroups
 // that run, so whatever a workgroup waits for is done by a workgroup that already runs and waits, if
 // at all, for a lower ticket only; layer 1 waits for nobody.  Hence every wait ends, whatever the
-// order in which workgroups are started and whatever else runs on the GPU.
+// order in which workgroups are started and whatever else runs on the GPU.  (Counters that another call
+// writes over, against the rules, end them too: see handover.h.)
 template <int C>
 __global__ __launch_bounds__(4 * C) void hash_recurrence(float *pre, const float *__restrict__ w_hh1,
                                                          const float *__restrict__ w_ih2, const float *__restrict__ w_hh2,
@@ -526,7 +529,8 @@ __global__ __launch_bounds__(4 * C) void hash_recurrence(float *pre, const float
     if (threadIdx.x == 0) lds.ticket = __hip_atomic_fetch_add(counters, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(lds.ticket);
-    const int role = ticket / n_seq, seq = ticket % n_seq;
+    const Role of = role_of(ticket, n_seq);
+    const int role = of.what, seq = of.seq;
     float *p = pre + (size_t)seq * T * 4 * C, *a = h1 + (size_t)seq * T * C, *b = h2 + (size_t)seq * T * C;
     int *layer1_done = counters + kLine * (1 + 2 * seq), *gates_done = layer1_done + kLine;
     if (role == 0) lstm_layer<C, false, true>(p, w_hh1, T, a, nullptr, layer1_done, lds);

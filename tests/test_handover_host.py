@@ -21,6 +21,22 @@ extern "C" int walk(int T, char *out, int *chunk)
     return n;
 }
 extern "C" int steps_per_chunk() { return kSteps; }
+extern "C" void role(int ticket, int n_seq, int *what, int *seq)
+{
+    const Role r = role_of(ticket, n_seq);
+    *what = r.what;
+    *seq = r.seq;
+}
+// Waits for 1, 2, .. n on a counter that shows values[0 .. count) and then the last one for ever; returns the
+// peeks it took, and in *seen what it went on with.
+extern "C" long long waits(int n, const int *values, int count, int *seen)
+{
+    long long peeks = 0;
+    *seen = 0;
+    for (int want = 1; want <= n; ++want) wait_for(want, *seen, [&] { return values[peeks++ < count ? peeks - 1 : count - 1]; });
+    return peeks;
+}
+extern "C" int most_peeks() { return kMostPeeks; }
 """
 
 
@@ -32,7 +48,9 @@ def lib(tmp_path_factory):
         f.write(SOURCE)
     subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas", "-I" + CSRC, "-o", so, src],
                    check=True)
-    return ctypes.CDLL(so)
+    lib = ctypes.CDLL(so)
+    lib.waits.restype = ctypes.c_longlong
+    return lib
 
 
 def walk(lib, T):
@@ -70,3 +88,35 @@ def test_a_counted_chunk_has_arrived(lib, T):
     for c in range(K):
         assert stored[c] < posts[c] and (c + 1 == K or posts[c] < stored[c + 1])
         assert "B" in names[events.index(("t", c)):stored[c]]
+
+
+@pytest.mark.parametrize("n_seq", [1, 2, 7, 85])
+def test_every_ticket_is_a_role_of_a_sequence(lib, n_seq):
+    """3 * n_seq tickets are all roles of all sequences, lower roles first; any other number stays in range."""
+    def role(ticket):
+        what, seq = ctypes.c_int(-1), ctypes.c_int(-1)
+        lib.role(ticket, n_seq, ctypes.byref(what), ctypes.byref(seq))
+        return what.value, seq.value
+    assert [role(t) for t in range(3 * n_seq)] == [(w, s) for w in range(3) for s in range(n_seq)]
+    for t in [-1, -2, -n_seq, -3 * n_seq - 1, -2**31, 2**31 - 1, 3 * n_seq, 0x7FC00000, -0x7FC00000]:
+        what, seq = role(t)
+        assert 0 <= what <= 2 and 0 <= seq < n_seq, t
+
+
+def waits(lib, n, values):
+    seen = ctypes.c_int(-1)
+    peeks = lib.waits(n, (ctypes.c_int * len(values))(*values), len(values), ctypes.byref(seen))
+    return peeks, seen.value
+
+
+def test_a_wait_takes_what_arrives(lib):
+    assert waits(lib, 3, [0, 0, 1, 1, 2, 3]) == (6, 3)
+    assert waits(lib, 5, [0, 5]) == (2, 5)               # what has been seen is not looked at again
+    assert waits(lib, 4, [2, 0, 0, 3, 4]) == (5, 4)      # a counter that was cleared meanwhile
+
+
+@pytest.mark.parametrize("stuck", [0, 1, 3, -2**31])
+def test_a_wait_for_what_never_arrives_ends_and_is_the_last(lib, stuck):
+    """The counter stays below what is waited for: the wait gives up once, and no later wait looks at it again."""
+    peeks, seen = waits(lib, 512, [stuck])
+    assert peeks <= lib.most_peeks() + 4 and seen == 2**31 - 1
