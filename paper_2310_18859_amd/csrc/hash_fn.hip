@@ -65,6 +65,12 @@ __device__ __forceinline__ f32x4 mfma4(const f32x4 &a, const f32x4 &b, f32x4 d)
 // The loads above stay above: a wavefront has them all in flight (the compiler would rather save registers).
 __device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
 __device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+// Parameters, which the caller may hand over at the address of any float.
+__device__ __forceinline__ f32x4 load4_param(const float *p)
+{
+    typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+    return *reinterpret_cast<const f32x4_any *>(p);
+}
 
 // ---- exchange between lanes ---------------------------------------------------------------------
 template <int CTRL>
@@ -177,19 +183,31 @@ struct TileRow<__bf16> {
         for (int e = 0; e < 8; ++e) v[e] = (float)q[e];
     }
 };
+// A piece whose address is a multiple of its values' size only.
+__device__ __forceinline__ void copy_piece(const float *p, char *dst)
+{
+    *reinterpret_cast<f32x4 *>(dst) = f32x4{p[0], p[1], p[2], p[3]};
+}
+__device__ __forceinline__ void copy_piece(const __bf16 *p, char *dst)
+{
+    *reinterpret_cast<bf16x8 *>(dst) = bf16x8{p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]};
+}
 // The loads of one wavefront for tiles of ROWS rows of a [rows, k] matrix, shared by SHARE wavefronts.
 // Every wavefront issues kLoads per tile (a tile of fewer loads is loaded twice over, with the same
-// bytes); rows and columns past the end repeat the last ones.
-template <typename T, int ROWS, int SHARE>
+// bytes); rows and columns past the end repeat the last ones.  DIRECT: the matrix starts at a 16-byte
+// boundary, as a load into LDS wants it; otherwise the values go through registers.
+template <typename T, int ROWS, int SHARE, bool DIRECT>
 struct TileLoader {
     static constexpr int kAll = ROWS / TileRow<T>::kRowsPerLoad, kLoads = (kAll + SHARE - 1) / SHARE;
     static_assert(ROWS % TileRow<T>::kRowsPerLoad == 0 && (kAll % SHARE == 0 || kAll < SHARE), "whole loads");
     __amdgpu_buffer_rsrc_t rsrc;
+    const T *base;
     int row_at[kLoads], piece[kLoads], dst[kLoads], last;
     __device__ __forceinline__ TileLoader(const T *first_row, int rows_left, int k, int lane, int share)
     {
         const int rows = min(rows_left, ROWS);
         rsrc = make_rsrc(first_row, (uint32_t)rows * (uint32_t)k * (uint32_t)sizeof(T));
+        base = first_row;
         last = k * (int)sizeof(T) - 16;
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) {
@@ -202,10 +220,20 @@ struct TileLoader {
     __device__ __forceinline__ void issue(int step, char *tile) const
     {
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i)
-            load_to_lds(rsrc, row_at[i] + min(step * TileRow<T>::kBytes + piece[i], last), tile + dst[i]);
+        for (int i = 0; i < kLoads; ++i) {
+            const int at = row_at[i] + min(step * TileRow<T>::kBytes + piece[i], last);
+            if constexpr (DIRECT) load_to_lds(rsrc, at, tile + dst[i]);
+            else copy_piece(base + at / (int)sizeof(T), tile + dst[i] + (threadIdx.x & 63) * 16);
+        }
     }
 };
+// All but the last N of this wavefront's tile loads have arrived.
+template <int N, bool DIRECT>
+__device__ __forceinline__ void tiles_arrived()
+{
+    if (DIRECT) wait_memory<N>();
+    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
 
 // ---- dense stages -------------------------------------------------------------------------------
 // out[n, u] = bias_a[u] + bias_b[u] + sum_i in[n, i] w[u, i] for n_tokens tokens and `units` units (w is
@@ -220,7 +248,7 @@ struct TileLoader {
 //    once and the weights are spread over 64 workgroups.
 //  * Large ones by the matrix units: 2 x 2 tiles per wavefront.
 // Also clears the counters of the recurrence behind it.
-template <int TU, int TT, int WU, int WT, int KS, int G, int NB, typename IN>
+template <int TU, int TT, int WU, int WT, int KS, int G, int NB, typename IN, bool DIRECT>
 __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, const float *__restrict__ w,
                                                   const float *__restrict__ bias_a, const float *__restrict__ bias_b, int k,
                                                   int units, int n_tokens, float *__restrict__ out,
@@ -230,8 +258,8 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
     constexpr int kShare = KS == 1 ? 4 : 1;
     constexpr int WR = WU * TU * 16, XR = WT * TT * 16;        // rows staged together
     constexpr int kW = WR * TileRow<float>::kBytes, kStep = kW + XR * TileRow<IN>::kBytes, kStage = G * kStep;
-    typedef TileLoader<float, WR, kShare> LoadW;
-    typedef TileLoader<IN, XR, kShare> LoadX;
+    typedef TileLoader<float, WR, kShare, DIRECT> LoadW;
+    typedef TileLoader<IN, XR, kShare, DIRECT> LoadX;
     constexpr int kStageLoads = G * (LoadW::kLoads + LoadX::kLoads);
     __shared__ __attribute__((aligned(1024))) char ring[(4 / kShare) * NB * kStage];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), col = lane & 15, g = lane >> 4;
@@ -257,7 +285,7 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
         for (int b = 0; b < NB - 1; ++b) issue(first + b * G, b);
         int slot = 0;
         for (int s = first; s < last; s += G) {
-            wait_memory<(NB - 2) * kStageLoads>();
+            tiles_arrived<(NB - 2) * kStageLoads, DIRECT>();
             if (KS == 1) __builtin_amdgcn_s_barrier();         // everyone's part of this stage is here, and the slot
                                                                // filled next has been read by everyone
             issue(s + (NB - 1) * G, slot == 0 ? NB - 1 : slot - 1);
@@ -288,7 +316,7 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
                         for (int i = 0; i < TU; ++i)
                             acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][i][e], b[h][m][e], acc[i][m], 0, 0, 0);
         }
-        wait_memory<0>();                                      // the last loads still write LDS
+        tiles_arrived<0, DIRECT>();                            // the last loads still write LDS
     }
     if (KS > 1) {                                              // the parts of the sum meet in the first wavefront
         __shared__ f32x4 parts[KS][64];
@@ -301,8 +329,8 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
 #pragma unroll
     for (int i = 0; i < TU; ++i) {
         const int u = u0 + (wu * TU + i) * 16 + 4 * g;
-        f32x4 bias = load4(bias_a + u);
-        if (bias_b) bias += load4(bias_b + u);
+        f32x4 bias = load4_param(bias_a + u);
+        if (bias_b) bias += load4_param(bias_b + u);
 #pragma unroll
         for (int m = 0; m < TT; ++m) {
             const int n = n0 + (wt * TT + m) * 16 + col;
@@ -372,7 +400,7 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
         const float *row = w_hh + (size_t)((id & 3) * C + (tid >> 3) * 2 + (id >> 2)) * C + l8 * kSeg;
 #pragma unroll
         for (int i = 0; i < kSeg; i += 4) {
-            const f32x4 v = load4(row + i);
+            const f32x4 v = load4_param(row + i);
             w[j][i] = v[0];
             w[j][i + 1] = v[1];
             w[j][i + 2] = v[2];
@@ -471,7 +499,7 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
     float w[C];                                                // row tid
 #pragma unroll
     for (int k = 0; k < C; k += 4) {
-        const f32x4 v = load4(w_ih + (size_t)tid * C + k);
+        const f32x4 v = load4_param(w_ih + (size_t)tid * C + k);
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[k + e] = v[e];
     }
@@ -683,15 +711,15 @@ __global__ __launch_bounds__(512) void hash_attention(const float *__restrict__ 
 template <int C, int NT, int TT>
 constexpr int heads_lds_bytes() { return C / 32 * (NT + TT) * 16 * TileRow<float>::kBytes; }
 
-template <int C, int NT, int TT>
+template <int C, int NT, int TT, bool DIRECT>
 __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, const float *__restrict__ w_out,
                                                   const float *__restrict__ b_out, int E, int top_k, int n_tokens,
                                                   int32_t *__restrict__ ids, float *__restrict__ alpha)
 {
     constexpr int kPitch = NT * 16 + 16, kMine = (NT + 3) / 4, kSteps32 = C / 32;
     constexpr int kW = NT * 16 * TileRow<float>::kBytes, kStage = kW + TT * 16 * TileRow<float>::kBytes;
-    typedef TileLoader<float, NT * 16, 4> LoadW;
-    typedef TileLoader<float, TT * 16, 4> LoadX;
+    typedef TileLoader<float, NT * 16, 4, DIRECT> LoadW;
+    typedef TileLoader<float, TT * 16, 4, DIRECT> LoadX;
     constexpr int kStepLoads = LoadW::kLoads + LoadX::kLoads;
     static_assert(TT * 16 * kPitch * 4 <= heads_lds_bytes<C, NT, TT>(), "the logits replace the operands");
     static_assert((kSteps32 - 1) * kStepLoads <= 63, "vmcnt range");
@@ -726,17 +754,17 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
                     acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[m][e], acc[i][m], 0, 0, 0);
         }
     };
-    wait_memory<(kSteps32 - 1) * kStepLoads>();
+    tiles_arrived<(kSteps32 - 1) * kStepLoads, DIRECT>();
     __builtin_amdgcn_s_barrier();
     multiply(0);
-    wait_memory<(kSteps32 - 2) * kStepLoads>();
+    tiles_arrived<(kSteps32 - 2) * kStepLoads, DIRECT>();
     __builtin_amdgcn_s_barrier();
     multiply(1);
     if (kSteps32 > 2) {
-        wait_memory<kStepLoads>();
+        tiles_arrived<kStepLoads, DIRECT>();
         __builtin_amdgcn_s_barrier();
         multiply(2);
-        wait_memory<0>();
+        tiles_arrived<0, DIRECT>();
         __builtin_amdgcn_s_barrier();
         multiply(3);
     }
@@ -826,12 +854,17 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
         hipLaunchKernelGGL(kernel, dim3((N + tokens - 1) / tokens, units / rows), dim3(256), 0, st, in, w, ba, bb, k, units, N, out,
                            counters, n_clear);
     };
-    if (N >= 6144) dense(hash_dense<2, 2, 2, 2, 1, 2, 4, __bf16>, 64, 64, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
-    else if (N >= 2048) dense(hash_dense<1, 2, 2, 2, 1, 2, 4, __bf16>, 64, 32, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
-    else dense(hash_dense<1, 1, 1, 1, 4, 2, 4, __bf16>, 16, 16, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
+    // Tiles are loaded straight into LDS, 16 bytes at a time, where x and the parameters start at a 16-byte
+    // boundary (rows are multiples of 16 bytes).  Elsewhere the smallest tiles go through registers.
+    const bool direct = ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(x)) & 15u) == 0;
+    if (!direct) dense(hash_dense<1, 1, 1, 1, 4, 2, 4, __bf16, false>, 16, 16, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
+    else if (N >= 6144) dense(hash_dense<2, 2, 2, 2, 1, 2, 4, __bf16, true>, 64, 64, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
+    else if (N >= 2048) dense(hash_dense<1, 2, 2, 2, 1, 2, 4, __bf16, true>, 64, 32, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
+    else dense(hash_dense<1, 1, 1, 1, 4, 2, 4, __bf16, true>, 16, 16, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
     auto gates = [&](const float *in, const float *w_ih, const float *b_ih, const float *b_hh) {
-        if (N >= 2048) dense(hash_dense<2, 2, 2, 2, 1, 2, 2, float>, 64, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
-        else dense(hash_dense<1, 1, 4, 1, 1, 2, 3, float>, 16, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
+        if (!direct) dense(hash_dense<1, 1, 4, 1, 1, 2, 3, float, false>, 16, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
+        else if (N >= 2048) dense(hash_dense<2, 2, 2, 2, 1, 2, 2, float, true>, 64, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
+        else dense(hash_dense<1, 1, 4, 1, 1, 2, 3, float, true>, 16, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
     };
     gates(c0, w_ih1, b_ih1, b_hh1);
     if (n_seq <= kSideBySide) {
@@ -854,25 +887,27 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
     hipLaunchKernelGGL(hash_attention<C>, dim3(n_seq * blocks_per_seq), dim3(512), score_bytes, st, h2, c0, T, queries,
                        blocks_per_seq, pitch, r);
     hipError_t err = hipSuccess;
-    auto heads = [&](auto nt, auto tt) {
+    auto heads = [&](auto nt, auto tt, auto dir) {
         constexpr int NT = decltype(nt)::value, TT = decltype(tt)::value, kBytes = heads_lds_bytes<C, NT, TT>();
+        constexpr bool DIRECT = decltype(dir)::value;
         if (kBytes > 64 * 1024) {
-            static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&hash_heads<C, NT, TT>),
+            static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&hash_heads<C, NT, TT, DIRECT>),
                                                                   hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
             err = allowed;
             if (err != hipSuccess) return;
         }
-        hipLaunchKernelGGL((hash_heads<C, NT, TT>), dim3((N + TT * 16 - 1) / (TT * 16), sh.L), dim3(256), kBytes, st, r, w_out,
+        hipLaunchKernelGGL((hash_heads<C, NT, TT, DIRECT>), dim3((N + TT * 16 - 1) / (TT * 16), sh.L), dim3(256), kBytes, st, r, w_out,
                            b_out, sh.E, sh.top_k, N, ids, alpha);
     };
-    auto heads_of = [&](auto tt) {
-        if (sh.E <= 16) heads(std::integral_constant<int, 1>(), tt);
-        else if (sh.E <= 64) heads(std::integral_constant<int, 4>(), tt);
-        else if (sh.E <= 128) heads(std::integral_constant<int, 8>(), tt);
-        else heads(std::integral_constant<int, 16>(), tt);
+    auto heads_of = [&](auto tt, auto dir) {
+        if (sh.E <= 16) heads(std::integral_constant<int, 1>(), tt, dir);
+        else if (sh.E <= 64) heads(std::integral_constant<int, 4>(), tt, dir);
+        else if (sh.E <= 128) heads(std::integral_constant<int, 8>(), tt, dir);
+        else heads(std::integral_constant<int, 16>(), tt, dir);
     };
-    if (N >= 2048) heads_of(std::integral_constant<int, 2>());
-    else heads_of(std::integral_constant<int, 1>());
+    if (!direct) heads_of(std::integral_constant<int, 1>(), std::false_type());
+    else if (N >= 2048) heads_of(std::integral_constant<int, 2>(), std::true_type());
+    else heads_of(std::integral_constant<int, 1>(), std::true_type());
     if (err != hipSuccess) return (int)err;
     return (int)hipGetLastError();
 }

@@ -146,6 +146,40 @@ def test_a_token_that_is_not_a_number_leaves_earlier_tokens_as_they_are(n_seq, T
     assert np.array_equal(ids[:, T:], clean_ids[:, T:]) and np.array_equal(alpha[:, T:], clean_alpha[:, T:])
 
 
+@pytest.mark.parametrize("x_off,p_off", [(2, 0), (8, 0), (0, 4), (14, 12)])
+@pytest.mark.parametrize("d,C,L,E,k,n_seq,T", [
+    (200, 128, 2, 12, 2, 2, 21),          # every number of expert tiles, both widths, ragged rows and columns
+    (64, 64, 2, 33, 1, 1, 40),
+    (64, 128, 2, 70, 1, 1, 9),
+    (72, 64, 1, 250, 3, 1, 17),
+    (64, 128, 1, 20, 1, 32, 64),          # as many tokens as take larger tiles when they are aligned
+])
+def test_hash_forward_off_a_16_byte_boundary(d, C, L, E, k, n_seq, T, x_off, p_off):
+    """Embeddings at the address of any bf16 value, parameters at that of any float (a slice of a larger tensor)."""
+    say(f"hash function d={d} C={C} E={E} {n_seq} x {T}, x {x_off} and parameters {p_off} bytes off")
+    dev, N = torch.device("cuda:0"), n_seq * T
+    rng = np.random.default_rng(d + E)
+    cfg = sm.SidaHashConfig(d, C, L, E, k, T)
+    params = make_params(rng, d, C, L, E)
+    flat = np.concatenate([params[n].reshape(-1) for n, _ in hash_fn.param_shapes(d, C, L, E)])
+    x_bits = f32_to_bf16_bits(rng.standard_normal((N, d)).astype(np.float32))
+    pd = torch.zeros(flat.size + 8, device=dev)[p_off // 4:][:flat.size]
+    pd.copy_(torch.from_numpy(flat))
+    xd = torch.zeros(N * d + 8, dtype=torch.int16, device=dev)[x_off // 2:][:N * d]
+    xd.copy_(torch.from_numpy(x_bits.reshape(-1).view(np.int16)))
+    assert xd.data_ptr() % 16 == x_off and pd.data_ptr() % 16 == p_off
+    ids = torch.full((L, N, k), -1, dtype=torch.int32, device=dev)
+    alpha = torch.zeros((L, N, k), device=dev)
+    ws = torch.zeros(sm.hash_workspace_bytes(cfg, N), dtype=torch.uint8, device=dev)
+    torch.cuda.synchronize()
+    sm.hash_forward(cfg, pd, xd, n_seq, T, ids, alpha, ws, None)
+    torch.cuda.synchronize()
+    ids, alpha, x = ids.cpu().numpy(), alpha.cpu().numpy(), bf16_bits_to_f32(x_bits)
+    for b in range(n_seq):
+        at = slice(b * T, (b + 1) * T)
+        assert_agrees(ids[:, at], alpha[:, at], hash_fn.hash_forward(params, x[at], L, E, k)[2], k)
+
+
 def test_predicted_table_drives_the_layer():
     """Hash-building side to inference side: the predicted ids / alpha of layer l (top-2) are planned
     and run through the MoE layer, and the result equals the oracle's layer on the same table."""
