@@ -600,9 +600,9 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
     constexpr int kLdsBytes = (NB + 1) * BM * 128 + kWaves * 32 * (NS * 64 + 16) +
                               kWaves * (FUSE == kPlain ? 0 : (FUSE == kGather ? 256 : 2 * BM * 4));
-    static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&grouped_gemm_nt<BM, NS, NB, RELU, FUSE>),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (allowed != hipSuccess) return (int)allowed;
+    static LdsGrant grant;
+    const int rc = allow_lds(grant, reinterpret_cast<const void *>(&grouped_gemm_nt<BM, NS, NB, RELU, FUSE>), kLdsBytes);
+    if (rc) return rc;
     GemmArgs g = a;
     g.stream_once = worth_streaming(a);
     const int n_tiles_n = a.N / (kWaves * NS * 32);
@@ -680,6 +680,14 @@ int launch_shape(const GemmArgs &a, int tile_m, hipStream_t st, const LaunchEven
 }
 
 }  // namespace
+
+int allow_lds(LdsGrant &grant, const void *kernel, int bytes)
+{
+    int device = -1;
+    const hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return (int)e;
+    return grant.on(device, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
 
 void forget_stream(hipStream_t st)
 {

@@ -880,21 +880,20 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
     const int queries = 16 * pitch * 4 <= kMaxScoreBytes ? 16 : 8;
     const int score_bytes = queries * pitch * 4, blocks_per_seq = (T + queries - 1) / queries;
     if (score_bytes > 64 * 1024) {
-        static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&hash_attention<C>),
-                                                              hipFuncAttributeMaxDynamicSharedMemorySize, kMaxScoreBytes);
-        if (allowed != hipSuccess) return (int)allowed;
+        static LdsGrant grant;
+        const int rc = allow_lds(grant, reinterpret_cast<const void *>(&hash_attention<C>), kMaxScoreBytes);
+        if (rc) return rc;
     }
     hipLaunchKernelGGL(hash_attention<C>, dim3(n_seq * blocks_per_seq), dim3(512), score_bytes, st, h2, c0, T, queries,
                        blocks_per_seq, pitch, r);
-    hipError_t err = hipSuccess;
+    int err = 0;
     auto heads = [&](auto nt, auto tt, auto dir) {
         constexpr int NT = decltype(nt)::value, TT = decltype(tt)::value, kBytes = heads_lds_bytes<C, NT, TT>();
         constexpr bool DIRECT = decltype(dir)::value;
         if (kBytes > 64 * 1024) {
-            static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(&hash_heads<C, NT, TT, DIRECT>),
-                                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
-            err = allowed;
-            if (err != hipSuccess) return;
+            static LdsGrant grant;
+            err = allow_lds(grant, reinterpret_cast<const void *>(&hash_heads<C, NT, TT, DIRECT>), kBytes);
+            if (err) return;
         }
         hipLaunchKernelGGL((hash_heads<C, NT, TT, DIRECT>), dim3((N + TT * 16 - 1) / (TT * 16), sh.L), dim3(256), kBytes, st, r, w_out,
                            b_out, sh.E, sh.top_k, N, ids, alpha);
@@ -908,7 +907,7 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
     if (!direct) heads_of(std::integral_constant<int, 1>(), std::false_type());
     else if (N >= 2048) heads_of(std::integral_constant<int, 2>(), std::true_type());
     else heads_of(std::integral_constant<int, 1>(), std::true_type());
-    if (err != hipSuccess) return (int)err;
+    if (err) return err;
     return (int)hipGetLastError();
 }
 

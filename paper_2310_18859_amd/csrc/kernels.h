@@ -4,7 +4,12 @@
 
 #include <cstdint>
 
+#include "lds_grant.h"
+
 namespace sida {
+
+// Lets `kernel` be launched with up to `bytes` of dynamic LDS on the current device.
+int allow_lds(LdsGrant &grant, const void *kernel, int bytes);
 
 // The activated experts of one layer in the order their token tiles are scheduled: wave by wave,
 // inside a wave the expert with the most tokens first (so the long experts do not end up as the
