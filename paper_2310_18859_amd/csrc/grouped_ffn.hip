@@ -35,6 +35,8 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include <cstddef>
 #include <mutex>
 #include <unordered_map>
@@ -167,21 +169,19 @@ __device__ __forceinline__ void stream_tile(const GemmArgs &g, const i32x4 &td, 
             for (int s = 0; s < NS; ++s)
                 w[i][j][s] = load_frag<ONCE>(w_rsrc, lane * 16, (stripe * NS + s) * (32 * K * 2) + (k0 + f) * 2048 + j * 1024);
     };
-#pragma unroll
-    for (int i = 0; i < D; ++i) load_w(i, min(i, n - 1));
     int tok_v[kT];
+    auto find_rows = [&]() {
 #pragma unroll
-    for (int j = 0; j < kT; ++j) {
-        if (FUSE == kGather && g.top_k != 1) src[j] /= g.top_k;
-        // rows past the end are out of the descriptor's range: zeros, no request
-        tok_v[j] = j * 16 + (lane >> 2) < rows ? src[j] * K * 2 + (lane & 3) * 16 : INT32_MIN;
-    }
+        for (int j = 0; j < kT; ++j) {
+            if (FUSE == kGather && g.top_k != 1) src[j] /= g.top_k;
+            // rows past the end are out of the descriptor's range: zeros, no request
+            tok_v[j] = j * 16 + (lane >> 2) < rows ? src[j] * K * 2 + (lane & 3) * 16 : INT32_MIN;
+        }
+    };
     auto load_t = [&](int i, int f) {
 #pragma unroll
         for (int j = 0; j < kT; ++j) t[i][j] = load_frag<false>(a_rsrc, tok_v[j], (k0 + f) * 64);
     };
-#pragma unroll
-    for (int i = 0; i < D; ++i) load_t(i, min(i, n - 1));
     f32x16 acc[NS][MI];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -208,20 +208,80 @@ __device__ __forceinline__ void stream_tile(const GemmArgs &g, const i32x4 &td, 
                 for (int s = 0; s < NS; ++s) acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[i][j][s], x, acc[s][m], 0, 0, 0);
             }
     };
-    int f = 0;
+    // Loads run D steps ahead.  Tiles of at most 32 rows load every step once: with the last step loaded again where
+    // D steps ahead are past the end, K = 1024 cost 12 loads for 8 steps (64 experts x 16 tokens, 1024 x 4096: first
+    // GEMM 106 us, 93 this way; 200 x 24 tokens, 384 x 1536: 67 and 54).  A load under a branch is waited for as if it
+    // had not been made, too early for the loads behind it; hence no branch in the loop, and a sum of at most D steps
+    // written out for each length.  Taller tiles (D = 3) do repeat the last step: at most two loads too many, and the
+    // form without them is slower (8 experts x 48 tokens, second GEMM: 10.1 us against 11.2).
+    auto start = [&](auto steps) {
+#pragma unroll
+        for (int i = 0; i < decltype(steps)::value; ++i) load_w(i, min(i, n - 1));
+        find_rows();
+#pragma unroll
+        for (int i = 0; i < decltype(steps)::value; ++i) load_t(i, min(i, n - 1));
+        __builtin_amdgcn_sched_barrier(0);                      // all in flight before the first product
+    };
+    if constexpr (MI > 1) {
+        start(std::integral_constant<int, D>());
+        int f = 0;
 #pragma clang loop unroll(disable)
-    for (; f + D < n; f += D) {
+        for (; f + D < n; f += D) {
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                multiply(i);
+                const int at = min(f + D + i, n - 1);
+                load_w(i, at);
+                load_t(i, at);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            if (i == 0 || f + i < n) multiply(i);
+    } else if (n <= D) {
+        auto short_sum = [&](auto steps) {
+            if (n != decltype(steps)::value) return;
+            start(steps);
+#pragma unroll
+            for (int i = 0; i < decltype(steps)::value; ++i) multiply(i);
+        };
+        static_assert(MI > 1 || D == 6, "lengths written out");
+        short_sum(std::integral_constant<int, 1>());
+        short_sum(std::integral_constant<int, 2>());
+        short_sum(std::integral_constant<int, 3>());
+        short_sum(std::integral_constant<int, 4>());
+        short_sum(std::integral_constant<int, 5>());
+        short_sum(std::integral_constant<int, 6>());
+    } else {
+        start(std::integral_constant<int, D>());
+        int f = 0;
+#pragma clang loop unroll(disable)
+        for (; f + 2 * D <= n; f += D) {
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                multiply(i);
+                load_w(i, f + D + i);
+                load_t(i, f + D + i);
+            }
+        }
+        const int left = n - f;                                 // D .. 2 D - 1
 #pragma unroll
         for (int i = 0; i < D; ++i) {
             multiply(i);
-            const int at = min(f + D + i, n - 1);
-            load_w(i, at);
-            load_t(i, at);
+            if (D + i < left) {
+                load_w(i, f + D + i);
+                load_t(i, f + D + i);
+            }
         }
-    }
 #pragma unroll
-    for (int i = 0; i < D; ++i)
-        if (i == 0 || f + i < n) multiply(i);
+        for (int i = 0; i < D - 1; ++i)
+            if (D + i < left) multiply(i);
+    }
+    // Where the results go is looked at here and no earlier: a wait for these loads, the kernel's first, would be a
+    // wait in front of the sum.
+    if (FUSE == kScatter)
+#pragma unroll
+        for (int m = 0; m < MI; ++m) asm volatile("" : "+v"(dst[m]), "+v"(gate[m]));
     // The parts of the sum meet in LDS, stripe by stripe.  A lane holds 4 x 4 consecutive output columns
     // 8q + 4*half .. of its token; wavefront q sums column group q.
 #pragma unroll
