@@ -173,9 +173,9 @@ struct LayerSchedule {
     int32_t few_rows[SIDA_MAX_E];     // token rows of those
 };
 
-// How a layer's experts are cut into tiles, by its token counts alone (not by its waves: a wavefront sums
-// over K in another order where tiles are streamed, and a layer gives the same bits in one wave as in
-// many).
+// How a layer's experts are cut into tiles.  A wavefront sums over K in another order where tiles are streamed, so
+// `few` depends on the token counts and the experts' size alone: a layer gives the same bits in one wave as in many.
+// tile_m may depend on the waves, since it changes the order of no sum.
 struct TileRule {
     int32_t tile_m;                   // token rows per tile, 64 or 128
     int32_t few;                      // experts of at most this many tokens are streamed, in tiles of 64 rows
@@ -188,21 +188,32 @@ struct TileRule {
 // Switch-base-128 shape: 64-row tiles are 8-10 % faster at 8-16 tokens per expert, even at 64, and
 // 6 % slower at 128 tokens per expert.)
 // Streamed (see grouped_ffn.hip) are
-//  * all tiles of a layer of few tiles, where walking them leaves most compute units idle - up to 20
-//    (16 experts, 300 tokens, Zipf(1): 51 -> 41 us a layer; 8 experts, 400 tokens: 46 -> 35 us; 32 tiles of 64
-//    rows: 56 -> 67 us) -
-//  * and of a layer of at most 10 rows per tile with hardly an expert of more than one (128 experts, 128
-//    tokens: 92 -> 81 us; 64 experts, 300 tokens, Zipf(1.2): 88 -> 80 us);
-//  * of a layer of many experts (fewer do not fill the chip beside the tiles that are walked) the experts
-//    with at most 64 tokens, as long as these have no more than 32 on average (128 experts: 2000 tokens,
-//    Zipf(1), 225 -> 210 us; 5461 tokens 277 -> 254 us; 39 tokens each 244 -> 253 us) and the others do
-//    not outweigh them by far (16384 tokens: 319 -> 325 us).
-TileRule tile_rule(const sida_plan *p)
+//  * all tiles of a layer of few tiles, where walking them leaves most compute units idle - up to 20, and up to two
+//    stripes of 32 weight rows per compute unit (256 of them) in the narrower GEMM (768 x 3072, walked and streamed:
+//    16 experts x 8 tokens 67 and 56 us a layer, 20 x 48 58 and 57; 32 tiles of 64 rows 56 and 67; 1024 x 4096:
+//    16 x 48 77 and 71, 20 x 48 88 and 94);
+//  * and of a layer of at most 10 rows per tile with hardly an expert of more than one (128 x 8: 208 and 188 us;
+//    1024 x 4096: 64 x 8 180 and 172; 384 x 1536: 200 x 8 96 and 84);
+//  * of a layer of many experts those with at most 64 tokens, as long as the others do not outweigh them by far (128
+//    experts, Zipf(1), 7680 tokens 271 and 261; 16384 tokens 319 and 325) and they have
+//    - beside tiles that are walked, at most 32 on average, and one and a half workgroups of 64 weight rows per compute
+//      unit in the narrower GEMM (Zipf(1), 24 tokens on average: 48 experts of 384 x 1536 32 and 36 us, 96 of them 62 and
+//      60; 48 of 512 x 2048 57 and 59, 64 of them 73 and 66);
+//    - alone, at most 24, or 32 where the rounds of 512 tiles of 128 weight rows that walking them takes would be a
+//      fifth empty (768 x 3072: 128 experts x 16 218 and 214 us, x 24 227 and 227, x 32 237 and 245; 48 x 28, rounds 36 %
+//      empty, 106 and 94; 1024 x 4096, whole rounds: 64 x 28 192 and 198), or 16 with less than two workgroups per
+//      compute unit (64 experts of 384 x 1536: x 16 39 and 39, x 24 41 and 43; 48 of 640 x 2560: 64 and 62, 67 and 69);
+//      with at most one, walking leaves most of the chip idle again (48 of 256 x 1024 x 28: 22.4 and 21.7).
+// With 128 columns the four parts of a sum are one step each, and many such tiles are better walked (x 8 tokens: 48
+// experts 14 and 13 us, 200 experts 20 and 23).
+// The counts stand for the whole chip, also on a stream with fewer compute units: the bits of a layer do not depend on
+// the stream.
+TileRule tile_rule(const sida_plan *p, const sida_config &cfg)
 {
-    int64_t t64 = 0, t128 = 0, n_few = 0, few_rows = 0, rows = 0;
+    int64_t t64 = 0, t128 = 0, n_few = 0, few_rows = 0, rows_all = 0;
     for (int32_t i = 0; i < p->n_active; ++i) {
         const int32_t n = p->counts[p->order[i]];
-        rows += n;
+        rows_all += n;
         t64 += (n + kGemmTileSmall - 1) / kGemmTileSmall;
         t128 += (n + kGemmTileM - 1) / kGemmTileM;
         if (n <= kGemmTileSmall) {
@@ -210,17 +221,28 @@ TileRule tile_rule(const sida_plan *p)
             few_rows += n;
         }
     }
-    if (t64 <= 20 || (rows <= 10 * t64 && 8 * t64 <= 9 * p->n_active)) return TileRule{kGemmTileSmall, INT32_MAX};
+    const int64_t narrow = std::min(cfg.d_model, cfg.d_ff);
+    const bool worth = narrow >= 256 || p->n_active <= 96;
+    if (t64 <= 20 && t64 * (narrow / 32) <= 2 * 256) return TileRule{kGemmTileSmall, INT32_MAX};
+    if (worth && rows_all <= 10 * t64 && 8 * t64 <= 9 * p->n_active) return TileRule{kGemmTileSmall, INT32_MAX};
     // A layer that is cut into waves launches a few experts at a time: small launches, hidden
     // behind the copies; 64-row tiles give them more (and deeper-fetching) tiles.
     const int32_t tile_m = p->n_waves > 1 || 5 * t64 <= 6 * t128 ? kGemmTileSmall : kGemmTileM;
-    const bool stream = p->n_active >= 48 && few_rows <= 32 * n_few && rows <= 64 * (int64_t)p->n_active;
+    const int64_t wgs = n_few * (narrow / 64);                // of the narrower GEMM
+    const bool alone = n_few == p->n_active;
+    const auto rounds = [&](int64_t n) {                      // of 512 tiles, in shares of the tiles there are
+        const int64_t t = n_few * (n / 128);
+        return (double)((t + 511) / 512 * 512) / (double)t;
+    };
+    int64_t most = wgs >= 384 ? 32 : 0;                       // tokens of a streamed expert, on average
+    if (alone) most = wgs <= 256 ? 32 : wgs < 512 ? 16 : rounds(cfg.d_model) + rounds(cfg.d_ff) > 2.5 ? 32 : 24;
+    const bool stream = worth && p->n_active >= 48 && few_rows <= most * n_few && rows_all <= 64 * (int64_t)p->n_active;
     return TileRule{tile_m, stream ? kGemmTileSmall : 0};
 }
 
-void build_schedule(const sida_plan *p, LayerSchedule *s)
+void build_schedule(const sida_plan *p, const sida_config &cfg, LayerSchedule *s)
 {
-    const TileRule rule = tile_rule(p);
+    const TileRule rule = tile_rule(p, cfg);
     const int32_t tile_m = rule.tile_m;
     int32_t idx[SIDA_MAX_E];
     for (int32_t i = 0; i < p->n_active; ++i) idx[i] = p->order[i];     // already grouped by wave
@@ -506,7 +528,7 @@ int forward_layers(sida_ctx *c, int32_t n, const LayerArgs *layers, void *ws_dev
                 ws = carve(c->cfg, p->T, ws_dev);
                 if (i + 1 < group_end) at.move(&ws, (size_t)(i - li));
                 const sida_plan *pi = layers[i].plan;
-                build_schedule(pi, &scheds[i - li]);
+                build_schedule(pi, c->cfg, &scheds[i - li]);
                 jobs[i - li] = sort_job(ws, layers[i].ids, fused ? layers[i].alpha : nullptr, &scheds[i - li].tbl);
             }
             rc = launch_sorts(c, jobs, group_end - li, p->T, compute);
@@ -1007,7 +1029,7 @@ int sida_grouped_ffn(sida_ctx *c, const sida_plan *plan, int32_t wave, void *wor
     rc = check_ws(c, plan->T, workspace_dev, workspace_bytes);
     if (rc) return rc;
     LayerSchedule sched;
-    build_schedule(plan, &sched);
+    build_schedule(plan, c->cfg, &sched);
     const Ws ws = carve(c->cfg, plan->T, workspace_dev);
     rc = launch_tiles(c, sched, ws, static_cast<hipStream_t>(stream));
     if (rc) return rc;
