@@ -511,19 +511,23 @@ bool sort_in_one_launch(int32_t T) { return T <= kChunksT; }
 int launch_sort(const SortJob *jobs, int32_t n, int32_t T, int32_t E, int32_t max_tiles, hipStream_t st)
 {
     if (n < 1 || n > kSortJobs || (n > 1 && T > kChunksT)) return (int)hipErrorInvalidValue;
-    bool aligned = true;                                     // ids are read 16 bytes at a time
-    for (int32_t i = 0; i < n; ++i) aligned = aligned && (reinterpret_cast<uintptr_t>(jobs[i].ids) & 15u) == 0;
-    if (T <= kOneT || (T <= kChunksT && aligned)) {
-        SortJobs a;
-        for (int32_t i = 0; i < n; ++i) a.job[i] = jobs[i];
-        if (T <= 8 * kChunk) hipLaunchKernelGGL((sort_one<8, 1>), dim3(1, n), dim3(512), 0, st, a, T, E, max_tiles);
-        else if (T <= kOneT) hipLaunchKernelGGL((sort_one<16, 1>), dim3(1, n), dim3(1024), 0, st, a, T, E, max_tiles);
-        else hipLaunchKernelGGL(sort_chunks, dim3((T + kFineChunk - 1) / kFineChunk, n), dim3(256), 0, st, a, T, E, max_tiles);
-        return (int)hipGetLastError();
+    // sort_chunks reads ids 16 bytes at a time: a job whose ids are off that boundary takes three launches of its own
+    const auto joins = [&](const SortJob &j) {
+        return T <= kOneT || (T <= kChunksT && (reinterpret_cast<uintptr_t>(j.ids) & 15u) == 0);
+    };
+    SortJobs a;
+    int32_t m = 0;
+    for (int32_t i = 0; i < n; ++i)
+        if (joins(jobs[i])) a.job[m++] = jobs[i];
+    if (m > 0) {
+        if (T <= 8 * kChunk) hipLaunchKernelGGL((sort_one<8, 1>), dim3(1, m), dim3(512), 0, st, a, T, E, max_tiles);
+        else if (T <= kOneT) hipLaunchKernelGGL((sort_one<16, 1>), dim3(1, m), dim3(1024), 0, st, a, T, E, max_tiles);
+        else hipLaunchKernelGGL(sort_chunks, dim3((T + kFineChunk - 1) / kFineChunk, m), dim3(256), 0, st, a, T, E, max_tiles);
     }
     const int n_chunks = (T + kChunk - 1) / kChunk;
     for (int32_t i = 0; i < n; ++i) {
         const SortJob &j = jobs[i];
+        if (joins(j)) continue;
         hipLaunchKernelGGL(sort_hist, dim3(n_chunks), dim3(64), 0, st, j.ids, T, E, j.block_hist);
         hipLaunchKernelGGL(sort_scan, dim3(1), dim3(1024), 0, st, j.block_hist, n_chunks, E, T, j.counts, j.offsets, j.tbl,
                            j.tiles, max_tiles);

@@ -19,6 +19,8 @@ pytestmark = pytest.mark.gpu
     ("room-for-few", 200, 128, 128, [64] * 7, ()),                  # ... holds fewer than a launch sorts
     ("chunks", 8, 128, 256, [4097, 4097, 5000, 5000, 5000], ()),
     ("chunks-odd-address", 8, 128, 256, [5000] * 4, (1, 3)),        # ids are not on a 16-byte boundary
+    ("chunks-odd-first-and-last", 8, 128, 256, [4100] * 9, (0, 7, 8)),
+    ("chunks-all-odd", 8, 128, 256, [4100] * 3, (0, 1, 2)),
     ("one-workgroup-odd-address", 8, 128, 256, [999] * 3, (0,)),
 ])
 def test_layers_sorted_together(name, E, d, F, sizes, odd):
