@@ -424,12 +424,14 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
     // (l%8) ^ (row/2 & 7).  Wavefront w issues loads w*TL .. w*TL+TL-1 of every stage, i.e. token
     // rows 8*TL*w .. 8*TL*(w+1)-1, and the NS*4 fragments of its own weight stripes.
     const int sub_row = lane >> 3;
-    const int piece_of = lane & 7;
+    static_assert(TL % 2 == 0, "a wavefront's rows start at a multiple of 16");
+    const int first_row = wv * TL * 8 + sub_row;
+    const int piece = ((lane & 7) ^ (sub_row >> 1)) * 16;       // of load 0; 64 bytes on or back in every other load
     const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(g.A, g.a_bytes);
     const __amdgpu_buffer_rsrc_t map_rsrc = make_rsrc(g.perm, FUSE == kPlain ? 0u : (uint32_t)g.map_len * 4u);
     const __amdgpu_buffer_rsrc_t gate_rsrc = make_rsrc(g.gate_perm, FUSE == kScatter ? (uint32_t)g.map_len * 4u : 0u);
     __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(g.pool, 0);
-    int tok_v[TL], w_v[NS];                                     // per-lane byte offsets
+    int tok_v[TL], w_at[NS];                                    // byte offsets: per lane, and of the stripes
     int tok_s = 0, w_s = 0;                                     // running K offsets (uniform)
     bool w_once = false;                                        // cache policy of the weight loads (uniform)
     // kGather: perm of this wavefront's 8*TL token rows of a tile (rows past its end repeat the last one) -> side
@@ -439,18 +441,17 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
     auto point = [&](const Coord &c, int slot) {
 #pragma unroll
         for (int j = 0; j < TL; ++j) {
-            const int r = (wv * TL + j) * 8 + sub_row;          // row in the tile
-            const int ra = min(r, c.rows - 1);                  // rows past the end re-read the last one
+            const int ra = min(first_row + j * 8, c.rows - 1);  // rows past the end re-read the last one
             int src = c.row0 + ra;
             if (FUSE == kGather) {                              // row ra of the tile is one of token src / top_k
                 src = reinterpret_cast<const int *>(side)[j * 8 + sub_row];
                 if (g.top_k != 1) src /= g.top_k;
             }
-            tok_v[j] = src * K * 2 + (piece_of ^ ((r >> 1) & 7)) * 16;
+            tok_v[j] = src * K * 2 + (piece ^ ((j & 1) * 64));
         }
         w_rsrc = make_rsrc(g.pool + (size_t)slot * g.expert_bytes + g.w_off, (uint32_t)N * (uint32_t)K * 2u);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) w_v[s] = (c.nt * (BN / 32) + wv * NS + s) * stripe_bytes + lane * 16;
+        for (int s = 0; s < NS; ++s) w_at[s] = (c.nt * (BN / 32) + wv * NS + s) * stripe_bytes;
         tok_s = 0;
         w_s = 0;
         w_once = c.once;
@@ -471,21 +472,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<true>(w_rsrc, w_v[s], w_s + ks * 1024);
+                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<true>(w_rsrc, lane * 16, w_at[s] + w_s + ks * 1024);
         } else {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<false>(w_rsrc, w_v[s], w_s + ks * 1024);
+                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<false>(w_rsrc, lane * 16, w_at[s] + w_s + ks * 1024);
         }
         w_s += 4096;
     };
 
     // ---- compute side
     const int frag_row = lane & 31, half = lane >> 5;
-    int x_at[KS];                                               // fragment offsets inside a stage
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) x_at[ks] = frag_row * 128 + (((ks * 2 + half) ^ ((frag_row >> 1) & 7)) * 16);
+    // fragment ks of a 32-row block is at stage + block + (x_at ^ 32 ks): stages and blocks are whole rows
+    const int x_at = frag_row * 128 + ((half ^ ((frag_row >> 1) & 7)) * 16);
     f32x16 acc[NS][MI];
     auto clear = [&]() {
 #pragma unroll
@@ -583,9 +583,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
                 // A fragment of the next 32-row block is read as soon as its predecessor has been multiplied, so
                 // that LDS answers behind the products.  Blocks past the tile's end are not multiplied (the
                 // first of them is read, to no effect).
-                const char *st = lds + rd_off;
+                const int st = rd_off + x_at;
                 bf16x8 xf[KS];
-                auto read = [&](int im, int ks) { xf[ks] = *reinterpret_cast<const bf16x8 *>(st + im * 4096 + x_at[ks]); };
+                auto read = [&](int im, int ks) { xf[ks] = *reinterpret_cast<const bf16x8 *>(lds + (st ^ (ks * 32)) + im * 4096); };
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) read(0, ks);
 #pragma unroll
