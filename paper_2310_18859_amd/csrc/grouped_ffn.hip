@@ -246,12 +246,12 @@ __device__ __forceinline__ void stream_tile(const GemmArgs &g, const i32x4 &td, 
             for (int i = 0; i < decltype(steps)::value; ++i) multiply(i);
         };
         static_assert(MI > 1 || D == 6, "lengths written out");
-        short_sum(std::integral_constant<int, 1>());
-        short_sum(std::integral_constant<int, 2>());
-        short_sum(std::integral_constant<int, 3>());
-        short_sum(std::integral_constant<int, 4>());
-        short_sum(std::integral_constant<int, 5>());
         short_sum(std::integral_constant<int, 6>());
+        short_sum(std::integral_constant<int, 5>());
+        short_sum(std::integral_constant<int, 4>());
+        short_sum(std::integral_constant<int, 3>());
+        short_sum(std::integral_constant<int, 2>());
+        short_sum(std::integral_constant<int, 1>());
     } else {
         start(std::integral_constant<int, D>());
         int f = 0;
