@@ -104,14 +104,17 @@ typedef struct sida_plan {
 } sida_plan;
 
 /* Byte offsets of the regions inside the caller's workspace for a call with T tokens (tests and
- * profilers read intermediates through these). */
+ * profilers read intermediates through these).  On the fused path (sida_set_fusion) x_perm is scratch:
+ * sida_run_layers sorts consecutive layers of equally many tokens together, and all but the last of
+ * such a group keep counts, offsets, perm, inv, gate_perm and tiles there; the regions of these names
+ * hold the last layer of the group, also while earlier ones compute. */
 typedef struct sida_ws_layout {
     size_t counts;      /* int32 [E]                    tokens per expert                     */
     size_t offsets;     /* int32 [E+1]                  exclusive prefix sum                  */
     size_t block_hist;  /* int32 [n_blocks*E]           per-block histograms, then bases      */
     size_t perm;        /* int32 [T]   perm[r] = t      stable order by (expert, token)       */
     size_t inv;         /* int32 [T]   inv[t]  = r                                            */
-    size_t x_perm;      /* bf16  [T, d_model]           x rows in perm order                  */
+    size_t x_perm;      /* bf16  [T, d_model]           x rows in perm order (separate passes) */
     size_t h;           /* bf16  [T, d_ff]              relu(x_perm W_in^T), perm order       */
     size_t y_perm;      /* bf16  [T, d_model]           expert outputs, perm order            */
     size_t tiles;       /* int32 [4 * (T/64 + E + 1)]   token-tile descriptors of the grouped FFN */
@@ -275,7 +278,7 @@ int sida_moe_layer_forward(sida_ctx *ctx, const sida_plan *plan, const void *x_d
 int sida_set_top_k(sida_ctx *ctx, int32_t k);
 
 /* Folds the permute-gather into the first GEMM's token-row loads (rows are read from x through
- * the sort's index, x_perm is never written) and the gate-weighted scatter-combine into the second
+ * the sort's index, x_perm holds no rows) and the gate-weighted scatter-combine into the second
  * GEMM's result stores (with top-1 routing every y row is written exactly once, by the tile that
  * holds its token; y_perm is never written).  Same arithmetic, bit-identical y; two launches and
  * about two thirds of the dispatch/combine HBM traffic less per layer.  With more than one expert
@@ -310,7 +313,10 @@ int sida_debug_mismatch_layer(const sida_ctx *ctx);
 /* Convenience: forwards n consecutive planned layers, keeping the copy stream one wave ahead of
  * the compute across layer boundaries too (the first wave of layer i+1 is copied while the last
  * wave of layer i computes).  plans[i], x_dev[i], ids_dev[i], alpha_dev[i], y_dev[i] belong to
- * the i-th layer of the call; arrays of pointers live in host memory. */
+ * the i-th layer of the call; arrays of pointers live in host memory.  The ids and gate values of
+ * several layers are read in front of the first of them (the fused path sorts up to eight at once):
+ * all of them have to be there before the call's work on compute_stream begins, none may be a
+ * layer's result. */
 int sida_run_layers(sida_ctx *ctx, int32_t n, const sida_plan *const *plans,
                     const void *const *x_dev, const int32_t *const *ids_dev,
                     const float *const *alpha_dev, void *const *y_dev, void *workspace_dev,
@@ -345,7 +351,8 @@ int sida_combine(sida_ctx *ctx, const float *alpha_dev, int32_t T, void *y_dev,
  *   LSTM layer 2: the same four,
  *   w_out [L*E, C], b_out [L*E]                                       (head l = rows l*E .. l*E+E-1).
  * x_dev: device bf16 [n_seq * seq_len, d_model], sequences one after the other (attention and the
- * LSTM never cross a sequence boundary).  Outputs, device: ids_dev int32 and alpha_dev fp32, both
+ * LSTM never cross a sequence boundary).  params_dev and x_dev may lie at any address of a float and a
+ * bf16 value; on a 16-byte boundary, both of them, the call is faster.  Outputs, device: ids_dev int32 and alpha_dev fp32, both
  * [L, n_seq * seq_len, top_k] - layer l's slice is exactly the ids / alpha array that
  * sida_moe_plan (after a copy to the host) and sida_moe_layer_forward take (with sida_set_top_k).
  * workspace_dev: device, 256-byte aligned, >= sida_hash_workspace_bytes(n_seq * seq_len), of this call

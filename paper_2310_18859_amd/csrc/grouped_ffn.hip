@@ -134,6 +134,9 @@ struct GemmArgs {
 // this way).  Rows past the tile's end are outside the buffer descriptor: no request.
 // Measured against the 64-row tiles of the kernel below: 52 experts x 2.5 tokens 46 / 44 -> 39 / 40 us per
 // GEMM (6.1 TB/s of weights), 128 x 12: 107 / 99 -> 95 / 97 us, 8 x 8: 11 / 14 -> 10 / 8 us.
+// Sums in four parts are no less exact: outputs of layers of 21 to 1111 tokens (384 to 1024 columns) against sums in 64
+// bits rounded to bf16 at the same places, relative 2-norms, 1.2e-4 walked and 0.8e-4 streamed (medians of 12);
+// against 64 bits throughout, where the roundings to bf16 decide, 2.87e-3 both.
 template <int NS, int MI, int D, bool RELU, int FUSE, bool ONCE>
 __device__ __forceinline__ void stream_tile(const GemmArgs &g, const i32x4 &td, int stripe, f32x4 *red)
 {
@@ -582,7 +585,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
                 issue_tokens();
                 // A fragment of the next 32-row block is read as soon as its predecessor has been multiplied, so
                 // that LDS answers behind the products.  Blocks past the tile's end are not multiplied (the
-                // first of them is read, to no effect).
+                // first of them is read, to no effect).  Full tiles gain from it (GEMM 1 / 2, read ahead and not:
+                // 8 experts x 2048 rows 84.3 / 81.6 and 85.6 / 83.7 us, of 1024 x 4096 139.9 / 147.0 and 143.3 /
+                // 157.9), partly filled ones do not (64 experts, 8192 tokens, Zipf(1.2) 90.3 / 88.6 and 90.0 / 89.2).
                 const int st = rd_off + x_at;
                 bf16x8 xf[KS];
                 auto read = [&](int im, int ks) { xf[ks] = *reinterpret_cast<const bf16x8 *>(lds + (st ^ (ks * 32)) + im * 4096); };

@@ -14,11 +14,14 @@ pytestmark = pytest.mark.gpu
 
 EDGES = [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64]
 SEVERAL = [65, 130, 1, 64, 129]                        # experts of several streamed tiles
-# 50 experts of 1..45 tokens beside six of 65..250, which are walked in larger tiles
+# 50 experts of 1..45 tokens beside six of 65..250: too few to be streamed beside those, all are walked
 BESIDE = [1 + (7 * i) % 45 for i in range(50)] + [65, 96, 127, 128, 129, 250]
 # as many more as fill the chip beside the larger tiles of a layer of 256 columns
 BESIDE_MANY = [1 + (7 * i) % 45 for i in range(130)] + [65, 96, 127, 128, 129, 250]
 FEWER = [1, 64, 17, 31, 32, 33]
+# more than ten tokens each and no larger tiles: streamed where they leave most of the chip idle or fill it
+ALONE = [12 + (5 * i) % 20 for i in range(60)]
+ALONE_MANY = [12 + (5 * i) % 20 for i in range(70)]
 
 
 def ids_with_counts(counts, seed):
@@ -45,6 +48,9 @@ def forward(r, x_bits, ids, alpha):
     ("beside-larger", BESIDE, 128, 896),
     ("beside-many", BESIDE_MANY, 256, 512),
     ("beside-many", BESIDE_MANY, 384, 640),
+    ("alone", ALONE, 256, 512),
+    ("alone", ALONE_MANY, 512, 896),
+    ("alone-walked", ALONE_MANY, 384, 256),             # between the two
     # every length of a sum up to two rounds of the steps that are loaded ahead, and one more
     ("lengths", FEWER, 512, 1024),                      # 4 and 8 steps
     ("lengths", FEWER, 1152, 1280),                     # 9 and 10

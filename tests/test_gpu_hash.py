@@ -47,10 +47,9 @@ def run_hash(cfg, params, x_bits, n_seq, T):
     (256, 128, 2, 16, 3, 3, 70),
     (768, 128, 6, 128, 1, 2, 128),
     (768, 128, 6, 128, 3, 1, 200),
-    # the dense stages take blocks of 8 tokens from 4096 tokens up and of 2 from 1024 up (ragged last block) ...
+    # some thousand tokens, ragged; with wide embeddings (d of 2056 and 6400), and with many logits per token
     (256, 128, 2, 16, 1, 33, 125),
     (64, 64, 2, 8, 2, 9, 115),
-    # ... unless the inputs / logits of a block would not fit the LDS budget: 8 -> 2, 2 -> 1
     (2056, 64, 1, 4, 1, 33, 125),
     (6400, 64, 1, 4, 1, 9, 115),
     (64, 64, 9, 256, 2, 33, 125),
