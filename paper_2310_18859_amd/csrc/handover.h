@@ -32,15 +32,15 @@ constexpr int kMostPeeks = 1 << 20, kGaveUp = 0x7fffffff;
 template <class Peek>
 SIDA_HD void wait_for(int want, int &seen, Peek &&peek)
 {
+    if (seen >= want) return;
+    int left = kMostPeeks, now;
 #pragma clang loop unroll(disable)
-    for (int left = kMostPeeks; seen < want; --left) {
-        if (left == 0) {
+    while ((now = peek()) < want)
+        if (--left == 0) {
             seen = kGaveUp;
             return;
         }
-        const int now = peek();
-        seen = now > seen ? now : seen;
-    }
+    seen = now;
 }
 
 // The walk of one wavefront of an LSTM layer's workgroup over a sequence of T time steps:
