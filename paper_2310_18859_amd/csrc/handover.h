@@ -64,15 +64,23 @@ SIDA_HD void walk_chunks(int T, Take &&take, Store &&store, Step &&step, Fetch &
         const int n = T - c * STEPS < STEPS ? T - c * STEPS : STEPS;
         take(c);
         if (c > 0) store(c - 1);
-        int i = 0;
+        if (n == STEPS) {                                      // written out: a step's addresses become constants
+#pragma unroll
+            for (int i = 0; i < 3; ++i) step();
+            if (POST && c > 0) post();
+#pragma unroll
+            for (int i = 3; i < STEPS / 2; ++i) step();
+            if (c + 1 < chunks) fetch(c + 1);
+#pragma unroll
+            for (int i = STEPS / 2; i < STEPS; ++i) step();
+        } else {                                               // the last chunk
+            int i = 0;
 #pragma clang loop unroll(disable)
-        for (; i < (n < 3 ? n : 3); ++i) step();
-        if (POST && c > 0) post();
+            for (; i < (n < 3 ? n : 3); ++i) step();
+            if (POST && c > 0) post();
 #pragma clang loop unroll(disable)
-        for (; i < (n < STEPS / 2 ? n : STEPS / 2); ++i) step();
-        if (c + 1 < chunks) fetch(c + 1);
-#pragma clang loop unroll(disable)
-        for (; i < n; ++i) step();
+            for (; i < n; ++i) step();
+        }
     }
     store(chunks - 1);
     if (POST) {

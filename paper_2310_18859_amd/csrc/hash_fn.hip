@@ -18,8 +18,8 @@
 // scalar-per-lane fp32 multiply-adds); with the weights as the first operand a lane ends up with
 // four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
-// It is what bounds a call: 0.6 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
-// four clocks apiece (0.43 us at 2.4 GHz), and some 50 other instructions.  Measured against one launch per layer and
+// It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
+// four clocks apiece (0.43 us at 2.4 GHz), and some 42 other instructions.  Measured against one launch per layer and
 // stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 120 us, 8 of 333 tokens
 // (top-3) 1059 -> 271 us, 64 of 128 tokens 609 -> 172 us.
 #include <hip/hip_runtime.h>
@@ -85,7 +85,7 @@ __device__ __forceinline__ float quad(float v)                 // value of anoth
 }
 // Reductions over the 16 lanes of a row: lane ^ 1, lane ^ 2, then mirrored halves (their quads agree) and
 // mirrored rows; f(v, value of the other lane).
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kHalfMirror = 0x141, kMirror = 0x140;
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
 __device__ __forceinline__ float row_sum(float v)
 {
     v += quad<kXor1>(v);
@@ -366,6 +366,14 @@ __device__ __forceinline__ float gate_value(float v, const GateKind &k)
     return fabsf(v) < k.small ? t : fmaf(k.gain, n, 1.f - k.gain);
 }
 
+// sum + v of the quad's lane 1 * x, as one instruction (the compiler makes it a move and a multiply-add).
+__device__ __forceinline__ float fma_of_gate1(float v, float x, float sum)
+{
+    // a value from another lane may be read two instructions after it was written
+    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "+v"(sum) : "v"(v), "v"(x));
+    return sum;
+}
+
 template <int C>
 struct RecurrenceLds {
     static constexpr int kSeg = C / 8, kSegPitch = kSeg + 4;   // the eight segments start in different banks
@@ -384,8 +392,12 @@ struct RecurrenceLds {
 // quarters 0.65 us).  Slot j of lane l of the eight is row j ^ l, so that seven adds of permuted lanes
 // leave row l's sum in lane l; thread 4u+s then has gate s of unit u, the four gates meet in quad permutes
 // too, and a step has one barrier and no global access: pre-activations come and states go a chunk of
-// steps at a time.  What is left of a step is the issue of 128 multiply-adds and about 50 other
-// instructions per wavefront, two wavefronts per SIMD, and the latency from barrier to barrier.
+// steps at a time.  What is left of a step is the issue of 128 multiply-adds and about 42 other
+// instructions per wavefront, two wavefronts per SIMD, nearly back to back: each instruction less is
+// 8 clocks of about 1350 a step.  Hence whole chunks are written out (addresses become offsets), lane 0
+// of a quad alone carries the cell's state, and sums of permuted lanes are one instruction each: 9
+// instructions fewer, same bits, 1 x 128 tokens 122.1 -> 117.5 us, 8 x 333 271.8 -> 262.5, 64 x 128
+// 174.5 -> 170.
 //   WAIT   pre arrives in chunks from another workgroup (progress in *arrived)
 //   POST   out is handed on to another workgroup (progress in *done: wavefronts x chunks)
 template <int C, bool WAIT, bool POST>
@@ -459,9 +471,9 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
         // lane ^ 7 (mirrored halves) holds the row in the slot ^ 7; then the quad
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] += quad<kHalfMirror>(acc[j ^ 7]);
-        const float z = (acc[0] + quad<kXor1>(acc[1])) + (quad<kXor2>(acc[2]) + quad<kXor3>(acc[3]));
+        const float z = (acc[0] + quad<kXor1>(acc[1])) + quad<kXor2>(acc[2] + quad<kXor1>(acc[3]));
         const float a = gate_value(z, mine);
-        cell = quad<0x55>(a) * cell + quad<0x00>(a) * quad<0xAA>(a);
+        cell = fma_of_gate1(a, cell, a * quad<0xAA>(a));      // the state of the quad's lane 0; what the others hold is not read
         row[h_out] = quad<0xFF>(a) * gate_value(cell, of_cell);
         h_in = row + l8 * kSegPitch;
         row += kRow;
