@@ -52,13 +52,17 @@ SIDA_HD void wait_for(int want, int &seen, Peek &&peek)
 //   barrier()  a barrier of the workgroup
 // The reader takes a count of (c + 1) * wavefronts for "chunk c has arrived".  That holds only while no
 // wavefront posts twice before all others have posted once: between any two posts stands a barrier.
-// Inside the walk the steps bring it (the post of chunk c - 1 follows at most three steps of chunk c);
+// Inside the walk the steps bring it (the post of chunk c - 1 follows at most two steps of chunk c);
 // the last chunk may end right after that post, hence the barrier in front of the final one.
-// The store of a chunk's states gets three steps to complete, the loads of the next chunk's inputs get the
-// second half of a chunk.
+// The store of a chunk's states gets two steps to complete, the loads of the next chunk's inputs the last two
+// of a chunk: both are about as long as they take, and each step more is a step by which the second layer
+// ends later (three steps and the second half of a chunk: 1 x 128 tokens 117.5 us, 115.8 this way; 8 x 333
+// 262.5 and 261.1, 64 x 128 170 and 168.5; posts after one step or fetches after seven gain no more).
+constexpr int kPostAfter = 2, kFetchAfter = kSteps - 2;
 template <int STEPS, bool POST, class Take, class Store, class Step, class Fetch, class Post, class Barrier>
 SIDA_HD void walk_chunks(int T, Take &&take, Store &&store, Step &&step, Fetch &&fetch, Post &&post, Barrier &&barrier)
 {
+    static_assert(kPostAfter <= kFetchAfter && kFetchAfter <= STEPS, "steps of a chunk");
     const int chunks = (T + STEPS - 1) / STEPS;
     for (int c = 0; c < chunks; ++c) {
         const int n = T - c * STEPS < STEPS ? T - c * STEPS : STEPS;
@@ -66,17 +70,17 @@ SIDA_HD void walk_chunks(int T, Take &&take, Store &&store, Step &&step, Fetch &
         if (c > 0) store(c - 1);
         if (n == STEPS) {                                      // written out: a step's addresses become constants
 #pragma unroll
-            for (int i = 0; i < 3; ++i) step();
+            for (int i = 0; i < kPostAfter; ++i) step();
             if (POST && c > 0) post();
 #pragma unroll
-            for (int i = 3; i < STEPS / 2; ++i) step();
+            for (int i = kPostAfter; i < kFetchAfter; ++i) step();
             if (c + 1 < chunks) fetch(c + 1);
 #pragma unroll
-            for (int i = STEPS / 2; i < STEPS; ++i) step();
+            for (int i = kFetchAfter; i < STEPS; ++i) step();
         } else {                                               // the last chunk
             int i = 0;
 #pragma clang loop unroll(disable)
-            for (; i < (n < 3 ? n : 3); ++i) step();
+            for (; i < (n < kPostAfter ? n : kPostAfter); ++i) step();
             if (POST && c > 0) post();
 #pragma clang loop unroll(disable)
             for (; i < n; ++i) step();
