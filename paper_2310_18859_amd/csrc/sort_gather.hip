@@ -206,41 +206,53 @@ __global__ __launch_bounds__(64) void sort_rank(const int32_t *__restrict__ ids,
 }
 
 // The whole sort in one workgroup for layer calls of up to 4096 tokens (from one or two sequences
-// per batch, the paper's serving regime, upwards): wavefront w owns chunks w*CPW .. w*CPW+CPW-1,
+// per batch, the paper's serving regime, upwards): wavefront w owns chunk w of ROUNDS * 64 tokens,
 // the per-chunk histograms and bases live in LDS, and the three launches above shrink to one.
-// Same results.  NWV wavefronts x CPW chunks of 256 tokens.  Measured: 9 us up to 2048 tokens and
+// Same results.  Up to 512 tokens a chunk is one round for each of the eight wavefronts: with chunks of
+// 256 tokens one or two of them ranked four rounds in a row (that and the early loads: a layer of 8
+// experts and 256 tokens 29.0 -> 27.0 us).  Measured: 9 us up to 2048 tokens and
 // 10 us (14 us when the gate values move along) at 4096 against 17-19 us for the three launches; at
 // 8192 tokens (16 x 2 chunks) 15 us and 24 us, the latter slower than the three launches.
 constexpr int kOneT = 4096;      // most tokens the single-workgroup sort takes
 
-template <int NWV, int CPW>
+template <int NWV, int ROUNDS>
 __global__ __launch_bounds__(NWV * 64) void sort_one(const SortJobs jobs, int T, int E, int max_tiles)
 {
     SIDA_SORT_JOB(jobs.job[blockIdx.y]);
-    constexpr int NCH = NWV * CPW;
-    __shared__ int hist[NCH][kMaxE];               // per-chunk histogram, then first output row of (chunk, expert)
+    constexpr int kTokens = ROUNDS * 64;           // of a wavefront
+    __shared__ int hist[NWV][kMaxE];               // per-chunk histogram, then first output row of (chunk, expert)
     __shared__ int s_off[kMaxE + 1];
     __shared__ int s_wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    for (int i = tid; i < NCH * kMaxE; i += NWV * 64) (&hist[0][0])[i] = 0;
+    // Everything that is read from memory is asked for here, so that its latency is paid once: a sort of one or two
+    // sequences is little else (gate values and the expert table looked at where they are used: 2 us more).
+    int my_id[ROUNDS];
+    float my_alpha[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int t = wv * kTokens + r * 64 + lane;
+        my_id[r] = t < T ? ids[t] : 0;
+        my_alpha[r] = alpha && t < T ? alpha[t] : 0.f;
+    }
+    int ex = 0, slot = 0;
+    if (tid < tbl.n) {
+        ex = tbl.expert[tid];
+        slot = tbl.slot[tid];
+    }
+    for (int i = tid; i < NWV * kMaxE; i += NWV * 64) (&hist[0][0])[i] = 0;
     __syncthreads();
-
-    int my_id[CPW][kChunk / 64];
 #pragma unroll
-    for (int j = 0; j < CPW; ++j)
-#pragma unroll
-        for (int r = 0; r < kChunk / 64; ++r) {
-            const int t = (wv * CPW + j) * kChunk + r * 64 + lane;
-            my_id[j][r] = t < T ? clamp_id(ids[t], E) : -1;
-            if (my_id[j][r] >= 0) atomicAdd(&hist[wv * CPW + j][my_id[j][r]], 1);
-        }
+    for (int r = 0; r < ROUNDS; ++r) {
+        my_id[r] = wv * kTokens + r * 64 + lane < T ? clamp_id(my_id[r], E) : -1;
+        if (my_id[r] >= 0) atomicAdd(&hist[wv][my_id[r]], 1);
+    }
     __syncthreads();
 
     // expert totals -> offsets (threads 0..255: one expert each), then the bases of every chunk
     int total = 0, incl = 0;
     if (tid < 256) {
         if (tid < E)
-            for (int c = 0; c < NCH; ++c) total += hist[c][tid];
+            for (int c = 0; c < NWV; ++c) total += hist[c][tid];
         incl = total;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -262,7 +274,7 @@ __global__ __launch_bounds__(NWV * 64) void sort_one(const SortJobs jobs, int T,
                 s_off[E] = T;
             }
             int run = excl;
-            for (int c = 0; c < NCH; ++c) {
+            for (int c = 0; c < NWV; ++c) {
                 const int v = hist[c][tid];
                 hist[c][tid] = run;
                 run += v;
@@ -273,10 +285,8 @@ __global__ __launch_bounds__(NWV * 64) void sort_one(const SortJobs jobs, int T,
 
     // token tiles of the grouped FFN (as in sort_scan)
     if (tbl.n > 0) {
-        int ex = 0, slot = 0, off = 0, cnt = 0, n_t = 0;
+        int off = 0, cnt = 0, n_t = 0;
         if (tid < tbl.n) {
-            ex = tbl.expert[tid];
-            slot = tbl.slot[tid];
             off = s_off[ex];
             cnt = s_off[ex + 1] - off;
             n_t = (cnt + tbl.tile_m - 1) / tbl.tile_m;
@@ -306,33 +316,30 @@ __global__ __launch_bounds__(NWV * 64) void sort_one(const SortJobs jobs, int T,
         }
     }
 
-    // ranks: wavefront w walks its chunks in rounds of 64 tokens (LDS accesses of one wavefront
+    // ranks: wavefront w walks its chunk in rounds of 64 tokens (LDS accesses of one wavefront
     // execute in program order, so the reads of a round precede its updates)
     const unsigned long long below = (1ull << lane) - 1ull;
+    int *next_row = hist[wv];
 #pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-        int *next_row = hist[wv * CPW + j];
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int t = wv * kTokens + r * 64 + lane;
+        const bool live = my_id[r] >= 0;
+        const int k = live ? my_id[r] : 0;
+        unsigned long long same = __ballot(live);
 #pragma unroll
-        for (int r = 0; r < kChunk / 64; ++r) {
-            const int t = (wv * CPW + j) * kChunk + r * 64 + lane;
-            const bool live = my_id[j][r] >= 0;
-            const int k = live ? my_id[j][r] : 0;
-            unsigned long long same = __ballot(live);
-#pragma unroll
-            for (int bit = 0; bit < 8; ++bit) {
-                const unsigned long long b = __ballot((k >> bit) & 1);
-                same &= ((k >> bit) & 1) ? b : ~b;
-            }
-            int row = 0;
-            if (live) row = next_row[k] + __popcll(same & below);
-            __builtin_amdgcn_wave_barrier();
-            if (live && (same & below) == 0) next_row[k] += __popcll(same);
-            __builtin_amdgcn_wave_barrier();
-            if (live) {
-                perm[row] = t;
-                inv[t] = row;
-                if (alpha) gate_perm[row] = alpha[t];
-            }
+        for (int bit = 0; bit < 8; ++bit) {
+            const unsigned long long b = __ballot((k >> bit) & 1);
+            same &= ((k >> bit) & 1) ? b : ~b;
+        }
+        int row = 0;
+        if (live) row = next_row[k] + __popcll(same & below);
+        __builtin_amdgcn_wave_barrier();
+        if (live && (same & below) == 0) next_row[k] += __popcll(same);
+        __builtin_amdgcn_wave_barrier();
+        if (live) {
+            perm[row] = t;
+            inv[t] = row;
+            if (alpha) gate_perm[row] = my_alpha[r];
         }
     }
 }
@@ -520,8 +527,9 @@ int launch_sort(const SortJob *jobs, int32_t n, int32_t T, int32_t E, int32_t ma
     for (int32_t i = 0; i < n; ++i)
         if (joins(jobs[i])) a.job[m++] = jobs[i];
     if (m > 0) {
-        if (T <= 8 * kChunk) hipLaunchKernelGGL((sort_one<8, 1>), dim3(1, m), dim3(512), 0, st, a, T, E, max_tiles);
-        else if (T <= kOneT) hipLaunchKernelGGL((sort_one<16, 1>), dim3(1, m), dim3(1024), 0, st, a, T, E, max_tiles);
+        if (T <= 8 * 64) hipLaunchKernelGGL((sort_one<8, 1>), dim3(1, m), dim3(512), 0, st, a, T, E, max_tiles);
+        else if (T <= 8 * kChunk) hipLaunchKernelGGL((sort_one<8, kChunk / 64>), dim3(1, m), dim3(512), 0, st, a, T, E, max_tiles);
+        else if (T <= kOneT) hipLaunchKernelGGL((sort_one<16, kChunk / 64>), dim3(1, m), dim3(1024), 0, st, a, T, E, max_tiles);
         else hipLaunchKernelGGL(sort_chunks, dim3((T + kFineChunk - 1) / kFineChunk, m), dim3(256), 0, st, a, T, E, max_tiles);
     }
     const int n_chunks = (T + kChunk - 1) / kChunk;
