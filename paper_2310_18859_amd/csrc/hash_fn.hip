@@ -20,8 +20,8 @@
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
 // It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
 // four clocks apiece (0.43 us at 2.4 GHz), and some 42 other instructions.  Measured against one launch per layer and
-// stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 120 us, 8 of 333 tokens
-// (top-3) 1059 -> 271 us, 64 of 128 tokens 609 -> 172 us.
+// stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 116 us, 8 of 333 tokens
+// (top-3) 1059 -> 261 us, 64 of 128 tokens 609 -> 169 us.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
