@@ -11,15 +11,18 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = r"""
 #include "handover.h"
 using namespace sida;
-// The walk of a posting layer over T steps as text: t/s/f = take, store, fetch a chunk; B = a barrier; P = a post.
-extern "C" int walk(int T, char *out, int *chunk)
+// The walk of a layer over T steps as text: t/s/f = take, store, fetch a chunk; S = a step, which ends with a
+// barrier; B = a barrier of its own; P = a post.
+template <bool POST>
+int walk_of(int T, char *out, int *chunk)
 {
     int n = 0;
     auto put = [&](char what, int c) { out[n] = what; chunk[n++] = c; };
-    walk_chunks<kSteps, true>(T, [&](int c) { put('t', c); }, [&](int c) { put('s', c); }, [&] { put('B', -1); },
+    walk_chunks<kSteps, POST>(T, [&](int c) { put('t', c); }, [&](int c) { put('s', c); }, [&] { put('S', -1); },
                               [&](int c) { put('f', c); }, [&] { put('P', -1); }, [&] { put('B', -1); });
     return n;
 }
+extern "C" int walk(int T, bool post, char *out, int *chunk) { return post ? walk_of<true>(T, out, chunk) : walk_of<false>(T, out, chunk); }
 extern "C" int steps_per_chunk() { return kSteps; }
 extern "C" void role(int ticket, int n_seq, int *what, int *seq)
 {
@@ -53,17 +56,43 @@ def lib(tmp_path_factory):
     return lib
 
 
-def walk(lib, T):
+def walk(lib, T, post=True):
     out, chunk = ctypes.create_string_buffer(16 * T + 64), (ctypes.c_int * (16 * T + 64))()
-    n = lib.walk(T, out, chunk)
+    n = lib.walk(T, ctypes.c_bool(post), out, chunk)
     return [(out.raw[i:i + 1].decode(), chunk[i]) for i in range(n)]
 
 
-@pytest.mark.parametrize("T", list(range(1, 34)) + [89, 125, 128, 333, 385, 4096])
+LENGTHS = list(range(1, 34)) + [89, 125, 128, 333, 385, 4096]
+
+
+@pytest.mark.parametrize("post", [True, False])
+@pytest.mark.parametrize("T", LENGTHS)
+def test_every_chunk_is_walked_whole(lib, T, post):
+    """Between take(c) and take(c + 1): the states of chunk c - 1 are stored before the first step, every time step of
+    chunk c is made once, and chunk c + 1's inputs are asked for (they replace chunk c's, which take(c) has put away)."""
+    events, steps = walk(lib, T, post), lib.steps_per_chunk()
+    K = -(-T // steps)
+    taken = [i for i, (w, _) in enumerate(events) if w == "t"]
+    assert taken[0] == 0 and [events[i][1] for i in taken] == list(range(K))
+    end_of_walk = max(i for i, (w, _) in enumerate(events) if w == "s")
+    for c, (begin, end) in enumerate(zip(taken, taken[1:] + [end_of_walk])):
+        part = events[begin + 1:end]
+        names = [w for w, _ in part]
+        assert names.count("S") == min(steps, T - c * steps)
+        assert [e for e in part if e[0] == "s"] == [("s", c - 1)] * (c > 0)
+        assert c == 0 or names[0] == "s"
+        assert [e for e in part if e[0] == "f"] == [("f", c + 1)] * (c + 1 < K)
+        assert names.count("P") == (post and c > 0) and "B" not in names
+    # the last chunk's states leave after the last step (and after the post of those before them)
+    assert events[end_of_walk] == ("s", K - 1) and [w for w, _ in events[end_of_walk + 1:]] == ["B", "P"] * post
+
+
+@pytest.mark.parametrize("T", LENGTHS)
 def test_a_counted_chunk_has_arrived(lib, T):
     """Wavefronts run freely between two barriers.  Whatever their order, a count of (c + 1) * wavefronts is
     reached only when every wavefront has posted chunk c."""
     events, K = walk(lib, T), -(-T // lib.steps_per_chunk())
+    events = [("B" if w == "S" else w, c) for w, c in events]
     intervals = [[]]
     for what, c in events:
         if what == "B":
