@@ -91,6 +91,11 @@ def test_hash_forward_against_oracle(d, C, L, E, k, n_seq, T):
     # the most sequences whose layers run side by side, and one more
     (64, 64, 1, 4, 1, 85, 11),
     (64, 64, 1, 4, 1, 86, 11),
+    # layer after layer: whole chunks in a row at both widths, with a partial one at the end and without
+    (64, 128, 1, 4, 1, 86, 27),
+    (64, 128, 1, 4, 1, 96, 40),
+    (64, 64, 1, 4, 1, 86, 29),
+    (64, 64, 1, 4, 1, 96, 40),
     # d_model with a remainder of 8 / 24 / 40 over a stage of the dense stage's operands; less than one stage
     (8, 64, 1, 4, 1, 1, 3),
     (200, 128, 1, 4, 1, 1, 20),
