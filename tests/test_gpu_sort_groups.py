@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("name,E,d,F,sizes,odd", [
     ("more-than-a-launch", 16, 128, 256, [700] * 17, ()),           # groups of 8, 8 and 1
     ("sizes-change", 16, 128, 256, [300, 300, 64, 301, 301, 300, 2100, 2100], ()),
+    ("one-round-a-wavefront", 16, 128, 256, [511, 512, 512, 513, 513], ()),
     ("no-room", 200, 128, 128, [8] * 3, ()),                        # x_perm is smaller than one layer's sort
     ("room-for-few", 200, 128, 128, [64] * 7, ()),                  # ... holds fewer than a launch sorts
     ("chunks", 8, 128, 256, [4097, 4097, 5000, 5000, 5000], ()),

@@ -25,7 +25,8 @@ def ids_for(rng, kind, T, E):
 @pytest.mark.parametrize("T,E,kind", [
     (1, 1, "one"), (1, 8, "uniform"), (63, 8, "uniform"), (64, 8, "zipf"), (65, 3, "uniform"),
     (255, 64, "zipf"), (256, 256, "uniform"), (257, 256, "zipf"), (1000, 7, "one"), (1023, 128, "zipf"),
-    (511, 130, "zipf"), (512, 256, "one"), (513, 64, "zipf"),          # around its chunks of one round
+    # around its chunks of one round, all of them full and of mixed ids
+    (511, 130, "zipf"), (512, 256, "one"), (512, 256, "uniform"), (512, 128, "zipf"), (513, 64, "zipf"),
     (2047, 200, "zipf"), (2048, 128, "uniform"), (2049, 128, "zipf"),    # around the single-workgroup sort's limit
     (4095, 128, "zipf"), (4096, 256, "uniform"), (5000, 256, "uniform"), (4097, 64, "zipf"),
     (8191, 128, "zipf"), (8192, 256, "zipf"), (8193, 128, "uniform"),                    # ... and its larger shapes
