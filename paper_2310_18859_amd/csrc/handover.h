@@ -55,9 +55,15 @@ SIDA_HD void wait_for(int want, int &seen, Peek &&peek)
 // Inside the walk the steps bring it (the post of chunk c - 1 follows at most two steps of chunk c);
 // the last chunk may end right after that post, hence the barrier in front of the final one.
 // The store of a chunk's states gets two steps to complete, the loads of the next chunk's inputs the last two
-// of a chunk: both are about as long as they take, and each step more is a step by which the second layer
-// ends later (three steps and the second half of a chunk: 1 x 128 tokens 117.5 us, 115.8 this way; 8 x 333
-// 262.5 and 261.1, 64 x 128 170 and 168.5; posts after one step or fetches after seven gain no more).
+// of a chunk: each step more is a step by which the second layer ends later.  Measured at both widths, also where
+// the layers run one after the other and nobody follows, against three steps and the second half of a chunk
+// (us a call, d = 768, 6 x 128 experts, one per token):
+//             1 x 128          8 x 333          64 x 128         96 x 85 (layer after layer)
+//   C = 128   112.8 -> 111.5   260.2 -> 258.6   168.2 -> 166.6   201.8 -> 201.4
+//   C = 64     74.8 ->  73.9   166.9 -> 166.0   107.9 -> 106.9   123.8 -> 123.6
+// Loads that nobody is waited for need no more than two steps (96 x 85 with loads after step 2: 201.8 and 123.8).
+// Posts after one step are 0.5 us less at C = 128 and up to 1 us more at C = 64 (8 x 333); loads after step 7
+// are within 0.5 us of these everywhere.
 constexpr int kPostAfter = 2, kFetchAfter = kSteps - 2;
 template <int STEPS, bool POST, class Take, class Store, class Step, class Fetch, class Post, class Barrier>
 SIDA_HD void walk_chunks(int T, Take &&take, Store &&store, Step &&step, Fetch &&fetch, Post &&post, Barrier &&barrier)

@@ -19,7 +19,7 @@
 // four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
 // It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
-// four clocks apiece (0.43 us at 2.4 GHz), and some 42 other instructions.  Measured against one launch per layer and
+// four clocks apiece (0.43 us at 2.4 GHz), 42 other vector instructions and 20 that are none.  Measured against one launch per layer and
 // stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 116 us, 8 of 333 tokens
 // (top-3) 1059 -> 261 us, 64 of 128 tokens 609 -> 169 us.
 #include <hip/hip_runtime.h>
@@ -369,7 +369,8 @@ __device__ __forceinline__ float gate_value(float v, const GateKind &k)
 // sum + v of the quad's lane 1 * x, as one instruction (the compiler makes it a move and a multiply-add).
 __device__ __forceinline__ float fma_of_gate1(float v, float x, float sum)
 {
-    // a value from another lane may be read two instructions after it was written
+    // A value from another lane may be read two instructions after it was written.  The compiler sees to that in its
+    // own code, not in front of this; the wait stays here, also where what it put in front has waited already.
     asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "+v"(sum) : "v"(v), "v"(x));
     return sum;
 }
@@ -392,12 +393,14 @@ struct RecurrenceLds {
 // quarters 0.65 us).  Slot j of lane l of the eight is row j ^ l, so that seven adds of permuted lanes
 // leave row l's sum in lane l; thread 4u+s then has gate s of unit u, the four gates meet in quad permutes
 // too, and a step has one barrier and no global access: pre-activations come and states go a chunk of
-// steps at a time.  What is left of a step is the issue of 128 multiply-adds and about 42 other
-// instructions per wavefront, two wavefronts per SIMD, nearly back to back: each instruction less is
-// 8 clocks of about 1350 a step.  Hence whole chunks are written out (addresses become offsets), lane 0
-// of a quad alone carries the cell's state, and sums of permuted lanes are one instruction each: 9
-// instructions fewer, same bits, 1 x 128 tokens 122.1 -> 117.5 us, 8 x 333 271.8 -> 262.5, 64 x 128
-// 174.5 -> 170.
+// steps at a time.  What is left of a step at C = 128 is the issue of 128 multiply-adds, 42 other vector
+// instructions and 20 that are none (8 s_nop, 6 LDS accesses, 5 waits, the barrier) per wavefront, two
+// wavefronts per SIMD, nearly back to back: each vector instruction less is 8 clocks of about 1350 a step.
+// Hence whole chunks are written out (addresses become offsets; the kernel's code doubles to 27 KB), lane 0
+// of a quad alone carries the cell's state, and sums of permuted lanes are one instruction each, with the
+// same bits.  One taken back at a time, us a call, and all three in front (1 x 128, 8 x 333, 96 x 85 tokens):
+// 112.8, 260.2, 201.8; chunks walked in a loop 115.9, 267.7, 205.5; the state in every lane 113.2, 260.9, 202.8;
+// the sum with a permuted value more 113.0, 260.7, 201.8.
 //   WAIT   pre arrives in chunks from another workgroup (progress in *arrived)
 //   POST   out is handed on to another workgroup (progress in *done: wavefronts x chunks)
 template <int C, bool WAIT, bool POST>

@@ -25,7 +25,7 @@ namespace sida {
 
 namespace {
 
-constexpr int kChunk = 256;      // tokens per wavefront (4 rounds of 64)
+constexpr int kChunk = 256;      // tokens that a wavefront ranks (4 rounds of 64); sort_one up to 512 tokens takes 64
 constexpr int kMaxE = 256;
 
 // The jobs of a launch, by value; row y of the grid does job y.
@@ -209,10 +209,11 @@ __global__ __launch_bounds__(64) void sort_rank(const int32_t *__restrict__ ids,
 // per batch, the paper's serving regime, upwards): wavefront w owns chunk w of ROUNDS * 64 tokens,
 // the per-chunk histograms and bases live in LDS, and the three launches above shrink to one.
 // Same results.  Up to 512 tokens a chunk is one round for each of the eight wavefronts: with chunks of
-// 256 tokens one or two of them ranked four rounds in a row (that and the early loads: a layer of 8
-// experts and 256 tokens 29.0 -> 27.0 us).  Measured: 9 us up to 2048 tokens and
-// 10 us (14 us when the gate values move along) at 4096 against 17-19 us for the three launches; at
-// 8192 tokens (16 x 2 chunks) 15 us and 24 us, the latter slower than the three launches.
+// 256 tokens one or two of them rank four rounds in a row, as three or four still do from 513 to 1024
+// tokens.  Kernel time with gate values and 128 experts, before the one-round chunks and the early loads ->
+// now: 256 tokens 5.0 -> 3.4 us, 512 5.1 -> 3.6, 513 5.2 -> 4.4, 1024 5.2 -> 4.5, 2048 5.6 -> 4.8, 2049
+// 5.7 -> 5.6, 4096 6.8 -> 6.5; 8, 64 and 256 experts alike, but for 8 experts and 2049 tokens, 5.7 -> 5.9.  A layer
+// of 8 experts and 256 tokens, one call behind another, 26.1 -> 23.8 us.  The three launches took 17-19 us with their gaps at 4096 tokens.
 constexpr int kOneT = 4096;      // most tokens the single-workgroup sort takes
 
 template <int NWV, int ROUNDS>
