@@ -70,7 +70,7 @@ void layout(const sida_config &cfg, int32_t T, sida_ws_layout *o)
     o->h = take(2 * (size_t)T * (size_t)cfg.d_ff);
     o->y_perm = take(2 * (size_t)T * (size_t)cfg.d_model);
     o->tiles = take(sizeof(TileDesc) * max_tiles(cfg, T));
-    o->sink = take(kGemmSinkBytes);
+    o->sink = take(64 * 1024);
     o->gate_perm = take(sizeof(float) * (size_t)T);
     o->total = off;
 }
@@ -80,7 +80,6 @@ struct Ws {
     void *x_perm, *h, *y_perm;
     TileDesc *tiles;
     int32_t max_tiles;
-    void *sink;
     float *gate_perm;
 };
 
@@ -92,7 +91,7 @@ Ws carve(const sida_config &cfg, int32_t T, void *base)
     return Ws{(int32_t *)(b + l.counts), (int32_t *)(b + l.offsets), (int32_t *)(b + l.block_hist),
               (int32_t *)(b + l.perm),   (int32_t *)(b + l.inv),     b + l.x_perm,
               b + l.h,                   b + l.y_perm,               (TileDesc *)(b + l.tiles),
-              (int32_t)max_tiles(cfg, T), b + l.sink, (float *)(b + l.gate_perm)};
+              (int32_t)max_tiles(cfg, T), (float *)(b + l.gate_perm)};
 }
 
 int check_plan(const sida_ctx *c, const sida_plan *p)
@@ -400,14 +399,14 @@ int launch_wave_ffn(sida_ctx *c, const LayerSchedule &s, int32_t w, const Ws &ws
         TimedKernel tk(c, SIDA_K_GEMM1);
         HIP_TRY(c, (hipError_t)launch_ffn_gemm1(x ? x : ws.x_perm, ws.h, c->pool, c->expert_bytes, tiles,
                                                 s.m_tiles[w] - s.m_few[w], s.m_tall[w], s.m_few[w], s.few_rows[w],
-                                                c->cfg.d_model, c->cfg.d_ff, ws.sink, st, tk.get(),
+                                                c->cfg.d_model, c->cfg.d_ff, st, tk.get(),
                                                 x ? T / c->top_k : T, x ? ws.perm : nullptr, T, c->top_k, s.tbl.tile_m));
     }
     {
         TimedKernel tk(c, SIDA_K_GEMM2);
         HIP_TRY(c, (hipError_t)launch_ffn_gemm2(ws.h, y ? y : ws.y_perm, c->pool, c->expert_bytes, tiles,
                                                 s.m_tiles[w] - s.m_few[w], s.m_tall[w], s.m_few[w], s.few_rows[w],
-                                                c->cfg.d_model, c->cfg.d_ff, ws.sink, st, tk.get(), T,
+                                                c->cfg.d_model, c->cfg.d_ff, st, tk.get(), T,
                                                 y ? ws.perm : nullptr, y ? ws.gate_perm : nullptr, s.tbl.tile_m));
     }
     return SIDA_OK;

@@ -86,6 +86,15 @@ __device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t r, int voffse
     return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, voffset, soffset, STREAM ? 2 : 0));
 }
 
+// 16 bytes per lane out; lanes whose offset is past the descriptor's end write nothing.  The whole offset goes through the
+// lanes' register: with part of it in a scalar register the compiler takes the registers of the 16 bytes as free in the
+// next instruction, and a vector instruction there changed bytes that were still to be stored (seen as wrong rows where
+// the store met a cold address translation).  Without, it keeps them for the wait state that such a store needs.
+__device__ __forceinline__ void store_row_piece(__amdgpu_buffer_rsrc_t r, bf16x8 v, int offset)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, offset, 0, 0);
+}
+
 // FUSE selects what the token rows are addressed through:
 //   kPlain    A rows and C rows are the tile's rows row0 .. row0+rows-1 (x_perm -> h -> y_perm);
 //   kGather   A is x in token order: row r of the tile is read from x[perm[row0 + r] / top_k]
@@ -111,8 +120,7 @@ struct GemmArgs {
     int m_tiles, m_tall, gm, nw, N, K;      // gm x nw: block of the tile order (tile_order.h)
     int m_few, few_rows;         // few-token tiles behind the m_tiles others, and their rows
     int big_wgs;                 // workgroups that walk the m_tiles tiles
-    uint32_t a_bytes;            // bytes of A
-    char *sink;
+    uint32_t a_bytes, c_bytes;   // bytes of A and C
     const int32_t *perm;         // fused modes: row maps, `map_len` entries
     const float *gate_perm;
     int map_len, top_k;
@@ -350,8 +358,8 @@ __global__ __launch_bounds__(kWaves * 64, NS == 1 ? 3 : 2) void stream_gemm_nt(c
 //
 // (tile, K-step) is ONE stream of steps: the loads run NB steps ahead of the MFMAs (K/64 is a
 // multiple of NB), also across
-// tile boundaries (the last NB steps of a tile already fetch the next one; a workgroup's last tile
-// fetches its own first steps once more, unused, so that the loop has no data-dependent branch).
+// tile boundaries (the last NB steps of a tile already fetch the next one; behind a workgroup's last tile
+// they ask for nothing, see point_nowhere).
 // Per step a wavefront executes: one s_waitcnt, one s_barrier, its share of the token loads, and
 // per 16 K values BM/32 LDS fragment reads, NS*BM/32 MFMAs and NS weight-fragment loads.
 template <int BM, int NS, int NB, bool RELU, int FUSE>
@@ -376,7 +384,6 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
     constexpr int kSide = FUSE == kPlain ? 0 : (FUSE == kGather ? 256 : 2 * BM * 4);   // row maps, per wavefront
     static_assert(QN % NWV == 0 && TL * 8 <= 64, "token loads per wavefront");
     static_assert(kBase + STORES + 4 <= 63, "vmcnt range");
-    static_assert(NWV * 64 * 16 <= kGemmSinkBytes / 2, "sink size");
     static_assert(kRingBytes + kStage + NWV * kSide <= 80 * 1024, "two workgroups per compute unit");
     static_assert(kRingBytes + kStage >= kStreamLdsBytes, "the few-token tiles' LDS");
 
@@ -399,9 +406,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
     const int n = (total - wg + G - 1) / G;                     // tiles of this workgroup
     const int nkk = K / (64 * NB);
     const int stripe_bytes = 32 * K * 2;
-    // results of rows past a tile's end go to a scratch sink (every thread issues all its stores,
-    // the waits count them); the two workgroups of a compute unit may share it
-    __bf16 *const sink = reinterpret_cast<__bf16 *>(g.sink) + (size_t)tid * 8;
+    const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(g.C, g.c_bytes);
 
     struct Coord {
         int row0, rows, nt;
@@ -458,6 +463,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
         tok_s = 0;
         w_s = 0;
         w_once = c.once;
+    };
+    // Behind a workgroup's last tile: loads past the descriptors' ends, which ask for nothing, so that the loop has no
+    // data-dependent branch around a load.  (The last tile's first steps fetched once more were two steps of 512
+    // workgroups, 50 MB of a launch's 900; 128 experts, 16384 tokens, first GEMM 153 -> 150 us with it and with rows
+    // past a tile's end no longer written.)
+    auto point_nowhere = [&]() {
+#pragma unroll
+        for (int j = 0; j < TL; ++j) tok_v[j] = INT32_MIN;
+        w_rsrc = make_rsrc(g.pool, 0);
     };
     int wr_off = 0;                                             // ring offset of the stage filled next
     auto issue_tokens = [&]() {
@@ -539,9 +553,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
                 const int r = i * RPI + srow;
                 const int m = im * 32 + r;
                 const bf16x8 v = *reinterpret_cast<const bf16x8 *>(stg + r * kOutPitch + seg * 16);
-                const int out_row = FUSE == kScatter ? reinterpret_cast<const int *>(side)[m] : c.row0 + m;
-                __bf16 *dst = m < c.rows ? g.C + (size_t)out_row * N + (size_t)c.nt * BN + wv * kOutCols + seg * 8 : sink;
-                *reinterpret_cast<bf16x8 *>(dst) = v;
+                // of the row, what differs between lanes (kPlain: all of it but srow is uniform)
+                const int lane_row = FUSE == kScatter ? reinterpret_cast<const int *>(side)[m] : srow;
+                const int base_row = FUSE == kScatter ? 0 : c.row0 + im * 32 + i * RPI;
+                // rows past the tile's end are stored out of range: nothing is written, but every thread issues all its
+                // stores and the waits count them
+                const int at = lane_row * N * 2 + seg * 16 + (base_row * N + c.nt * BN + wv * kOutCols) * 2;
+                store_row_piece(c_rsrc, v, m < c.rows ? at : INT32_MIN);
             }
         }
     };
@@ -573,7 +591,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
         for (int kk = 0; kk < nkk; ++kk) {
             if (kk == nkk - 1) {                                // all loads of this tile have been issued
                 if (FUSE == kGather && nkk == 1) wait_loads<0>();   // else a wait of an earlier step covered the row map
-                point(nc, next_slot);
+                if (t + 1 < n) point(nc, next_slot);
+                else point_nowhere();
             }
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
@@ -761,7 +780,7 @@ void forget_stream(hipStream_t st)
 }
 
 int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t expert_bytes, const TileDesc *tiles,
-                     int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F, void *sink, hipStream_t st,
+                     int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F, hipStream_t st,
                      const LaunchEvents *ev, int32_t a_rows, const int32_t *perm, int32_t map_len, int32_t top_k,
                      int32_t tile_m)
 {
@@ -779,7 +798,7 @@ int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t exper
     a.N = F;
     a.K = d;
     a.a_bytes = (uint32_t)((size_t)a_rows * d * 2);
-    a.sink = (char *)sink;
+    a.c_bytes = (uint32_t)((size_t)map_len * F * 2);
     a.perm = perm;
     a.map_len = map_len;
     a.top_k = top_k;
@@ -787,7 +806,7 @@ int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t exper
 }
 
 int launch_ffn_gemm2(const void *h, void *y_perm, const char *pool, size_t expert_bytes, const TileDesc *tiles,
-                     int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F, void *sink, hipStream_t st,
+                     int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F, hipStream_t st,
                      const LaunchEvents *ev, int32_t a_rows, const int32_t *perm, const float *gate_perm, int32_t tile_m)
 {
     GemmArgs a{};
@@ -804,7 +823,7 @@ int launch_ffn_gemm2(const void *h, void *y_perm, const char *pool, size_t exper
     a.N = d;
     a.K = F;
     a.a_bytes = (uint32_t)((size_t)a_rows * F * 2);
-    a.sink = (char *)sink + kGemmSinkBytes / 2;              // GEMM 1 and GEMM 2 of concurrent streams do not share
+    a.c_bytes = (uint32_t)((size_t)a_rows * d * 2);
     a.perm = perm;
     a.gate_perm = gate_perm;
     a.map_len = a_rows;

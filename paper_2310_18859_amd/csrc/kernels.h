@@ -61,7 +61,6 @@ int launch_gather(const void *x, const int32_t *perm, int32_t T, int32_t d, void
 // first m_tall of them belong to experts with more than one tile; tile_m = rows per tile (64 when
 // most experts of the layer have at most 64 tokens, 128 otherwise).  Behind them come m_few tiles of at
 // most 64 rows each, few_rows altogether, that are streamed rather than walked.
-// sink: kGemmSinkBytes of device scratch that absorbs the stores of rows past a tile's end.
 // With a row map (perm, and for GEMM 2 gate_perm) the gather / combine passes are folded in:
 // GEMM 1 then reads row r from x[perm[r] / k] (x_perm = x in token order, k rows per token), GEMM 2 writes
 // bf16(gate_perm[r] * result row r) to y[perm[r]] (y_perm = y in token order).
@@ -69,11 +68,11 @@ int launch_gather(const void *x, const int32_t *perm, int32_t T, int32_t d, void
 // The experts are read from their pool slots in the slot layout below.
 int launch_ffn_gemm1(const void *x_perm, void *h, const char *pool, size_t expert_bytes,
                      const TileDesc *tiles, int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F,
-                     void *sink, hipStream_t st, const LaunchEvents *ev, int32_t a_rows,
+                     hipStream_t st, const LaunchEvents *ev, int32_t a_rows,
                      const int32_t *perm = nullptr, int32_t map_len = 0, int32_t k = 1, int32_t tile_m = 128);
 int launch_ffn_gemm2(const void *h, void *y_perm, const char *pool, size_t expert_bytes,
                      const TileDesc *tiles, int32_t m_tiles, int32_t m_tall, int32_t m_few, int32_t few_rows, int32_t d, int32_t F,
-                     void *sink, hipStream_t st, const LaunchEvents *ev, int32_t a_rows,
+                     hipStream_t st, const LaunchEvents *ev, int32_t a_rows,
                      const int32_t *perm = nullptr, const float *gate_perm = nullptr, int32_t tile_m = 128);
 
 // Slot layout.  The host block of an expert is W_in [F, d] then W_out [d, F], row-major (the ABI);
@@ -133,7 +132,6 @@ int launch_hash_forward(const HashShape &sh, const float *params, const void *x,
 constexpr size_t kHashStaticScratchBytes = size_t(16) << 20;
 int hash_static_scratch(float **out);
 
-constexpr int kGemmSinkBytes = 64 * 1024;
 constexpr int kGemmTileM = 128;   // token rows per GEMM tile of large launches
 constexpr int kGemmTileSmall = 64; // ... of small launches
 
