@@ -90,9 +90,10 @@ __device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t r, int voffse
 // lanes' register: with part of it in a scalar register the compiler takes the registers of the 16 bytes as free in the
 // next instruction, and a vector instruction there changed bytes that were still to be stored (seen as wrong rows where
 // the store met a cold address translation).  Without, it keeps them for the wait state that such a store needs.
+template <bool STREAM>
 __device__ __forceinline__ void store_row_piece(__amdgpu_buffer_rsrc_t r, bf16x8 v, int offset)
 {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, offset, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, offset, 0, STREAM ? 2 : 0);
 }
 
 // FUSE selects what the token rows are addressed through:
@@ -124,7 +125,6 @@ struct GemmArgs {
     const int32_t *perm;         // fused modes: row maps, `map_len` entries
     const float *gate_perm;
     int map_len, top_k;
-    bool stream_once;            // weights of experts with a single token tile take the streaming cache policy
 };
 
 // ---- experts with few tokens ----------------------------------------------------------------------
@@ -362,7 +362,12 @@ __global__ __launch_bounds__(kWaves * 64, NS == 1 ? 3 : 2) void stream_gemm_nt(c
 // they ask for nothing, see point_nowhere).
 // Per step a wavefront executes: one s_waitcnt, one s_barrier, its share of the token loads, and
 // per 16 K values BM/32 LDS fragment reads, NS*BM/32 MFMAs and NS weight-fragment loads.
-template <int BM, int NS, int NB, bool RELU, int FUSE>
+//
+// ONCE: the weights of single-tile experts are streamed past L2's replacement (worth_streaming), and so are the results,
+// which would push the many-token experts' weights and the token rows out of the L2s.  128 experts, 16384 tokens, GEMMs
+// 155.6 / 160.1 -> 153.2 / 159.0 us, layers of 128 experts x 4096 tokens 4 % faster; but with 16 experts x 4096 tokens,
+// whose weights the Infinity Cache holds, 5 % slower, and 7 % with 64 experts x 8192 tokens of 384 x 1536.
+template <int BM, int NS, int NB, bool RELU, int FUSE, bool ONCE>
 __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs g)
 {
     constexpr int NWV = kWaves, BN = NWV * NS * 32;
@@ -390,8 +395,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     if ((int)blockIdx.x >= g.big_wgs) {
         f32x4 *red = reinterpret_cast<f32x4 *>(lds);
-        if (g.stream_once) stream_block<kFewStripes, RELU, FUSE, true>(g, (int)blockIdx.x - g.big_wgs, red);
-        else stream_block<kFewStripes, RELU, FUSE, false>(g, (int)blockIdx.x - g.big_wgs, red);
+        stream_block<kFewStripes, RELU, FUSE, ONCE>(g, (int)blockIdx.x - g.big_wgs, red);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63;
@@ -423,7 +427,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
                       offsetof(TileDesc, rows) == 8, "a tile descriptor is read as four ints");
         typedef const __attribute__((address_space(4))) i32x4 *ConstTiles;
         const i32x4 td = ((ConstTiles)(uintptr_t)g.tiles)[mt];  // slot, row0, rows, expert
-        *c = Coord{td.y, td.z, nt, g.stream_once && mt >= g.m_tall};
+        *c = Coord{td.y, td.z, nt, ONCE && mt >= g.m_tall};
         return td.x;
     };
 
@@ -485,7 +489,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
     // read by this tile's workgroups only: streamed past L2's replacement, they leave the token tiles
     // and the many-token experts' weights in place.  (A uniform branch around two equal sets of loads.)
     auto issue_weights = [&](bf16x8 (&wb)[KS][NS]) {
-        if (w_once) {
+        if (ONCE && w_once) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -559,7 +563,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
                 // rows past the tile's end are stored out of range: nothing is written, but every thread issues all its
                 // stores and the waits count them
                 const int at = lane_row * N * 2 + seg * 16 + (base_row * N + c.nt * BN + wv * kOutCols) * 2;
-                store_row_piece(c_rsrc, v, m < c.rows ? at : INT32_MIN);
+                store_row_piece<ONCE>(c_rsrc, v, m < c.rows ? at : INT32_MIN);
             }
         }
     };
@@ -679,16 +683,15 @@ bool worth_streaming(const GemmArgs &a) { return (int64_t)(a.m_tiles - a.m_tall 
 // and the rest to the stream of few-token workgroups, which also fills the slots that come free: a compute
 // unit that multiplies and streams at a time.  (128 experts, 5461 tokens, Zipf(1): 132 / 141 us as one
 // kind of tile, 126 / 126 us; with three quarters or all slots 128 / 126 and 131 / 126 us.)
-template <int BM, int NS, int NB, bool RELU, int FUSE>
+template <int BM, int NS, int NB, bool RELU, int FUSE, bool ONCE>
 int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
     constexpr int kLdsBytes = (NB + 1) * BM * 128 + kWaves * 32 * (NS * 64 + 16) +
                               kWaves * (FUSE == kPlain ? 0 : (FUSE == kGather ? 256 : 2 * BM * 4));
     static LdsGrant grant;
-    const int rc = allow_lds(grant, reinterpret_cast<const void *>(&grouped_gemm_nt<BM, NS, NB, RELU, FUSE>), kLdsBytes);
+    const int rc = allow_lds(grant, reinterpret_cast<const void *>(&grouped_gemm_nt<BM, NS, NB, RELU, FUSE, ONCE>), kLdsBytes);
     if (rc) return rc;
     GemmArgs g = a;
-    g.stream_once = worth_streaming(a);
     const int n_tiles_n = a.N / (kWaves * NS * 32);
     g.gm = tile_group_height(a.m_tiles, a.m_tall, a.K > a.N);
     g.nw = tile_block_width(n_tiles_n, g.gm);
@@ -696,7 +699,7 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
     const int cap = (a.m_few ? 1 : 2) * stream_compute_units(st);  // two workgroups per compute unit
     g.big_wgs = total < cap ? (total + 7) / 8 * 8 : cap;     // multiple of 8 XCDs
     const int few_wgs = (a.m_few * (a.N / (32 * kFewStripes)) + 7) / 8 * 8;
-    hipExtLaunchKernelGGL((grouped_gemm_nt<BM, NS, NB, RELU, FUSE>), dim3(g.big_wgs + few_wgs), dim3(kWaves * 64), kLdsBytes, st,
+    hipExtLaunchKernelGGL((grouped_gemm_nt<BM, NS, NB, RELU, FUSE, ONCE>), dim3(g.big_wgs + few_wgs), dim3(kWaves * 64), kLdsBytes, st,
                           ev ? ev->start : nullptr, ev ? ev->stop : nullptr, 0, g);
     return (int)hipGetLastError();
 }
@@ -722,10 +725,11 @@ int launch_width(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
     // (64 experts, 8192 tokens, second GEMM: 95 -> 87 us; 32 experts x 62 tokens, first GEMM: 38 -> 34 us;
     // many-token experts prefer the wide tile at any count).
     if (wide && 4 * t_wide <= 3 * slots && 2 * a.m_tall <= a.m_tiles) wide = false;
-    if (wide) return launch_as<BM, 2, 2, RELU, FUSE>(a, st, ev);
+    const bool once = worth_streaming(a);
+    if (wide) return once ? launch_as<BM, 2, 2, RELU, FUSE, true>(a, st, ev) : launch_as<BM, 2, 2, RELU, FUSE, false>(a, st, ev);
     if constexpr (BM == kGemmTileSmall)
-        if (a.K % 256 == 0) return launch_as<BM, 1, 4, RELU, FUSE>(a, st, ev);
-    return launch_as<BM, 1, 2, RELU, FUSE>(a, st, ev);
+        if (a.K % 256 == 0) return once ? launch_as<BM, 1, 4, RELU, FUSE, true>(a, st, ev) : launch_as<BM, 1, 4, RELU, FUSE, false>(a, st, ev);
+    return once ? launch_as<BM, 1, 2, RELU, FUSE, true>(a, st, ev) : launch_as<BM, 1, 2, RELU, FUSE, false>(a, st, ev);
 }
 
 // A launch of few-token tiles only.  One stripe per workgroup keeps most workgroups going; two, which
