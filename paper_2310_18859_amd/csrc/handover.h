@@ -10,7 +10,12 @@
 
 namespace sida {
 
-constexpr int kSteps = 8;        // time steps per chunk of the hand-over between the layers
+// Time steps per chunk of the hand-over between the layers, of layers 128 wide and of narrower ones.  Layer 2 ends about
+// two chunks behind layer 1, so a short chunk ends earlier: eight steps and four, us a call, C = 128: 1 x 128 tokens
+// 112.2 -> 107.5, 8 x 333 260.9 -> 254.2, 64 x 128 167.3 -> 161.9, 2 x 512 351.8 -> 344.1, 96 x 85 (layer after layer)
+// 202.7 -> 201.3.  A chunk's own work is the same for any width; at C = 64, where a step is shorter, it makes 8 x 333
+// tokens slower (167.9 -> 170.6; 1 x 128 74.0 -> 72.4).
+constexpr int kSteps = 4, kStepsNarrow = 8;
 
 // What a workgroup does, by the ticket it drew: layer 1 of a sequence (0), the gate pre-activations between
 // the layers (1), layer 2 (2).  Any number is a valid ticket: the counters stand in the caller's workspace,
@@ -54,21 +59,20 @@ SIDA_HD void wait_for(int want, int &seen, Peek &&peek)
 // wavefront posts twice before all others have posted once: between any two posts stands a barrier.
 // Inside the walk the steps bring it (the post of chunk c - 1 follows at most two steps of chunk c);
 // the last chunk may end right after that post, hence the barrier in front of the final one.
-// The store of a chunk's states gets two steps to complete, the loads of the next chunk's inputs the last two
-// of a chunk: each step more is a step by which the second layer ends later.  Measured at both widths, also where
-// the layers run one after the other and nobody follows, against three steps and the second half of a chunk
-// (us a call, d = 768, 6 x 128 experts, one per token):
-//             1 x 128          8 x 333          64 x 128         96 x 85 (layer after layer)
-//   C = 128   112.8 -> 111.5   260.2 -> 258.6   168.2 -> 166.6   201.8 -> 201.4
-//   C = 64     74.8 ->  73.9   166.9 -> 166.0   107.9 -> 106.9   123.8 -> 123.6
-// Loads that nobody is waited for need no more than two steps (96 x 85 with loads after step 2: 201.8 and 123.8).
-// Posts after one step are 0.5 us less at C = 128 and up to 1 us more at C = 64 (8 x 333); loads after step 7
-// are within 0.5 us of these everywhere.
-constexpr int kPostAfter = 2, kFetchAfter = kSteps - 2;
+// The store of a chunk's states gets a quarter of a chunk to complete, the loads of the next chunk's inputs its last
+// quarter: each step more is a step by which the second layer ends later.  Chunks of four steps, posts and loads after
+// steps 1 and 3, 2 and 2, 1 and 2, 2 and 3 (C = 128, us a call, d = 768, 6 x 128 experts, one per token; 8 x 333 three):
+//   1 x 128 107.5, 109.9, 108.1, 107.9;  8 x 333 254.2, 259.1, 256.6, 254.8;  64 x 128 161.9, 164.4, 162.7, 162.5
+// Chunks of eight, after steps 2 and 6 and after 3 and 4: C = 64 1 x 128 73.9 and 74.8, 8 x 333 166.0 and 166.9, 64 x 128
+// 106.9 and 107.9, 96 x 85 (layer after layer) 123.6 and 123.8; posts after one step up to 1 us more (8 x 333).
+template <int STEPS>
+constexpr int kPostAfter = STEPS / 4;
+template <int STEPS>
+constexpr int kFetchAfter = STEPS - STEPS / 4;
 template <int STEPS, bool POST, class Take, class Store, class Step, class Fetch, class Post, class Barrier>
 SIDA_HD void walk_chunks(int T, Take &&take, Store &&store, Step &&step, Fetch &&fetch, Post &&post, Barrier &&barrier)
 {
-    static_assert(kPostAfter <= kFetchAfter && kFetchAfter <= STEPS, "steps of a chunk");
+    static_assert(kPostAfter<STEPS> <= kFetchAfter<STEPS> && kFetchAfter<STEPS> <= STEPS, "steps of a chunk");
     const int chunks = (T + STEPS - 1) / STEPS;
     for (int c = 0; c < chunks; ++c) {
         const int n = T - c * STEPS < STEPS ? T - c * STEPS : STEPS;
@@ -76,17 +80,17 @@ SIDA_HD void walk_chunks(int T, Take &&take, Store &&store, Step &&step, Fetch &
         if (c > 0) store(c - 1);
         if (n == STEPS) {                                      // written out: a step's addresses become constants
 #pragma unroll
-            for (int i = 0; i < kPostAfter; ++i) step();
+            for (int i = 0; i < kPostAfter<STEPS>; ++i) step();
             if (POST && c > 0) post();
 #pragma unroll
-            for (int i = kPostAfter; i < kFetchAfter; ++i) step();
+            for (int i = kPostAfter<STEPS>; i < kFetchAfter<STEPS>; ++i) step();
             if (c + 1 < chunks) fetch(c + 1);
 #pragma unroll
-            for (int i = kFetchAfter; i < STEPS; ++i) step();
+            for (int i = kFetchAfter<STEPS>; i < STEPS; ++i) step();
         } else {                                               // the last chunk
             int i = 0;
 #pragma clang loop unroll(disable)
-            for (; i < (n < kPostAfter ? n : kPostAfter); ++i) step();
+            for (; i < (n < kPostAfter<STEPS> ? n : kPostAfter<STEPS>); ++i) step();
             if (POST && c > 0) post();
 #pragma clang loop unroll(disable)
             for (; i < n; ++i) step();

@@ -376,13 +376,16 @@ __device__ __forceinline__ float fma_of_gate1(float v, float x, float sum)
 }
 
 template <int C>
+constexpr int kChunk = C == 128 ? kSteps : kStepsNarrow;       // time steps handed over together
+
+template <int C>
 struct RecurrenceLds {
     static constexpr int kSeg = C / 8, kSegPitch = kSeg + 4;   // the eight segments start in different banks
     static constexpr int kRow = 8 * kSegPitch;
-    float h[2 * kSteps][kRow];                                 // the state after each step of two chunks
-    float pre[kSteps][4 * C];                                  // gate pre-activations of a chunk; a thread reads what it wrote
+    float h[2 * kChunk<C>][kRow];                               // the state after each step of two chunks
+    float pre[kChunk<C>][4 * C];                                // gate pre-activations of a chunk; a thread reads what it wrote
     static constexpr int kInPitch = C + 16;
-    float in[2][kSteps * kInPitch];                            // layer 2's inputs of a chunk
+    float in[2][kChunk<C> * kInPitch];                           // layer 2's inputs of a chunk
     int ticket;
 };
 
@@ -408,6 +411,7 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
                                            float *__restrict__ out, const int *arrived, int *done, RecurrenceLds<C> &lds)
 {
     constexpr int kSeg = RecurrenceLds<C>::kSeg, kSegPitch = RecurrenceLds<C>::kSegPitch, kRow = RecurrenceLds<C>::kRow;
+    constexpr int kSteps = kChunk<C>;
     const int tid = threadIdx.x, u = tid >> 2, s = tid & 3;
     const int l8 = tid & 7;
     float w[8][kSeg];
@@ -441,12 +445,14 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
         for (int i = 0; i < kSteps; ++i) next[i] = load_f32<WAIT ? kAgent : 0>(pre_rsrc, (c * kSteps + i) * 4 * C * 4 + my_gate);
         if (WAIT) ahead = peek(arrived);                       // looked at when the next chunk is due
     };
-    // chunk c's states, two per thread, from LDS to global memory (past the end: dropped)
+    // chunk c's states, from LDS to global memory (past the end: dropped)
     auto store_chunk = [&](int c) {
-        const int step = 2 * tid / C, unit = 2 * tid % C;
-        const f32x2 v = *reinterpret_cast<const f32x2 *>(&lds.h[(c & 1) * kSteps + step][(unit / kSeg) * kSegPitch + unit % kSeg]);
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), out_rsrc, ((c * kSteps + step) * C + unit) * 4, 0,
-                                              POST ? kAgent : 0);
+        constexpr int kOwn = kSteps / 4;
+        static_assert(kOwn == 1 || kOwn == 2, "states of a chunk per thread");
+        const int step = kOwn * tid / C, unit = kOwn * tid % C, at = ((c * kSteps + step) * C + unit) * 4;
+        const float *from = &lds.h[(c & 1) * kSteps + step][(unit / kSeg) * kSegPitch + unit % kSeg];
+        if constexpr (kOwn == 1) store_f32<POST ? kAgent : 0>(out_rsrc, at, *from);
+        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, *reinterpret_cast<const f32x2 *>(from)), out_rsrc, at, 0, POST ? kAgent : 0);
     };
     // a wavefront's part of one more chunk of states has left for good
     auto post = [&]() {
@@ -500,7 +506,7 @@ __device__ __forceinline__ void mfma_rows(float a, const float *b, f32x4 &even, 
     ((((J & 1) ? odd : even) = __builtin_amdgcn_mfma_f32_4x4x1f32(a, b[J], (J & 1) ? odd : even, 4, J, 0)), ...);
 }
 
-// Layer 2's gate pre-activations for one sequence, a chunk of kSteps tokens at a time as layer 1
+// Layer 2's gate pre-activations for one sequence, a chunk of tokens at a time as layer 1
 // finishes them.  They replace layer 1's in `pre`: layer 1 has consumed a token's before it hands the
 // token on.  A thread keeps its gate row of W_ih in registers, the tokens are the rows of a matrix
 // product of few rows (blocks of 4: a 16-row product took 3.4 us a chunk and held layer 2 up, 5 us
@@ -511,7 +517,8 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
                                               float *__restrict__ pre, const int *arrived, int *done, RecurrenceLds<C> &lds)
 {
     constexpr int kPitch = RecurrenceLds<C>::kInPitch;
-    static_assert(kSteps == 8 && kSteps * C / 4 <= 4 * C, "two blocks of four tokens, one 16-byte load per thread and chunk");
+    constexpr int kSteps = kChunk<C>, kBlocks = kSteps / 4;
+    static_assert(kSteps % 4 == 0 && kSteps * C / 4 <= 4 * C, "blocks of four tokens, one 16-byte load per thread and chunk");
     const int tid = threadIdx.x, lane = tid & 63;
     float w[C];                                                // row tid
 #pragma unroll
@@ -533,9 +540,9 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
             *reinterpret_cast<i32x4 *>(in + (tid / (C / 4)) * kPitch + (tid % (C / 4)) * 4) = v;
         }
         lds_barrier();
-        f32x4 even[2], odd[2];
+        f32x4 even[kBlocks], odd[kBlocks];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int q = 0; q < kBlocks; ++q) {
             even[q] = f32x4{bias, bias, bias, bias};
             odd[q] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -543,10 +550,10 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
 #pragma unroll
         for (int k = 0; k < C / 16; ++k)
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
+            for (int q = 0; q < kBlocks; ++q)
                 mfma_rows(ip[q * 4 * kPitch + k * 16], w + k * 16, even[q], odd[q], std::make_integer_sequence<int, 16>());
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
+        for (int q = 0; q < kBlocks; ++q)
 #pragma unroll
             for (int i = 0; i < 4; ++i)                        // past the end: dropped
                 store_f32<kAgent>(pre_rsrc, ((c * kSteps + q * 4 + i) * 4 * C + tid) * 4, even[q][i] + odd[q][i]);
@@ -558,7 +565,7 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
 
 // Both LSTM layers of every sequence in one launch of 3 workgroups per sequence: layer 1, the gate
 // pre-activations between the layers, layer 2; the latter two work behind layer 1, chunk by chunk,
-// so that a call takes T plus about 30 steps instead of 2T.  A workgroup takes its role by ticket:
+// so that a call takes T plus about 20 steps instead of 2T.  A workgroup takes its role by ticket:
 // first all of layer 1, then all in between, then all of layer 2.  Tickets are drawn by workgroups
 // that run, so whatever a workgroup waits for is done by a workgroup that already runs and waits, if
 // at all, for a lower ticket only; layer 1 waits for nobody.  Hence every wait ends, whatever the
