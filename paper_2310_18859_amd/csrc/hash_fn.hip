@@ -8,14 +8,14 @@
 // the residual adds the token's own compressed embedding; alpha = SoftMax probability of the
 // expert within its layer's head; the k largest are kept, ties to the lower expert id.
 //
-// All arithmetic is fp32 (bf16 inputs would move the predicted probabilities by more than the parity
+// All values and sums are fp32 (rounded to bf16 they would move the predicted probabilities by more than the parity
 // bound).  Five launches per call:
 //   hash_dense      c0 = x W_in^T + b, and again for layer 1's gate pre-activations
 //   hash_recurrence both LSTM layers at once, layer 2 a few steps behind layer 1
 //   hash_attention  scores, SparseMax, weighted sum and residual, for blocks of 16 queries
 //   hash_heads      logits, SoftMax and the k best, for blocks of tokens and a MoE layer each
 // The contractions run on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32, twice the rate of
-// scalar-per-lane fp32 multiply-adds); with the weights as the first operand a lane ends up with
+// scalar-per-lane fp32 multiply-adds), that of the bf16 embeddings on the bf16 one (hash_dense); with the weights as the first operand a lane ends up with
 // four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
 // It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
@@ -176,13 +176,32 @@ struct TileRow<__bf16> {
     static constexpr int kBytes = 64, kRowsPerLoad = 16;
     static __device__ __forceinline__ int row(int lane) { return lane >> 2; }
     static __device__ __forceinline__ int piece(int lane, int row) { return (lane & 3) ^ ((row >> 1) & 3); }
-    static __device__ __forceinline__ void read(const char *tile, int row, int g, float (&v)[8])
+    static __device__ __forceinline__ void read(const char *tile, int row, int g, bf16x8 &v)
     {
-        const bf16x8 q = *reinterpret_cast<const bf16x8 *>(tile + row * kBytes + ((g ^ ((row >> 1) & 3)) * 16));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (float)q[e];
+        v = *reinterpret_cast<const bf16x8 *>(tile + row * kBytes + ((g ^ ((row >> 1) & 3)) * 16));
     }
 };
+// v = hi + mid + lo exactly (bf16 has 8 of the 24 bits; an infinite v has lo = NaN).
+__device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &hi, bf16x8 &mid, bf16x8 &lo)
+{
+    unsigned int h[8], m[8], l[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        h[e] = __builtin_bit_cast(unsigned int, v[e]);
+        const float rest = v[e] - __builtin_bit_cast(float, h[e] & 0xffff0000u);
+        m[e] = __builtin_bit_cast(unsigned int, rest);
+        l[e] = __builtin_bit_cast(unsigned int, rest - __builtin_bit_cast(float, m[e] & 0xffff0000u));
+    }
+    auto upper = [](const unsigned int (&w)[8]) {              // of every word the upper half
+        i32x4 p;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = (int)__builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x07060302u);
+        return __builtin_bit_cast(bf16x8, p);
+    };
+    hi = upper(h);
+    mid = upper(m);
+    lo = upper(l);
+}
 // A piece whose address is a multiple of its values' size only.
 __device__ __forceinline__ void copy_piece(const float *p, char *dst)
 {
@@ -246,7 +265,12 @@ __device__ __forceinline__ void tiles_arrived()
 //    (128 tokens: 33 us when 8 workgroups of 16 tokens read all weights each): one tile per wavefront
 //    and the long sum over d_model in four parts, so that the operands of a wavefront are in flight at
 //    once and the weights are spread over 64 workgroups.
-//  * Large ones by the matrix units: 2 x 2 tiles per wavefront.
+//  * Large ones by the matrix units: 4 or 2 x 2 tiles per wavefront.
+// Embeddings are bf16, so their product with fp32 weights goes through the bf16 matrix instruction, of 16 times the rate:
+// a weight is the sum of three bf16 values, exactly, every product is exact, and the sums are fp32 as before.  8192 tokens
+// of 768: 64 x 128 tokens 162.0 -> 152.1 us a call (1 x 4 tiles, so that a weight is split once per workgroup), 8 x 333
+// 254.4 -> 249.5, 32 x 200 at C = 64 135.3 -> 125.4.  alpha against 64 bits over eight batches of 2060 to 8192 tokens, d of
+// 256 to 2056 (2-norm, relative): 0.44e-6 - 1.07e-6 before, 0.31e-6 - 0.84e-6 this way, smaller in each.
 // Also clears the counters of the recurrence behind it.
 template <int TU, int TT, int WU, int WT, int KS, int G, int NB, typename IN, bool DIRECT>
 __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, const float *__restrict__ w,
@@ -256,6 +280,7 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
 {
     static_assert(WU * WT * KS == 4 && (KS == 1 || (KS == 4 && TU * TT == 1)), "wavefronts of a workgroup");
     constexpr int kShare = KS == 1 ? 4 : 1;
+    constexpr bool kSplit = std::is_same<IN, __bf16>::value;   // the weights, into three bf16 parts
     constexpr int WR = WU * TU * 16, XR = WT * TT * 16;        // rows staged together
     constexpr int kW = WR * TileRow<float>::kBytes, kStep = kW + XR * TileRow<IN>::kBytes, kStage = G * kStep;
     typedef TileLoader<float, WR, kShare, DIRECT> LoadW;
@@ -291,7 +316,8 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
             issue(s + (NB - 1) * G, slot == 0 ? NB - 1 : slot - 1);
             const char *tile = mine + slot * kStage;
             slot = slot + 1 == NB ? 0 : slot + 1;
-            float a[G][TU][8], b[G][TT][8];
+            float a[G][TU][8];
+            typename std::conditional<kSplit, bf16x8, float[8]>::type b[G][TT];
 #pragma unroll
             for (int h = 0; h < G; ++h) {
 #pragma unroll
@@ -307,14 +333,28 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
 #pragma unroll
                         for (int e = 0; e < 8; ++e) a[h][i][e] = (s + h) * 32 + 8 * g < end ? a[h][i][e] : 0.f;
 #pragma unroll
-            for (int h = 0; h < G; ++h)
+            for (int h = 0; h < G; ++h) {
+                if constexpr (kSplit) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
+                    for (int i = 0; i < TU; ++i) {
+                        bf16x8 part[3];
+                        split3(a[h][i], part[2], part[1], part[0]);
 #pragma unroll
-                    for (int m = 0; m < TT; ++m)
+                        for (int q = 0; q < 3; ++q)
 #pragma unroll
-                        for (int i = 0; i < TU; ++i)
-                            acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][i][e], b[h][m][e], acc[i][m], 0, 0, 0);
+                            for (int m = 0; m < TT; ++m)
+                                acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part[q], b[h][m], acc[i][m], 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+#pragma unroll
+                        for (int m = 0; m < TT; ++m)
+#pragma unroll
+                            for (int i = 0; i < TU; ++i)
+                                acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][i][e], b[h][m][e], acc[i][m], 0, 0, 0);
+                }
+            }
         }
         tiles_arrived<0, DIRECT>();                            // the last loads still write LDS
     }
@@ -882,7 +922,7 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
     // boundary (rows are multiples of 16 bytes).  Elsewhere the smallest tiles go through registers.
     const bool direct = ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(x)) & 15u) == 0;
     if (!direct) dense(hash_dense<1, 1, 1, 1, 4, 2, 4, __bf16, false>, 16, 16, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
-    else if (N >= 6144) dense(hash_dense<2, 2, 2, 2, 1, 2, 4, __bf16, true>, 64, 64, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
+    else if (N >= 6144) dense(hash_dense<1, 4, 4, 1, 1, 2, 4, __bf16, true>, 64, 64, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
     else if (N >= 2048) dense(hash_dense<1, 2, 2, 2, 1, 2, 4, __bf16, true>, 64, 32, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
     else dense(hash_dense<1, 1, 1, 1, 4, 2, 4, __bf16, true>, 16, 16, xb, w_in, b_in, nullptr, d, C, c0, n_counters);
     auto gates = [&](const float *in, const float *w_ih, const float *b_ih, const float *b_hh) {
