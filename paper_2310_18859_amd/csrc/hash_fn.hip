@@ -9,8 +9,8 @@
 // expert within its layer's head; the k largest are kept, ties to the lower expert id.
 //
 // All values and sums are fp32 (rounded to bf16 they would move the predicted probabilities by more than the parity
-// bound).  Five launches per call:
-//   hash_dense      c0 = x W_in^T + b, and again for layer 1's gate pre-activations
+// bound).  Four or five launches per call:
+//   hash_dense      c0 = x W_in^T + b, and again for layer 1's gate pre-activations (or in the next launch)
 //   hash_recurrence both LSTM layers at once, layer 2 a few steps behind layer 1
 //   hash_attention  scores, SparseMax, weighted sum and residual, for blocks of 16 queries
 //   hash_heads      logits, SoftMax and the k best, for blocks of tokens and a MoE layer each
@@ -20,8 +20,8 @@
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
 // It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
 // four clocks apiece (0.43 us at 2.4 GHz), 42 other vector instructions and 20 that are none.  Measured against one launch per layer and
-// stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 116 us, 8 of 333 tokens
-// (top-3) 1059 -> 261 us, 64 of 128 tokens 609 -> 169 us.
+// stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 107 us, 8 of 333 tokens
+// (top-3) 1059 -> 245 us, 64 of 128 tokens 609 -> 140 us.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -139,10 +139,10 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // Counters of one call, in the part of the workspace that the attention writes later: the ticket the
-// recurrence's workgroups draw their role from, then per sequence a 64-byte line for layer 1's and one
-// for layer 2's input progress (chunks times wavefronts, and chunks).  Cleared by the first launch.
+// recurrence's workgroups draw their role from, then per sequence a 64-byte line each for the progress of layer 1's
+// states (chunks times wavefronts), of layer 2's and of layer 1's inputs (chunks).  Cleared by the first launch.
 constexpr int kLine = 16;
-__host__ __device__ constexpr size_t counter_words(size_t n_seq) { return kLine * (1 + 2 * n_seq); }
+__host__ __device__ constexpr size_t counter_words(size_t n_seq) { return kLine * (1 + 3 * n_seq); }
 
 // ---- operand tiles in LDS -----------------------------------------------------------------------
 // Rows of 32 values, loaded straight into LDS with whole lines per request.  (Fetched as matrix operands,
@@ -461,7 +461,7 @@ struct RecurrenceLds {
     float h[2 * kChunk<C>][kRow];                               // the state after each step of two chunks
     float pre[kChunk<C>][4 * C];                                // gate pre-activations of a chunk; a thread reads what it wrote
     static constexpr int kInPitch = C + 16;
-    float in[2][kChunk<C> * kInPitch];                           // layer 2's inputs of a chunk
+    float in[2][8 * kInPitch];                             // inputs of up to eight steps, of which gate pre-activations are made
     int ticket;
 };
 
@@ -582,38 +582,46 @@ __device__ __forceinline__ void mfma_rows(float a, const float *b, f32x4 &even, 
     ((((J & 1) ? odd : even) = __builtin_amdgcn_mfma_f32_4x4x1f32(a, b[J], (J & 1) ? odd : even, 4, J, 0)), ...);
 }
 
-// Layer 2's gate pre-activations for one sequence, a chunk of tokens at a time as layer 1
-// finishes them.  They replace layer 1's in `pre`: layer 1 has consumed a token's before it hands the
+// A layer's gate pre-activations for one sequence, some tokens at a time.  FIRST: layer 1's, of the compressed embeddings,
+// which are all there: eight tokens at a time, ahead of layer 1.  Else layer 2's, a chunk at a time as layer 1
+// finishes them; they replace layer 1's in `pre`: layer 1 has consumed a token's before it hands the
 // token on.  A thread keeps its gate row of W_ih in registers, the tokens are the rows of a matrix
 // product of few rows (blocks of 4: a 16-row product took 3.4 us a chunk and held layer 2 up, 5 us
 // between chunks), and the results leave in whole lines.
-template <int C>
-__device__ __forceinline__ void gates_between(const float *__restrict__ h1, const float *__restrict__ w_ih,
-                                              const float *__restrict__ b_ih, const float *__restrict__ b_hh, int T,
-                                              float *__restrict__ pre, const int *arrived, int *done, RecurrenceLds<C> &lds)
+template <int C, bool FIRST>
+__device__ __forceinline__ void gates_ahead(const float *__restrict__ x, const float *__restrict__ w_ih,
+                                            const float *__restrict__ b_ih, const float *__restrict__ b_hh, int T,
+                                            float *__restrict__ pre, const int *arrived, int *done, RecurrenceLds<C> &lds)
 {
     constexpr int kPitch = RecurrenceLds<C>::kInPitch;
-    constexpr int kSteps = kChunk<C>, kBlocks = kSteps / 4;
-    static_assert(kSteps % 4 == 0 && kSteps * C / 4 <= 4 * C, "blocks of four tokens, one 16-byte load per thread and chunk");
+    constexpr int kTokens = FIRST ? 8 : kChunk<C>, kBlocks = kTokens / 4, kPolicy = FIRST ? 0 : kAgent;
+    static_assert(kTokens % 4 == 0 && kTokens <= 8 && kTokens % kChunk<C> == 0 && kTokens * C / 4 <= 4 * C, "whole blocks and chunks");
     const int tid = threadIdx.x, lane = tid & 63;
+    const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(x, (uint32_t)T * C * 4);
+    const __amdgpu_buffer_rsrc_t pre_rsrc = make_rsrc(pre, (uint32_t)T * 4 * C * 4);
+    auto load = [&](int c) {                                   // 16 bytes per thread; past the end: zeros
+        return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, (c * kTokens * C + tid * 4) * 4, 0, kPolicy));
+    };
+    const bool loads = tid < kTokens * C / 4;
+    i32x4 v = {};
+    if (FIRST && loads) v = load(0);
     float w[C];                                                // row tid
 #pragma unroll
     for (int k = 0; k < C; k += 4) {
-        const f32x4 v = load4_param(w_ih + (size_t)tid * C + k);
+        const f32x4 q = load4_param(w_ih + (size_t)tid * C + k);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[k + e] = v[e];
+        for (int e = 0; e < 4; ++e) w[k + e] = q[e];
     }
     const float bias = b_ih[tid] + b_hh[tid];
-    const __amdgpu_buffer_rsrc_t h_rsrc = make_rsrc(h1, (uint32_t)T * C * 4);
-    const __amdgpu_buffer_rsrc_t pre_rsrc = make_rsrc(pre, (uint32_t)T * 4 * C * 4);
-    const int chunks = (T + kSteps - 1) / kSteps;
+    const int rounds = (T + kTokens - 1) / kTokens;
     int seen = 0;
-    for (int c = 0; c < chunks; ++c) {
-        wait_for((c + 1) * (C / 16), seen, [&] { return __builtin_amdgcn_readfirstlane(peek(arrived)); });
+    for (int c = 0; c < rounds; ++c) {
+        if (!FIRST) wait_for((c + 1) * (C / 16), seen, [&] { return __builtin_amdgcn_readfirstlane(peek(arrived)); });
         float *in = lds.in[c & 1];
-        if (tid < kSteps * C / 4) {                            // past the end: zeros
-            const i32x4 v = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(h_rsrc, (c * kSteps * C + tid * 4) * 4, 0, kAgent));
+        if (loads) {
+            if (!FIRST) v = load(c);
             *reinterpret_cast<i32x4 *>(in + (tid / (C / 4)) * kPitch + (tid % (C / 4)) * 4) = v;
+            if (FIRST) v = load(c + 1);
         }
         lds_barrier();
         f32x4 even[kBlocks], odd[kBlocks];
@@ -632,23 +640,27 @@ __device__ __forceinline__ void gates_between(const float *__restrict__ h1, cons
         for (int q = 0; q < kBlocks; ++q)
 #pragma unroll
             for (int i = 0; i < 4; ++i)                        // past the end: dropped
-                store_f32<kAgent>(pre_rsrc, ((c * kSteps + q * 4 + i) * 4 * C + tid) * 4, even[q][i] + odd[q][i]);
+                store_f32<kAgent>(pre_rsrc, ((c * kTokens + q * 4 + i) * 4 * C + tid) * 4, even[q][i] + odd[q][i]);
         wait_memory<0>();
         lds_barrier();
-        if (tid == 0) publish(done, c + 1);
+        if (tid == 0) publish(done, (c + 1) * (kTokens / kChunk<C>));
     }
 }
 
-// Both LSTM layers of every sequence in one launch of 3 workgroups per sequence: layer 1, the gate
-// pre-activations between the layers, layer 2; the latter two work behind layer 1, chunk by chunk,
-// so that a call takes T plus about 20 steps instead of 2T.  A workgroup takes its role by ticket:
-// first all of layer 1, then all in between, then all of layer 2.  Tickets are drawn by workgroups
+// Both LSTM layers of every sequence in one launch of 3 or 4 workgroups per sequence: the gate pre-activations of
+// layer 1 (GATES; else a launch before has made them), layer 1, the gate pre-activations between the layers, layer 2; each
+// works behind the one before, chunk by chunk, so that a call takes T plus about 20 steps instead of 2T.  A workgroup takes
+// its role by ticket: first all of the first role, and so on.  Tickets are drawn by workgroups
 // that run, so whatever a workgroup waits for is done by a workgroup that already runs and waits, if
-// at all, for a lower ticket only; layer 1 waits for nobody.  Hence every wait ends, whatever the
+// at all, for a lower ticket only; the first role waits for nobody.  Hence every wait ends, whatever the
 // order in which workgroups are started and whatever else runs on the GPU.  (Counters that another call
 // writes over, against the rules, end them too: see handover.h.)
-template <int C>
-__global__ __launch_bounds__(4 * C) void hash_recurrence(float *pre, const float *__restrict__ w_hh1,
+// GATES saves a launch over all tokens, but layer 1 then waits for a compute unit that has to load its 256 KiB of weights
+// first (some 5 us); see run() for where it pays.
+template <int C, bool GATES>
+__global__ __launch_bounds__(4 * C) void hash_recurrence(float *pre, const float *__restrict__ c0, const float *__restrict__ w_ih1,
+                                                         const float *__restrict__ b_ih1, const float *__restrict__ b_hh1,
+                                                         const float *__restrict__ w_hh1,
                                                          const float *__restrict__ w_ih2, const float *__restrict__ w_hh2,
                                                          const float *__restrict__ b_ih2, const float *__restrict__ b_hh2,
                                                          int n_seq, int T, float *h1, float *h2, int *counters)
@@ -657,13 +669,15 @@ __global__ __launch_bounds__(4 * C) void hash_recurrence(float *pre, const float
     if (threadIdx.x == 0) lds.ticket = __hip_atomic_fetch_add(counters, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(lds.ticket);
-    const Role of = role_of(ticket, n_seq);
+    const bool gates_first = GATES && (unsigned)ticket < (unsigned)n_seq;
+    const Role of = gates_first ? Role{-1, ticket} : role_of(GATES ? ticket - n_seq : ticket, n_seq);
     const int role = of.what, seq = of.seq;
     float *p = pre + (size_t)seq * T * 4 * C, *a = h1 + (size_t)seq * T * C, *b = h2 + (size_t)seq * T * C;
-    int *layer1_done = counters + kLine * (1 + 2 * seq), *gates_done = layer1_done + kLine;
-    if (role == 0) lstm_layer<C, false, true>(p, w_hh1, T, a, nullptr, layer1_done, lds);
-    else if (role == 1) gates_between<C>(a, w_ih2, b_ih2, b_hh2, T, p, layer1_done, gates_done, lds);
-    else lstm_layer<C, true, false>(p, w_hh2, T, b, gates_done, nullptr, lds);
+    int *layer1_done = counters + kLine * (1 + 3 * seq), *gates2_done = layer1_done + kLine, *gates1_done = gates2_done + kLine;
+    if (GATES && role < 0) gates_ahead<C, true>(c0 + (size_t)seq * T * C, w_ih1, b_ih1, b_hh1, T, p, nullptr, gates1_done, lds);
+    else if (role == 0) lstm_layer<C, GATES, true>(p, w_hh1, T, a, gates1_done, layer1_done, lds);
+    else if (role == 1) gates_ahead<C, false>(a, w_ih2, b_ih2, b_hh2, T, p, layer1_done, gates2_done, lds);
+    else lstm_layer<C, true, false>(p, w_hh2, T, b, gates2_done, nullptr, lds);
 }
 
 // One layer alone, a workgroup per sequence: for batches of so many sequences that three workgroups
@@ -936,9 +950,14 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
 }
 
 // ---- one call -----------------------------------------------------------------------------------
-// Sequences whose layers run side by side: three workgroups each, one per compute unit (a workgroup of
-// the recurrence fills the registers of its compute unit).
+// Sequences whose layers run side by side: three workgroups each, or four with the gate pre-activations of layer 1 among
+// them, one per compute unit (a workgroup of the recurrence fills the registers of its compute unit).
 constexpr int kSideBySide = 256 / 3;
+// Gate pre-activations of layer 1 in the recurrence's launch, us a call, before -> with: C = 128 60 x 40 tokens 69.2 -> 67.1,
+// 48 x 128 141.4 -> 137.5, 64 x 128 145.6 -> 139.6, 64 x 100 126.8 -> 121.2, 16 x 192 162.6 -> 162.2; C = 64 60 x 40 50.5 ->
+// 48.0, 48 x 128 94.1 -> 91.3, 16 x 512 241.1 -> 241.6.  With few sequences or tokens the launch in front is short:
+// 1 x 128 106.9 -> 110.3, 2 x 512 339.8 -> 345.0, 8 x 333 243.9 -> 244.3, 12 x 333 at C = 64 160.0 -> 160.7.
+inline bool gates_in_recurrence(int n_seq, int tokens) { return n_seq >= 16 && n_seq <= 256 / 4 && tokens >= 2048; }
 constexpr int kMaxScoreBytes = 144 * 1024;                     // LDS for an attention block's scores
 
 template <int C>
@@ -954,7 +973,7 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
     // workspace
     float *c0 = ws, *pre = c0 + (size_t)N * C, *h1 = pre + (size_t)N * 4 * C, *h2 = h1 + (size_t)N * C,
           *r = h2 + (size_t)N * C;
-    int *counters = reinterpret_cast<int *>(r);                // N*C words, of which a sequence needs 2*kLine: C >= 4*kLine
+    int *counters = reinterpret_cast<int *>(r);                // N*C words, of which a sequence needs 3*kLine and the ticket kLine
     static_assert(C >= 4 * kLine, "counters fit");
     const __bf16 *xb = (const __bf16 *)x;
     // Tiles: as large as leave every compute unit (nearly) one workgroup.
@@ -976,10 +995,16 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
         else if (N >= 2048) dense(hash_dense<2, 2, 2, 2, 1, 2, 2, float, true>, 64, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
         else dense(hash_dense<1, 1, 4, 1, 1, 2, 3, float, true>, 16, 64, in, w_ih, b_ih, b_hh, C, 4 * C, pre, 0);
     };
-    gates(c0, w_ih1, b_ih1, b_hh1);
-    if (n_seq <= kSideBySide) {
-        hipLaunchKernelGGL(hash_recurrence<C>, dim3(3 * n_seq), dim3(4 * C), 0, st, pre, w_hh1, w_ih2, w_hh2, b_ih2, b_hh2,
-                           n_seq, T, h1, h2, counters);
+    auto recurrence = [&](auto kernel, int roles) {
+        hipLaunchKernelGGL(kernel, dim3(roles * n_seq), dim3(4 * C), 0, st, pre, c0, w_ih1, b_ih1, b_hh1, w_hh1, w_ih2, w_hh2, b_ih2,
+                           b_hh2, n_seq, T, h1, h2, counters);
+    };
+    const bool gates_too = gates_in_recurrence(n_seq, N);
+    if (!gates_too) gates(c0, w_ih1, b_ih1, b_hh1);
+    if (gates_too) {
+        recurrence(hash_recurrence<C, true>, 4);
+    } else if (n_seq <= kSideBySide) {
+        recurrence(hash_recurrence<C, false>, 3);
     } else {
         hipLaunchKernelGGL(hash_lstm<C>, dim3(n_seq), dim3(4 * C), 0, st, pre, w_hh1, T, h1);
         gates(h1, w_ih2, b_ih2, b_hh2);
