@@ -18,8 +18,8 @@
 // scalar-per-lane fp32 multiply-adds), or on the bf16 one with the values in exact parts (hash_dense, Parts); with the weights as the first operand a lane ends up with
 // four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
-// It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
-// four clocks apiece (0.43 us at 2.4 GHz), 42 other vector instructions and 20 that are none.  Measured against one launch per layer and
+// It is what bounds a call: 0.56 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
+// four clocks apiece (0.43 us at 2.4 GHz), 38 other vector instructions and 20 that are none.  Measured against one launch per layer and
 // stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 107 us, 8 of 333 tokens
 // (top-3) 1059 -> 245 us, 64 of 128 tokens 609 -> 140 us.
 #include <hip/hip_runtime.h>
@@ -472,9 +472,9 @@ struct RecurrenceLds {
 // quarters 0.65 us).  Slot j of lane l of the eight is row j ^ l, so that seven adds of permuted lanes
 // leave row l's sum in lane l; thread 4u+s then has gate s of unit u, the four gates meet in quad permutes
 // too, and a step has one barrier and no global access: pre-activations come and states go a chunk of
-// steps at a time.  What is left of a step at C = 128 is the issue of 128 multiply-adds, 42 other vector
+// steps at a time.  What is left of a step at C = 128 is the issue of 128 multiply-adds, 38 other vector
 // instructions and 20 that are none (8 s_nop, 6 LDS accesses, 5 waits, the barrier) per wavefront, two
-// wavefronts per SIMD, nearly back to back: each vector instruction less is 8 clocks of about 1350 a step.
+// wavefronts per SIMD, nearly back to back: each vector instruction less is 8 clocks of about 1330 a step.
 // Hence whole chunks are written out (addresses become offsets; the kernel's code doubles to 27 KB), lane 0
 // of a quad alone carries the cell's state, and sums of permuted lanes are one instruction each, with the
 // same bits.  One taken back at a time, us a call, and all three in front (1 x 128, 8 x 333, 96 x 85 tokens):
