@@ -181,7 +181,7 @@ struct TileRow<__bf16> {
         v = *reinterpret_cast<const bf16x8 *>(tile + row * kBytes + ((g ^ ((row >> 1) & 3)) * 16));
     }
 };
-// v = hi + mid + lo exactly (bf16 has 8 of the 24 bits; an infinite v has lo = NaN).
+// v = hi + mid + lo exactly (bf16 has 8 of the 24 bits).  An infinite v has a part that is NaN, see any_overflow.
 __device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &hi, bf16x8 &mid, bf16x8 &lo)
 {
     unsigned int h[8], m[8], l[8];
@@ -225,6 +225,28 @@ __device__ __forceinline__ f32x4 mfma_parts(const Parts &a, const Parts &b, f32x
     d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.mid, b.hi, d, 0, 0, 0);
     d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.hi, b.mid, d, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.hi, b.hi, d, 0, 0, 0);
+}
+// Infinities do not go through parts (they leave NaN behind, and parts that are 0 make NaN of an infinite factor): a sum
+// that comes out infinite or NaN is made again on the fp32 instruction, and that one counts.  One that comes out
+// finite had finite parts only.
+__device__ __forceinline__ bool overflowed(float v) { return !__builtin_isfinite(v); }
+template <int TU, int TT>
+__device__ __forceinline__ bool any_overflow(const f32x4 (&d)[TU][TT])    // in any lane
+{
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < TU; ++i)
+#pragma unroll
+        for (int m = 0; m < TT; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) any |= overflowed(d[i][m][e]);
+    return __any(any);
+}
+__device__ __forceinline__ f32x4 where_overflowed(f32x4 d, const f32x4 &other)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d[e] = overflowed(d[e]) ? other[e] : d[e];
+    return d;
 }
 // A piece whose address is a multiple of its values' size only.
 __device__ __forceinline__ void copy_piece(const float *p, char *dst)
@@ -305,6 +327,7 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
     static_assert(WU * WT * KS == 4 && (KS == 1 || (KS == 4 && TU * TT == 1)), "wavefronts of a workgroup");
     constexpr int kShare = KS == 1 ? 4 : 1;
     constexpr bool kSplit = std::is_same<IN, __bf16>::value;   // the weights, into three bf16 parts
+    constexpr bool kParts = kSplit || TU * TT > 1;             // ... or both operands
     constexpr int WR = WU * TU * 16, XR = WT * TT * 16;        // rows staged together
     constexpr int kW = WR * TileRow<float>::kBytes, kStep = kW + XR * TileRow<IN>::kBytes, kStage = G * kStep;
     typedef TileLoader<float, WR, kShare, DIRECT> LoadW;
@@ -369,7 +392,7 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
                             for (int m = 0; m < TT; ++m)
                                 acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part[q], b[h][m], acc[i][m], 0, 0, 0);
                     }
-                } else if constexpr (TU * TT > 1) {
+                } else if constexpr (kParts) {
                     Parts pa[TU], pb[TT];
 #pragma unroll
                     for (int i = 0; i < TU; ++i) pa[i] = parts_of(a[h][i]);
@@ -391,6 +414,21 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
             }
         }
         tiles_arrived<0, DIRECT>();                            // the last loads still write LDS
+        if (kParts && any_overflow(acc)) {
+#pragma unroll 1
+            for (int t = 0; t < TU * TT; ++t) {
+                const int i = t / TT, m = t % TT;
+                const float *row = w + (size_t)(u0 + (wu * TU + i) * 16 + col) * k;
+                const IN *token = in + (size_t)min(n0 + (wt * TT + m) * 16 + col, n_tokens - 1) * k;
+                f32x4 again = {};
+#pragma unroll 1
+                for (int at = first * 32; at < end; at += 4)   // k is a multiple of 4
+                    again = __builtin_amdgcn_mfma_f32_16x16x4f32(row[at + g], (float)token[at + g], again, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < TU * TT; ++j)
+                    if (j == t) acc[j / TT][j % TT] = where_overflowed(acc[j / TT][j % TT], again);
+            }
+        }
     }
     if (KS > 1) {                                              // the parts of the sum meet in the first wavefront
         __shared__ f32x4 parts[KS][64];
@@ -891,6 +929,25 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
         tiles_arrived<0, DIRECT>();
         __builtin_amdgcn_s_barrier();
         multiply(3);
+    }
+    if (TT > 1 && any_overflow(acc)) {
+#pragma unroll 1
+        for (int t = 0; t < kMine * TT; ++t) {
+            const int i = t / TT, m = t % TT;
+            if (NT < 4 && i * 4 + wv >= NT) continue;
+            f32x4 again = {};
+#pragma unroll 1
+            for (int s = 0; s < kSteps32; ++s) {
+                float a[8], b[8];
+                TileRow<float>::read(tiles + s * kStage, (i * 4 + wv) * 16 + col, g, a);
+                TileRow<float>::read(tiles + s * kStage + kW, m * 16 + col, g, b);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) again = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], again, 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < kMine * TT; ++j)
+                if (j == t) acc[j / TT][j % TT] = where_overflowed(acc[j / TT][j % TT], again);
+        }
     }
     lds_barrier();                                             // every operand has been read
 #pragma unroll

@@ -1,12 +1,12 @@
 """The hash function's products of values in bf16 parts, at the edges of what takes which tiles (2048 and 6144 tokens, rows and
 columns that fill no tile), against the float64 oracle - near enough that a lost third part of a value shows: the oracle with
-every weight cut to its first two parts is several times as far off as the bound."""
+every weight cut to its first two parts is several times as far off as the bound.  Then infinities."""
 import numpy as np
 import pytest
 
 import paper_2310_18859_amd as sm
 from oracle import hash_fn
-from test_gpu_hash import make_params, run_hash
+from test_gpu_hash import ALPHA_TOL, make_params, run_hash
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 
 pytestmark = pytest.mark.gpu
@@ -56,3 +56,40 @@ def test_parts_against_oracle(d, C, L, E, k, n_seq, T):
     lost = float(np.linalg.norm(oracle_alpha(two, x, cfg, ids) - want) / norm)
     print(f"relative error {err:.2e}, without the third parts {lost:.2e}", flush=True)
     assert err <= BOUND and lost > 3 * BOUND
+
+
+@pytest.mark.parametrize("C,n_seq,T", [(128, 1, 40), (128, 16, 128), (64, 70, 31), (128, 90, 69)])
+@pytest.mark.parametrize("where", ["w_in", "w_ih1", "w_ih2", "w_out", "x"])
+def test_infinities(where, C, n_seq, T):
+    """An infinite weight or embedding gives what sums of 32 bits give: saturated gates, an infinite logit - not NaN."""
+    rng = np.random.default_rng(T)
+    d, L, E, k, inf = 64, 2, 16, 2, np.float32(np.inf)
+    cfg = sm.SidaHashConfig(d, C, L, E, k, T)
+    params = make_params(rng, d, C, L, E)
+    x_bits = f32_to_bf16_bits(rng.standard_normal((n_seq * T, d)).astype(np.float32))
+    if where == "w_in":
+        params["w_in"][7, 9] = -inf
+    elif where == "w_out":
+        params["w_out"][[3, E + 5], 20] = inf, -inf
+    elif where == "x":
+        # every unit of this token's compressed embedding is infinite, by weights with parts that are 0, and every gate too
+        x_bits[T // 2, 9] = 0x7f80
+        params["w_in"][:, 9] = 0.25 + np.arange(C) % 3
+        params["w_ih1"] = np.abs(params["w_ih1"]) * rng.choice([-1, 1], (4 * C, 1)).astype(np.float32)
+    else:
+        params[where][rng.permutation(4 * C)[:30], rng.integers(0, C, 30)] = inf * rng.choice([-1, 1], 30).astype(np.float32)
+    x = bf16_bits_to_f32(x_bits).reshape(n_seq, T, d)
+    ids, alpha = run_hash(cfg, params, x_bits, n_seq, T)
+    with np.errstate(all="ignore"):
+        want = oracle_alpha(params, x, cfg, ids)
+    print(f"{np.isnan(want).mean():.4f} of the probabilities are no numbers", flush=True)
+    assert np.array_equal(np.isnan(alpha), np.isnan(want)) and np.isnan(want).all() == (where == "w_in")
+    np.testing.assert_allclose(alpha, want, atol=ALPHA_TOL)
+    if where == "w_in":                                                    # every token's unit 7 is infinite
+        assert np.isnan(alpha).all()
+        sign = np.where(x.reshape(-1, d)[:, 9] > 0, -1, 1)
+        first = np.argmax(params["w_out"][:, 7].reshape(L, 1, E) * sign[None, :, None] > 0, axis=2)
+        assert np.array_equal(ids[:, :, 0], first)
+    if where == "w_out":                                                   # the infinite logit is the largest
+        for l, e in ((0, 3), (1, 5)):
+            assert (ids[l, np.isnan(want[l, :, 0]), 0] == e).all()
