@@ -47,6 +47,7 @@ std::mutex g_scratch_mu;
 float *g_scratch_ptr[kMaxDevices] = {};
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
@@ -181,33 +182,36 @@ struct TileRow<__bf16> {
         v = *reinterpret_cast<const bf16x8 *>(tile + row * kBytes + ((g ^ ((row >> 1) & 3)) * 16));
     }
 };
-// v = hi + mid + lo exactly (bf16 has 8 of the 24 bits).  An infinite v has a part that is NaN, see any_overflow.
+// v = hi + mid + lo, exactly from 2^-109 on (bf16 has 8 of the 24 bits and ends at 2^-133).  hi and mid are rounded to
+// nearest, so mid is at most 2^-8 and lo at most 2^-17 of v's power of two, of either sign.  (Cut, at the same number of
+// instructions, they were up to 2^-7 and 2^-15 and of v's sign.)  An infinite v, or one that rounds to infinity, has a part
+// that is NaN, see any_overflow.
 __device__ __forceinline__ void split3(const float (&v)[8], bf16x8 &hi, bf16x8 &mid, bf16x8 &lo)
 {
-    unsigned int h[8], m[8], l[8];
+    i32x4 h, m, l;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        h[e] = __builtin_bit_cast(unsigned int, v[e]);
-        const float rest = v[e] - __builtin_bit_cast(float, h[e] & 0xffff0000u);
-        m[e] = __builtin_bit_cast(unsigned int, rest);
-        l[e] = __builtin_bit_cast(unsigned int, rest - __builtin_bit_cast(float, m[e] & 0xffff0000u));
+    for (int e = 0; e < 4; ++e) {
+        f32x2 rest{v[2 * e], v[2 * e + 1]};
+        auto take = [&] {                                      // the pair rounded, and what is left of it
+            const unsigned int pair = __builtin_bit_cast(unsigned int, __builtin_convertvector(rest, bf16x2));
+            rest[0] -= __builtin_bit_cast(float, pair << 16);
+            rest[1] -= __builtin_bit_cast(float, pair & 0xffff0000u);
+            return (int)pair;
+        };
+        h[e] = take();
+        m[e] = take();
+        l[e] = take();
     }
-    auto upper = [](const unsigned int (&w)[8]) {              // of every word the upper half
-        i32x4 p;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[e] = (int)__builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x07060302u);
-        return __builtin_bit_cast(bf16x8, p);
-    };
-    hi = upper(h);
-    mid = upper(m);
-    lo = upper(l);
+    hi = __builtin_bit_cast(bf16x8, h);
+    mid = __builtin_bit_cast(bf16x8, m);
+    lo = __builtin_bit_cast(bf16x8, l);
 }
-// The product of 16 x 32 and 32 x 16 fp32 values on the bf16 matrix instruction: of the nine products of their parts the
-// six that are above 2^-24 of the whole, small ones first.  96 clocks instead of 256, and 44 vector instructions to split
-// the values of an operand: worth it where an operand meets two others (2 x 2 tiles of a wavefront; the layers' gate
-// pre-activations and the heads of 2048 tokens and more: 64 x 128 tokens 151.1 -> 146.3 us a call, 8 x 333 247.7 -> 246.7,
-// 96 x 85 190.9 -> 184.2).  The longer sums of the instruction are rounded less often: alpha against 64 bits is nearer by
-// another 10 to 22 % in 14 batches of such sizes (2-norms, relative).
+// The product of 16 x 32 and 32 x 16 fp32 values on the bf16 matrix instruction: of the nine products of their parts all
+// but mid lo, lo mid and lo lo, which are together at most 2^-24 of the whole and of either sign; small ones first.  96
+// clocks instead of 256, and 44 vector instructions to split the values of an operand: worth it where an operand meets two
+// others (2 x 2 tiles of a wavefront; the layers' gate pre-activations and the heads of 2048 tokens and more: 64 x 128
+// tokens 151.1 -> 146.3 us a call, 8 x 333 247.7 -> 246.7, 96 x 85 190.9 -> 184.2).  The longer sums of the instruction are
+// rounded less often: alpha against 64 bits is nearer by another 10 to 22 % in 14 batches of such sizes (2-norms, relative).
 struct Parts {
     bf16x8 hi, mid, lo;
 };

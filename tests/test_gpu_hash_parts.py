@@ -1,6 +1,7 @@
 """The hash function's products of values in bf16 parts, at the edges of what takes which tiles (2048 and 6144 tokens, rows and
 columns that fill no tile), against the float64 oracle - near enough that a lost third part of a value shows: the oracle with
-every weight cut to its first two parts is several times as far off as the bound.  Then infinities."""
+every weight cut to its first two parts is several times as far off as the bound.  Then the bits that a
+product keeps, and infinities."""
 import numpy as np
 import pytest
 
@@ -58,8 +59,47 @@ def test_parts_against_oracle(d, C, L, E, k, n_seq, T):
     assert err <= BOUND and lost > 3 * BOUND
 
 
+def bits_at_the_edges(rng, n):
+    """Floats in [1, 2) whose mantissa ends just below or above where a part of eight bits ends, and random ones."""
+    edge = np.choose(rng.integers(0, 4, n), [1 << 16, 1 << 15, (1 << 16) | (1 << 15), 1 << 22])
+    near = (edge + rng.integers(-300, 301, n)) & 0x7fffff
+    mantissa = np.where(rng.random(n) < 0.75, near, rng.integers(0, 1 << 23, n))
+    return (mantissa.astype(np.uint32) | np.uint32(0x3f800000)).view(np.float32)
+
+
+@pytest.mark.parametrize("n_seq,T", [(16, 128), (70, 31)])
+def test_a_product_keeps_the_bits_of_its_factors(n_seq, T):
+    """Logits that are one product each, less its value rounded to 32 bits: what is left of a product of 2^20 shows units of
+    2^-24 of it.  Three are allowed, one each for the products of parts that are left out, for the sum's rounding and for
+    what the matrix instruction aligns its addends by.  The errors are of either sign (168 of them, root mean square 0.8:
+    their mean is within 0.25 by four of its deviations; with parts cut off it was -0.85 and -1.13, the largest 6.0)."""
+    rng = np.random.default_rng(T)
+    d, C, L, E, k = 64, 128, 24, 8, 8
+    cfg = sm.SidaHashConfig(d, C, L, E, k, T)
+    params = {n: np.zeros(s, np.float32) for n, s in hash_fn.param_shapes(d, C, L, E)}
+    params["w_in"][:, 5] = bits_at_the_edges(rng, C)                       # the state of every token, as it is
+    factor = bits_at_the_edges(rng, L * E) * np.float32(2 ** 20) * rng.choice([-1, 1], L * E).astype(np.float32)
+    unit = rng.integers(0, C, L * E)
+    factor[::E] = 0                                                        # expert 0 of a layer: logit 0
+    params["w_out"][np.arange(L * E), unit] = factor
+    exact = factor.astype(np.float64) * params["w_in"][unit, 5].astype(np.float64)
+    params["b_out"] = -exact.astype(np.float32)
+    x_bits = np.zeros((n_seq * T, d), np.uint16)
+    x_bits[:, 5] = 0x3f80
+    ids, alpha = run_hash(cfg, params, x_bits, n_seq, T)
+    by_expert = np.empty_like(alpha)
+    np.put_along_axis(by_expert, ids.astype(np.int64), alpha, axis=2)
+    logit = np.log(by_expert[:, :, 1:] / by_expert[:, :, :1]).astype(np.float64)
+    want = (exact + params["b_out"]).reshape(L, 1, E)[:, :, 1:]
+    units = (logit - want) / np.abs(exact).reshape(L, 1, E)[:, :, 1:] * 2.0 ** 24
+    units = units[:, 0] * np.sign(exact).reshape(L, E)[:, 1:]              # every token's are the same
+    most, mean = float(np.abs(units).max()), float(units.mean())
+    print(f"units of 2^-24: {units.min():.2f} to {units.max():.2f}, mean {mean:.3f}, rms {np.sqrt((units ** 2).mean()):.3f}", flush=True)
+    assert most <= 3.0 and abs(mean) <= 0.25 and (alpha == alpha[:, :1]).all()
+
+
 @pytest.mark.parametrize("C,n_seq,T", [(128, 1, 40), (128, 16, 128), (64, 70, 31), (128, 90, 69)])
-@pytest.mark.parametrize("where", ["w_in", "w_ih1", "w_ih2", "w_out", "x"])
+@pytest.mark.parametrize("where", ["w_in", "w_ih1", "w_ih2", "w_out", "x", "largest"])
 def test_infinities(where, C, n_seq, T):
     """An infinite weight or embedding gives what sums of 32 bits give: saturated gates, an infinite logit - not NaN."""
     rng = np.random.default_rng(T)
@@ -76,6 +116,8 @@ def test_infinities(where, C, n_seq, T):
         x_bits[T // 2, 9] = 0x7f80
         params["w_in"][:, 9] = 0.25 + np.arange(C) % 3
         params["w_ih1"] = np.abs(params["w_ih1"]) * rng.choice([-1, 1], (4 * C, 1)).astype(np.float32)
+    elif where == "largest":                                               # finite, but its first part is not
+        params["w_ih1"][rng.permutation(4 * C)[:30], rng.integers(0, C, 30)] = np.finfo(np.float32).max
     else:
         params[where][rng.permutation(4 * C)[:30], rng.integers(0, C, 30)] = inf * rng.choice([-1, 1], 30).astype(np.float32)
     x = bf16_bits_to_f32(x_bits).reshape(n_seq, T, d)
