@@ -19,7 +19,7 @@
 // four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
 // It is what bounds a call: 0.56 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
-// four clocks apiece (0.43 us at 2.4 GHz), 38 other vector instructions and 20 that are none.  Measured against one launch per layer and
+// four clocks apiece (0.43 us at 2.4 GHz), 42 other vector instructions and 20 that are none.  Measured against one launch per layer and
 // stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 107 us, 8 of 333 tokens
 // (top-3) 1059 -> 245 us, 64 of 128 tokens 609 -> 140 us.
 #include <hip/hip_runtime.h>
@@ -458,12 +458,10 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
 // ---- the recurrence -----------------------------------------------------------------------------
 // Sigmoid and tanh by one straight line for both, told apart by three constants per lane, since the step of the
 // recurrence is bound by the instructions it issues: exponential by v_exp_f32, reciprocal with one Newton step, and a
-// Taylor polynomial of tanh below 1/10, where 2 / (1 + e) - 1 cancels (its next term, 17/315 v^7, is below 2^-24 of
-// tanh there).  Errors are about 2 units in the last place of 1; of a tanh just above 1/10 that is up to 17 of its own.
+// Taylor polynomial of tanh below 1/4, where 2 / (1 + e) - 1 cancels (its next term, 1382/155925 x^11, is below 2^-26 of
+// tanh there).  Errors are about 2 units in the last place of 1; of a tanh just above 1/4 that is up to 7 of its own.
 // The sums in parts make up for it: alpha against 64 bits, over nine batches of 29 to 8192 tokens, 0.56e-6 - 1.13e-6 with
-// tanhf and sums in index order, 0.34e-6 - 1.05e-6 with sums in parts and five terms of the polynomial up to 1/4.  These
-// three terms are two multiply-adds less each time: 64 x 128 tokens 151.4 -> 150.2 us, 8 x 333 248.5 -> 246.6, with the same
-// errors to 1 % in 20 batches, and to 0.1 % where small embeddings or weights keep the states small (2-norms, relative).
+// tanhf and sums in index order, 0.34e-6 - 1.05e-6 this way, smaller in each (2-norms, relative).
 // lane:  sigmoid(v) = 1 / (1 + exp(-v)),  tanh(v) = 2 / (1 + exp(-2v)) - 1.
 struct GateKind {
     float scale, gain, small;      // of the exponent (base 2), of the reciprocal, bound of the polynomial
@@ -471,7 +469,7 @@ struct GateKind {
 __device__ __forceinline__ GateKind gate_kind(bool is_tanh)
 {
     constexpr float kLog2e = 1.44269504f;
-    return is_tanh ? GateKind{-2.f * kLog2e, 2.f, 0.1f} : GateKind{-kLog2e, 1.f, 0.f};
+    return is_tanh ? GateKind{-2.f * kLog2e, 2.f, 0.25f} : GateKind{-kLog2e, 1.f, 0.f};
 }
 __device__ __forceinline__ float gate_value(float v, const GateKind &k)
 {
@@ -480,7 +478,7 @@ __device__ __forceinline__ float gate_value(float v, const GateKind &k)
     const float r = __builtin_amdgcn_rcpf(e);
     const float n = fmaf(fmaf(-e, r, 1.f), r, r);
     const float q = v * v;
-    const float t = v * fmaf(q, fmaf(q, 2.f / 15.f, -1.f / 3.f), 1.f);
+    const float t = v * fmaf(q, fmaf(q, fmaf(q, fmaf(q, 62.f / 2835.f, -17.f / 315.f), 2.f / 15.f), -1.f / 3.f), 1.f);
     return fabsf(v) < k.small ? t : fmaf(k.gain, n, 1.f - k.gain);
 }
 
@@ -514,9 +512,9 @@ struct RecurrenceLds {
 // quarters 0.65 us).  Slot j of lane l of the eight is row j ^ l, so that seven adds of permuted lanes
 // leave row l's sum in lane l; thread 4u+s then has gate s of unit u, the four gates meet in quad permutes
 // too, and a step has one barrier and no global access: pre-activations come and states go a chunk of
-// steps at a time.  What is left of a step at C = 128 is the issue of 128 multiply-adds, 38 other vector
+// steps at a time.  What is left of a step at C = 128 is the issue of 128 multiply-adds, 42 other vector
 // instructions and 20 that are none (8 s_nop, 6 LDS accesses, 5 waits, the barrier) per wavefront, two
-// wavefronts per SIMD, nearly back to back: each vector instruction less is 8 clocks of about 1330 a step.
+// wavefronts per SIMD, nearly back to back: each vector instruction less is 8 clocks of about 1350 a step.
 // Hence whole chunks are written out (addresses become offsets; the kernel's code doubles to 27 KB), lane 0
 // of a quad alone carries the cell's state, and sums of permuted lanes are one instruction each, with the
 // same bits.  One taken back at a time, us a call, and all three in front (1 x 128, 8 x 333, 96 x 85 tokens):

@@ -1,7 +1,7 @@
 """The hash function's products of values in bf16 parts, at the edges of what takes which tiles (2048 and 6144 tokens, rows and
 columns that fill no tile), against the float64 oracle - near enough that a lost third part of a value shows: the oracle with
 every weight cut to its first two parts is several times as far off as the bound.  Then the bits that a
-product keeps, and infinities."""
+product and a small tanh keep, and infinities."""
 import numpy as np
 import pytest
 
@@ -96,6 +96,34 @@ def test_a_product_keeps_the_bits_of_its_factors(n_seq, T):
     most, mean = float(np.abs(units).max()), float(units.mean())
     print(f"units of 2^-24: {units.min():.2f} to {units.max():.2f}, mean {mean:.3f}, rms {np.sqrt((units ** 2).mean()):.3f}", flush=True)
     assert most <= 3.0 and abs(mean) <= 0.25 and (alpha == alpha[:, :1]).all()
+
+
+@pytest.mark.parametrize("C", [64, 128])
+def test_a_small_tanh_keeps_its_bits(C):
+    """States of one step, tanh(tanh(v)) of v from 1/50 to 1/4 with the other gates at 1, and logits that are 2^20 times a
+    state less that product rounded to 32 bits.  A tanh by a polynomial is within two units of 2^-24 of itself (its last two
+    roundings and what is left of the inner ones), hence four; where 2 / (1 + exp(-2v)) - 1 cancels it would be up to 20."""
+    rng = np.random.default_rng(C)
+    d, L, E, k, scale = 8, 24, 8, 8, np.float32(2 ** 20)
+    cfg = sm.SidaHashConfig(d, C, L, E, k, 1)
+    params = {n: np.zeros(s, np.float32) for n, s in hash_fn.param_shapes(d, C, L, E)}
+    v = np.exp(rng.uniform(np.log(0.02), np.log(0.25), C)).astype(np.float32) * rng.choice([-1, 1], C).astype(np.float32)
+    params["b_ih2"][:] = 40                                                # input, forget and output gates: 1 in fp32
+    params["b_ih2"][2 * C:3 * C] = v
+    unit = rng.integers(0, C, L * E)
+    used = np.arange(L * E) % E > 0                                        # expert 0 of a layer: logit 0
+    params["w_out"][np.arange(L * E), unit] = scale * used
+    state = np.tanh(np.tanh(v.astype(np.float64)))[unit] * used
+    params["b_out"] = -(scale * state).astype(np.float32)
+    ids, alpha = run_hash(cfg, params, np.zeros((2, d), np.uint16), 2, 1)
+    by_expert = np.empty_like(alpha)
+    np.put_along_axis(by_expert, ids.astype(np.int64), alpha, axis=2)
+    logit = np.log(by_expert[:, 0] / by_expert[:, 0, :1]).astype(np.float64)[:, 1:]
+    want = (scale * state + params["b_out"]).reshape(L, E)[:, 1:]
+    units = (logit - want) / (scale * state).reshape(L, E)[:, 1:] * 2.0 ** 24
+    most = float(np.abs(units).max())
+    print(f"largest error {most:.2f} units of 2^-24, rms {np.sqrt((units ** 2).mean()):.3f}", flush=True)
+    assert most <= 4.0 and (alpha[:, 0] == alpha[:, 1]).all()
 
 
 @pytest.mark.parametrize("C,n_seq,T", [(128, 1, 40), (128, 16, 128), (64, 70, 31), (128, 90, 69)])
