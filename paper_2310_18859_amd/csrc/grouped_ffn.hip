@@ -42,6 +42,7 @@
 #include <unordered_map>
 
 #include "kernels.h"
+#include "past_end.h"
 #include "tile_order.h"
 
 namespace sida {
@@ -186,7 +187,7 @@ __device__ __forceinline__ void stream_tile(const GemmArgs &g, const i32x4 &td, 
         for (int j = 0; j < kT; ++j) {
             if (FUSE == kGather && g.top_k != 1) src[j] /= g.top_k;
             // rows past the end are out of the descriptor's range: zeros, no request
-            tok_v[j] = j * 16 + (lane >> 2) < rows ? src[j] * K * 2 + (lane & 3) * 16 : INT32_MIN;
+            tok_v[j] = j * 16 + (lane >> 2) < rows ? src[j] * K * 2 + (lane & 3) * 16 : kPastEnd;
         }
     };
     auto load_t = [&](int i, int f) {
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
     const __amdgpu_buffer_rsrc_t map_rsrc = make_rsrc(g.perm, FUSE == kPlain ? 0u : (uint32_t)g.map_len * 4u);
     const __amdgpu_buffer_rsrc_t gate_rsrc = make_rsrc(g.gate_perm, FUSE == kScatter ? (uint32_t)g.map_len * 4u : 0u);
     __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(g.pool, 0);
-    int tok_v[TL], w_at[NS];                                    // byte offsets: per lane, and of the stripes
+    int tok_v[TL], w_at[NS], w_v = lane * 16;                   // byte offsets: per lane, of the stripes, in a fragment
     int tok_s = 0, w_s = 0;                                     // running K offsets (uniform)
     bool w_once = false;                                        // cache policy of the weight loads (uniform)
     // kGather: perm of this wavefront's 8*TL token rows of a tile (rows past its end repeat the last one) -> side
@@ -468,14 +469,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
         w_s = 0;
         w_once = c.once;
     };
-    // Behind a workgroup's last tile: loads past the descriptors' ends, which ask for nothing, so that the loop has no
-    // data-dependent branch around a load.  (The last tile's first steps fetched once more were two steps of 512
-    // workgroups, 50 MB of a launch's 900; 128 experts, 16384 tokens, first GEMM 153 -> 150 us with it and with rows
-    // past a tile's end no longer written.)
+    // Behind a workgroup's last tile: loads past the descriptors' ends (past_end.h), which ask for nothing, so that the loop
+    // has no data-dependent branch around a load.  (The last tile's first steps fetched once more were two steps of 512
+    // workgroups: 42 / 35 MB of the 898 / 909 that missed L2 at 128 experts, 16384 tokens.)
     auto point_nowhere = [&]() {
+        constexpr uint32_t kRow = 64 * NB * 2;                  // bytes of a row of either operand, at least: K is a multiple of 64 NB
+        static_assert(dropped(kRow, kPastEnd, last_token_scalar(NB)) && dropped(INT32_MAX, kPastEnd, 0) &&
+                      dropped(BN * kRow, kPastEnd, last_weight_scalar(NB)), "nothing is loaded");
 #pragma unroll
-        for (int j = 0; j < TL; ++j) tok_v[j] = INT32_MIN;
-        w_rsrc = make_rsrc(g.pool, 0);
+        for (int j = 0; j < TL; ++j) tok_v[j] = kPastEnd;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) w_at[s] = 0;
+        w_v = kPastEnd;
+        tok_s = 0;
+        w_s = 0;
     };
     int wr_off = 0;                                             // ring offset of the stage filled next
     auto issue_tokens = [&]() {
@@ -493,12 +500,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<true>(w_rsrc, lane * 16, w_at[s] + w_s + ks * 1024);
+                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<true>(w_rsrc, w_v, w_at[s] + w_s + ks * 1024);
         } else {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<false>(w_rsrc, lane * 16, w_at[s] + w_s + ks * 1024);
+                for (int s = 0; s < NS; ++s) wb[ks][s] = load_frag<false>(w_rsrc, w_v, w_at[s] + w_s + ks * 1024);
         }
         w_s += 4096;
     };
@@ -563,7 +570,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void grouped_gemm_nt(const GemmArgs
                 // rows past the tile's end are stored out of range: nothing is written, but every thread issues all its
                 // stores and the waits count them
                 const int at = lane_row * N * 2 + seg * 16 + (base_row * N + c.nt * BN + wv * kOutCols) * 2;
-                store_row_piece<ONCE>(c_rsrc, v, m < c.rows ? at : INT32_MIN);
+                store_row_piece<ONCE>(c_rsrc, v, m < c.rows ? at : kPastEnd);
             }
         }
     };
