@@ -28,6 +28,24 @@ SIDA_HD Role role_of(int ticket, int n_seq)
     const unsigned t = (unsigned)ticket, what = t / (unsigned)n_seq;
     return Role{what < 2u ? (int)what : 2, (int)(t % (unsigned)n_seq)};
 }
+// The same with layer 1's own gate pre-activations among the roles (-1), in front of the others.
+SIDA_HD Role role_of_four(int ticket, int n_seq)
+{
+    return (unsigned)ticket < (unsigned)n_seq ? Role{-1, ticket} : role_of((int)((unsigned)ticket - (unsigned)n_seq), n_seq);
+}
+
+// Counters of one call: the tickets drawn, then per sequence a 64-byte line each for the progress of layer 1's states
+// (chunks times wavefronts), of layer 2's inputs and of layer 1's inputs (chunks).
+constexpr int kLine = 16;        // words
+SIDA_HD constexpr int counter_words(int n_seq) { return kLine * (1 + 3 * n_seq); }
+SIDA_HD constexpr int layer1_line(int seq) { return kLine * (1 + 3 * seq); }
+SIDA_HD constexpr int gates2_line(int seq) { return layer1_line(seq) + kLine; }
+SIDA_HD constexpr int gates1_line(int seq) { return layer1_line(seq) + 2 * kLine; }
+
+// Gate pre-activations are made for some tokens at a time, whole chunks: layer 1's for kGateTokens, layer 2's for a chunk.
+// Chunks there when `rounds` of them have been stored; the reader waits for c + 1 before it loads chunk c.
+constexpr int kGateTokens = 8;
+SIDA_HD constexpr int chunks_there(int rounds, int tokens, int steps) { return rounds * (tokens / steps); }
 
 // Waits until the counter that peek() reads has reached `want`; `seen` is the most that it has shown.  In a
 // call that has its workspace to itself the counter gets there within microseconds: what is waited for is the

@@ -139,12 +139,6 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Counters of one call, in the part of the workspace that the attention writes later: the ticket the
-// recurrence's workgroups draw their role from, then per sequence a 64-byte line each for the progress of layer 1's
-// states (chunks times wavefronts), of layer 2's and of layer 1's inputs (chunks).  Cleared by the first launch.
-constexpr int kLine = 16;
-__host__ __device__ constexpr size_t counter_words(size_t n_seq) { return kLine * (1 + 3 * n_seq); }
-
 // ---- operand tiles in LDS -----------------------------------------------------------------------
 // Rows of 32 values, loaded straight into LDS with whole lines per request.  (Fetched as matrix operands,
 // 16 bytes of a different row in every lane, each lane is a cache access of its own: the dense stages
@@ -501,7 +495,7 @@ struct RecurrenceLds {
     float h[2 * kChunk<C>][kRow];                               // the state after each step of two chunks
     float pre[kChunk<C>][4 * C];                                // gate pre-activations of a chunk; a thread reads what it wrote
     static constexpr int kInPitch = C + 16;
-    float in[2][8 * kInPitch];                             // inputs of up to eight steps, of which gate pre-activations are made
+    float in[2][kGateTokens * kInPitch];                        // tokens of which gate pre-activations are made
     int ticket;
 };
 
@@ -634,8 +628,8 @@ __device__ __forceinline__ void gates_ahead(const float *__restrict__ x, const f
                                             float *__restrict__ pre, const int *arrived, int *done, RecurrenceLds<C> &lds)
 {
     constexpr int kPitch = RecurrenceLds<C>::kInPitch;
-    constexpr int kTokens = FIRST ? 8 : kChunk<C>, kBlocks = kTokens / 4, kPolicy = FIRST ? 0 : kAgent;
-    static_assert(kTokens % 4 == 0 && kTokens <= 8 && kTokens % kChunk<C> == 0 && kTokens * C / 4 <= 4 * C, "whole blocks and chunks");
+    constexpr int kTokens = FIRST ? kGateTokens : kChunk<C>, kBlocks = kTokens / 4, kPolicy = FIRST ? 0 : kAgent;
+    static_assert(kTokens % 4 == 0 && kTokens <= kGateTokens && kTokens % kChunk<C> == 0 && kTokens * C / 4 <= 4 * C, "whole blocks and chunks");
     const int tid = threadIdx.x, lane = tid & 63;
     const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(x, (uint32_t)T * C * 4);
     const __amdgpu_buffer_rsrc_t pre_rsrc = make_rsrc(pre, (uint32_t)T * 4 * C * 4);
@@ -683,7 +677,7 @@ __device__ __forceinline__ void gates_ahead(const float *__restrict__ x, const f
                 store_f32<kAgent>(pre_rsrc, ((c * kTokens + q * 4 + i) * 4 * C + tid) * 4, even[q][i] + odd[q][i]);
         wait_memory<0>();
         lds_barrier();
-        if (tid == 0) publish(done, (c + 1) * (kTokens / kChunk<C>));
+        if (tid == 0) publish(done, chunks_there(c + 1, kTokens, kChunk<C>));
     }
 }
 
@@ -709,11 +703,10 @@ __global__ __launch_bounds__(4 * C) void hash_recurrence(float *pre, const float
     if (threadIdx.x == 0) lds.ticket = __hip_atomic_fetch_add(counters, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(lds.ticket);
-    const bool gates_first = GATES && (unsigned)ticket < (unsigned)n_seq;
-    const Role of = gates_first ? Role{-1, ticket} : role_of(GATES ? ticket - n_seq : ticket, n_seq);
+    const Role of = GATES ? role_of_four(ticket, n_seq) : role_of(ticket, n_seq);
     const int role = of.what, seq = of.seq;
     float *p = pre + (size_t)seq * T * 4 * C, *a = h1 + (size_t)seq * T * C, *b = h2 + (size_t)seq * T * C;
-    int *layer1_done = counters + kLine * (1 + 3 * seq), *gates2_done = layer1_done + kLine, *gates1_done = gates2_done + kLine;
+    int *layer1_done = counters + layer1_line(seq), *gates2_done = counters + gates2_line(seq), *gates1_done = counters + gates1_line(seq);
     if (GATES && role < 0) gates_ahead<C, true>(c0 + (size_t)seq * T * C, w_ih1, b_ih1, b_hh1, T, p, nullptr, gates1_done, lds);
     else if (role == 0) lstm_layer<C, GATES, true>(p, w_hh1, T, a, gates1_done, layer1_done, lds);
     else if (role == 1) gates_ahead<C, false>(a, w_ih2, b_ih2, b_hh2, T, p, layer1_done, gates2_done, lds);
@@ -1032,11 +1025,12 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
     // workspace
     float *c0 = ws, *pre = c0 + (size_t)N * C, *h1 = pre + (size_t)N * 4 * C, *h2 = h1 + (size_t)N * C,
           *r = h2 + (size_t)N * C;
+    // Counters of the recurrence, in the part of the workspace that the attention writes later; cleared by the first launch.
     int *counters = reinterpret_cast<int *>(r);                // N*C words, of which a sequence needs 3*kLine and the ticket kLine
     static_assert(C >= 4 * kLine, "counters fit");
     const __bf16 *xb = (const __bf16 *)x;
     // Tiles: as large as leave every compute unit (nearly) one workgroup.
-    const int n_counters = n_seq <= kSideBySide ? (int)counter_words(n_seq) : 0;
+    const int n_counters = n_seq <= kSideBySide ? counter_words(n_seq) : 0;
     auto dense = [&](auto kernel, int tokens, int rows, auto in, const float *w, const float *ba, const float *bb, int k,
                      int units, float *out, int n_clear) {
         hipLaunchKernelGGL(kernel, dim3((N + tokens - 1) / tokens, units / rows), dim3(256), 0, st, in, w, ba, bb, k, units, N, out,
