@@ -118,7 +118,7 @@ typedef struct sida_ws_layout {
     size_t h;           /* bf16  [T, d_ff]              relu(x_perm W_in^T), perm order       */
     size_t y_perm;      /* bf16  [T, d_model]           expert outputs, perm order            */
     size_t tiles;       /* int32 [4 * (T/64 + E + 1)]   token-tile descriptors of the grouped FFN */
-    size_t sink;        /* 64 KiB, not used by this version */
+    size_t sink;        /* no bytes: kept for the layout of this struct        */
     size_t gate_perm;   /* fp32  [T]   gate_perm[r] = alpha[perm[r]]   (fused path only)      */
     size_t total;       /* bytes needed                                                       */
 } sida_ws_layout;

@@ -70,7 +70,7 @@ void layout(const sida_config &cfg, int32_t T, sida_ws_layout *o)
     o->h = take(2 * (size_t)T * (size_t)cfg.d_ff);
     o->y_perm = take(2 * (size_t)T * (size_t)cfg.d_model);
     o->tiles = take(sizeof(TileDesc) * max_tiles(cfg, T));
-    o->sink = take(64 * 1024);
+    o->sink = take(0);
     o->gate_perm = take(sizeof(float) * (size_t)T);
     o->total = off;
 }

@@ -137,6 +137,14 @@ def test_workspace_layout_is_aligned_and_ordered():
     assert ctx.expert_bytes() == 4 * 768 * 3072
 
 
+def test_workspace_holds_what_is_used_and_no_more():
+    T, E, d, F = 4999, 64, 768, 3072
+    lay = sm.Context(1, E, d, F, 8, 8, 5000).workspace_layout(T)
+    chunks = -(-(lay.perm - lay.block_hist) // (4 * E))                   # of the sort; a whole number and padding
+    used = [4 * E, 4 * (E + 1), 4 * E * chunks, 4 * T, 4 * T, 2 * T * d, 2 * T * F, 2 * T * d, 16 * (T // 64 + E + 1), 0, 4 * T]
+    assert lay.total <= sum(used) + 256 * len(used)
+
+
 def test_prefetch_mode_arguments():
     ctx = sm.Context(1, 4, 128, 128, 2, 1, 8)
     ctx.set_prefetch_mode("auto")
