@@ -126,7 +126,11 @@ def assert_agrees(got_ids, got_alpha, probs, k):
     assert (chosen.min(axis=2) >= np.sort(probs, axis=2)[:, :, -k] - ALPHA_TOL).all()
 
 
-@pytest.mark.parametrize("n_seq,T,bad", [(1, 40, 37), (2, 100, 99), (1, 100, 65), (1, 500, 470)])
+@pytest.mark.parametrize("n_seq,T,bad", [
+    (1, 40, 37), (2, 100, 99), (1, 100, 65), (1, 500, 470),
+    # products in parts: gates in the recurrence, in front of it, and layer after layer; larger tiles of embeddings
+    (16, 128, 77), (70, 31, 12), (90, 70, 33),
+])
 def test_a_token_that_is_not_a_number_leaves_earlier_tokens_as_they_are(n_seq, T, bad):
     """A NaN embedding at token t makes the LSTM states from t on NaN; their scores are NaN, their attention weights
     0: tokens before t are those of the sequence cut off at t; other sequences do not change at all."""

@@ -1,7 +1,7 @@
-"""The hash function's products of values in bf16 parts, at the edges of what takes which tiles (2048 and 6144 tokens, rows and
-columns that fill no tile), against the float64 oracle - near enough that a lost third part of a value shows: the oracle with
-every weight cut to its first two parts is several times as far off as the bound.  Then the bits that a
-product and a small tanh keep, and infinities."""
+"""The hash function's products of values in bf16 parts: at the edges of what takes which tiles (2048 and 6144 tokens, rows and
+columns that fill no tile) against the float64 oracle, with a control that all weights without their third parts are several
+times as far off as the bound; then the bits that one product keeps, in the heads and in layer 1's gates, each by itself; the
+bits that a small tanh keeps; infinities."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,8 @@ from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 pytestmark = pytest.mark.gpu
 
 # Observed 0.3e-6 to 0.6e-6; sums of fp32 values in another order differ by as much.  Without third parts, all weights or
-# those of the embeddings or heads alone: 8e-6 to 24e-6.
+# those of the embeddings or heads alone: 8e-6 to 24e-6.  (Of the gates' products one lost part moves alpha by no more than
+# the bound; test_a_gate_keeps_the_bits_of_its_factors looks at them.)
 BOUND = 2e-6
 
 
@@ -39,9 +40,9 @@ def oracle_alpha(params, x, cfg, ids):
     (768, 128, 1, 60, 2, 89, 69),         # 6141, experts that fill no tile, layers one after the other
     (136, 64, 2, 130, 1, 48, 128),        # 6144
     (1024, 64, 1, 16, 1, 49, 127),        # 6223
-    (64, 128, 1, 16, 1, 64, 33),          # as many sequences as have four workgroups each, and one more
+    (64, 128, 1, 16, 1, 64, 33),          # as many sequences as have four workgroups each, and one more: gates in parts
     (64, 128, 1, 16, 1, 65, 33),
-    (64, 64, 1, 16, 1, 15, 137),          # as few as have three
+    (64, 64, 1, 16, 1, 15, 137),          # as few as have three: gates in parts
 ])
 def test_parts_against_oracle(d, C, L, E, k, n_seq, T):
     rng = np.random.default_rng(d + T)
@@ -96,6 +97,46 @@ def test_a_product_keeps_the_bits_of_its_factors(n_seq, T):
     most, mean = float(np.abs(units).max()), float(units.mean())
     print(f"units of 2^-24: {units.min():.2f} to {units.max():.2f}, mean {mean:.3f}, rms {np.sqrt((units ** 2).mean()):.3f}", flush=True)
     assert most <= 3.0 and abs(mean) <= 0.25 and (alpha == alpha[:, :1]).all()
+
+
+@pytest.mark.parametrize("C,n_seq,T", [(128, 70, 31), (64, 90, 31), (128, 16, 128)])
+def test_a_gate_keeps_the_bits_of_its_factors(C, n_seq, T):
+    """The same of layer 1's gate pre-activations: one product each, less its value rounded to 32 bits, goes through the
+    two layers' four tanh, the other gates at 1 or 0 and nothing taken over from the step before, to the logits.  Without the
+    third part of weights or of states it would be off by up to 2^7 units.  (16 x 128: made in the recurrence, in fp32.)"""
+    rng = np.random.default_rng(C + n_seq)
+    d, L, E, k = 64, 24, 8, 8
+    cfg = sm.SidaHashConfig(d, C, L, E, k, T)
+    params = {n: np.zeros(s, np.float32) for n, s in hash_fn.param_shapes(d, C, L, E)}
+    params["w_in"][:, 5] = state = bits_at_the_edges(rng, C)
+    cell, column = slice(2 * C, 3 * C), rng.integers(0, C, C)
+    factor = bits_at_the_edges(rng, C) * np.float32(2 ** 20) * rng.choice([-1, 1], C).astype(np.float32)
+    exact = factor.astype(np.float64) * state[column].astype(np.float64)
+    params["w_ih1"][cell][np.arange(C), column] = factor
+    params["w_ih2"][cell][np.arange(C), np.arange(C)] = 1
+    for b in (params["b_ih1"], params["b_ih2"]):
+        b[:] = 40                                                          # input and output gates: 1 in fp32
+        b[C:2 * C] = -40                                                   # forget gates: 0
+        b[cell] = 0
+    params["b_ih1"][cell] = -exact.astype(np.float32)
+    unit = rng.integers(0, C, L * E)
+    used = np.arange(L * E) % E > 0                                        # expert 0 of a layer: logit 0
+    params["w_out"][np.arange(L * E), unit] = used
+    params["b_out"] = (-state[unit] * used).astype(np.float32)             # takes the residual off again
+    x_bits = np.zeros((n_seq * T, d), np.uint16)
+    x_bits[:, 5] = 0x3f80
+    ids, alpha = run_hash(cfg, params, x_bits, n_seq, T)
+    by_expert = np.empty_like(alpha)
+    np.put_along_axis(by_expert, ids.astype(np.int64), alpha, axis=2)
+    got = np.log((by_expert[:, :, 1:] / by_expert[:, :, :1]).astype(np.float64))
+    for _ in range(4):
+        got = np.arctanh(got)
+    z = exact[unit].reshape(L, 1, E)[:, :, 1:]
+    want = (exact + params["b_ih1"][cell])[unit].reshape(L, 1, E)[:, :, 1:]
+    units = (got - want) / z * 2.0 ** 24
+    most, mean = float(np.abs(units).max()), float(units[:, 0].mean())
+    print(f"units of 2^-24: {units.min():.2f} to {units.max():.2f}, mean {mean:.3f}, rms {np.sqrt((units ** 2).mean()):.3f}", flush=True)
+    assert most <= 3.0 and abs(mean) <= 0.25
 
 
 @pytest.mark.parametrize("C", [64, 128])
