@@ -227,23 +227,22 @@ __device__ __forceinline__ f32x4 mfma_parts(const Parts &a, const Parts &b, f32x
 // Infinities do not go through parts (they leave NaN behind, and parts that are 0 make NaN of an infinite factor): a sum
 // that comes out infinite or NaN is made again on the fp32 instruction, and that one counts.  One that comes out
 // finite had finite parts only.
-__device__ __forceinline__ bool overflowed(float v) { return !__builtin_isfinite(v); }
 template <int TU, int TT>
 __device__ __forceinline__ bool any_overflow(const f32x4 (&d)[TU][TT])    // in any lane
 {
-    bool any = false;
+    float none = 0.f;                                          // NaN once a value was infinite or NaN
 #pragma unroll
     for (int i = 0; i < TU; ++i)
 #pragma unroll
         for (int m = 0; m < TT; ++m)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) any |= overflowed(d[i][m][e]);
-    return __any(any);
+            for (int e = 0; e < 4; ++e) none = fmaf(d[i][m][e], 0.f, none);
+    return __any(none != none);
 }
 __device__ __forceinline__ f32x4 where_overflowed(f32x4 d, const f32x4 &other)
 {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) d[e] = overflowed(d[e]) ? other[e] : d[e];
+    for (int e = 0; e < 4; ++e) d[e] = __builtin_isfinite(d[e]) ? d[e] : other[e];
     return d;
 }
 // A piece whose address is a multiple of its values' size only.
@@ -874,6 +873,12 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
     float *logit = reinterpret_cast<float *>(tiles);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15, g = lane >> 4;
     const int l = blockIdx.y, n0 = blockIdx.x * TT * 16;
+    f32x4 bias[kMine];                                         // asked for first: behind the products they would be waited for
+#pragma unroll
+    for (int i = 0; i < kMine; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias[i][e] = b_out[l * E + min((i * 4 + wv) * 16 + 4 * g + e, E - 1)];
+    loads_issued();
     {
         const LoadW load_w(w_out + (size_t)l * E * C, E, C, lane, wv);
         const LoadX load_x(r + (size_t)n0 * C, n_tokens - n0, C, lane, wv);
@@ -949,12 +954,9 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
     for (int i = 0; i < kMine; ++i) {
         const int tile = i * 4 + wv;
         if (NT < 4 && tile >= NT) continue;
-        f32x4 bias;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bias[e] = b_out[l * E + min(tile * 16 + 4 * g + e, E - 1)];
 #pragma unroll
         for (int m = 0; m < TT; ++m)
-            *reinterpret_cast<f32x4 *>(&logit[(m * 16 + col) * kPitch + tile * 16 + 4 * g]) = acc[i][m] + bias;
+            *reinterpret_cast<f32x4 *>(&logit[(m * 16 + col) * kPitch + tile * 16 + 4 * g]) = acc[i][m] + bias[i];
     }
     __syncthreads();
 #pragma unroll 1
