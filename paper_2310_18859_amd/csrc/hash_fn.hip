@@ -15,13 +15,14 @@
 //   hash_attention  scores, SparseMax, weighted sum and residual, for blocks of 16 queries
 //   hash_heads      logits, SoftMax and the k best, for blocks of tokens and a MoE layer each
 // The contractions run on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32, twice the rate of
-// scalar-per-lane fp32 multiply-adds), or on the bf16 one with the values in exact parts (hash_dense, Parts); with the weights as the first operand a lane ends up with
-// four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
+// scalar-per-lane fp32 multiply-adds), or on the bf16 one with the values in exact parts (hash_dense, Parts); with the
+// weights as the first operand a lane ends up with four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
-// It is what bounds a call: 0.56 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
+// It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
 // four clocks apiece (0.43 us at 2.4 GHz), 42 other vector instructions and 20 that are none.  Measured against one launch per layer and
-// stage on the vector units (d = 768, C = 128, 6 x 128 experts): 1 sequence of 128 tokens 375 -> 107 us, 8 of 333 tokens
-// (top-3) 1059 -> 245 us, 64 of 128 tokens 609 -> 140 us.
+// stage on the vector units (d = 768, C = 128, 6 x 128 experts; calls of perf/cases.py, inputs changing): 1 sequence of
+// 128 tokens 375 -> 108 us, 8 of 333 tokens (top-3) 1059 -> 249 us, 64 of 128 tokens 609 -> 141 us (one batch called again
+// and again 148 to 153).
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -508,7 +509,7 @@ struct RecurrenceLds {
 // steps at a time.  What is left of a step at C = 128 is the issue of 128 multiply-adds, 42 other vector
 // instructions and 20 that are none (8 s_nop, 6 LDS accesses, 5 waits, the barrier) per wavefront, two
 // wavefronts per SIMD, nearly back to back: each vector instruction less is 8 clocks of about 1350 a step.
-// Hence whole chunks are written out (addresses become offsets; the kernel's code doubles to 27 KB), lane 0
+// Hence whole chunks are written out (addresses become offsets; the kernel's code grows to 17 - 21 KB), lane 0
 // of a quad alone carries the cell's state, and sums of permuted lanes are one instruction each, with the
 // same bits.  One taken back at a time, us a call, and all three in front (1 x 128, 8 x 333, 96 x 85 tokens):
 // 112.8, 260.2, 201.8; chunks walked in a loop 115.9, 267.7, 205.5; the state in every lane 113.2, 260.9, 202.8;
@@ -682,9 +683,9 @@ __device__ __forceinline__ void gates_ahead(const float *__restrict__ x, const f
 
 // Both LSTM layers of every sequence in one launch of 3 or 4 workgroups per sequence: the gate pre-activations of
 // layer 1 (GATES; else a launch before has made them), layer 1, the gate pre-activations between the layers, layer 2; each
-// works behind the one before, chunk by chunk, so that a call takes T plus about 20 steps instead of 2T.  A workgroup takes
-// its role by ticket: first all of the first role, and so on.  Tickets are drawn by workgroups
-// that run, so whatever a workgroup waits for is done by a workgroup that already runs and waits, if
+// works behind the one before, chunk by chunk, so that a call takes T plus about 20 steps (30 at C = 64, whose chunks are
+// longer) instead of 2T.  A workgroup takes its role by ticket: first all of the first role, and so on.  Tickets are drawn
+// by workgroups that run, so whatever a workgroup waits for is done by a workgroup that already runs and waits, if
 // at all, for a lower ticket only; the first role waits for nobody.  Hence every wait ends, whatever the
 // order in which workgroups are started and whatever else runs on the GPU.  (Counters that another call
 // writes over, against the rules, end them too: see handover.h.)
