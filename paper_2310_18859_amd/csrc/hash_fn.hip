@@ -311,7 +311,8 @@ __device__ __forceinline__ void tiles_arrived()
 //    once and the weights are spread over 64 workgroups.
 //  * Large ones by the matrix units: 4 or 2 x 2 tiles per wavefront.
 // Embeddings are bf16, so their product with fp32 weights goes through the bf16 matrix instruction, of 16 times the rate:
-// a weight is the sum of three bf16 values, exactly, every product is exact, and the sums are fp32 as before.  8192 tokens
+// a weight is the sum of three bf16 values, exactly, every product is exact, and the sums are fp32 as before.  (The
+// instruction does not normalise embeddings below 2^-126: their products keep fewer bits, 20 at 2^-130.)  8192 tokens
 // of 768: 64 x 128 tokens 162.0 -> 152.1 us a call (1 x 4 tiles, so that a weight is split once per workgroup), 8 x 333
 // 254.4 -> 249.5, 32 x 200 at C = 64 135.3 -> 125.4.  alpha against 64 bits over eight batches of 2060 to 8192 tokens, d of
 // 256 to 2056 (2-norm, relative): 0.44e-6 - 1.07e-6 before, 0.31e-6 - 0.84e-6 this way, smaller in each.

@@ -68,8 +68,13 @@ def bits_at_the_edges(rng, n):
     return (mantissa.astype(np.uint32) | np.uint32(0x3f800000)).view(np.float32)
 
 
-@pytest.mark.parametrize("n_seq,T", [(16, 128), (70, 31)])
-def test_a_product_keeps_the_bits_of_its_factors(n_seq, T):
+# Powers of two of the embedding, of its weights and of the heads' weights: 2^20 together.  Down to states and weights whose
+# last parts are below the smallest normal number.
+@pytest.mark.parametrize("n_seq,T,powers", [
+    (16, 128, (0, 0, 20)), (70, 31, (0, 0, 20)), (1, 64, (0, 0, 20)),
+    (16, 128, (0, -106, 126)), (16, 128, (0, 126, -106)), (16, 128, (127, -106, -1)),
+])
+def test_a_product_keeps_the_bits_of_its_factors(n_seq, T, powers):
     """Logits that are one product each, less its value rounded to 32 bits: what is left of a product of 2^20 shows units of
     2^-24 of it.  Three are allowed, one each for the products of parts that are left out, for the sum's rounding and for
     what the matrix instruction aligns its addends by.  The errors are of either sign (168 of them, root mean square 0.8:
@@ -78,15 +83,16 @@ def test_a_product_keeps_the_bits_of_its_factors(n_seq, T):
     d, C, L, E, k = 64, 128, 24, 8, 8
     cfg = sm.SidaHashConfig(d, C, L, E, k, T)
     params = {n: np.zeros(s, np.float32) for n, s in hash_fn.param_shapes(d, C, L, E)}
-    params["w_in"][:, 5] = bits_at_the_edges(rng, C)                       # the state of every token, as it is
-    factor = bits_at_the_edges(rng, L * E) * np.float32(2 ** 20) * rng.choice([-1, 1], L * E).astype(np.float32)
+    of_x, of_state, of_factor = powers
+    params["w_in"][:, 5] = np.ldexp(bits_at_the_edges(rng, C), of_state)
+    factor = np.ldexp(bits_at_the_edges(rng, L * E), of_factor) * rng.choice([-1, 1], L * E).astype(np.float32)
     unit = rng.integers(0, C, L * E)
     factor[::E] = 0                                                        # expert 0 of a layer: logit 0
     params["w_out"][np.arange(L * E), unit] = factor
-    exact = factor.astype(np.float64) * params["w_in"][unit, 5].astype(np.float64)
+    exact = np.ldexp(factor.astype(np.float64) * params["w_in"][unit, 5].astype(np.float64), of_x)
     params["b_out"] = -exact.astype(np.float32)
     x_bits = np.zeros((n_seq * T, d), np.uint16)
-    x_bits[:, 5] = 0x3f80
+    x_bits[:, 5] = f32_to_bf16_bits(np.ldexp(np.ones(1, np.float32), of_x))[0]   # every token's state: w_in's column times this
     ids, alpha = run_hash(cfg, params, x_bits, n_seq, T)
     by_expert = np.empty_like(alpha)
     np.put_along_axis(by_expert, ids.astype(np.int64), alpha, axis=2)
