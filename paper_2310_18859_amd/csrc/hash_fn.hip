@@ -417,12 +417,28 @@ __global__ __launch_bounds__(256) void hash_dense(const IN *__restrict__ in, con
 #pragma unroll 1
             for (int t = 0; t < TU * TT; ++t) {
                 const int i = t / TT, m = t % TT;
+                f32x4 d[1][1] = {acc[0][0]};                   // a token that is NaN is in one tile of four
+#pragma unroll
+                for (int j = 1; j < TU * TT; ++j)
+                    if (j == t) d[0][0] = acc[j / TT][j % TT];
+                if (!any_overflow(d)) continue;
                 const float *row = w + (size_t)(u0 + (wu * TU + i) * 16 + col) * k;
                 const IN *token = in + (size_t)min(n0 + (wt * TT + m) * 16 + col, n_tokens - 1) * k;
                 f32x4 again = {};
 #pragma unroll 1
-                for (int at = first * 32; at < end; at += 4)   // k is a multiple of 4
-                    again = __builtin_amdgcn_mfma_f32_16x16x4f32(row[at + g], (float)token[at + g], again, 0, 0, 0);
+                for (int s = first * 32; s < end; s += 32) {   // four such steps at a time were not faster
+                    float a[8] = {}, b[8] = {};
+                    const int at = s + 8 * g;
+                    if (at < end) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            a[e] = row[at + e];
+                            b[e] = (float)token[at + e];
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) again = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], again, 0, 0, 0);
+                }
 #pragma unroll
                 for (int j = 0; j < TU * TT; ++j)
                     if (j == t) acc[j / TT][j % TT] = where_overflowed(acc[j / TT][j % TT], again);
