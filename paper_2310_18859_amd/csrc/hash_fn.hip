@@ -18,8 +18,7 @@
 // scalar-per-lane fp32 multiply-adds), or on the bf16 one with the values in exact parts (hash_dense, Parts); with the
 // weights as the first operand a lane ends up with four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
-// It is what bounds a call: 0.57 us a time step at C = 128.  Two wavefronts per SIMD issue 128 multiply-adds each in it,
-// four clocks apiece (0.43 us at 2.4 GHz), 42 other vector instructions and 20 that are none.  Measured against one launch per layer and
+// It is what bounds a call: 0.55 us a time step at C = 128, see lstm_layer.  Measured against one launch per layer and
 // stage on the vector units (d = 768, C = 128, 6 x 128 experts; calls of perf/cases.py, inputs changing): 1 sequence of
 // 128 tokens 375 -> 108 us, 8 of 333 tokens (top-3) 1059 -> 249 us, 64 of 128 tokens 609 -> 141 us (one batch called again
 // and again 148 to 153).
@@ -493,13 +492,18 @@ __device__ __forceinline__ float gate_value(float v, const GateKind &k)
     return fabsf(v) < k.small ? t : fmaf(k.gain, n, 1.f - k.gain);
 }
 
-// sum + v of the quad's lane 1 * x, as one instruction (the compiler makes it a move and a multiply-add).
-__device__ __forceinline__ float fma_of_gate1(float v, float x, float sum)
+// v of the quad's lane 1 * x + v * v of the quad's lane 2: forget gate * state + input gate * cell gate, in lane 0.  Two
+// instructions (the compiler makes the second a move and a multiply-add).
+__device__ __forceinline__ float next_cell(float v, float x)
 {
     // A value from another lane may be read two instructions after it was written.  The compiler sees to that in its
     // own code, not in front of this; the wait stays here, also where what it put in front has waited already.
-    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "+v"(sum) : "v"(v), "v"(x));
-    return sum;
+    float cell;
+    asm("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, %1, %1 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "=&v"(cell) : "v"(v), "v"(x));
+    return cell;
 }
 
 template <int C>
@@ -509,6 +513,9 @@ template <int C>
 struct RecurrenceLds {
     static constexpr int kSeg = C / 8, kSegPitch = kSeg + 4;   // the eight segments start in different banks
     static constexpr int kRow = 8 * kSegPitch;
+    // Where a unit's state stands in a row.  Four units that are loaded together stand one on, in a circle, so that a
+    // unit's state comes into a register of odd number where its weights' is even, and the other way round.
+    static __device__ __forceinline__ int place(int unit) { return (unit / kSeg) * kSegPitch + (unit % kSeg & ~3) + ((unit + 1) & 3); }
     float h[2 * kChunk<C>][kRow];                               // the state after each step of two chunks
     float pre[kChunk<C>][4 * C];                                // gate pre-activations of a chunk; a thread reads what it wrote
     static constexpr int kInPitch = C + 16;
@@ -523,14 +530,22 @@ struct RecurrenceLds {
 // quarters 0.65 us).  Slot j of lane l of the eight is row j ^ l, so that seven adds of permuted lanes
 // leave row l's sum in lane l; thread 4u+s then has gate s of unit u, the four gates meet in quad permutes
 // too, and a step has one barrier and no global access: pre-activations come and states go a chunk of
-// steps at a time.  What is left of a step at C = 128 is the issue of 128 multiply-adds, 42 other vector
-// instructions and 20 that are none (8 s_nop, 6 LDS accesses, 5 waits, the barrier) per wavefront, two
-// wavefronts per SIMD, nearly back to back: each vector instruction less is 8 clocks of about 1350 a step.
-// Hence whole chunks are written out (addresses become offsets; the kernel's code grows to 17 - 21 KB), lane 0
+// steps at a time.
+// What a step at C = 128 is bound by, 1270 cycles: a wavefront issues one instruction of any kind in 4.1 cycles, 190 of them,
+// and waits for the barrier and its first state from LDS (240); two wavefronts per SIMD multiply side by side (128 each in
+// 526 cycles), but sums of permuted lanes and exponentials keep the SIMD to themselves, and the second wavefront ends 160
+// later.  Registers stand in two banks, of even and of odd numbers, and a pair of multiply-adds of two wavefronts gets
+// four operands from each: one whose three are all even (or odd) makes the other wavefront wait for four cycles.
+// 66 of a step's were, when a unit's weights and state came out of 16-byte loads in the same order; with place() 2
+// are, and a step takes 1284 cycles instead of 1308 (bits unchanged); both products of the cell in one piece 1270.
+// Whole chunks are written out (addresses become offsets; the kernel's code grows to 17 - 21 KB), lane 0
 // of a quad alone carries the cell's state, and sums of permuted lanes are one instruction each, with the
-// same bits.  One taken back at a time, us a call, and all three in front (1 x 128, 8 x 333, 96 x 85 tokens):
+// same bits.  One taken back at a time, us a call, and all three in front (1 x 128, 8 x 333, 96 x 85 tokens; of an earlier build):
 // 112.8, 260.2, 201.8; chunks walked in a loop 115.9, 267.7, 205.5; the state in every lane 113.2, 260.9, 202.8;
 // the sum with a permuted value more 113.0, 260.7, 201.8.
+// Tried on it without gain: the own wavefront's columns ahead of the barrier, rows finished one after the other so that sums meet behind
+// products, 32 columns a lane in four accumulators, and the two wavefronts of a SIMD half a step apart with two barriers a
+// step (1254 to 1480 cycles).
 //   WAIT   pre arrives in chunks from another workgroup (progress in *arrived)
 //   POST   out is handed on to another workgroup (progress in *done: wavefronts x chunks)
 template <int C, bool WAIT, bool POST>
@@ -559,7 +574,7 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
     const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc(out, (uint32_t)T * C * 4);
     const int my_gate = (s * C + u) * 4;
     // this unit's place in a row of the state; the quad's other lanes write to the row's unused places
-    const int h_out = s == 0 ? (u / kSeg) * kSegPitch + u % kSeg : (u % 8) * kSegPitch + kSeg + s;
+    const int h_out = s == 0 ? RecurrenceLds<C>::place(u) : (u % 8) * kSegPitch + kSeg + s;
     if (tid < kRow) lds.h[2 * kSteps - 1][tid] = 0.f;          // "the step before the first"
     int seen = 0, ahead = 0;
     float next[kSteps];
@@ -577,9 +592,12 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
         constexpr int kOwn = kSteps / 4;
         static_assert(kOwn == 1 || kOwn == 2, "states of a chunk per thread");
         const int step = kOwn * tid / C, unit = kOwn * tid % C, at = ((c * kSteps + step) * C + unit) * 4;
-        const float *from = &lds.h[(c & 1) * kSteps + step][(unit / kSeg) * kSegPitch + unit % kSeg];
-        if constexpr (kOwn == 1) store_f32<POST ? kAgent : 0>(out_rsrc, at, *from);
-        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, *reinterpret_cast<const f32x2 *>(from)), out_rsrc, at, 0, POST ? kAgent : 0);
+        const float *from = lds.h[(c & 1) * kSteps + step];
+        if constexpr (kOwn == 1) store_f32<POST ? kAgent : 0>(out_rsrc, at, from[RecurrenceLds<C>::place(unit)]);
+        else {
+            const f32x2 v{from[RecurrenceLds<C>::place(unit)], from[RecurrenceLds<C>::place(unit + 1)]};
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), out_rsrc, at, 0, POST ? kAgent : 0);
+        }
     };
     // a wavefront's part of one more chunk of states has left for good
     auto post = [&]() {
@@ -602,14 +620,14 @@ __device__ __forceinline__ void lstm_layer(const float *__restrict__ pre, const 
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) acc[j] = fmaf(w[j][k + e], hv[e], acc[j]);
+                for (int j = 0; j < 8; ++j) acc[j] = fmaf(w[j][k + e], hv[(e + 1) & 3], acc[j]);   // see place()
         }
         // lane ^ 7 (mirrored halves) holds the row in the slot ^ 7; then the quad
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] += quad<kHalfMirror>(acc[j ^ 7]);
         const float z = (acc[0] + quad<kXor1>(acc[1])) + quad<kXor2>(acc[2] + quad<kXor1>(acc[3]));
         const float a = gate_value(z, mine);
-        cell = fma_of_gate1(a, cell, a * quad<0xAA>(a));      // the state of the quad's lane 0; what the others hold is not read
+        cell = next_cell(a, cell);                             // the state of the quad's lane 0; what the others hold is not read
         row[h_out] = quad<0xFF>(a) * gate_value(cell, of_cell);
         h_in = row + l8 * kSegPitch;
         row += kRow;
