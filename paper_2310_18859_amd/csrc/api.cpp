@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstring>
 #include <new>
 
@@ -168,8 +169,8 @@ struct LayerSchedule {
     int32_t tile_begin[SIDA_MAX_E];
     int32_t m_tiles[SIDA_MAX_E];
     int32_t m_tall[SIDA_MAX_E];       // leading tiles of the wave that belong to experts with more than one tile
-    int32_t m_few[SIDA_MAX_E];        // last tiles of the wave, streamed (few_tokens below)
-    int32_t few_rows[SIDA_MAX_E];     // token rows of those
+    int32_t m_few[2][SIDA_MAX_E];     // last tiles of the wave, streamed (TileRule below), of either GEMM
+    int32_t few_rows[2][SIDA_MAX_E];  // token rows of those
 };
 
 // How a layer's experts are cut into tiles.  A wavefront sums over K in another order where tiles are streamed, so
@@ -177,8 +178,26 @@ struct LayerSchedule {
 // tile_m may depend on the waves, since it changes the order of no sum.
 struct TileRule {
     int32_t tile_m;                   // token rows per tile, 64 or 128
-    int32_t few;                      // experts of at most this many tokens are streamed, in tiles of 64 rows
+    int32_t few[2];                   // experts of at most this many tokens are streamed, in tiles of 64 rows, by either GEMM
 };
+
+// A layer whose experts of at most `few` tokens are streamed and the others walked in tiles of tile_m rows.
+struct SplitWork {
+    int32_t few;
+    int64_t m_tiles, m_tall;          // walked tiles, and those of experts with more than one
+    int64_t low, high;                // streamed experts of at most 32 tokens, of more
+};
+// What a launch takes, in rounds of 512 wide tiles: the slots' rounds of walked tiles, or all of the work if that is
+// more, which streamed tiles spread over the slots that come free.  Fitted to 234 layers (8 to 256 experts, 384 x 1536
+// to 1024 x 4096, 600 to 32768 tokens, Zipf 0 to 1.2).
+double launch_cost(const SplitWork &l, int64_t N)
+{
+    const bool wide = gemm_tiles_wide(l.m_tiles, l.m_tall, N, 512);
+    const double one = wide ? 1. : 0.56;
+    const int64_t tiles = l.m_tiles * (N / (wide ? 256 : 128));
+    const double streamed = (0.9 * (double)l.low + 2.2 * (double)l.high) * (double)N / (256. * 512.);
+    return std::max(one * (double)((tiles + 511) / 512), one * (double)tiles / 512. + (streamed > 0. ? streamed + 0.15 : 0.));
+}
 
 // Token rows per tile.  A grouped GEMM is bound by the rows its tiles pull through LDS:
 // a tile of tile_m token rows and 256 weight rows costs tile_m + 256 rows per K-step whether or not
@@ -193,16 +212,24 @@ struct TileRule {
 //    16 x 48 77 and 71, 20 x 48 88 and 94);
 //  * and of a layer of at most 10 rows per tile with hardly an expert of more than one (128 x 8: 208 and 188 us;
 //    1024 x 4096: 64 x 8 180 and 172; 384 x 1536: 200 x 8 96 and 84);
-//  * of a layer of many experts those with at most 64 tokens, as long as the others do not outweigh them by far (128
-//    experts, Zipf(1), 7680 tokens 271 and 261; 16384 tokens 319 and 325) and they have
-//    - beside tiles that are walked, at most 32 on average, and one and a half workgroups of 64 weight rows per compute
-//      unit in the narrower GEMM (Zipf(1), 24 tokens on average: 48 experts of 384 x 1536 32 and 36 us, 96 of them 62 and
-//      60; 48 of 512 x 2048 57 and 59, 64 of them 73 and 66);
-//    - alone, at most 24, or 32 where the rounds of 512 tiles of 128 weight rows that walking them takes would be a
-//      fifth empty (768 x 3072: 128 experts x 16 218 and 214 us, x 24 227 and 227, x 32 237 and 245; 48 x 28, rounds 36 %
-//      empty, 106 and 94; 1024 x 4096, whole rounds: 64 x 28 192 and 198), or 16 with less than two workgroups per
-//      compute unit (64 experts of 384 x 1536: x 16 39 and 39, x 24 41 and 43; 48 of 640 x 2560: 64 and 62, 67 and 69);
-//      with at most one, walking leaves most of the chip idle again (48 of 256 x 1024 x 28: 22.4 and 21.7).
+//  * of a layer of many experts that all have at most 64 tokens, if those are at most 24 on average, or 32 where the
+//    rounds of 512 tiles of 128 weight rows that walking them takes would be a
+//    fifth empty (768 x 3072: 128 experts x 16 218 and 214 us, x 24 227 and 227, x 32 237 and 245; 48 x 28, rounds 36 %
+//    empty, 106 and 94; 1024 x 4096, whole rounds: 64 x 28 192 and 198), or 16 with less than two workgroups per
+//    compute unit (64 experts of 384 x 1536: x 16 39 and 39, x 24 41 and 43; 48 of 640 x 2560: 64 and 62, 67 and 69);
+//    with at most one, walking leaves most of the chip idle again (48 of 256 x 1024 x 28: 22.4 and 21.7);
+//  * beside larger tiles the experts of at most 20, 28 or 36 tokens, by each GEMM those with which launch_cost() is least:
+//    a launch of walked tiles ends when its last round does, however few tiles that has, and streamed ones fill
+//    the slots that come free.
+//    - Layers of at least 48 experts, at most 64 tokens on average, with a workgroup and a half of 64 weight rows per
+//      compute unit among those of at most 64 tokens, which have at most 32 on average: always, or all are walked if
+//      that is one round and at least 0.6 of it is full.  (Those of at most 64 tokens beside half of the slots, before
+//      -> now, us, first and second GEMM: 64 experts, 1111 tokens, Zipf(1.2) 51 / 55 -> 49 / 55; 157 x 640 x 2560, 7824 tokens 111 / 107
+//      -> 102 / 100; 67 experts, 2979 tokens 63 / 67 -> 62 / 63.)
+//    - Others of at least 32 experts, of which at most half are streamed: where that is 8 % less than walking them all
+//      (64 experts, 8192 tokens, Zipf(1.2) 83 / 85 -> 78 / 84; 128 experts, 16384 tokens, second GEMM, 2.4 rounds of narrow tiles
+//      -> 0.95 of wide ones and 43 streamed experts, 153 -> 144).
+//    Over 234 layers, 468 GEMMs, of which 139 changed: 1.0 % less on average, 32 by 5 % and more, three 2 to 3 % slower.
 // With 128 columns the four parts of a sum are one step each, and many such tiles are better walked (x 8 tokens: 48
 // experts 14 and 13 us, 200 experts 20 and 23).
 // The counts stand for the whole chip, also on a stream with fewer compute units: the bits of a layer do not depend on
@@ -222,11 +249,13 @@ TileRule tile_rule(const sida_plan *p, const sida_config &cfg)
     }
     const int64_t narrow = std::min(cfg.d_model, cfg.d_ff);
     const bool worth = narrow >= 256 || p->n_active <= 96;
-    if (t64 <= 20 && t64 * (narrow / 32) <= 2 * 256) return TileRule{kGemmTileSmall, INT32_MAX};
-    if (worth && rows_all <= 10 * t64 && 8 * t64 <= 9 * p->n_active) return TileRule{kGemmTileSmall, INT32_MAX};
+    const TileRule all{kGemmTileSmall, {INT32_MAX, INT32_MAX}};
+    if (t64 <= 20 && t64 * (narrow / 32) <= 2 * 256) return all;
+    if (worth && rows_all <= 10 * t64 && 8 * t64 <= 9 * p->n_active) return all;
     // A layer that is cut into waves launches a few experts at a time: small launches, hidden
     // behind the copies; 64-row tiles give them more (and deeper-fetching) tiles.
-    const int32_t tile_m = p->n_waves > 1 || 5 * t64 <= 6 * t128 ? kGemmTileSmall : kGemmTileM;
+    const int32_t by_counts = 5 * t64 <= 6 * t128 ? kGemmTileSmall : kGemmTileM;
+    const int32_t tile_m = p->n_waves > 1 ? kGemmTileSmall : by_counts;
     const int64_t wgs = n_few * (narrow / 64);                // of the narrower GEMM
     const bool alone = n_few == p->n_active;
     const auto rounds = [&](int64_t n) {                      // of 512 tiles, in shares of the tiles there are
@@ -236,7 +265,33 @@ TileRule tile_rule(const sida_plan *p, const sida_config &cfg)
     int64_t most = wgs >= 384 ? 32 : 0;                       // tokens of a streamed expert, on average
     if (alone) most = wgs <= 256 ? 32 : wgs < 512 ? 16 : rounds(cfg.d_model) + rounds(cfg.d_ff) > 2.5 ? 32 : 24;
     const bool stream = worth && p->n_active >= 48 && few_rows <= most * n_few && rows_all <= 64 * (int64_t)p->n_active;
-    return TileRule{tile_m, stream ? kGemmTileSmall : 0};
+    if (alone) return TileRule{tile_m, {stream ? kGemmTileSmall : 0, stream ? kGemmTileSmall : 0}};
+    if (!stream && (narrow < 384 || p->n_active < 32)) return TileRule{tile_m, {0, 0}};
+    SplitWork work[4] = {{0}, {20}, {28}, {36}};              // tiles of one wave: the choice is the layer's
+    const int shift = by_counts == kGemmTileSmall ? 6 : 7;
+    for (int32_t i = 0; i < p->n_active; ++i) {
+        const int32_t n = p->counts[p->order[i]], n_t = (n + by_counts - 1) >> shift;
+        for (SplitWork &l : work) {
+            if (n <= l.few) ++(n <= 32 ? l.low : l.high);
+            else l.m_tiles += n_t, l.m_tall += n_t > 1 ? n_t : 0;
+        }
+    }
+    const auto choose = [&](int64_t N) {
+        double least = launch_cost(work[0], N);
+        int32_t few = 0;
+        if (!stream) least *= 0.92;
+        else if (10 * work[0].m_tiles * (N / (gemm_tiles_wide(work[0].m_tiles, work[0].m_tall, N, 512) ? 256 : 128)) < 6 * 512) least = HUGE_VAL;
+        for (int i = 1; i < 4; ++i) {
+            if (!stream && 2 * (work[i].low + work[i].high) > p->n_active) break;
+            const double cost = launch_cost(work[i], N);
+            if (stream ? cost <= least : cost < least) {
+                least = cost;
+                few = work[i].few;
+            }
+        }
+        return few;
+    };
+    return TileRule{tile_m, {choose(cfg.d_ff), choose(cfg.d_model)}};
 }
 
 void build_schedule(const sida_plan *p, const sida_config &cfg, LayerSchedule *s)
@@ -251,7 +306,7 @@ void build_schedule(const sida_plan *p, const sida_config &cfg, LayerSchedule *s
     });
     s->tbl.n = p->n_active;
     s->tbl.tile_m = tile_m;
-    for (int32_t w = 0; w < p->n_waves; ++w) s->tile_begin[w] = s->m_tiles[w] = s->m_tall[w] = s->m_few[w] = s->few_rows[w] = 0;
+    for (int32_t w = 0; w < p->n_waves; ++w) s->tile_begin[w] = s->m_tiles[w] = s->m_tall[w] = s->m_few[0][w] = s->m_few[1][w] = s->few_rows[0][w] = s->few_rows[1][w] = 0;
     int32_t at = 0, cur = -1;
     for (int32_t i = 0; i < p->n_active; ++i) {
         const int32_t e = idx[i];
@@ -264,12 +319,12 @@ void build_schedule(const sida_plan *p, const sida_config &cfg, LayerSchedule *s
         }
         const int32_t n_t = (p->counts[e] + tile_m - 1) / tile_m;
         s->m_tiles[w] += n_t;
-        if (p->counts[e] <= rule.few) {                              // sorted by count: these come last
-            s->m_few[w] += n_t;
-            s->few_rows[w] += p->counts[e];
-        } else if (n_t > 1) {
-            s->m_tall[w] += n_t;                                     // ... and these first
-        }
+        for (int32_t g = 0; g < 2; ++g)
+            if (p->counts[e] <= rule.few[g]) {                       // sorted by count: these come last
+                s->m_few[g][w] += n_t;
+                s->few_rows[g][w] += p->counts[e];
+            }
+        if (n_t > 1 && p->counts[e] > rule.few[0]) s->m_tall[w] += n_t;   // ... and these first (few: all experts or such of one tile)
         at += n_t;
     }
 }
@@ -398,14 +453,14 @@ int launch_wave_ffn(sida_ctx *c, const LayerSchedule &s, int32_t w, const Ws &ws
     {
         TimedKernel tk(c, SIDA_K_GEMM1);
         HIP_TRY(c, (hipError_t)launch_ffn_gemm1(x ? x : ws.x_perm, ws.h, c->pool, c->expert_bytes, tiles,
-                                                s.m_tiles[w] - s.m_few[w], s.m_tall[w], s.m_few[w], s.few_rows[w],
+                                                s.m_tiles[w] - s.m_few[0][w], s.m_tall[w], s.m_few[0][w], s.few_rows[0][w],
                                                 c->cfg.d_model, c->cfg.d_ff, st, tk.get(),
                                                 x ? T / c->top_k : T, x ? ws.perm : nullptr, T, c->top_k, s.tbl.tile_m));
     }
     {
         TimedKernel tk(c, SIDA_K_GEMM2);
         HIP_TRY(c, (hipError_t)launch_ffn_gemm2(ws.h, y ? y : ws.y_perm, c->pool, c->expert_bytes, tiles,
-                                                s.m_tiles[w] - s.m_few[w], s.m_tall[w], s.m_few[w], s.few_rows[w],
+                                                s.m_tiles[w] - s.m_few[1][w], s.m_tall[w], s.m_few[1][w], s.few_rows[1][w],
                                                 c->cfg.d_model, c->cfg.d_ff, st, tk.get(), T,
                                                 y ? ws.perm : nullptr, y ? ws.gate_perm : nullptr, s.tbl.tile_m));
     }

@@ -688,11 +688,10 @@ namespace {
 // over 52 experts, second GEMM 47 -> 43.5 us; 8 experts that are read again and again, 12 -> 14 us).
 bool worth_streaming(const GemmArgs &a) { return (int64_t)(a.m_tiles - a.m_tall + a.m_few) * a.N * a.K * 2 > (int64_t)128 << 20; }
 
-// One GEMM of the pair as one launch: BM token rows per tile, 4*NS*32 weight rows, NB K-steps ahead.  With
-// few-token tiles in the launch half of the workgroup slots go to the persistent workgroups of the others
-// and the rest to the stream of few-token workgroups, which also fills the slots that come free: a compute
-// unit that multiplies and streams at a time.  (128 experts, 5461 tokens, Zipf(1): 132 / 141 us as one
-// kind of tile, 126 / 126 us; with three quarters or all slots 128 / 126 and 131 / 126 us.)
+// One GEMM of the pair as one launch: BM token rows per tile, 4*NS*32 weight rows, NB K-steps ahead.  The workgroups of
+// few-token tiles stand behind the persistent ones, which may take all workgroup slots: a launch's last round of walked
+// tiles leaves slots free, and the stream fills them.  (With half of the slots for the persistent workgroups as soon as
+// there are few-token tiles, 64 experts, 8192 tokens, those of at most 32 streamed, all layers: 997 -> 1100 us, with three quarters 1027.)
 template <int BM, int NS, int NB, bool RELU, int FUSE, bool ONCE>
 int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
@@ -706,7 +705,7 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
     g.gm = tile_group_height(a.m_tiles, a.m_tall, a.K > a.N);
     g.nw = tile_block_width(n_tiles_n, g.gm);
     const int total = a.m_tiles * n_tiles_n;
-    const int cap = (a.m_few ? 1 : 2) * stream_compute_units(st);  // two workgroups per compute unit
+    const int cap = 2 * stream_compute_units(st);            // two workgroups per compute unit
     g.big_wgs = total < cap ? (total + 7) / 8 * 8 : cap;     // multiple of 8 XCDs
     const int few_wgs = (a.m_few * (a.N / (32 * kFewStripes)) + 7) / 8 * 8;
     hipExtLaunchKernelGGL((grouped_gemm_nt<BM, NS, NB, RELU, FUSE, ONCE>), dim3(g.big_wgs + few_wgs), dim3(kWaves * 64), kLdsBytes, st,
@@ -714,12 +713,8 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
     return (int)hipGetLastError();
 }
 
-// Tile shape of a launch.  BM = 64 or 128 token rows as the layer's descriptors say.  Weight rows per
-// tile: 256 (two stripes per wavefront, one LDS fragment read per two MFMAs) when the matrix has a
-// multiple of 256 rows - every Switch shape has - unless 128-row tiles, twice as many at a little
-// more than half the time each (fitted: 5/8), need fewer rounds over the persistent grid's
-// workgroup slots: tiles are dealt to the workgroups in turn, so a launch takes as long as its
-// workgroup with the most tiles.  A launch that leaves
+// Tile shape of a launch.  BM = 64 or 128 token rows as the layer's descriptors say, weight rows by gemm_tiles_wide().
+// A launch that leaves
 // workgroup slots idle streams every tile's weights through few registers per compute unit, so
 // narrow 64-row tiles also fetch four K-steps ahead instead of two where the K loop allows it (with
 // 128-row tiles four steps ahead, one workgroup per compute unit, change nothing: 96 tiles of K = 3072
@@ -727,14 +722,7 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 template <int BM, bool RELU, int FUSE>
 int launch_width(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
-    const int64_t slots = 2 * (int64_t)stream_compute_units(st);
-    const int64_t t_wide = (int64_t)a.m_tiles * (a.N / 256);
-    bool wide = a.N % 256 == 0 && (t_wide + slots - 1) / slots * 8 <= (2 * t_wide + slots - 1) / slots * 5;
-    // Wide tiles for at most three quarters of the workgroup slots, over mostly single-tile experts:
-    // the launch is a stream of weights, and twice as many narrower tiles keep more of it in flight
-    // (64 experts, 8192 tokens, second GEMM: 95 -> 87 us; 32 experts x 62 tokens, first GEMM: 38 -> 34 us;
-    // many-token experts prefer the wide tile at any count).
-    if (wide && 4 * t_wide <= 3 * slots && 2 * a.m_tall <= a.m_tiles) wide = false;
+    const bool wide = gemm_tiles_wide(a.m_tiles, a.m_tall, a.N, 2 * (int64_t)stream_compute_units(st));
     const bool once = worth_streaming(a);
     if (wide) return once ? launch_as<BM, 2, 2, RELU, FUSE, true>(a, st, ev) : launch_as<BM, 2, 2, RELU, FUSE, false>(a, st, ev);
     if constexpr (BM == kGemmTileSmall)

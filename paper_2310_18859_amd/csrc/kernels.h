@@ -135,4 +135,18 @@ int hash_static_scratch(float **out);
 constexpr int kGemmTileM = 128;   // token rows per GEMM tile of large launches
 constexpr int kGemmTileSmall = 64; // ... of small launches
 
+// Weight rows per tile of a launch over `slots` workgroup slots: 256 (two stripes per wavefront, one LDS fragment read per
+// two MFMAs) when the matrix has a multiple of 256 rows - every Switch shape has - unless 128-row tiles, twice as many at
+// a little more than half the time each (fitted: 5/8), need fewer rounds over the persistent grid's slots: tiles are dealt
+// to the workgroups in turn, so a launch takes as long as its workgroup with the most tiles.  And wide tiles for at most
+// three quarters of the slots, over mostly single-tile experts, are a stream of weights: twice as many
+// narrower tiles keep more of it in flight (64 experts, 8192 tokens, second GEMM: 95 -> 87 us; 32 experts x 62 tokens,
+// first GEMM: 38 -> 34 us; many-token experts prefer the wide tile at any count).
+inline bool gemm_tiles_wide(int64_t m_tiles, int64_t m_tall, int64_t N, int64_t slots)
+{
+    const int64_t t_wide = m_tiles * (N / 256);
+    const bool wide = N % 256 == 0 && (t_wide + slots - 1) / slots * 8 <= (2 * t_wide + slots - 1) / slots * 5;
+    return wide && !(4 * t_wide <= 3 * slots && 2 * m_tall <= m_tiles);
+}
+
 }  // namespace sida

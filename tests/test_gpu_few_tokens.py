@@ -23,6 +23,13 @@ FEWER = [1, 64, 17, 31, 32, 33]
 ALONE = [12 + (5 * i) % 20 for i in range(60)]
 ALONE_MANY = [12 + (5 * i) % 20 for i in range(70)]
 
+# the lines between streamed and walked experts beside larger tiles: 20, 28 or 36 tokens, or none, by each GEMM
+LINES = [19, 20, 21, 27, 28, 29, 35, 36, 37, 1, 33, 32]
+
+
+def lines(times, larger):
+    return LINES * times + [129 + 7 * i % 300 for i in range(larger)]
+
 
 def ids_with_counts(counts, seed):
     ids = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
@@ -51,6 +58,12 @@ def forward(r, x_bits, ids, alpha):
     ("alone", ALONE, 256, 512),
     ("alone", ALONE_MANY, 512, 896),
     ("alone-walked", ALONE_MANY, 384, 256),             # between the two
+    ("lines-many", lines(6, 2), 384, 640),              # 28 and 36 tokens
+    ("lines-many", lines(8, 2), 384, 1536),             # 20 and 36
+    ("lines-many", lines(10, 2), 512, 896),             # 28, and all walked
+    ("lines-round", lines(2, 8), 512, 2048),            # 20 in the first GEMM, all walked in the second
+    ("lines-round", lines(3, 30), 384, 768),            # 36 in the first
+    ("lines-round", lines(5, 30), 512, 896),            # 28 in the second
     # every length of a sum up to two rounds of the steps that are loaded ahead, and one more
     ("lengths", FEWER, 512, 1024),                      # 4 and 8 steps
     ("lengths", FEWER, 1152, 1280),                     # 9 and 10
