@@ -890,6 +890,48 @@ __global__ __launch_bounds__(512) void hash_attention(const float *__restrict__ 
 // takes TT*16 tokens and one layer: all operands go to LDS at once, its four wavefronts make NT tiles of
 // 16 experts in turn (matrix product, experts as rows), hand the logits over in LDS, and then take a
 // token per 16 lanes with NT logits in each lane's registers.
+// The k most probable experts of a token: 16 lanes hold its logits, NT each (experts col, col + 16, ...).
+template <int NT>
+__device__ __forceinline__ void best_experts(const float *row, int l, int n, int n_tokens, int E, int top_k, int col,
+                                             int32_t *__restrict__ ids, float *__restrict__ alpha)
+{
+    float z[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) z[i] = i * 16 + col < E ? row[i * 16 + col] : -FLT_MAX;
+    float mx = -FLT_MAX, sum = 0.f;
+    for (int j = 0; j < top_k; ++j) {
+        // Largest remaining logit (NaN is none), ties to the lower expert id: the largest first and then whose it is, which
+        // takes half of the instructions that carrying both along does (8192 tokens, 6 layers of 128 experts 21.2 -> 19.8
+        // us, 2664 tokens 10.6 -> 9.9).
+        float best = -FLT_MAX;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) best = fmaxf(best, z[i]);
+        best = row_max(best);
+        int arg = E;
+#pragma unroll
+        for (int i = NT - 1; i >= 0; --i) arg = z[i] == best ? i * 16 + col : arg;
+        arg = best > -FLT_MAX ? arg : E;
+        arg = min(arg, dpp<kXor1>(arg));
+        arg = min(arg, dpp<kXor2>(arg));
+        arg = min(arg, dpp<kHalfMirror>(arg));
+        arg = min(arg, dpp<kMirror>(arg));
+        if (j == 0) {
+            mx = best;
+#pragma unroll
+            for (int i = 0; i < NT; ++i) sum += __expf(z[i] - mx);         // an expert that is not there adds nothing
+            sum = row_sum(sum);
+        }
+        if (col == 0 && n < n_tokens) {
+            const size_t at = ((size_t)l * n_tokens + n) * top_k + j;
+            ids[at] = arg < E ? arg : 0;
+            alpha[at] = __expf(best - mx) / sum;
+        }
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+            if (i * 16 + col == arg) z[i] = -FLT_MAX;                      // taken
+    }
+}
+
 template <int C, int NT, int TT>
 constexpr int heads_lds_bytes() { return C / 32 * (NT + TT) * 16 * TileRow<float>::kBytes; }
 
@@ -997,45 +1039,8 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
     __syncthreads();
 #pragma unroll 1
     for (int m = 0; m < TT; ++m) {
-        const int tok = m * 16 + wv * 4 + g, n = n0 + tok;
-        float z[NT];                                           // logits of experts col, col + 16, ...
-#pragma unroll
-        for (int i = 0; i < NT; ++i) z[i] = i * 16 + col < E ? logit[tok * kPitch + i * 16 + col] : -FLT_MAX;
-        float mx = -FLT_MAX, sum = 0.f;
-        for (int j = 0; j < top_k; ++j) {
-            // largest remaining logit, ties to the lower expert id
-            float best = -FLT_MAX;
-            int arg = E;
-#pragma unroll
-            for (int i = 0; i < NT; ++i)
-                if (z[i] > best) {
-                    best = z[i];
-                    arg = i * 16 + col;
-                }
-            auto meet = [&](float ob, int oa) {
-                const bool other = ob > best || (ob == best && oa < arg);
-                best = other ? ob : best;
-                arg = other ? oa : arg;
-            };
-            meet(quad<kXor1>(best), dpp<kXor1>(arg));
-            meet(quad<kXor2>(best), dpp<kXor2>(arg));
-            meet(quad<kHalfMirror>(best), dpp<kHalfMirror>(arg));
-            meet(quad<kMirror>(best), dpp<kMirror>(arg));
-            if (j == 0) {
-                mx = best;
-#pragma unroll
-                for (int i = 0; i < NT; ++i) sum += __expf(z[i] - mx);     // an expert that is not there adds nothing
-                sum = row_sum(sum);
-            }
-            if (col == 0 && n < n_tokens) {
-                const size_t at = ((size_t)l * n_tokens + n) * top_k + j;
-                ids[at] = arg < E ? arg : 0;
-                alpha[at] = __expf(best - mx) / sum;
-            }
-#pragma unroll
-            for (int i = 0; i < NT; ++i)
-                if (i * 16 + col == arg) z[i] = -FLT_MAX;                  // taken
-        }
+        const int tok = m * 16 + wv * 4 + g;
+        best_experts<NT>(logit + tok * kPitch, l, n0 + tok, n_tokens, E, top_k, col, ids, alpha);
     }
 }
 
