@@ -1044,6 +1044,114 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
     }
 }
 
+// The same for many tokens and layers, all products through bf16 parts.  Above, a workgroup fetches and cuts a layer's
+// weights (64 KiB of 128 experts) for 32 tokens, and cutting them takes as long as multiplying: 8192 tokens, 6
+// layers of 128 experts 19.8 us, of which the matrix instructions take 4.  Here WAVES wavefronts keep the layer's weights, cut
+// once, in registers (NT / WAVES tiles of 16 experts each) and walk over tiles of 16 * TT tokens.  A wavefront cuts one
+// 16 x 32 piece of the next tile and puts the parts into LDS in the order in which the matrix instruction takes
+// them, so that nothing is cut twice; the piece behind it is on its way from memory meanwhile.  One barrier a
+// tile: parts and logits have two places each.  17.1 us (5 before the first product), 12 layers of 64 experts 25.0 -> 17.6, 6 layers of
+// 256 experts 45.4 -> 28.5; bits unchanged.
+template <int C, int NT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 2) void hash_heads_walk(const float *__restrict__ r, const float *__restrict__ w_out,
+                                                                 const float *__restrict__ b_out, int E, int top_k, int n_tokens,
+                                                                 int32_t *__restrict__ ids, float *__restrict__ alpha)
+{
+    constexpr int kMine = NT / WAVES, TT = WAVES / 4, kSteps32 = C / 32, kPitch = NT * 16 + 16, kTokens = 16 * TT;
+    static_assert(NT % WAVES == 0 && WAVES % 4 == 0 && kSteps32 <= 4, "tiles and pieces of a wavefront");
+    __shared__ bf16x8 parts[2][TT][kSteps32][3][64];
+    __shared__ __attribute__((aligned(16))) float logit[2][kTokens * kPitch];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15, g = lane >> 4;
+    const int l = blockIdx.y, tiles = (n_tokens + kTokens - 1) / kTokens, stride = gridDim.x;
+    const float *w_l = w_out + (size_t)l * E * C;
+    // this wavefront's piece of a tile: 16 tokens, 32 of the C values
+    const int piece_t = wv >> 2, piece_s = wv & 3;
+    const bool cuts = piece_s < kSteps32;
+    const __amdgpu_buffer_rsrc_t r_rsrc = make_rsrc(r, (uint32_t)n_tokens * C * 4);
+    f32x4 raw[2];
+    auto ask = [&](int tile) {                                 // past the end: zeros
+        const int at = ((tile * kTokens + piece_t * 16 + col) * C + piece_s * 32 + 8 * g) * 4;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) raw[h] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, at + h * 16, 0, 0));
+    };
+    auto cut = [&](int buf) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = raw[e >> 2][e & 3];
+        const Parts p = parts_of(v);
+        parts[buf][piece_t][piece_s][0][lane] = p.hi;
+        parts[buf][piece_t][piece_s][1][lane] = p.mid;
+        parts[buf][piece_t][piece_s][2][lane] = p.lo;
+    };
+    int tile = blockIdx.x;
+    if (cuts) ask(tile);
+    f32x4 bias[kMine];
+    Parts w[kMine][kSteps32];
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        const int first = (i * WAVES + wv) * 16;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias[i][e] = b_out[l * E + min(first + 4 * g + e, E - 1)];
+        const float *row = w_l + (size_t)min(first + col, E - 1) * C + 8 * g;
+#pragma unroll
+        for (int s = 0; s < kSteps32; ++s) {
+            float v[8];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 q = load4_param(row + s * 32 + 4 * h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = q[e];
+            }
+            w[i][s] = parts_of(v);
+        }
+    }
+    if (cuts) {
+        cut(0);
+        ask(tile + stride);
+    }
+    lds_barrier();
+    for (int buf = 0; tile < tiles; tile += stride, buf ^= 1) {
+        f32x4 acc[kMine][TT] = {};
+#pragma unroll
+        for (int s = 0; s < kSteps32; ++s)
+#pragma unroll
+            for (int m = 0; m < TT; ++m) {
+                const Parts x{parts[buf][m][s][0][lane], parts[buf][m][s][1][lane], parts[buf][m][s][2][lane]};
+#pragma unroll
+                for (int i = 0; i < kMine; ++i) acc[i][m] = mfma_parts(w[i][s], x, acc[i][m]);
+            }
+        if (any_overflow(acc)) {
+#pragma unroll 1
+            for (int t = 0; t < kMine * TT; ++t) {
+                const int i = t / TT, m = t % TT;
+                const float *row = w_l + (size_t)min((i * WAVES + wv) * 16 + col, E - 1) * C + 8 * g;
+                const float *token = r + (size_t)min(tile * kTokens + m * 16 + col, n_tokens - 1) * C + 8 * g;
+                f32x4 again = {};
+#pragma unroll 1
+                for (int s = 0; s < kSteps32; ++s)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        again = __builtin_amdgcn_mfma_f32_16x16x4f32(row[s * 32 + e], token[s * 32 + e], again, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < kMine * TT; ++j)
+                    if (j == t) acc[j / TT][j % TT] = where_overflowed(acc[j / TT][j % TT], again);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kMine; ++i)
+#pragma unroll
+            for (int m = 0; m < TT; ++m)
+                *reinterpret_cast<f32x4 *>(&logit[buf][(m * 16 + col) * kPitch + (i * WAVES + wv) * 16 + 4 * g]) = acc[i][m] + bias[i];
+        if (cuts) {
+            cut(buf ^ 1);
+            ask(tile + 2 * stride);
+        }
+        lds_barrier();
+        const int tok = wv * 4 + g;
+        best_experts<NT>(&logit[buf][tok * kPitch], l, tile * kTokens + tok, n_tokens, E, top_k, col, ids, alpha);
+    }
+}
+
 // ---- one call -----------------------------------------------------------------------------------
 // Sequences whose layers run side by side: three workgroups each, or four with the gate pre-activations of layer 1 among
 // them, one per compute unit (a workgroup of the recurrence fills the registers of its compute unit).
@@ -1135,7 +1243,23 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
         else if (sh.E <= 128) heads(std::integral_constant<int, 8>(), tt, dir);
         else heads(std::integral_constant<int, 16>(), tt, dir);
     };
-    if (!direct) heads_of(std::integral_constant<int, 1>(), std::false_type());
+    // Weights cut once pay with more work than that, us, per workgroup and walked: C = 128 128 experts, 6 layers x 4096
+    // tokens 11.6 and 12.1, x 6144 17.2 and 14.6; 12 layers of 64 x 2500 9.4 and 9.9, x 4096 13.5 and 11.5; 3 of 256 x 2500 9.7
+    // and 9.4.  C = 64 6 of 128 x 4096 7.3 and 8.0, x 5500 10.0 and 9.7; 3 of 256 x 2048 6.5 and 6.1.
+    auto walk = [&](auto nt, auto waves) {
+        constexpr int NT = decltype(nt)::value, WAVES = decltype(waves)::value;
+        const int tiles = (N + WAVES * 4 - 1) / (WAVES * 4);
+        const int most = max(1, (WAVES == 4 ? 3 : 1) * 256 / sh.L);        // workgroups of a layer, all resident at a time
+        const int each = (tiles + most - 1) / most;
+        hipLaunchKernelGGL((hash_heads_walk<C, NT, WAVES>), dim3((tiles + each - 1) / each, sh.L), dim3(WAVES * 64), 0, st, r, w_out,
+                           b_out, sh.E, sh.top_k, N, ids, alpha);
+    };
+    const int64_t rows = (int64_t)N * sh.L;
+    const bool walks = direct && N >= 2048 && N < INT32_MAX / (4 * C) && sh.E > 16 && rows >= (sh.E <= 128 ? 32768 : 6144);
+    if (walks && sh.E <= 64) walk(std::integral_constant<int, 4>(), std::integral_constant<int, 4>());
+    else if (walks && sh.E <= 128) walk(std::integral_constant<int, 8>(), std::integral_constant<int, 4>());
+    else if (walks) walk(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
+    else if (!direct) heads_of(std::integral_constant<int, 1>(), std::false_type());
     else if (N >= 2048) heads_of(std::integral_constant<int, 2>(), std::true_type());
     else heads_of(std::integral_constant<int, 1>(), std::true_type());
     if (err) return err;

@@ -43,6 +43,10 @@ def oracle_alpha(params, x, cfg, ids):
     (64, 128, 1, 16, 1, 64, 33),          # as many sequences as have four workgroups each, and one more: gates in parts
     (64, 128, 1, 16, 1, 65, 33),
     (64, 64, 1, 16, 1, 15, 137),          # as few as have three: gates in parts
+    (64, 128, 16, 60, 1, 16, 129),        # heads that keep their weights: 2064 tokens, experts that fill no tile
+    (64, 64, 16, 128, 3, 64, 33),         # ... of two steps of the sum, 2112 tokens
+    (64, 128, 3, 250, 2, 17, 121),        # ... of eight wavefronts, a last tile of 9 of 32 tokens
+    (64, 64, 3, 256, 1, 64, 32),          # ... as few as that
 ])
 def test_parts_against_oracle(d, C, L, E, k, n_seq, T):
     rng = np.random.default_rng(d + T)
@@ -175,10 +179,10 @@ def test_a_small_tanh_keeps_its_bits(C):
 
 @pytest.mark.parametrize("C,n_seq,T", [(128, 1, 40), (128, 16, 128), (64, 70, 31), (128, 90, 69)])
 @pytest.mark.parametrize("where", ["w_in", "w_ih1", "w_ih2", "w_out", "x", "largest"])
-def test_infinities(where, C, n_seq, T):
+def test_infinities(where, C, n_seq, T, L=2, E=16):
     """An infinite weight or embedding gives what sums of 32 bits give: saturated gates, an infinite logit - not NaN."""
     rng = np.random.default_rng(T)
-    d, L, E, k, inf = 64, 2, 16, 2, np.float32(np.inf)
+    d, k, inf = 64, 2, np.float32(np.inf)
     cfg = sm.SidaHashConfig(d, C, L, E, k, T)
     params = make_params(rng, d, C, L, E)
     x_bits = f32_to_bf16_bits(rng.standard_normal((n_seq * T, d)).astype(np.float32))
@@ -210,3 +214,33 @@ def test_infinities(where, C, n_seq, T):
     if where == "w_out":                                                   # the infinite logit is the largest
         for l, e in ((0, 3), (1, 5)):
             assert (ids[l, np.isnan(want[l, :, 0]), 0] == e).all()
+
+
+@pytest.mark.parametrize("C,L,E", [(128, 16, 20), (64, 16, 100), (128, 3, 200)])
+@pytest.mark.parametrize("where", ["w_out", "x"])
+def test_infinities_in_heads_that_keep_their_weights(where, C, L, E):
+    test_infinities(where, C, 16, 129, L, E)
+
+
+@pytest.mark.parametrize("C,L,E,n_seq,T", [(128, 2, 40, 2, 9), (128, 1, 100, 16, 128), (64, 16, 100, 64, 33), (128, 3, 250, 17, 121)])
+def test_equal_logits(C, L, E, n_seq, T):
+    """Experts of the same weights have the same logits: the lower id comes first.  Of a logit that is no number or -inf
+    nothing is chosen, as long as there are others."""
+    rng = np.random.default_rng(E)
+    d, k, apart = 64, 3, 17
+    cfg = sm.SidaHashConfig(d, C, L, E, k, T)
+    params = make_params(rng, d, C, L, E)
+    w, b = params["w_out"].reshape(L, E, C), params["b_out"].reshape(L, E)
+    w[:] = w[:, np.arange(E) % apart]
+    b[:] = b[:, np.arange(E) % apart]
+    b[:, 3] = np.nan
+    b[:, 5::apart] = -np.inf
+    x_bits = f32_to_bf16_bits(rng.standard_normal((n_seq * T, d)).astype(np.float32))
+    ids, alpha = run_hash(cfg, params, x_bits, n_seq, T)
+    first = ids[..., 0]
+    assert np.isin(first % apart, [e for e in range(apart) if e != 5]).all()
+    least = np.where(first % apart == 3, 3 + apart, first % apart)
+    assert np.array_equal(first, least)
+    assert np.array_equal(ids[..., 1], first + apart)              # its double
+    third = first + 2 * apart
+    assert np.array_equal(ids[..., 2][third < E], third[third < E])
