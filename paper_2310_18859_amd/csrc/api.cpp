@@ -184,7 +184,7 @@ struct TileRule {
 // A layer whose experts of at most `few` tokens are streamed and the others walked in tiles of tile_m rows.
 struct SplitWork {
     int32_t few;
-    int64_t m_tiles, m_tall;          // walked tiles, and those of experts with more than one
+    int64_t m_tiles;                  // walked tiles
     int64_t low, high;                // streamed experts of at most 32 tokens, of more
 };
 // What a launch takes, in rounds of 512 wide tiles: the slots' rounds of walked tiles, or all of the work if that is
@@ -192,7 +192,7 @@ struct SplitWork {
 // to 1024 x 4096, 600 to 32768 tokens, Zipf 0 to 1.2).
 double launch_cost(const SplitWork &l, int64_t N)
 {
-    const bool wide = gemm_tiles_wide(l.m_tiles, l.m_tall, N, 512);
+    const bool wide = gemm_tiles_wide(l.m_tiles, N, 512);
     const double one = wide ? 1. : 0.56;
     const int64_t tiles = l.m_tiles * (N / (wide ? 256 : 128));
     const double streamed = (0.9 * (double)l.low + 2.2 * (double)l.high) * (double)N / (256. * 512.);
@@ -273,14 +273,14 @@ TileRule tile_rule(const sida_plan *p, const sida_config &cfg)
         const int32_t n = p->counts[p->order[i]], n_t = (n + by_counts - 1) >> shift;
         for (SplitWork &l : work) {
             if (n <= l.few) ++(n <= 32 ? l.low : l.high);
-            else l.m_tiles += n_t, l.m_tall += n_t > 1 ? n_t : 0;
+            else l.m_tiles += n_t;
         }
     }
     const auto choose = [&](int64_t N) {
         double least = launch_cost(work[0], N);
         int32_t few = 0;
         if (!stream) least *= 0.92;
-        else if (10 * work[0].m_tiles * (N / (gemm_tiles_wide(work[0].m_tiles, work[0].m_tall, N, 512) ? 256 : 128)) < 6 * 512) least = HUGE_VAL;
+        else if (10 * work[0].m_tiles * (N / (gemm_tiles_wide(work[0].m_tiles, N, 512) ? 256 : 128)) < 6 * 512) least = HUGE_VAL;
         for (int i = 1; i < 4; ++i) {
             if (!stream && 2 * (work[i].low + work[i].high) > p->n_active) break;
             const double cost = launch_cost(work[i], N);
