@@ -13,15 +13,15 @@
 //   hash_dense      c0 = x W_in^T + b, and again for layer 1's gate pre-activations (or in the next launch)
 //   hash_recurrence both LSTM layers at once, layer 2 a few steps behind layer 1
 //   hash_attention  scores, SparseMax, weighted sum and residual, for blocks of 16 queries
-//   hash_heads      logits, SoftMax and the k best, for blocks of tokens and a MoE layer each
+//   hash_heads      logits, SoftMax and the k best, for blocks of tokens and a MoE layer each (or hash_heads_walk)
 // The contractions run on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32, twice the rate of
 // scalar-per-lane fp32 multiply-adds), or on the bf16 one with the values in exact parts (hash_dense, Parts); with the
 // weights as the first operand a lane ends up with four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
 // It is what bounds a call: 0.55 us a time step at C = 128, see lstm_layer.  Measured against one launch per layer and
 // stage on the vector units (d = 768, C = 128, 6 x 128 experts; calls of perf/cases.py, inputs changing): 1 sequence of
-// 128 tokens 375 -> 108 us, 8 of 333 tokens (top-3) 1059 -> 249 us, 64 of 128 tokens 609 -> 141 us (one batch called again
-// and again 148 to 153).
+// 128 tokens 375 -> 107 us, 8 of 333 tokens (top-3) 1059 -> 243 us, 64 of 128 tokens 609 -> 136 us (one batch called again
+// and again 147).
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
