@@ -5,6 +5,7 @@
 #include <cstdint>
 
 #include "lds_grant.h"
+#include "tile_rule.h"
 
 namespace sida {
 
@@ -131,27 +132,5 @@ int launch_hash_forward(const HashShape &sh, const float *params, const void *x,
 // (kHashStaticScratchBytes bytes, 256-byte aligned); looked up once per device.  Returns a hipError_t.
 constexpr size_t kHashStaticScratchBytes = size_t(16) << 20;
 int hash_static_scratch(float **out);
-
-constexpr int kGemmTileM = 128;   // token rows per GEMM tile of large launches
-constexpr int kGemmTileSmall = 64; // ... of small launches
-
-// Weight rows per tile of a launch over `slots` workgroup slots, where the matrix has a multiple of 256: 256 (two stripes
-// per wavefront, one LDS fragment read per two MFMAs, the token rows fetched half as often) or 128, twice as many at a
-// little more than half the time each.  Tiles are dealt to the workgroups in turn, so what counts is how full the rounds are that 128-row
-// tiles take.  Time of wide over narrow of some 200 GEMMs (layers of
-// 16 to 256 experts, 600 to 32768 tokens, 384 x 1536 to 1024 x 4096), by those rounds:
-//   below 0.5    1.0 - 1.5   half of the slots idle, or more
-//   0.75 - 0.92  0.90 - 1.06, 0.977 on average
-//   1.0 - 1.45   0.93 - 1.15  a second round of few tiles ends sooner than one round of wide ones
-//   1.45 - 2     0.87 - 1.02
-//   2.0 - 2.2    0.93 - 1.02
-//   above        0.88 - 1.00, 0.93 on average (three above 1.04 of 47)
-// (Taken by whole rounds, as before, 2.2 to 3 rounds were walked narrow: 34 experts, 29171 tokens, second GEMM 168 us and
-// 148; 69 experts, 18073 tokens of 1024 x 4096 222 and 203; and 1.1 to 1.45 wide: 44 experts, 5918 tokens 132 and 121.)
-inline bool gemm_tiles_wide(int64_t m_tiles, int64_t N, int64_t slots)
-{
-    const int64_t narrow = 100 * m_tiles * (N / 128);
-    return N % 256 == 0 && (narrow >= 145 * slots || (narrow >= 77 * slots && narrow <= 92 * slots));
-}
 
 }  // namespace sida

@@ -1,0 +1,154 @@
+// How the experts of a layer are cut into tiles of the grouped GEMMs, which of them are streamed, and how wide a launch's
+// tiles are.  Plain integer and double arithmetic, without HIP, so that the rules can be checked without a GPU.
+#pragma once
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+namespace sida {
+
+constexpr int kGemmTileM = 128;   // token rows per GEMM tile of large launches
+constexpr int kGemmTileSmall = 64; // ... of small launches
+
+// Weight rows per tile of a launch over `slots` workgroup slots, where the matrix has a multiple of 256: 256 (two stripes
+// per wavefront, one LDS fragment read per two MFMAs, the token rows fetched half as often) or 128, twice as many at a
+// little more than half the time each.  Tiles are dealt to the workgroups in turn, so what counts is how full the rounds are that 128-row
+// tiles take.  Time of wide over narrow of some 200 GEMMs (layers of
+// 16 to 256 experts, 600 to 32768 tokens, 384 x 1536 to 1024 x 4096), by those rounds:
+//   below 0.5    1.0 - 1.5   half of the slots idle, or more
+//   0.75 - 0.92  0.90 - 1.06, 0.977 on average
+//   1.0 - 1.45   0.93 - 1.15  a second round of few tiles ends sooner than one round of wide ones
+//   1.45 - 2     0.87 - 1.02
+//   2.0 - 2.2    0.93 - 1.02
+//   above        0.88 - 1.00, 0.93 on average (three above 1.04 of 47)
+// (Taken by whole rounds, as before, 2.2 to 3 rounds were walked narrow: 34 experts, 29171 tokens, second GEMM 168 us and
+// 148; 69 experts, 18073 tokens of 1024 x 4096 222 and 203; and 1.1 to 1.45 wide: 44 experts, 5918 tokens 132 and 121.)
+inline bool gemm_tiles_wide(int64_t m_tiles, int64_t N, int64_t slots)
+{
+    const int64_t narrow = 100 * m_tiles * (N / 128);
+    return N % 256 == 0 && (narrow >= 145 * slots || (narrow >= 77 * slots && narrow <= 92 * slots));
+}
+
+// How a layer's experts are cut into tiles.  A wavefront sums over K in another order where tiles are streamed, so
+// `few` depends on the token counts and the experts' size alone: a layer gives the same bits in one wave as in many.
+// tile_m may depend on the waves, since it changes the order of no sum.
+struct TileRule {
+    int32_t tile_m;                   // token rows per tile, 64 or 128
+    int32_t few[2];                   // experts of at most this many tokens are streamed, in tiles of 64 rows, by either GEMM
+};
+
+// A layer whose experts of at most `few` tokens are streamed and the others walked in tiles of tile_m rows.
+struct SplitWork {
+    int32_t few;
+    int64_t m_tiles;                  // walked tiles
+    int64_t low, high;                // streamed experts of at most 32 tokens, of more
+};
+// What a launch takes, in rounds of 512 wide tiles: the slots' rounds of walked tiles, or all of the work if that is
+// more, which streamed tiles spread over the slots that come free.  Fitted to 234 layers (8 to 256 experts, 384 x 1536
+// to 1024 x 4096, 600 to 32768 tokens, Zipf 0 to 1.2).
+inline double launch_cost(const SplitWork &l, int64_t N)
+{
+    const bool wide = gemm_tiles_wide(l.m_tiles, N, 512);
+    const double one = wide ? 1. : 0.56;
+    const int64_t tiles = l.m_tiles * (N / (wide ? 256 : 128));
+    const double streamed = (0.9 * (double)l.low + 2.2 * (double)l.high) * (double)N / (256. * 512.);
+    return std::max(one * (double)((tiles + 511) / 512), one * (double)tiles / 512. + (streamed > 0. ? streamed + 0.15 : 0.));
+}
+
+// Token rows per tile.  A grouped GEMM is bound by the rows its tiles pull through LDS:
+// a tile of tile_m token rows and 256 weight rows costs tile_m + 256 rows per K-step whether or not
+// all its token rows exist.  64-row tiles pay when most experts have at most 64 tokens, i.e. when
+// halving the tile height adds few tiles: tiles(64) * 320 <= tiles(128) * 384.  (Measured on the
+// Switch-base-128 shape: 64-row tiles are 8-10 % faster at 8-16 tokens per expert, even at 64, and
+// 6 % slower at 128 tokens per expert.)
+// Streamed (see grouped_ffn.hip) are
+//  * all tiles of a layer of few tiles, where walking them leaves most compute units idle - up to 20, and up to two
+//    stripes of 32 weight rows per compute unit (256 of them) in the narrower GEMM (768 x 3072, walked and streamed:
+//    16 experts x 8 tokens 67 and 56 us a layer, 20 x 48 58 and 57; 32 tiles of 64 rows 56 and 67; 1024 x 4096:
+//    16 x 48 77 and 71, 20 x 48 88 and 94);
+//  * and of a layer of at most 10 rows per tile with hardly an expert of more than one (128 x 8: 208 and 188 us;
+//    1024 x 4096: 64 x 8 180 and 172; 384 x 1536: 200 x 8 96 and 84);
+//  * of a layer of many experts that all have at most 64 tokens, if those are at most 24 on average, or 32 where the
+//    rounds of 512 tiles of 128 weight rows that walking them takes would be a
+//    fifth empty (768 x 3072: 128 experts x 16 218 and 214 us, x 24 227 and 227, x 32 237 and 245; 48 x 28, rounds 36 %
+//    empty, 106 and 94; 1024 x 4096, whole rounds: 64 x 28 192 and 198), or 16 with less than two workgroups per
+//    compute unit (64 experts of 384 x 1536: x 16 39 and 39, x 24 41 and 43; 48 of 640 x 2560: 64 and 62, 67 and 69);
+//    with at most one, walking leaves most of the chip idle again (48 of 256 x 1024 x 28: 22.4 and 21.7);
+//  * beside larger tiles the experts of at most 20, 28 or 36 tokens, by each GEMM those with which launch_cost() is least:
+//    a launch of walked tiles ends when its last round does, however few tiles that has, and streamed ones fill
+//    the slots that come free.
+//    - Layers of at least 48 experts, at most 64 tokens on average, with a workgroup and a half of 64 weight rows per
+//      compute unit among those of at most 64 tokens, which have at most 32 on average: always, or all are walked if
+//      that is one round and at least 0.6 of it is full.  (Those of at most 64 tokens beside half of the slots, before
+//      -> now, us, first and second GEMM: 64 experts, 1111 tokens, Zipf(1.2) 51 / 55 -> 49 / 55; 157 x 640 x 2560, 7824 tokens 111 / 107
+//      -> 102 / 100; 67 experts, 2979 tokens 63 / 67 -> 62 / 63.)
+//    - Others of at least 32 experts, of which at most half are streamed: where that is 8 % less than walking them all
+//      (64 experts, 8192 tokens, Zipf(1.2) 83 / 85 -> 78 / 84; 128 experts, 16384 tokens, second GEMM, 2.4 rounds of narrow tiles
+//      -> 0.95 of wide ones and 43 streamed experts, 153 -> 144).
+//    Over 234 layers, 468 GEMMs, of which 139 changed: 1.0 % less on average, 32 by 5 % and more, three 2 to 3 % slower.
+// With 128 columns the four parts of a sum are one step each, and many such tiles are better walked (x 8 tokens: 48
+// experts 14 and 13 us, 200 experts 20 and 23).
+// The counts stand for the whole chip, also on a stream with fewer compute units: the bits of a layer do not depend on
+// the stream.
+// counts: tokens of the n activated experts, in any order; in_waves: they run in more than one wave.
+inline TileRule tile_rule(const int32_t *counts, int32_t n_active, int32_t d_model, int32_t d_ff, bool in_waves)
+{
+    int64_t t64 = 0, t128 = 0, n_few = 0, few_rows = 0, rows_all = 0;
+    for (int32_t i = 0; i < n_active; ++i) {
+        const int32_t n = counts[i];
+        rows_all += n;
+        t64 += (n + kGemmTileSmall - 1) / kGemmTileSmall;
+        t128 += (n + kGemmTileM - 1) / kGemmTileM;
+        if (n <= kGemmTileSmall) {
+            ++n_few;
+            few_rows += n;
+        }
+    }
+    const int64_t narrow = std::min(d_model, d_ff);
+    const bool worth = narrow >= 256 || n_active <= 96;
+    const TileRule all{kGemmTileSmall, {INT32_MAX, INT32_MAX}};
+    if (t64 <= 20 && t64 * (narrow / 32) <= 2 * 256) return all;
+    if (worth && rows_all <= 10 * t64 && 8 * t64 <= 9 * n_active) return all;
+    // A layer that is cut into waves launches a few experts at a time: small launches, hidden
+    // behind the copies; 64-row tiles give them more (and deeper-fetching) tiles.
+    const int32_t by_counts = 5 * t64 <= 6 * t128 ? kGemmTileSmall : kGemmTileM;
+    const int32_t tile_m = in_waves ? kGemmTileSmall : by_counts;
+    const int64_t wgs = n_few * (narrow / 64);                // of the narrower GEMM
+    const bool alone = n_few == n_active;
+    const auto rounds = [&](int64_t n) {                      // of 512 tiles, in shares of the tiles there are
+        const int64_t t = n_few * (n / 128);
+        return (double)((t + 511) / 512 * 512) / (double)t;
+    };
+    int64_t most = wgs >= 384 ? 32 : 0;                       // tokens of a streamed expert, on average
+    if (alone) most = wgs <= 256 ? 32 : wgs < 512 ? 16 : rounds(d_model) + rounds(d_ff) > 2.5 ? 32 : 24;
+    const bool stream = worth && n_active >= 48 && few_rows <= most * n_few && rows_all <= 64 * (int64_t)n_active;
+    if (alone) return TileRule{tile_m, {stream ? kGemmTileSmall : 0, stream ? kGemmTileSmall : 0}};
+    if (!stream && (narrow < 384 || n_active < 32)) return TileRule{tile_m, {0, 0}};
+    SplitWork work[4] = {{0}, {20}, {28}, {36}};              // tiles of one wave: the choice is the layer's
+    const int shift = by_counts == kGemmTileSmall ? 6 : 7;
+    for (int32_t i = 0; i < n_active; ++i) {
+        const int32_t n = counts[i], n_t = (n + by_counts - 1) >> shift;
+        for (SplitWork &l : work) {
+            if (n <= l.few) ++(n <= 32 ? l.low : l.high);
+            else l.m_tiles += n_t;
+        }
+    }
+    const auto choose = [&](int64_t N) {
+        double least = launch_cost(work[0], N);
+        int32_t few = 0;
+        if (!stream) least *= 0.92;
+        else if (10 * work[0].m_tiles * (N / (gemm_tiles_wide(work[0].m_tiles, N, 512) ? 256 : 128)) < 6 * 512) least = HUGE_VAL;
+        for (int i = 1; i < 4; ++i) {
+            if (!stream && 2 * (work[i].low + work[i].high) > n_active) break;
+            const double cost = launch_cost(work[i], N);
+            if (stream ? cost <= least : cost < least) {
+                least = cost;
+                few = work[i].few;
+            }
+        }
+        return few;
+    };
+    return TileRule{tile_m, {choose(d_ff), choose(d_model)}};
+}
+
+}  // namespace sida

@@ -1,0 +1,87 @@
+"""How a layer's experts are cut into tiles and which are streamed (csrc/tile_rule.h), checked without a GPU: for layers whose
+time was measured, and for the layers by which the GPU tests stand on either side of the rule's lines."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2310_18859_amd", "csrc")
+ALL, NONE = 2**31 - 1, 0
+
+SOURCE = r"""
+#include "tile_rule.h"
+using namespace sida;
+extern "C" void rule(const int *counts, int n, int d, int F, int in_waves, int *out)
+{
+    const TileRule r = tile_rule(counts, n, d, F, in_waves != 0);
+    out[0] = r.tile_m;
+    out[1] = r.few[0];
+    out[2] = r.few[1];
+}
+extern "C" bool wide(long m_tiles, long N, long slots) { return gemm_tiles_wide(m_tiles, N, slots); }
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tile_rule")
+    src, so = str(d / "rule.cpp"), str(d / "rule.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + CSRC, "-o", so, src], check=True)
+    lib = ctypes.CDLL(so)
+    lib.wide.restype = ctypes.c_bool
+    lib.wide.argtypes = [ctypes.c_long] * 3
+    return lib
+
+
+def pick(lib, counts, d, F, waves=False):
+    """tile_m, and the most tokens of a streamed expert in either GEMM."""
+    out = (ctypes.c_int * 3)()
+    lib.rule((ctypes.c_int * len(counts))(*counts), len(counts), d, F, int(waves), out)
+    return tuple(out)
+
+
+def zipf(E, T, s):
+    """T tokens over E experts, by expected counts."""
+    p = [1. / (i + 1) ** s for i in range(E)]
+    ends = [round(T * sum(p[:i + 1]) / sum(p)) for i in range(E)]
+    return [n for n in (b - a for a, b in zip([0] + ends, ends)) if n]
+
+
+@pytest.mark.parametrize("counts,d,F,want", [
+    ([32] * 8, 768, 3072, (64, ALL, ALL)),                              # few tiles
+    (zipf(128, 512, 0.), 768, 3072, (64, ALL, ALL)),                    # hardly an expert of more than one row block
+    ([20] * 128, 768, 3072, (64, 64, 64)),                              # many experts of few tokens
+    ([48] * 128, 768, 3072, (64, NONE, NONE)),                          # ... of more
+    ([256] * 128, 768, 3072, (128, NONE, NONE)),
+    ([2048] * 8, 768, 3072, (128, NONE, NONE)),
+])
+def test_layers_of_one_kind_of_expert(lib, counts, d, F, want):
+    assert pick(lib, counts, d, F) == want
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_streamed_experts_do_not_depend_on_the_order_or_the_waves(lib, seed):
+    """... which would change the order of sums."""
+    import random
+    rng = random.Random(seed)
+    E, s = rng.randint(8, 256), rng.choice((0., 0.8, 1., 1.2))
+    d, F = rng.choice(((384, 1536), (512, 2048), (640, 2560), (768, 3072), (1024, 4096)))
+    counts = zipf(E, int(E * 2 ** rng.uniform(2, 8)), s)
+    want = pick(lib, counts, d, F)
+    rng.shuffle(counts)
+    assert pick(lib, counts, d, F) == want
+    assert pick(lib, counts, d, F, waves=True) == (64,) + want[1:]
+    assert all(f in (0, 20, 28, 36, 64, ALL) for f in want[1:])
+
+
+@pytest.mark.parametrize("N", [256, 768, 1024, 3072])
+def test_widths(lib, N):
+    """Wide from 0.77 to 0.92 and from 1.45 rounds of narrow tiles on."""
+    for slots in (512, 256, 16):
+        for m in range(1, 2 * slots):
+            r = m * (N // 128) / slots
+            assert lib.wide(m, N, slots) == (0.77 <= r <= 0.92 or r >= 1.45), (m, slots, r)
+    assert not any(lib.wide(m, 640, 512) for m in range(2000))              # not a multiple of 256
