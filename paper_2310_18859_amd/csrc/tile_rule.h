@@ -44,15 +44,22 @@ struct SplitWork {
     int64_t low, high;                // streamed experts of at most 32 tokens, of more
 };
 // What a launch takes, in rounds of 512 wide tiles: the slots' rounds of walked tiles, or all of the work if that is
-// more, which streamed tiles spread over the slots that come free.  Fitted to 234 layers (8 to 256 experts, 384 x 1536
+// more, which streamed tiles spread over the slots that come free.  full: more than 64 tokens per expert, on average, or
+// more than 32 per few-token one.  Fitted to 234 layers (8 to 256 experts, 384 x 1536
 // to 1024 x 4096, 600 to 32768 tokens, Zipf 0 to 1.2).
-inline double launch_cost(const SplitWork &l, int64_t N)
+inline double launch_cost(const SplitWork &l, int64_t N, bool full)
 {
-    const bool wide = gemm_tiles_wide(l.m_tiles, N, 512);
-    const double one = wide ? 1. : 0.56;
-    const int64_t tiles = l.m_tiles * (N / (wide ? 256 : 128));
+    const int64_t tiles = l.m_tiles * (N / 128);              // narrow ones, 0.56 of a wide one each
     const double streamed = (0.9 * (double)l.low + 2.2 * (double)l.high) * (double)N / (256. * 512.);
-    return std::max(one * (double)((tiles + 511) / 512), one * (double)tiles / 512. + (streamed > 0. ? streamed + 0.15 : 0.));
+    const double also = streamed > 0. ? streamed + 0.15 : 0.;
+    if (!gemm_tiles_wide(l.m_tiles, N, 512)) return std::max(0.56 * (double)((tiles + 511) / 512), 0.56 * (double)tiles / 512. + also);
+    const double walked = (double)tiles / 1024.;
+    // Wide tiles for less than half of the slots run alone on their compute units and take little more than half of the
+    // time (second GEMM of 768 x 3072, 0.77 to 0.92 rounds of narrow tiles: 50 to 63 us, a whole round 100), most where they
+    // are full of tokens; the more, the more of the other slots streamed tiles take.
+    const double alone = full ? 0.65 : 0.55;
+    const double round = walked < 0.5 ? alone + (1. - alone) * std::min(1., streamed / (1. - walked)) : std::ceil(walked);
+    return std::max(round, walked + also);
 }
 
 // Token rows per tile.  A grouped GEMM is bound by the rows its tiles pull through LDS:
@@ -78,14 +85,16 @@ inline double launch_cost(const SplitWork &l, int64_t N)
 //    a launch of walked tiles ends when its last round does, however few tiles that has, and streamed ones fill
 //    the slots that come free.
 //    - Layers of at least 48 experts, at most 64 tokens on average, with a workgroup and a half of 64 weight rows per
-//      compute unit among those of at most 64 tokens, which have at most 32 on average: always, or all are walked if
-//      that is one round and at least 0.6 of it is full.  (Those of at most 64 tokens beside half of the slots, before
-//      -> now, us, first and second GEMM: 64 experts, 1111 tokens, Zipf(1.2) 51 / 55 -> 49 / 55; 157 x 640 x 2560, 7824 tokens 111 / 107
-//      -> 102 / 100; 67 experts, 2979 tokens 63 / 67 -> 62 / 63.)
+//      compute unit among those of at most 64 tokens, which have at most 32 on average: always where the narrow tiles of
+//      all experts are less than 0.6 of a round, else where that is no more than walking them all.  (Those of at most 64 tokens beside half of the slots, before -> now, us, first
+//      and second GEMM: 157 experts, 640 x 2560, 7824 tokens 111 / 107 -> 102 / 100; 64 experts, 1111 tokens, Zipf(1.2)
+//      51 / 55 -> 49 / 51; 67 experts, 2979 tokens 63 / 67 -> 62 / 63, the second all walked, as in the layer before.)
 //    - Others of at least 32 experts, of which at most half are streamed: where that is 8 % less than walking them all
-//      (64 experts, 8192 tokens, Zipf(1.2) 83 / 85 -> 78 / 84; 128 experts, 16384 tokens, second GEMM, 2.4 rounds of narrow tiles
+//      (64 experts, 8192 tokens, Zipf(1.2) 83 / 85 -> 78 / 82; 128 experts, 16384 tokens, second GEMM, 2.4 rounds of narrow tiles
 //      -> 0.95 of wide ones and 43 streamed experts, 153 -> 144).
-//    Over 234 layers, 468 GEMMs, of which 139 changed: 1.0 % less on average, 32 by 5 % and more, three 2 to 3 % slower.
+//    Counting a whole round for wide tiles that are part of one chose otherwise in 1.4 % of drawn layers; 56 drawn from
+//    those GEMMs take 1.9 % less this way on average, 27 of them 2 % and more, five 3 to 8 % more (second GEMMs: 55 experts,
+//    1890 tokens 57.3 -> 49.8; 101 experts, 1173 tokens of 512 x 2048 43.5 -> 37.0; 58 experts, 3693 tokens 60.1 -> 65.1).
 // With 128 columns the four parts of a sum are one step each, and many such tiles are better walked (x 8 tokens: 48
 // experts 14 and 13 us, 200 experts 20 and 23).
 // The counts stand for the whole chip, also on a stream with fewer compute units: the bits of a layer do not depend on
@@ -134,13 +143,13 @@ inline TileRule tile_rule(const int32_t *counts, int32_t n_active, int32_t d_mod
         }
     }
     const auto choose = [&](int64_t N) {
-        double least = launch_cost(work[0], N);
+        double least = launch_cost(work[0], N, !stream);
         int32_t few = 0;
         if (!stream) least *= 0.92;
-        else if (10 * work[0].m_tiles * (N / (gemm_tiles_wide(work[0].m_tiles, N, 512) ? 256 : 128)) < 6 * 512) least = HUGE_VAL;
+        else if (10 * work[0].m_tiles * (N / 128) < 6 * 512) least = HUGE_VAL;
         for (int i = 1; i < 4; ++i) {
             if (!stream && 2 * (work[i].low + work[i].high) > n_active) break;
-            const double cost = launch_cost(work[i], N);
+            const double cost = launch_cost(work[i], N, !stream);
             if (stream ? cost <= least : cost < least) {
                 least = cost;
                 few = work[i].few;

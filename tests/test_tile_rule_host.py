@@ -19,6 +19,7 @@ extern "C" void rule(const int *counts, int n, int d, int F, int in_waves, int *
     out[1] = r.few[0];
     out[2] = r.few[1];
 }
+extern "C" double cost(long m_tiles, long low, long high, long N, bool full) { return launch_cost({0, m_tiles, low, high}, N, full); }
 extern "C" bool wide(long m_tiles, long N, long slots) { return gemm_tiles_wide(m_tiles, N, slots); }
 """
 
@@ -33,6 +34,8 @@ def lib(tmp_path_factory):
     lib = ctypes.CDLL(so)
     lib.wide.restype = ctypes.c_bool
     lib.wide.argtypes = [ctypes.c_long] * 3
+    lib.cost.restype = ctypes.c_double
+    lib.cost.argtypes = [ctypes.c_long] * 4 + [ctypes.c_bool]
     return lib
 
 
@@ -85,3 +88,29 @@ def test_widths(lib, N):
             r = m * (N // 128) / slots
             assert lib.wide(m, N, slots) == (0.77 <= r <= 0.92 or r >= 1.45), (m, slots, r)
     assert not any(lib.wide(m, 640, 512) for m in range(2000))              # not a multiple of 256
+
+
+@pytest.mark.parametrize("E,T,s,d", [(66, 1664, 1., 768), (61, 1507, 1.2, 768), (67, 2979, 1.2, 768), (64, 1111, 1.2, 768),
+                                     (55, 2094, 1.2, 768), (101, 1173, 1., 512)])
+def test_wide_tiles_for_part_of_the_slots_are_walked(lib, E, T, s, d):
+    """Second GEMMs of 0.77 to 0.92 rounds of narrow tiles, for which wide ones take as long: walking them all takes 50 to 63
+    us (768 x 3072), streaming the smallest beside the others 4 to 9 us more."""
+    counts = zipf(E, T, s)
+    tile_m, _, second = pick(lib, counts, d, 4 * d)
+    m_tiles = sum(-(-n // tile_m) for n in counts)
+    assert 0.77 * 512 <= m_tiles * (d // 128) <= 0.92 * 512 and lib.wide(m_tiles, d, 512)
+    assert second == NONE
+
+
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("N", [256, 768, 1024, 3072])
+def test_cost_of_a_round(lib, N, full):
+    """What a launch of walked tiles is taken to cost does not jump where their width changes inside a round, and a few
+    streamed experts more add their own share at the most."""
+    per = N // 128
+    one = [lib.cost(m, 0, 0, N, full) for m in range(1, 512 // per + 1)]
+    assert all(0.55 <= c <= 0.65 for c in one)
+    for m in range(1, 6 * 512 // per):
+        for low in (1, 10, 40):
+            cost, more = lib.cost(m, low, 0, N, full), lib.cost(m, low + 1, 0, N, full)
+            assert cost <= more <= cost + 2 * 0.9 * N / (256 * 512) + 1e-9, (m, low)
