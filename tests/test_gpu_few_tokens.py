@@ -46,30 +46,41 @@ def forward(r, x_bits, ids, alpha):
     return plan, y
 
 
-@pytest.mark.parametrize("name,counts,d,F", [
-    ("edges", EDGES, 128, 128),                         # one step of 32 K values per wavefront
-    ("edges", EDGES, 384, 640),                         # 3 and 5 steps: less than are loaded ahead
-    ("edges", EDGES, 768, 3072),
-    ("several-tiles", SEVERAL, 256, 896),               # 7 steps
-    ("beside-larger", BESIDE, 256, 512),
-    ("beside-larger", BESIDE, 128, 896),
-    ("beside-many", BESIDE_MANY, 256, 512),
-    ("beside-many", BESIDE_MANY, 384, 640),
-    ("alone", ALONE, 256, 512),
-    ("alone", ALONE_MANY, 512, 896),
-    ("alone-walked", ALONE_MANY, 384, 256),             # between the two
-    ("lines-many", lines(6, 2), 384, 640),              # 28 and 36 tokens
-    ("lines-many", lines(8, 2), 384, 1536),             # 20 and 36
-    ("lines-many", lines(10, 2), 512, 896),             # 28, and all walked
-    ("lines-round", lines(2, 8), 512, 2048),            # 20 in the first GEMM, all walked in the second
-    ("lines-round", lines(3, 30), 384, 768),            # 36 in the first
-    ("lines-round", lines(5, 30), 512, 896),            # 28 in the second
+ALL = 2**31 - 1
+# name, counts, d, F, and the most tokens of a streamed expert in either GEMM (test_tile_rule_host.py looks whether it is so)
+CASES = [
+    ("edges", EDGES, 128, 128, (ALL, ALL)),             # one step of 32 K values per wavefront
+    ("edges", EDGES, 384, 640, (ALL, ALL)),             # 3 and 5 steps: less than are loaded ahead
+    ("edges", EDGES, 768, 3072, (ALL, ALL)),
+    ("several-tiles", SEVERAL, 256, 896, (ALL, ALL)),   # 7 steps
+    ("beside-larger", BESIDE, 256, 512, (0, 0)),
+    ("beside-larger", BESIDE, 128, 896, (0, 0)),
+    ("beside-many", BESIDE_MANY, 256, 512, (28, 36)),
+    ("beside-many", BESIDE_MANY, 384, 640, (28, 0)),
+    ("alone", ALONE, 256, 512, (64, 64)),
+    ("alone", ALONE_MANY, 512, 896, (64, 64)),
+    ("alone-walked", ALONE_MANY, 384, 256, (0, 0)),     # between the two
+    ("lines-many", lines(6, 2), 384, 640, (28, 36)),
+    ("lines-many", lines(8, 2), 384, 1536, (20, 36)),
+    ("lines-many", lines(10, 2), 512, 896, (28, 0)),
+    ("lines-many", lines(10, 4), 512, 1024, (20, 20)),
+    ("lines-many", lines(4, 2), 896, 512, (36, 28)),
+    # layers whose larger experts weigh more
+    ("lines-round", lines(2, 8), 512, 2048, (0, 0)),
+    ("lines-round", lines(3, 30), 384, 768, (36, 0)),
+    ("lines-round", lines(5, 30), 512, 896, (0, 20)),
+    ("lines-round", lines(5, 10), 384, 768, (20, 0)),   # beside tiles of 64 rows
+    ("lines-round", lines(5, 20), 512, 896, (28, 28)),
+    ("lines-round", lines(2, 30), 896, 512, (0, 36)),
     # every length of a sum up to two rounds of the steps that are loaded ahead, and one more
-    ("lengths", FEWER, 512, 1024),                      # 4 and 8 steps
-    ("lengths", FEWER, 1152, 1280),                     # 9 and 10
-    ("lengths", FEWER, 1408, 1536),                     # 11 and 12
-    ("lengths", FEWER, 256, 1664),                      # 2 and 13
-])
+    ("lengths", FEWER, 512, 1024, (ALL, ALL)),          # 4 and 8 steps
+    ("lengths", FEWER, 1152, 1280, (ALL, ALL)),         # 9 and 10
+    ("lengths", FEWER, 1408, 1536, (ALL, ALL)),         # 11 and 12
+    ("lengths", FEWER, 256, 1664, (ALL, ALL)),          # 2 and 13
+]
+
+
+@pytest.mark.parametrize("name,counts,d,F", [c[:4] for c in CASES])
 def test_few_token_experts(name, counts, d, F):
     T, E = sum(counts), len(counts)
     say(f"few-token experts: {name} E={E} T={T} d={d} F={F}")

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+import test_gpu_few_tokens
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2310_18859_amd", "csrc")
 ALL, NONE = 2**31 - 1, 0
 
@@ -114,3 +116,11 @@ def test_cost_of_a_round(lib, N, full):
         for low in (1, 10, 40):
             cost, more = lib.cost(m, low, 0, N, full), lib.cost(m, low + 1, 0, N, full)
             assert cost <= more <= cost + 2 * 0.9 * N / (256 * 512) + 1e-9, (m, low)
+
+
+@pytest.mark.parametrize("case", range(len(test_gpu_few_tokens.CASES)))
+def test_layers_of_the_gpu_test_are_cut_as_it_says(lib, case):
+    """... and so are the sizes on either side of the lines of 20, 28 and 36 tokens streamed and walked there."""
+    name, counts, d, F, want = test_gpu_few_tokens.CASES[case]
+    assert pick(lib, counts, d, F)[1:] == want
+    assert not name.startswith("lines") or all(n in counts for few in want if few for n in (few, few + 1))
