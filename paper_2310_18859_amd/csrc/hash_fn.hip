@@ -30,6 +30,7 @@
 #include <utility>
 
 #include "handover.h"
+#include "heads_walk.h"
 #include "kernels.h"
 
 namespace sida {
@@ -1057,8 +1058,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void hash_heads_walk(const float *__
                                                                  const float *__restrict__ b_out, int E, int top_k, int n_tokens,
                                                                  int32_t *__restrict__ ids, float *__restrict__ alpha)
 {
-    constexpr int kMine = NT / WAVES, TT = WAVES / 4, kSteps32 = C / 32, kPitch = NT * 16 + 16, kTokens = 16 * TT;
-    static_assert(NT % WAVES == 0 && WAVES % 4 == 0 && kSteps32 <= 4, "tiles and pieces of a wavefront");
+    constexpr int kMine = NT / WAVES, TT = WAVES / 4, kSteps32 = C / 32, kPitch = NT * 16 + 16, kTokens = heads_walk_tokens(WAVES);
+    static_assert(NT % WAVES == 0 && WAVES % 4 == 0 && kTokens == 16 * TT && kSteps32 <= 4, "tiles and pieces of a wavefront");
     __shared__ bf16x8 parts[2][TT][kSteps32][3][64];
     __shared__ __attribute__((aligned(16))) float logit[2][kTokens * kPitch];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15, g = lane >> 4;
@@ -1243,19 +1244,12 @@ int run(const HashShape &sh, const float *p, const void *x, int n_seq, int T, in
         else if (sh.E <= 128) heads(std::integral_constant<int, 8>(), tt, dir);
         else heads(std::integral_constant<int, 16>(), tt, dir);
     };
-    // Weights cut once pay with more work than that, us, per workgroup and walked: C = 128 128 experts, 6 layers x 4096
-    // tokens 11.6 and 12.1, x 6144 17.2 and 14.6; 12 layers of 64 x 2500 9.4 and 9.9, x 4096 13.5 and 11.5; 3 of 256 x 2500 9.7
-    // and 9.4.  C = 64 6 of 128 x 4096 7.3 and 8.0, x 5500 10.0 and 9.7; 3 of 256 x 2048 6.5 and 6.1.
     auto walk = [&](auto nt, auto waves) {
         constexpr int NT = decltype(nt)::value, WAVES = decltype(waves)::value;
-        const int tiles = (N + WAVES * 4 - 1) / (WAVES * 4);
-        const int most = max(1, (WAVES == 4 ? 3 : 1) * 256 / sh.L);        // workgroups of a layer, all resident at a time
-        const int each = (tiles + most - 1) / most;
-        hipLaunchKernelGGL((hash_heads_walk<C, NT, WAVES>), dim3((tiles + each - 1) / each, sh.L), dim3(WAVES * 64), 0, st, r, w_out,
-                           b_out, sh.E, sh.top_k, N, ids, alpha);
+        hipLaunchKernelGGL((hash_heads_walk<C, NT, WAVES>), dim3(heads_walk_workgroups(N, sh.L, WAVES), sh.L), dim3(WAVES * 64), 0, st, r,
+                           w_out, b_out, sh.E, sh.top_k, N, ids, alpha);
     };
-    const int64_t rows = (int64_t)N * sh.L;
-    const bool walks = direct && N >= 2048 && N < INT32_MAX / (4 * C) && sh.E > 16 && rows >= (sh.E <= 128 ? 32768 : 6144);
+    const bool walks = direct && heads_walk(C, sh.E, sh.L, N);
     if (walks && sh.E <= 64) walk(std::integral_constant<int, 4>(), std::integral_constant<int, 4>());
     else if (walks && sh.E <= 128) walk(std::integral_constant<int, 8>(), std::integral_constant<int, 4>());
     else if (walks) walk(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
