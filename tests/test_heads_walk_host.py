@@ -67,6 +67,8 @@ def test_every_tile_has_a_workgroup(lib, E, L, N):
     (128, 128, 6, 8192, True), (128, 128, 6, 5462, True), (128, 128, 6, 5461, False), (128, 16, 16, 8192, False),
     (128, 17, 16, 2048, True), (128, 17, 17, 2047, False), (128, 250, 3, 2048, True), (128, 250, 2, 3071, False),
     (128, 250, 2, 3072, True), (64, 128, 12, 2731, True),
+    (64, 20, 400, 2048, False), (64, 20, 260, 2048, False), (64, 30, 260, 6144, False), (64, 60, 129, 2048, True), (64, 60, 14, 2600, True),
+    (128, 20, 400, 2048, True), (64, 150, 52, 2048, True), (64, 250, 1, 6144, True),
 ])
 def test_calls_that_walk(lib, C, E, L, N, want):
     assert lib.walks(C, E, L, N) == want
