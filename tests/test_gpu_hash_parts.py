@@ -34,6 +34,15 @@ def oracle_alpha(params, x, cfg, ids):
     return np.take_along_axis(probs, ids.astype(np.int64), axis=2)
 
 
+# C, L, E, n_seq, T of heads that keep their weights and walk over at least three tiles of tokens per workgroup, the last one
+# ragged but for 6144 tokens (test_heads_walk_host.py looks whether they do): 64, 128 and 256 experts' places, two and four
+# steps of the sum
+WALKED = [(128, 16, 60, 16, 129), (128, 6, 128, 16, 384), (64, 16, 128, 64, 33), (128, 8, 100, 33, 125), (64, 9, 40, 37, 100),
+          (128, 9, 250, 33, 125), (64, 9, 200, 33, 125)]
+# ... of more than 128 experts that do not, from 2048 tokens on
+NOT_WALKED = [(128, 1, 130, 21, 100), (64, 2, 250, 21, 100)]
+
+
 @pytest.mark.parametrize("d,C,L,E,k,n_seq,T", [
     (64, 128, 2, 16, 1, 23, 89),          # 2047 tokens: one tile per wavefront
     (72, 128, 2, 16, 1, 16, 128),         # 2048, and a row of embeddings that ends inside a step
@@ -43,11 +52,9 @@ def oracle_alpha(params, x, cfg, ids):
     (64, 128, 1, 16, 1, 64, 33),          # as many sequences as have four workgroups each, and one more: gates in parts
     (64, 128, 1, 16, 1, 65, 33),
     (64, 64, 1, 16, 1, 15, 137),          # as few as have three: gates in parts
-    (64, 128, 16, 60, 1, 16, 129),        # heads that keep their weights: 2064 tokens, experts that fill no tile
-    (64, 64, 16, 128, 3, 64, 33),         # ... of two steps of the sum, 2112 tokens
-    (64, 128, 3, 250, 2, 17, 121),        # ... of eight wavefronts, a last tile of 9 of 32 tokens
+    (64, 128, 3, 250, 2, 17, 121),        # heads that keep their weights, one tile per workgroup: a last one of 9 of 32 tokens
     (64, 64, 3, 256, 1, 64, 32),          # ... as few as that
-])
+] + [(64, C, L, E, 1 + i % 3, n_seq, T) for i, (C, L, E, n_seq, T) in enumerate(WALKED + NOT_WALKED)])
 def test_parts_against_oracle(d, C, L, E, k, n_seq, T):
     rng = np.random.default_rng(d + T)
     cfg = sm.SidaHashConfig(d, C, L, E, k, T)
@@ -222,7 +229,7 @@ def test_infinities_in_heads_that_keep_their_weights(where, C, L, E):
     test_infinities(where, C, 16, 129, L, E)
 
 
-@pytest.mark.parametrize("C,L,E,n_seq,T", [(128, 2, 40, 2, 9), (128, 1, 100, 16, 128), (64, 16, 100, 64, 33), (128, 3, 250, 17, 121)])
+@pytest.mark.parametrize("C,L,E,n_seq,T", [(128, 2, 40, 2, 9), (128, 1, 100, 16, 128), (64, 16, 100, 64, 33), (128, 3, 250, 17, 121)] + WALKED + NOT_WALKED)
 def test_equal_logits(C, L, E, n_seq, T):
     """Experts of the same weights have the same logits: the lower id comes first.  Of a logit that is no number or -inf
     nothing is chosen, as long as there are others."""

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_hash_parts import NOT_WALKED, WALKED
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2310_18859_amd", "csrc")
 
 SOURCE = r"""
@@ -72,3 +74,11 @@ def test_every_tile_has_a_workgroup(lib, E, L, N):
 ])
 def test_calls_that_walk(lib, C, E, L, N, want):
     assert lib.walks(C, E, L, N) == want
+
+
+@pytest.mark.parametrize("C,L,E,n_seq,T", WALKED + NOT_WALKED)
+def test_calls_of_the_gpu_test_walk_as_it_says(lib, C, L, E, n_seq, T):
+    N, walked = n_seq * T, (C, L, E, n_seq, T) in WALKED
+    groups, tiles, tokens = launch(lib, E, L, N)
+    assert lib.walks(C, E, L, N) == walked and N >= 2048
+    assert not walked or -(-tiles // groups) >= 3
