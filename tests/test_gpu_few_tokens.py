@@ -63,20 +63,21 @@ CASES = [
     ("lines-many", lines(6, 2), 384, 640, (28, 36)),
     ("lines-many", lines(8, 2), 384, 1536, (20, 36)),
     ("lines-many", lines(10, 2), 512, 896, (28, 0)),
-    ("lines-many", lines(10, 4), 512, 1024, (20, 20)),
-    ("lines-many", lines(4, 2), 896, 512, (36, 28)),
     # layers whose larger experts weigh more
     ("lines-round", lines(2, 8), 512, 2048, (0, 0)),
     ("lines-round", lines(3, 30), 384, 768, (36, 0)),
     ("lines-round", lines(5, 30), 512, 896, (0, 20)),
-    ("lines-round", lines(5, 10), 384, 768, (20, 0)),   # beside tiles of 64 rows
-    ("lines-round", lines(5, 20), 512, 896, (28, 28)),
-    ("lines-round", lines(2, 30), 896, 512, (0, 36)),
     # every length of a sum up to two rounds of the steps that are loaded ahead, and one more
     ("lengths", FEWER, 512, 1024, (ALL, ALL)),          # 4 and 8 steps
     ("lengths", FEWER, 1152, 1280, (ALL, ALL)),         # 9 and 10
     ("lengths", FEWER, 1408, 1536, (ALL, ALL)),         # 11 and 12
     ("lengths", FEWER, 256, 1664, (ALL, ALL)),          # 2 and 13
+    # more layers on either side of the lines
+    ("lines-many", lines(10, 4), 512, 1024, (20, 20)),
+    ("lines-many", lines(4, 2), 896, 512, (36, 28)),
+    ("lines-round", lines(5, 10), 384, 768, (20, 0)),   # beside tiles of 64 rows
+    ("lines-round", lines(5, 20), 512, 896, (28, 28)),
+    ("lines-round", lines(2, 30), 896, 512, (0, 36)),
 ]
 
 
