@@ -18,10 +18,9 @@
 // scalar-per-lane fp32 multiply-adds), or on the bf16 one with the values in exact parts (hash_dense, Parts); with the
 // weights as the first operand a lane ends up with four consecutive output units of one token.  The recurrence is a chain of matrix-vector products,
 // where 15 of the instruction's 16 columns would idle, and stays on the vector units.
-// It is what bounds a call: 0.55 us a time step at C = 128, see lstm_layer.  Measured against one launch per layer and
+// It is what bounds a call: 0.53 us a time step at C = 128, see lstm_layer.  Measured against one launch per layer and
 // stage on the vector units (d = 768, C = 128, 6 x 128 experts; calls of perf/cases.py, inputs changing): 1 sequence of
-// 128 tokens 375 -> 107 us, 8 of 333 tokens (top-3) 1059 -> 243 us, 64 of 128 tokens 609 -> 136 us (one batch called again
-// and again 147).
+// 128 tokens 375 -> 107 us, 8 of 333 tokens (top-3) 1059 -> 243 us, 64 of 128 tokens 609 -> 136 us.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -887,10 +886,6 @@ __global__ __launch_bounds__(512) void hash_attention(const float *__restrict__ 
 }
 
 // ---- heads --------------------------------------------------------------------------------------
-// Per MoE layer the E logits of a token, their SoftMax, and the k most probable experts.  A workgroup
-// takes TT*16 tokens and one layer: all operands go to LDS at once, its four wavefronts make NT tiles of
-// 16 experts in turn (matrix product, experts as rows), hand the logits over in LDS, and then take a
-// token per 16 lanes with NT logits in each lane's registers.
 // The k most probable experts of a token: 16 lanes hold its logits, NT each (experts col, col + 16, ...).
 template <int NT>
 __device__ __forceinline__ void best_experts(const float *row, int l, int n, int n_tokens, int E, int top_k, int col,
@@ -933,6 +928,10 @@ __device__ __forceinline__ void best_experts(const float *row, int l, int n, int
     }
 }
 
+// Per MoE layer the E logits of a token, their SoftMax, and the k most probable experts.  A workgroup
+// takes TT*16 tokens and one layer: all operands go to LDS at once, its four wavefronts make NT tiles of
+// 16 experts in turn (matrix product, experts as rows), hand the logits over in LDS, and then take a
+// token per 16 lanes with NT logits in each lane's registers.
 template <int C, int NT, int TT>
 constexpr int heads_lds_bytes() { return C / 32 * (NT + TT) * 16 * TileRow<float>::kBytes; }
 
@@ -1045,7 +1044,7 @@ __global__ __launch_bounds__(256) void hash_heads(const float *__restrict__ r, c
     }
 }
 
-// The same for many tokens and layers, all products through bf16 parts.  Above, a workgroup fetches and cuts a layer's
+// The same for many tokens and layers, all products through bf16 parts.  In hash_heads a workgroup fetches and cuts a layer's
 // weights (64 KiB of 128 experts) for 32 tokens, and cutting them takes as long as multiplying: 8192 tokens, 6
 // layers of 128 experts 19.8 us, of which the matrix instructions take 4.  Here WAVES wavefronts keep the layer's weights, cut
 // once, in registers (NT / WAVES tiles of 16 experts each) and walk over tiles of 16 * TT tokens.  A wavefront cuts one
