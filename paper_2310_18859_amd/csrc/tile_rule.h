@@ -13,15 +13,22 @@ constexpr int kGemmTileSmall = 64; // ... of small launches
 // Weight rows per tile of a launch over `slots` workgroup slots, where the matrix has a multiple of 256: 256 (two stripes
 // per wavefront, one LDS fragment read per two MFMAs, the token rows fetched half as often) or 128, twice as many at a
 // little more than half the time each.  Tiles are dealt to the workgroups in turn, so what counts is how full the rounds are that 128-row
-// tiles take.  Time of wide over narrow of some 200 GEMMs (layers of
-// 16 to 256 experts, 600 to 32768 tokens, 384 x 1536 to 1024 x 4096), by those rounds:
-//   below 0.5    1.0 - 1.5   half of the slots idle, or more
-//   0.75 - 0.92  0.90 - 1.06, 0.977 on average
-//   1.0 - 1.45   0.93 - 1.15  a second round of few tiles ends sooner than one round of wide ones
-//   1.45 - 2     0.87 - 1.02
-//   2.0 - 2.2    0.93 - 1.02
-//   above        0.88 - 1.00, 0.93 on average (three above 1.04 of 47)
-// (Taken by whole rounds, as before, 2.2 to 3 rounds were walked narrow: 34 experts, 29171 tokens, second GEMM 168 us and
+// tiles take.  Time of wide over narrow of 699 GEMMs, all experts walked (392 layers of 16 to 256 experts, 600 to 32768
+// tokens, Zipf 0 to 1.2, 384 x 1536 to 1024 x 4096), by those rounds: least, mean, most, and how many are above 1.04
+//   below 0.5    1.22 1.40 1.64   46 of 46   half of the slots idle, or more
+//   0.5 - 0.65   0.89 1.03 1.47   12 of 40
+//   0.65 - 0.77  0.87 0.97 1.10    5 of 40   (walked narrow all the same; taken wide, 3 % less on average)
+//   0.77 - 0.92  0.90 0.98 1.06    2 of 40
+//   0.92 - 1     0.90 0.99 1.06    5 of 40
+//   1 - 1.2      0.96 1.09 1.18   31 of 40   a second round of few tiles ends sooner than one round of wide ones
+//   1.2 - 1.45   0.98 1.10 1.17   38 of 40
+//   1.45 - 2     0.82 0.93 1.05    1 of 45
+//   2 - 2.2      0.85 1.01 1.12   12 of 41
+//   2.2 - 3      0.85 0.98 1.10    7 of 72
+//   3 - 4        0.87 0.96 1.09    3 of 82
+//   4 - 6        0.84 0.95 1.04    1 of 70
+//   above        0.81 0.93 1.04    0 of 103
+// (Taken by whole rounds 2.2 to 3 rounds were walked narrow: 34 experts, 29171 tokens, second GEMM 168 us and
 // 148; 69 experts, 18073 tokens of 1024 x 4096 222 and 203; and 1.1 to 1.45 wide: 44 experts, 5918 tokens 132 and 121.)
 inline bool gemm_tiles_wide(int64_t m_tiles, int64_t N, int64_t slots)
 {
@@ -45,8 +52,8 @@ struct SplitWork {
 };
 // What a launch takes, in rounds of 512 wide tiles: the slots' rounds of walked tiles, or all of the work if that is
 // more, which streamed tiles spread over the slots that come free.  full: more than 64 tokens per expert, on average, or
-// more than 32 per few-token one.  Fitted to 234 layers (8 to 256 experts, 384 x 1536
-// to 1024 x 4096, 600 to 32768 tokens, Zipf 0 to 1.2).
+// more than 32 per few-token one.  Fitted to 360 layers (8 to 256 experts, 384 x 1536
+// to 1024 x 4096, 600 to 32768 tokens, Zipf 0 to 1.2), every threshold timed with either width.
 inline double launch_cost(const SplitWork &l, int64_t N, bool full)
 {
     const int64_t tiles = l.m_tiles * (N / 128);              // narrow ones, 0.56 of a wide one each
@@ -86,12 +93,13 @@ inline double launch_cost(const SplitWork &l, int64_t N, bool full)
 //    the slots that come free.
 //    - Layers of at least 48 experts, at most 64 tokens on average, with a workgroup and a half of 64 weight rows per
 //      compute unit among those of at most 64 tokens, which have at most 32 on average: always where the narrow tiles of
-//      all experts are less than 0.6 of a round, else where that is no more than walking them all.  (Those of at most 64 tokens beside half of the slots, before -> now, us, first
-//      and second GEMM: 157 experts, 640 x 2560, 7824 tokens 111 / 107 -> 102 / 100; 64 experts, 1111 tokens, Zipf(1.2)
-//      51 / 55 -> 49 / 51; 67 experts, 2979 tokens 63 / 67 -> 62 / 63, the second all walked, as in the layer before.)
+//      all experts are less than 0.6 of a round, else where that is no more than walking them all.  (Those of at most 64
+//      tokens beside half of the slots -> now, us, first and second GEMM: 157 experts, 640 x 2560, 7824 tokens 109 / 108 ->
+//      102 / 105; 64 experts, 1111 tokens, Zipf(1.2) 52 / 56 -> 51 / 53; 67 experts, 2979 tokens 63 / 66 -> 58 / 63, the second
+//      all walked, as in the layer before.)
 //    - Others of at least 32 experts, of which at most half are streamed: where that is 8 % less than walking them all
-//      (64 experts, 8192 tokens, Zipf(1.2) 83 / 85 -> 78 / 82; 128 experts, 16384 tokens, second GEMM, 2.4 rounds of narrow tiles
-//      -> 0.95 of wide ones and 43 streamed experts, 153 -> 144).
+//      (64 experts, 8192 tokens, Zipf(1.2) 87 / 86 -> 81 / 81; 128 experts, 16384 tokens, second GEMM, 2.4 rounds of narrow tiles
+//      -> 0.95 of wide ones and 43 streamed experts, 153 -> 147).
 //    Counting a whole round for wide tiles that are part of one chose otherwise in 1.4 % of drawn layers; 56 drawn from
 //    those GEMMs take 1.9 % less this way on average, 27 of them 2 % and more, five 3 to 8 % more (second GEMMs: 55 experts,
 //    1890 tokens 57.3 -> 49.8; 101 experts, 1173 tokens of 512 x 2048 43.5 -> 37.0; 58 experts, 3693 tokens 60.1 -> 65.1).
