@@ -722,7 +722,7 @@ int launch_as(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 template <int BM, bool RELU, int FUSE>
 int launch_width(const GemmArgs &a, hipStream_t st, const LaunchEvents *ev)
 {
-    const bool wide = gemm_tiles_wide(a.m_tiles, a.N, 2 * (int64_t)stream_compute_units(st));
+    const bool wide = gemm_tiles_wide(a.m_tiles, a.m_tall, a.m_few > 0, a.N, a.K, 2 * (int64_t)stream_compute_units(st));
     const bool once = worth_streaming(a);
     if (wide) return once ? launch_as<BM, 2, 2, RELU, FUSE, true>(a, st, ev) : launch_as<BM, 2, 2, RELU, FUSE, false>(a, st, ev);
     if constexpr (BM == kGemmTileSmall)

@@ -13,27 +13,40 @@ constexpr int kGemmTileSmall = 64; // ... of small launches
 // Weight rows per tile of a launch over `slots` workgroup slots, where the matrix has a multiple of 256: 256 (two stripes
 // per wavefront, one LDS fragment read per two MFMAs, the token rows fetched half as often) or 128, twice as many at a
 // little more than half the time each.  Tiles are dealt to the workgroups in turn, so what counts is how full the rounds are that 128-row
-// tiles take.  Time of wide over narrow of 699 GEMMs, all experts walked (392 layers of 16 to 256 experts, 600 to 32768
-// tokens, Zipf 0 to 1.2, 384 x 1536 to 1024 x 4096), by those rounds: least, mean, most, and how many are above 1.04
-//   below 0.5    1.22 1.40 1.64   46 of 46   half of the slots idle, or more
-//   0.5 - 0.65   0.89 1.03 1.47   12 of 40
-//   0.65 - 0.77  0.87 0.97 1.10    5 of 40   (walked narrow all the same; taken wide, 3 % less on average)
-//   0.77 - 0.92  0.90 0.98 1.06    2 of 40
-//   0.92 - 1     0.90 0.99 1.06    5 of 40
-//   1 - 1.2      0.96 1.09 1.18   31 of 40   a second round of few tiles ends sooner than one round of wide ones
-//   1.2 - 1.45   0.98 1.10 1.17   38 of 40
-//   1.45 - 2     0.82 0.93 1.05    1 of 45
-//   2 - 2.2      0.85 1.01 1.12   12 of 41
-//   2.2 - 3      0.85 0.98 1.10    7 of 72
-//   3 - 4        0.87 0.96 1.09    3 of 82
-//   4 - 6        0.84 0.95 1.04    1 of 70
-//   above        0.81 0.93 1.04    0 of 103
-// (Taken by whole rounds 2.2 to 3 rounds were walked narrow: 34 experts, 29171 tokens, second GEMM 168 us and
-// 148; 69 experts, 18073 tokens of 1024 x 4096 222 and 203; and 1.1 to 1.45 wide: 44 experts, 5918 tokens 132 and 121.)
-inline bool gemm_tiles_wide(int64_t m_tiles, int64_t N, int64_t slots)
+// tiles take; and many-token experts gain more from wide tiles than experts of one tile, long rows (K > N, a second
+// GEMM) more than short ones.  Time of wide over narrow of 2483 GEMMs (1127 layers of 8 to 256 experts, 300 to 32768
+// tokens, Zipf 0 to 1.2, 384 x 1536 to 1024 x 4096), least, mean and most, by rounds of narrow tiles; walked launches apart
+// by whether more than half of the tiles belong to experts of several (tall), and launches with streamed experts:
+//               short rows                       long rows                       streamed
+//               others          tall             others          tall
+//   0   - 0.5                                    1.20 1.39 1.63  1.19 1.45 1.57  0.97 1.06 1.35
+//   0.5 - 0.65                                   0.84 0.99 1.42  0.90 1.01 1.45  0.96 1.00 1.13
+//       - 0.77  0.93 0.99 1.11  0.98 1.04 1.10   0.83 0.96 1.04  0.91 0.98 1.06  0.96 1.00 1.12
+//       - 0.92  0.94 1.00 1.04  0.96 1.05 1.22   0.93 0.97 1.06  0.89 0.98 1.08  0.94 0.98 1.05
+//       - 1     0.92 1.01 1.09  0.99 1.05 1.20   0.92 0.99 1.05  0.86 0.96 1.01  0.90 0.96 1.01
+//       - 1.2   1.07 1.14 1.21  1.01 1.12 1.21   1.02 1.11 1.16  0.99 1.07 1.14  0.95 0.97 1.01
+//       - 1.45  1.00 1.11 1.21  0.98 1.10 1.29   1.02 1.10 1.15  0.99 1.06 1.14  0.97 1.01 1.06
+//       - 1.5   1.00 1.07 1.14  0.92 1.05 1.18   0.92 1.05 1.10  0.91 1.00 1.11  0.95 0.98 1.01
+//       - 2     0.89 0.97 1.03  0.87 0.93 0.99   0.86 0.93 1.01  0.81 0.88 0.95  0.86 0.95 1.01
+//       - 2.2   1.00 1.05 1.11  0.94 1.01 1.05   0.96 1.05 1.13  0.92 0.98 1.03  0.96 0.98 1.01
+//       - 2.4   0.96 1.02 1.08  0.91 1.00 1.06   0.94 1.03 1.11  0.91 0.96 1.03  0.99 0.99 1.00
+//       - 2.7   0.91 0.96 1.04  0.86 0.93 1.03   0.90 0.98 1.09  0.85 0.91 0.97  0.98 0.99 1.00
+//       - 3     0.85 0.95 0.99  0.85 0.92 0.99   0.92 0.96 1.00  0.84 0.89 0.93  0.91 0.98 1.00
+//   above       0.88 0.98 1.07  0.81 0.89 1.01                                   0.85 0.94 1.00
+// The lines below are on average 0.6 % behind the better width of each, by whole rounds (wide from one to two and from three
+// on, but for at most three quarters of the slots over mostly single tiles) 1.6 %.  With one line at 1.45 rounds and all of 0.77 to 0.92 wide, 1.0 %, small layers
+// were slowed: 9 experts x 187 tokens, first GEMM 17.3 -> 20.5 us, 44 x 19 40.3 -> 43.9, 31 experts, 516 tokens of 1024 x 4096 47.6 -> 51.5.
+// 0.65 to 0.77 and 0.92 to 1 are narrow throughout.
+inline bool gemm_tiles_wide(int64_t m_tiles, int64_t m_tall, bool streamed, int64_t N, int64_t K, int64_t slots)
 {
-    const int64_t narrow = 100 * m_tiles * (N / 128);
-    return N % 256 == 0 && (narrow >= 145 * slots || (narrow >= 77 * slots && narrow <= 92 * slots));
+    if (N % 256 != 0) return false;
+    const int64_t narrow = 100 * m_tiles * (N / 128);         // rounds of narrow tiles, in 100ths of `slots`
+    const bool long_rows = K > N, tall = 2 * m_tall > m_tiles, part = narrow >= 77 * slots && narrow <= 92 * slots;
+    if (streamed) return narrow >= 145 * slots || (long_rows && part);
+    if (narrow <= 150 * slots) return long_rows && (part || (tall && narrow >= 145 * slots));
+    if (narrow > 200 * slots && narrow <= 220 * slots) return long_rows && tall;
+    if (narrow > 220 * slots && narrow <= 240 * slots) return 4 * m_tall > m_tiles;
+    return true;
 }
 
 // How a layer's experts are cut into tiles.  A wavefront sums over K in another order where tiles are streamed, so
@@ -59,7 +72,9 @@ inline double launch_cost(const SplitWork &l, int64_t N, bool full)
     const int64_t tiles = l.m_tiles * (N / 128);              // narrow ones, 0.56 of a wide one each
     const double streamed = (0.9 * (double)l.low + 2.2 * (double)l.high) * (double)N / (256. * 512.);
     const double also = streamed > 0. ? streamed + 0.15 : 0.;
-    if (!gemm_tiles_wide(l.m_tiles, N, 512)) return std::max(0.56 * (double)((tiles + 511) / 512), 0.56 * (double)tiles / 512. + also);
+    // The fit's two lines; gemm_tiles_wide() has more of them, which take 0 to 5 % off.
+    const bool wide = N % 256 == 0 && (100 * tiles >= 145 * 512 || (100 * tiles >= 77 * 512 && 100 * tiles <= 92 * 512));
+    if (!wide) return std::max(0.56 * (double)((tiles + 511) / 512), 0.56 * (double)tiles / 512. + also);
     const double walked = (double)tiles / 1024.;
     // Wide tiles for less than half of the slots run alone on their compute units and take little more than half of the
     // time (second GEMM of 768 x 3072, 0.77 to 0.92 rounds of narrow tiles: 50 to 63 us, a whole round 100), most where they

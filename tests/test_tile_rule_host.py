@@ -22,7 +22,10 @@ extern "C" void rule(const int *counts, int n, int d, int F, int in_waves, int *
     out[2] = r.few[1];
 }
 extern "C" double cost(long m_tiles, long low, long high, long N, bool full) { return launch_cost({0, m_tiles, low, high}, N, full); }
-extern "C" bool wide(long m_tiles, long N, long slots) { return gemm_tiles_wide(m_tiles, N, slots); }
+extern "C" bool wide(long m_tiles, long m_tall, bool streamed, long N, long K, long slots)
+{
+    return gemm_tiles_wide(m_tiles, m_tall, streamed, N, K, slots);
+}
 """
 
 
@@ -35,7 +38,7 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + CSRC, "-o", so, src], check=True)
     lib = ctypes.CDLL(so)
     lib.wide.restype = ctypes.c_bool
-    lib.wide.argtypes = [ctypes.c_long] * 3
+    lib.wide.argtypes = [ctypes.c_long] * 2 + [ctypes.c_bool] + [ctypes.c_long] * 3
     lib.cost.restype = ctypes.c_double
     lib.cost.argtypes = [ctypes.c_long] * 4 + [ctypes.c_bool]
     return lib
@@ -84,12 +87,57 @@ def test_streamed_experts_do_not_depend_on_the_order_or_the_waves(lib, seed):
 
 @pytest.mark.parametrize("N", [256, 768, 1024, 3072])
 def test_widths(lib, N):
-    """Wide from 0.77 to 0.92 and from 1.45 rounds of narrow tiles on."""
+    """By rounds of narrow tiles: wide above 2.4 and from above 1.5 to 2; else for long rows or tall tiles, or beside streamed
+    experts."""
     for slots in (512, 256, 16):
         for m in range(1, 2 * slots):
             r = m * (N // 128) / slots
-            assert lib.wide(m, N, slots) == (0.77 <= r <= 0.92 or r >= 1.45), (m, slots, r)
-    assert not any(lib.wide(m, 640, 512) for m in range(2000))              # not a multiple of 256
+            for streamed, K, tall in ((s, K, t) for s in (False, True) for K in (N // 2, N, 4 * N) for t in (0, m // 4, m // 4 + 1, m // 2, m // 2 + 1, m)):
+                part, most = K > N and 0.77 <= r <= 0.92, 2 * tall > m
+                if streamed:
+                    want = part or r >= 1.45
+                elif r <= 1.5:
+                    want = part or (K > N and most and r >= 1.45)
+                elif 2 < r <= 2.4:
+                    want = K > N and most if r <= 2.2 else 4 * tall > m
+                else:
+                    want = True
+                assert lib.wide(m, tall, streamed, N, K, slots) == want, (m, tall, streamed, K, slots, r)
+    assert not any(lib.wide(m, 0, s, 640, 1280, 512) for m in range(2000) for s in (False, True))   # not a multiple of 256
+
+
+def launch_widths(lib, counts, d, F):
+    """Whether either GEMM of a layer on the whole chip runs in wide tiles."""
+    tile_m, *few = pick(lib, counts, d, F)
+    out = []
+    for f, N, K in ((few[0], F, d), (few[1], d, F)):
+        tiles = [-(-n // tile_m) for n in counts if n > f]
+        out.append(lib.wide(sum(tiles), sum(t for t in tiles if t > 1), min(counts) <= f, N, K, 512))
+    return tuple(out)
+
+
+@pytest.mark.parametrize("counts,d", [
+    ([188] * 9, 768),                                                   # 0.84 rounds of narrow tiles, tall: 17 us, wide 20
+    ([217] * 18, 384),                                                  # ... 11.8 and 12.5
+    (zipf(24, 2500, 0.8), 768),                                         # 1.5 rounds: 31 and 34
+    ([28] * 32, 768),                                                   # ... 28.6 and 30.6
+    ([19] * 44, 768),                                                   # 2.06: 40.3 and 43.9
+    ([84] * 34, 1024),                                                  # 2.13: 57.9 and 61.3
+    ([81] * 37, 1024),                                                  # 2.31: 60.3 and 61.8
+])
+def test_first_gemms_that_narrow_tiles_take_less_time_for(lib, counts, d):
+    assert launch_widths(lib, counts, d, 4 * d)[0] is False
+
+
+@pytest.mark.parametrize("counts,d,want", [
+    ([256] * 128, 768, (True, True)),                                   # 12 and 3 rounds of narrow tiles
+    ([2048] * 8, 768, (True, True)),                                    # 6 and 1.5, of long rows
+    ([1280] * 18, 768, (True, True)),                                   # 8.4 and 2.1
+    ([128] * 180, 768, (True, False)),                                  # ... of experts of one tile
+    ([400] * 11, 768, (False, False)),                                  # 2.06, of short rows, and 0.52
+])
+def test_widths_of_larger_launches(lib, counts, d, want):
+    assert launch_widths(lib, counts, d, 4 * d) == want
 
 
 @pytest.mark.parametrize("E,T,s,d", [(66, 1664, 1., 768), (61, 1507, 1.2, 768), (67, 2979, 1.2, 768), (64, 1111, 1.2, 768),
@@ -100,7 +148,7 @@ def test_wide_tiles_for_part_of_the_slots_are_walked(lib, E, T, s, d):
     counts = zipf(E, T, s)
     tile_m, _, second = pick(lib, counts, d, 4 * d)
     m_tiles = sum(-(-n // tile_m) for n in counts)
-    assert 0.77 * 512 <= m_tiles * (d // 128) <= 0.92 * 512 and lib.wide(m_tiles, d, 512)
+    assert 0.77 * 512 <= m_tiles * (d // 128) <= 0.92 * 512 and launch_widths(lib, counts, d, 4 * d)[1]
     assert second == NONE
 
 
