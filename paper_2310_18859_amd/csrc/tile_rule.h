@@ -103,12 +103,14 @@ inline double launch_cost(const SplitWork &l, int64_t N, bool full)
 //    empty, 106 and 94; 1024 x 4096, whole rounds: 64 x 28 192 and 198), or 16 with less than two workgroups per
 //    compute unit (64 experts of 384 x 1536: x 16 39 and 39, x 24 41 and 43; 48 of 640 x 2560: 64 and 62, 67 and 69);
 //    with at most one, walking leaves most of the chip idle again (48 of 256 x 1024 x 28: 22.4 and 21.7);
-//  * beside larger tiles the experts of at most 20, 28 or 36 tokens, by each GEMM those with which launch_cost() is least:
+//  * beside larger tiles the experts of at most 20, 28, 36 or 64 tokens, by each GEMM those with which launch_cost() is least:
 //    a launch of walked tiles ends when its last round does, however few tiles that has, and streamed ones fill
 //    the slots that come free.
 //    - Layers of at least 48 experts, at most 64 tokens on average, with a workgroup and a half of 64 weight rows per
-//      compute unit among those of at most 64 tokens, which have at most 32 on average: always where the narrow tiles of
-//      all experts are less than 0.6 of a round, else where that is no more than walking them all.  (Those of at most 64
+//      compute unit among those of at most 64 tokens, which have at most 32 on average: where that is no more than
+//      walking them all.  Where the narrow tiles of all experts are less than 0.65 of a round, those of at most 64 tokens: most slots are
+//      idle, and streams fill them (85 second GEMMs of 384 x 1536 to 768 x 3072: with 36 tokens at the most 3.6 % more on average, up to
+//      8; 49 experts, 1852 tokens of 640 x 2560 37.3 -> 39.0 us, 54, 1778 of 512 x 2048 30.2 -> 31.7).  (Those of at most 64
 //      tokens beside half of the slots -> now, us, first and second GEMM: 157 experts, 640 x 2560, 7824 tokens 109 / 108 ->
 //      102 / 105; 64 experts, 1111 tokens, Zipf(1.2) 52 / 56 -> 51 / 53; 67 experts, 2979 tokens 63 / 66 -> 58 / 63, the second
 //      all walked, as in the layer before.)
@@ -166,10 +168,10 @@ inline TileRule tile_rule(const int32_t *counts, int32_t n_active, int32_t d_mod
         }
     }
     const auto choose = [&](int64_t N) {
+        if (stream && 100 * work[0].m_tiles * (N / 128) < 65 * 512) return (int32_t)kGemmTileSmall;
         double least = launch_cost(work[0], N, !stream);
         int32_t few = 0;
         if (!stream) least *= 0.92;
-        else if (10 * work[0].m_tiles * (N / 128) < 6 * 512) least = HUGE_VAL;
         for (int i = 1; i < 4; ++i) {
             if (!stream && 2 * (work[i].low + work[i].high) > n_active) break;
             const double cost = launch_cost(work[i], N, !stream);

@@ -55,13 +55,13 @@ CASES = [
     ("several-tiles", SEVERAL, 256, 896, (ALL, ALL)),   # 7 steps
     ("beside-larger", BESIDE, 256, 512, (0, 0)),
     ("beside-larger", BESIDE, 128, 896, (0, 0)),
-    ("beside-many", BESIDE_MANY, 256, 512, (28, 36)),
+    ("beside-many", BESIDE_MANY, 256, 512, (28, 64)),
     ("beside-many", BESIDE_MANY, 384, 640, (28, 0)),
     ("alone", ALONE, 256, 512, (64, 64)),
     ("alone", ALONE_MANY, 512, 896, (64, 64)),
     ("alone-walked", ALONE_MANY, 384, 256, (0, 0)),     # between the two
-    ("lines-many", lines(6, 2), 384, 640, (28, 36)),
-    ("lines-many", lines(8, 2), 384, 1536, (20, 36)),
+    ("lines-many", lines(6, 2), 384, 640, (28, 64)),
+    ("lines-many", lines(8, 2), 384, 1536, (20, 64)),
     ("lines-many", lines(10, 2), 512, 896, (28, 0)),
     # layers whose larger experts weigh more
     ("lines-round", lines(2, 8), 512, 2048, (0, 0)),
@@ -74,10 +74,13 @@ CASES = [
     ("lengths", FEWER, 256, 1664, (ALL, ALL)),          # 2 and 13
     # more layers on either side of the lines
     ("lines-many", lines(10, 4), 512, 1024, (20, 20)),
-    ("lines-many", lines(4, 2), 896, 512, (36, 28)),
+    ("lines-many", lines(4, 2), 896, 512, (64, 28)),
     ("lines-round", lines(5, 10), 384, 768, (20, 0)),   # beside tiles of 64 rows
     ("lines-round", lines(5, 20), 512, 896, (28, 28)),
     ("lines-round", lines(2, 30), 896, 512, (0, 36)),
+    ("lines-many", lines(6, 4), 896, 512, (36, 28)),
+    ("lines-part", [64, 65, 63] * 2 + lines(6, 1), 512, 896, (28, 64)),
+    ("lines-part", [64, 65, 63] * 2 + lines(4, 1), 896, 512, (64, 0)),
 ]
 
 
