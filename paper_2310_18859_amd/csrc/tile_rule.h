@@ -114,7 +114,8 @@ inline double launch_cost(const SplitWork &l, int64_t N, bool full)
 //      tokens beside half of the slots -> now, us, first and second GEMM: 157 experts, 640 x 2560, 7824 tokens 109 / 108 ->
 //      102 / 105; 64 experts, 1111 tokens, Zipf(1.2) 52 / 56 -> 51 / 53; 67 experts, 2979 tokens 63 / 66 -> 58 / 63, the second
 //      all walked, as in the layer before.)
-//    - Others of at least 32 experts, of which at most half are streamed: where that is 8 % less than walking them all
+//    - Others of at least 32 experts, of which at most half are streamed: where narrow tiles of all experts are more than one round (16
+//      second GEMMs of 0.77 to 1, chosen by cost: 1.7 % more than walked on average, up to 6) and that is 8 % less than walking them all
 //      (64 experts, 8192 tokens, Zipf(1.2) 87 / 86 -> 81 / 81; 128 experts, 16384 tokens, second GEMM, 2.4 rounds of narrow tiles
 //      -> 0.95 of wide ones and 43 streamed experts, 153 -> 147).
 //    Counting a whole round for wide tiles that are part of one chose otherwise in 1.4 % of drawn layers; 56 drawn from
@@ -168,7 +169,9 @@ inline TileRule tile_rule(const int32_t *counts, int32_t n_active, int32_t d_mod
         }
     }
     const auto choose = [&](int64_t N) {
-        if (stream && 100 * work[0].m_tiles * (N / 128) < 65 * 512) return (int32_t)kGemmTileSmall;
+        const int64_t tiles = work[0].m_tiles * (N / 128);
+        if (stream && 100 * tiles < 65 * 512) return (int32_t)kGemmTileSmall;
+        if (!stream && tiles <= 512) return 0;
         double least = launch_cost(work[0], N, !stream);
         int32_t few = 0;
         if (!stream) least *= 0.92;

@@ -76,9 +76,10 @@ CASES = [
     ("lines-many", lines(10, 4), 512, 1024, (20, 20)),
     ("lines-many", lines(4, 2), 896, 512, (64, 28)),
     ("lines-round", lines(5, 10), 384, 768, (20, 0)),   # beside tiles of 64 rows
-    ("lines-round", lines(5, 20), 512, 896, (28, 28)),
+    ("lines-round", lines(5, 20), 512, 896, (28, 0)),
     ("lines-round", lines(2, 30), 896, 512, (0, 36)),
     ("lines-many", lines(6, 4), 896, 512, (36, 28)),
+    ("lines-round", lines(4, 35), 512, 896, (0, 28)),
     ("lines-part", [64, 65, 63] * 2 + lines(6, 1), 512, 896, (28, 64)),
     ("lines-part", [64, 65, 63] * 2 + lines(4, 1), 896, 512, (64, 0)),
 ]
